@@ -221,6 +221,19 @@ int taq_cross_attn_batched(int R, const taq_request* table, const taq_shape* sha
  * token-sensitivity experiment (Section III-B, Eq. 1) on block outputs. x, y, out device memory; out 8-byte aligned. */
 int taq_mse_f16(const void* x_f16, const void* y_f16, size_t n, double* out, void* hip_stream);
 
+/* The token-sensitivity sweep of Section III-B, Eq. 1, in full precision (shape->bits_q = bits_prob = bits_proj = 16,
+ * H <= 32): for each of `ntok` distinct text tokens and each of `nbits` (1 or 2) widths (8 or 4), the mean squared change
+ * of the fp16 block output when only that token's K and V rows are quantized to that width.
+ *   tokens, bits    : HOST arrays, read before the call returns
+ *   Wk, Wv, Wq, Wo  : f16 matrices; scales as for taq_cross_attn with bits_proj = 16
+ *   out             : f64 [nbits][ntok] device memory
+ *   workspace       : taq_token_sensitivity_bytes() bytes of scratch
+ * shape->bits_kv and prob_grid are ignored. */
+int taq_token_sensitivity_bytes(const taq_shape* shape, int ntok, int nbits, size_t* bytes);
+int taq_token_sensitivity(const void* hidden, const void* context, const void* Wk, const void* Wv, const void* Wq,
+                          const void* Wo, const float* scales, const int* tokens, int ntok, const int* bits, int nbits,
+                          const taq_shape* shape, double* out, void* workspace, void* hip_stream);
+
 /* Expand qkv_packed into plain arrays (for tests). Any output may be NULL.
  *   k_codes, v_codes : i8  [B, T, C]  (int4 codes sign-extended; zeros on protected rows)
  *   k_scales,v_scales: f32 [B, H, T]  (zeros on protected rows)

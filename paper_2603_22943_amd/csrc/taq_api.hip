@@ -139,8 +139,8 @@ static int quantize_kv_impl(const void* context, const uint8_t* trigger_mask, co
         TAQ_TRY_HIP(launch_kv_prep(nullptr, M, x_code, s_x, nullptr, nullptr, s.C, reinterpret_cast<int8_t*>(ws + W.w_code),
                                    reinterpret_cast<float*>(ws + W.s_w), s.Cc, trigger_mask, s.B, s.T, s.bits_kv, ntrig,
                                    trig_idx, slot_of, st));
-        TAQ_TRY_HIP(launch_gemm_fp(context, false, static_cast<const __half*>(Wk), nullptr, M, s.C, s.Cc, rows_f, nullptr, 2 * s.C, st));
-        TAQ_TRY_HIP(launch_gemm_fp(context, false, static_cast<const __half*>(Wv), nullptr, M, s.C, s.Cc, rows_f + s.C, nullptr, 2 * s.C, st));
+        TAQ_TRY_HIP(launch_gemm_kv_rows(static_cast<const __half*>(context), static_cast<const __half*>(Wk),
+                                        static_cast<const __half*>(Wv), M, s.C, s.Cc, rows_f, st));
         TAQ_TRY_HIP(launch_kv_pack(rows_f, slot_of, s.B, s.T, s.C, s.H, s.bits_kv, pk + L.k_code, pk + L.v_code,
                                    reinterpret_cast<float*>(pk + L.s_k), reinterpret_cast<float*>(pk + L.s_v), st));
         TAQ_TRY_HIP(launch_kv_image(pk, s, st));
@@ -413,6 +413,46 @@ int taq_mse_f16(const void* x_f16, const void* y_f16, size_t n, double* out, voi
         return TAQ_ERR_MISALIGNED;
     TAQ_TRY_HIP(launch_mse_f16(static_cast<const __half*>(x_f16), static_cast<const __half*>(y_f16), n, out,
                                static_cast<hipStream_t>(hip_stream)));
+    return TAQ_OK;
+}
+
+static int check_sensitivity(const taq_shape* s, int ntok, int nbits) {
+    const int rc = check_shape(s, true);
+    if (rc != TAQ_OK) return rc;
+    if (s->bits_q != 16 || s->bits_prob != 16 || s->bits_proj != 16) return TAQ_ERR_UNSUPPORTED_BITS;
+    if (s->H > TAQ_SENS_MAX_H) return TAQ_ERR_BAD_SHAPE;
+    if (ntok < 1 || ntok > s->T || nbits < 1 || nbits > 2) return TAQ_ERR_INVALID_ARG;
+    return TAQ_OK;
+}
+
+int taq_token_sensitivity_bytes(const taq_shape* shape, int ntok, int nbits, size_t* bytes) {
+    if (!bytes) return TAQ_ERR_INVALID_ARG;
+    const int rc = check_sensitivity(shape, ntok, nbits);
+    if (rc != TAQ_OK) return rc;
+    *bytes = sens_workspace(*shape, ntok, nbits).total;
+    return TAQ_OK;
+}
+
+int taq_token_sensitivity(const void* hidden, const void* context, const void* Wk, const void* Wv, const void* Wq,
+                          const void* Wo, const float* scales, const int* tokens, int ntok, const int* bits, int nbits,
+                          const taq_shape* shape, double* out, void* workspace, void* hip_stream) {
+    const int rc = check_sensitivity(shape, ntok, nbits);
+    if (rc != TAQ_OK) return rc;
+    if (!hidden || !context || !Wk || !Wv || !Wq || !Wo || !scales || !tokens || !bits || !out || !workspace) return TAQ_ERR_INVALID_ARG;
+    if (misaligned(hidden) || misaligned(context) || misaligned(Wk) || misaligned(Wv) || misaligned(Wq) || misaligned(Wo) ||
+        misaligned(scales) || misaligned(workspace) || (reinterpret_cast<uintptr_t>(out) & 7u))
+        return TAQ_ERR_MISALIGNED;
+    for (int j = 0; j < nbits; ++j)
+        if (bits[j] != 8 && bits[j] != 4) return TAQ_ERR_UNSUPPORTED_BITS;
+    bool seen[TAQ_MAX_T] = {};
+    for (int k = 0; k < ntok; ++k) {
+        if (tokens[k] < 0 || tokens[k] >= shape->T || seen[tokens[k]]) return TAQ_ERR_INVALID_ARG;
+        seen[tokens[k]] = true;
+    }
+    TAQ_TRY_HIP(launch_token_sensitivity(hidden, context, static_cast<const __half*>(Wk), static_cast<const __half*>(Wv),
+                                         static_cast<const __half*>(Wq), static_cast<const __half*>(Wo), scales + 2 * shape->C, tokens,
+                                         ntok, bits, nbits, *shape, out, static_cast<uint8_t*>(workspace),
+                                         static_cast<hipStream_t>(hip_stream)));
     return TAQ_OK;
 }
 

@@ -274,9 +274,16 @@ hipError_t launch_gemm_i8(const int8_t* A, const float* sa, const int8_t* W, con
                           int ldo, hipStream_t st);
 
 // Full-precision stages (shape.bits_proj / bits_q / bits_prob = 16), float32 arithmetic:
-//   out[m][n] = sum_k A[m][k] * W[n][k] (+ bias[n]); A f16 or f32 [M][K], W f16 [N][K]; float32 and / or fp16 result
+//   out[m][n] = sum_k A[m][k] * W[n][k] (+ bias[n]); A f16 or f32 [M][K], W f16 [N][K]; float32 and / or fp16 result;
+//   with fp16 rows one float32 FMA chain per output in K order
 hipError_t launch_gemm_fp(const void* A, bool a_is_f32, const __half* W, const float* bias, int M, int N, int K,
                           float* out_f32, __half* out_f16, int ldo, hipStream_t st);
+//   K and V rows of a context in one launch: rows_f [M][2C], the same sums as two calls of launch_gemm_fp
+hipError_t launch_gemm_kv_rows(const __half* context, const __half* Wk, const __half* Wv, int M, int C, int K, float* rows_f, hipStream_t st);
+//   fp16 rows on the matrix cores (any order of summation: for sums that no quantizer reads), out f32 [M][N]
+hipError_t launch_gemm_f16(const __half* A, const __half* W, int M, int N, int K, float* out, hipStream_t st);
+//   the same as launch_gemm_fp for every head's slice of the contraction by itself: out[m][h][n] = sum over k in head h (A f32 [M][K], K = H*d)
+hipError_t launch_gemm_f32_heads(const float* A, const __half* W, int M, int N, int K, int H, float* out, hipStream_t st);
 //   protected K / V rows (fp16, compacted by slot, plus the transposed V copy) from float32 projection rows [B*T][2C]
 hipError_t launch_kv_rows_from_f32(const float* rows_f, const int* ntrig, const int* trig_idx, int B, int T, int C,
                                    __half* k16, __half* v16, __half* v16t, hipStream_t st);
@@ -285,6 +292,25 @@ hipError_t launch_attn_fp(const float* q_f, const int8_t* q_code, const float* s
                           float* o_f, uint8_t* p_code, hipStream_t st);
 //   mean squared difference of two fp16 arrays into a device double
 hipError_t launch_mse_f16(const __half* x, const __half* y, size_t n, double* out, hipStream_t st);
+
+// Token-sensitivity sweep of Eq. (1) in full precision (taq_sens.hip): workspace sections and the launch sequence.
+#define TAQ_SENS_MAX_H 32
+struct SensWorkspace {
+    size_t rows_f;  // f32 [B*T][2C]             projection rows of the text tokens
+    size_t kx, vx;  // f32, 1+nb planes of [B*T][C]: fp16 rows as float32, then the change each width makes (K in operand order)
+    size_t va;      // f32 [1+nb][B*T][H][C]     the V planes through each head's slice of to_out
+    size_t q_f;     // f32 [B*N][C]
+    size_t o;       // f32 [chunk][C]            reference attention output
+    size_t p;       // f32 [chunk][H][C]         ... through each head's slice of to_out
+    size_t ab;      // f32 [chunk][ntok][nb][H][2]
+    size_t part;    // f64 [nb][ntok][npart]     partial sums of squares
+    size_t total;
+    int np, chunk, npart;
+};
+SensWorkspace sens_workspace(const taq_shape& s, int ntok, int nbits);
+hipError_t launch_token_sensitivity(const void* hidden, const void* context, const __half* Wk, const __half* Wv, const __half* Wq,
+                                    const __half* Wo, const float* bias, const int* tokens, int ntok, const int* bits, int nbits,
+                                    const taq_shape& s, double* out, uint8_t* ws, hipStream_t st);
 
 // K~/V~ image for the fused kernel, from the codes and scales already in qkv_packed.
 hipError_t launch_kv_image(uint8_t* packed, const taq_shape& s, hipStream_t st);

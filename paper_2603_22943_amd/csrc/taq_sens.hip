@@ -1,0 +1,429 @@
+// The token-sensitivity experiment (PersonalQ, Section III-B, Eq. 1) on block outputs, as one call: for every swept text
+// token i and bit width b, the mean squared change of the block output when only the K and V rows of token i are
+// quantized to b bits and everything else stays in full precision.
+//
+// Running the block once per (i, b) repeats almost all of its work. With p = A[n, i] of head h, r = exp(sigma q.(k' - k))
+// and g = 1 + p (r - 1), replacing row i by (k', v') moves the head's attention output by
+//     dO = alpha (O - v) + beta (v' - v),      alpha = p (1 - r) / g,   beta = p r / g
+// (1 - r taken from expm1: no cancellation), and to_out is linear, so with P[n, h] = Wo_h O[n, h], a[i, h] = Wo_h v and
+// D[i, h] = Wo_h (v' - v), each formed once,
+//     y'(i, b)[n] = y[n] + sum_h ( alpha (P[n, h] - a[i, h]) + beta D[i, h] ),
+// H multiply-adds per output element and term instead of the whole block. Everything is float32 (float64 in the sums of
+// squares); the outputs are rounded to fp16 on both sides before the difference is taken, as the block stores them.
+#include "taq_internal.h"
+
+namespace taq {
+
+typedef float sens_floatx4_t __attribute__((ext_vector_type(4)));
+
+struct SensDims {
+    int B, N, C, H, d, T;
+    int Np;             // image tokens per batch element, padded to a multiple of 32 (rows of the chunked arrays)
+    int nk;             // swept tokens
+    float sigma;        // softmax scale
+    float qmax[2];      // grids of the widths: 127 or 7
+    unsigned char tok[TAQ_MAX_T];  // swept tokens
+    signed char slot[TAQ_MAX_T];   // place of text token t among them, or -1
+};
+
+// ---------------------------------------------------------------- K, V rows: fp16 rows and the change quantization makes
+// rows_f [B*T][2C] -> plane 0 = the row as the block stores it (fp16), plane 1 + j = code * s - that row (Eq. 2 at width
+// j). V: vx[plane][b*T + t][C]. K in the order the score MFMAs read it, zero past the head and past the last token:
+// kx[b][h][d/16 step][plane][tile of 16 tokens][lane = token + 16 * quarter][4 channels], one KiB per operand.
+// One workgroup per (text token, batch element), tokens padded to whole tiles; per-head maxima through LDS atomics.
+__device__ __forceinline__ size_t sens_kx_at(const SensDims& D, int nplanes, int b, int h, int k, int plane, int t) {
+    const int S = (D.d + 15) >> 4, MT = (D.T + 15) >> 4;
+    return ((((((size_t)b * D.H + h) * S + (k >> 4)) * nplanes + plane) * MT + (t >> 4)) * 64 + (t & 15) + 16 * ((k & 15) >> 2)) * 4;
+}
+
+template <int NB>
+__global__ __launch_bounds__(256) void sens_rows_kernel(const float* __restrict__ rows_f, SensDims D, float* __restrict__ kx,
+                                                        float* __restrict__ vx) {
+    __shared__ unsigned smax[2 * TAQ_MAX_H];
+    const int t = blockIdx.x, b = blockIdx.y;
+    const int d16 = (D.d + 15) & ~15;
+    const bool live = t < D.T;
+    for (int v = threadIdx.x; v < D.H * d16 / 4; v += 256) {  // padding of the K operands
+        const int h = v / (d16 / 4), k = 4 * (v % (d16 / 4));
+        if (!live || k >= D.d)
+#pragma unroll
+            for (int j = 0; j <= NB; ++j)
+                *reinterpret_cast<float4*>(kx + sens_kx_at(D, 1 + NB, b, h, k, j, t)) = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (!live) return;
+    for (int g = threadIdx.x; g < 2 * D.H; g += 256) smax[g] = 0u;
+    __syncthreads();
+    const int bt = b * D.T + t;
+    const float4* xr = reinterpret_cast<const float4*>(rows_f + (size_t)bt * 2 * D.C);
+    const int nv = D.C >> 1;
+    for (int v = threadIdx.x; v < nv; v += 256) {
+        const float4 f = xr[v];
+        atomicMax(&smax[(v * 4) / D.d], __float_as_uint(fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w)))));
+    }
+    __syncthreads();
+    const size_t plane = (size_t)D.B * D.T * D.C;
+    for (int v = threadIdx.x; v < nv; v += 256) {
+        const int ch = v * 4;
+        const bool isk = ch < D.C;
+        const float4 f = xr[v];
+        const float fv[4] = {f.x, f.y, f.z, f.w};
+        const float amax = __uint_as_float(smax[ch / D.d]), safe = amax == 0.f ? 1.f : amax;
+        auto put = [&](int j, float4 o) {
+            if (isk) *reinterpret_cast<float4*>(kx + sens_kx_at(D, 1 + NB, b, ch / D.d, ch % D.d, j, t)) = o;
+            else *reinterpret_cast<float4*>(vx + (size_t)j * plane + (size_t)bt * D.C + ch - D.C) = o;
+        };
+        float st[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) st[i] = __half2float(__float2half_rn(fv[i]));
+        put(0, make_float4(st[0], st[1], st[2], st[3]));
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const float s = amax == 0.f ? 1.f : amax / D.qmax[j];
+            float o[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float code = fminf(fmaxf(__builtin_rintf((fv[i] * D.qmax[j]) / safe), -D.qmax[j]), D.qmax[j]);
+                o[i] = __builtin_fmaf(code, s, -st[i]);
+            }
+            put(1 + j, make_float4(o[0], o[1], o[2], o[3]));
+        }
+    }
+}
+
+__device__ __forceinline__ float sens_quad_max(float x) {  // over the lanes l, l^16, l^32, l^48
+    x = fmaxf(x, __shfl_xor(x, 16));
+    return fmaxf(x, __shfl_xor(x, 32));
+}
+__device__ __forceinline__ float sens_quad_sum(float x) {
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
+// ---------------------------------------------------------------- attention of the reference block and the sweep's factors
+// One workgroup of one wavefront per (16 image tokens, head) (spread over the compute units: 4 in a workgroup left most
+// of them idle): S^T = K Q^T and the score changes (k' - k) Q^T of every text token, softmax, O^T = V^T A^T, all with
+// V_MFMA_F32_16X16X4_F32 (text tokens or channels along the rows, image tokens along the columns: the accumulator
+// registers of the scores are the B operand of the last product). A chain of latencies: each step's operands are
+// requested while the step before is multiplied. o [row][C], ab [row][nk][NB][H]{alpha, beta}, rows counted from row0
+// over all batch elements, D.Np of them each. MT: tiles of 16 text tokens.
+template <int NB, int MT>
+__global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__ q_f, const float* __restrict__ kx,
+                                                        const float* __restrict__ vx, SensDims D, int row0,
+                                                        float* __restrict__ o, float* __restrict__ ab) {
+    const int lane = threadIdx.x, r16 = lane & 15, q = lane >> 4;
+    const int tile = blockIdx.x, h = blockIdx.y;
+    const int row = tile * 16 + r16;  // of the chunk
+    const int b = (row0 + tile * 16) / D.Np, np = (row0 + row) % D.Np, n = np < D.N ? np : D.N - 1;
+    const int d = D.d, C = D.C, T = D.T, S16 = (d + 15) >> 4;
+    constexpr int NP = (1 + NB) * MT;  // operands of a step
+    sens_floatx4_t S[1 + NB][MT];
+#pragma unroll
+    for (int j = 0; j <= NB; ++j)
+#pragma unroll
+        for (int tt = 0; tt < MT; ++tt) S[j][tt] = (sens_floatx4_t){0.f, 0.f, 0.f, 0.f};
+    const float* qr = q_f + ((size_t)b * D.N + n) * C + h * d;
+    const float4* kr = reinterpret_cast<const float4*>(kx) + ((size_t)b * D.H + h) * S16 * NP * 64 + lane;
+    float4 kv[NP], qv;
+    auto fetch = [&](int s) {
+        const int sc = s < S16 ? s : S16 - 1, k = 16 * sc + 4 * q;
+        qv = *reinterpret_cast<const float4*>(qr + (k < d ? k : 0));  // (meets zeros of K past the head)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) kv[p] = kr[((size_t)sc * NP + p) * 64];
+    };
+    fetch(0);
+    for (int s = 0; s < S16; ++s) {
+        float4 kc[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) kc[p] = kv[p];
+        const float qe[4] = {qv.x, qv.y, qv.z, qv.w};
+        fetch(s + 1);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const float ke[4] = {kc[p].x, kc[p].y, kc[p].z, kc[p].w};
+                S[p / MT][p % MT] = __builtin_amdgcn_mfma_f32_16x16x4f32(ke[e], qe[e], S[p / MT][p % MT], 0, 0, 0);
+            }
+    }
+    // this lane: text tokens 16*tt + 4*q + i of image token r16
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool live = 16 * tt + 4 * q + i < T;
+            S[0][tt][i] = live ? S[0][tt][i] * D.sigma : -__builtin_inff();
+            mx = fmaxf(mx, S[0][tt][i]);
+        }
+    mx = sens_quad_max(mx);
+    float Z = 0.f;
+#pragma unroll
+    for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            S[0][tt][i] = __expf(S[0][tt][i] - mx);
+            Z += S[0][tt][i];
+        }
+    Z = sens_quad_sum(Z);
+#pragma unroll
+    for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float p = S[0][tt][i] / Z;
+            S[0][tt][i] = p;
+            const int t = 16 * tt + 4 * q + i;
+            const int k = t < T ? D.slot[t] : -1;
+            if (k >= 0) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const float em = expm1f(S[1 + j][tt][i] * D.sigma), g = 1.f + p * em;  // r - 1, Z' / Z
+                    float2 f;
+                    f.x = -(p * em) / g;
+                    f.y = p * (1.f + em) / g;
+                    reinterpret_cast<float2*>(ab)[(((size_t)row * D.nk + k) * NB + j) * D.H + h] = f;
+                }
+            }
+        }
+    float va[MT][4];
+    auto fetch_v = [&](int j0) {
+        const int c = j0 + r16 < d ? j0 + r16 : d - 1;
+#pragma unroll
+        for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int t = 16 * tt + 4 * q + i;
+                va[tt][i] = vx[((size_t)b * T + (t < T ? t : T - 1)) * C + h * d + c];  // (weight 0 past the last token)
+            }
+    };
+    fetch_v(0);
+    for (int j0 = 0; j0 < d; j0 += 16) {
+        float vc[MT][4];
+#pragma unroll
+        for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) vc[tt][i] = va[tt][i];
+        fetch_v(j0 + 16);
+        sens_floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[tt][i], S[0][tt][i], acc, 0, 0, 0);
+        if (j0 + 4 * q < d)
+            *reinterpret_cast<float4*>(o + (size_t)row * C + h * d + j0 + 4 * q) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    }
+}
+
+// ---------------------------------------------------------------- outputs of every (token, width) and their squared changes
+// A wavefront owns NR rows x 64 channels: P of all heads sits in registers (NR * HT of them), the factors alpha, beta of a
+// row are wave-uniform (scalar loads), a and D come one coalesced load per head and are shared by the NR rows; the four
+// wavefronts of a workgroup take neighbouring rows of the same channels, so that those loads meet in the compute unit's
+// cache. Bound by vector issue: HT * (1 + 2 NB) multiply-adds per output element and swept token.
+// Sums of squares in float64: per lane over the rows, then across lanes through LDS, 16 (token, width) pairs at a time.
+template <int HT, int NR, int NB, bool EXACT>
+__global__ __launch_bounds__(256) void sens_main_kernel(const float* __restrict__ P, const float* __restrict__ ab,
+                                                        const float* __restrict__ va, const float* __restrict__ bias, SensDims D,
+                                                        int row0, int kper, double* __restrict__ part, int part0, int npart) {
+    constexpr int CHUNK = 16;
+    __shared__ double red[4][CHUNK][65];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int H = EXACT ? HT : D.H, C = D.C;
+    const int c = blockIdx.y * 64 + lane, cc = c < C ? c : C - 1;
+    const int row = ((int)blockIdx.x * 4 + wave) * NR;  // first row of this wavefront, within the chunk
+    const int b = (row0 + row) / D.Np, np0 = (row0 + row) % D.Np;
+    float p[NR][HT], ys[NR];
+    float y16[NR];
+    const float bc = bias[cc];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        float y = 0.f;
+#pragma unroll
+        for (int h = 0; h < HT; ++h) {
+            p[r][h] = (EXACT || h < H) ? P[((size_t)(row + r) * H + h) * C + cc] : 0.f;
+            y += p[r][h];
+        }
+        ys[r] = y + bc;
+        y16[r] = __half2float(__float2half_rn(ys[r]));
+    }
+    const int k0 = blockIdx.z * kper, k1 = k0 + kper < D.nk ? k0 + kper : D.nk;
+    const size_t plane = (size_t)D.B * D.T * H * C;
+    const bool cin = c < C;
+    for (int kb = k0; kb < k1; kb += CHUNK / NB) {
+#pragma unroll 1
+        for (int kk = 0; kk < CHUNK / NB && kb + kk < k1; ++kk) {
+            const int k = kb + kk;
+            const float* vr = va + ((size_t)b * D.T + D.tok[k]) * H * C + cc;
+            float a[HT], dl[NB][HT];
+#pragma unroll
+            for (int h = 0; h < HT; ++h) {
+                const bool in = EXACT || h < H;
+                a[h] = in ? vr[(size_t)h * C] : 0.f;
+#pragma unroll
+                for (int j = 0; j < NB; ++j) dl[j][h] = in ? vr[(size_t)(1 + j) * plane + (size_t)h * C] : 0.f;
+            }
+            double s[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) s[j] = 0.0;
+            const float* f = ab + ((size_t)row * D.nk + k) * NB * H * 2;
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const float* fr = f + (size_t)r * D.nk * NB * H * 2;
+                float y[NB];
+#pragma unroll
+                for (int j = 0; j < NB; ++j) y[j] = ys[r];
+#pragma unroll
+                for (int h = 0; h < HT; ++h) {
+                    if (EXACT || h < H) {
+                        const float pm = p[r][h] - a[h];
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) {
+                            y[j] = __builtin_fmaf(fr[(j * H + h) * 2], pm, y[j]);
+                            y[j] = __builtin_fmaf(fr[(j * H + h) * 2 + 1], dl[j][h], y[j]);
+                        }
+                    }
+                }
+                if (np0 + r < D.N && cin) {
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {
+                        const double df = (double)(__half2float(__float2half_rn(y[j])) - y16[r]);  // (exact: both are fp16 numbers)
+                        s[j] = __builtin_fma(df, df, s[j]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) red[wave][kk * NB + j][lane] = s[j];
+        }
+        __syncthreads();
+        {
+            const int e = lane >> 2, k = kb + e / NB;  // four lanes per (token, width) pair
+            double t = 0.0;
+#pragma unroll
+            for (int u = 0; u < 16; ++u) t += red[wave][e][(lane & 3) * 16 + u];
+            t += __shfl_xor(t, 1);
+            t += __shfl_xor(t, 2);
+            if ((lane & 3) == 0 && k < k1)
+                part[((size_t)(e % NB) * D.nk + k) * npart + part0 + ((int)blockIdx.x * 4 + wave) * (int)gridDim.y + (int)blockIdx.y] = t;
+        }
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(256) void sens_reduce_kernel(const double* __restrict__ part, int npart, double count, double* __restrict__ out) {
+    __shared__ double red[256];
+    const double* p = part + (size_t)blockIdx.x * npart;
+    double s = 0.0;
+    for (int i = threadIdx.x; i < npart; i += 256) s += p[i];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[blockIdx.x] = red[0] / count;
+}
+
+// ---------------------------------------------------------------- host side
+namespace {
+int rows_per_wave(int H) { return H <= 8 ? 8 : H <= 16 ? 4 : 2; }
+}  // namespace
+
+SensWorkspace sens_workspace(const taq_shape& s, int ntok, int nbits) {
+    SensWorkspace W;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
+    const size_t BT = (size_t)s.B * s.T, C = s.C, H = s.H;
+    W.np = (int)align_up(s.N, 32);
+    const size_t rows = (size_t)s.B * W.np;
+    // rows per pass: P and the factors of a chunk stay within 128 MiB (whole 64-row GEMM tiles)
+    const size_t per_row = (H * C + C + (size_t)ntok * nbits * H * 2) * 4;
+    size_t chunk = ((size_t)128 << 20) / per_row / 64 * 64;
+    chunk = chunk < 64 ? 64 : chunk;
+    W.chunk = (int)(chunk < rows ? chunk : rows);
+    W.rows_f = take(BT * 2 * C * 4);
+    W.kx = take((1 + nbits) * s.B * align_up(s.T, 16) * H * align_up(C / H, 16) * 4);
+    W.vx = take((1 + nbits) * BT * C * 4);
+    W.va = take((1 + nbits) * BT * H * C * 4);
+    W.q_f = take((size_t)s.B * s.N * C * 4);
+    W.o = take((size_t)W.chunk * C * 4);
+    W.p = take((size_t)W.chunk * H * C * 4);
+    W.ab = take((size_t)W.chunk * ntok * nbits * H * 2 * 4);
+    W.npart = (int)(rows / rows_per_wave(s.H) * ((C + 63) / 64));
+    W.part = take((size_t)W.npart * ntok * nbits * 8);
+    W.total = off;
+    return W;
+}
+
+template <int NB>
+static hipError_t sens_run(const void* hidden, const void* context, const __half* Wk, const __half* Wv, const __half* Wq,
+                           const __half* Wo, const float* bias, const int* tokens, int ntok, const int* bits, const taq_shape& s,
+                           double* out, uint8_t* ws, hipStream_t st) {
+    const SensWorkspace W = sens_workspace(s, ntok, NB);
+    SensDims D;
+    D.B = s.B; D.N = s.N; D.C = s.C; D.H = s.H; D.d = s.C / s.H; D.T = s.T;
+    D.Np = W.np;
+    D.nk = ntok;
+    D.sigma = s.softmax_scale != 0.f ? s.softmax_scale : 1.0f / sqrtf((float)D.d);
+    for (int j = 0; j < 2; ++j) D.qmax[j] = bits[j < NB ? j : 0] == 4 ? 7.f : 127.f;
+    for (int t = 0; t < TAQ_MAX_T; ++t) { D.slot[t] = -1; D.tok[t] = 0; }
+    for (int k = 0; k < ntok; ++k) {
+        D.tok[k] = (unsigned char)tokens[k];
+        D.slot[tokens[k]] = (signed char)k;
+    }
+    float* rows_f = reinterpret_cast<float*>(ws + W.rows_f);
+    float* kx = reinterpret_cast<float*>(ws + W.kx);
+    float* vx = reinterpret_cast<float*>(ws + W.vx);
+    float* va = reinterpret_cast<float*>(ws + W.va);
+    float* q_f = reinterpret_cast<float*>(ws + W.q_f);
+    float* o = reinterpret_cast<float*>(ws + W.o);
+    float* P = reinterpret_cast<float*>(ws + W.p);
+    float* ab = reinterpret_cast<float*>(ws + W.ab);
+    double* part = reinterpret_cast<double*>(ws + W.part);
+    const int BT = s.B * s.T, C = s.C, H = s.H, rows = s.B * W.np, NR = rows_per_wave(H);
+    hipError_t e;
+    if ((e = launch_gemm_kv_rows(static_cast<const __half*>(context), Wk, Wv, BT, C, s.Cc, rows_f, st)) != hipSuccess) return e;
+    if ((e = launch_gemm_f16(static_cast<const __half*>(hidden), Wq, s.B * s.N, C, C, q_f, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(sens_rows_kernel<NB>, dim3((s.T + 15) / 16 * 16, s.B), dim3(256), 0, st, rows_f, D, kx, vx);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_gemm_f32_heads(vx, Wo, (1 + NB) * BT, C, C, H, va, st)) != hipSuccess) return e;
+    for (int r0 = 0; r0 < rows; r0 += W.chunk) {
+        const int nr = rows - r0 < W.chunk ? rows - r0 : W.chunk;  // a multiple of 32
+#define TAQ_SENS_ATTN(MT) \
+    case MT: hipLaunchKernelGGL((sens_attn_kernel<NB, MT>), dim3(nr / 16, H), dim3(64), 0, st, q_f, kx, vx, D, r0, o, ab); break;
+        switch ((s.T + 15) / 16) {
+            TAQ_SENS_ATTN(1) TAQ_SENS_ATTN(2) TAQ_SENS_ATTN(3) TAQ_SENS_ATTN(4) TAQ_SENS_ATTN(5) TAQ_SENS_ATTN(6)
+            default: return hipErrorInvalidValue;
+        }
+#undef TAQ_SENS_ATTN
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = launch_gemm_f32_heads(o, Wo, nr, C, C, H, P, st)) != hipSuccess) return e;
+        const int gx = nr / (4 * NR), gy = (C + 63) / 64;
+        // split the swept tokens so that about four workgroups per compute unit are there, at least 8 tokens each (every
+        // part loads its rows of P again)
+        int split = 1024 / (gx * gy);
+        split = split < 1 ? 1 : split > (ntok + 7) / 8 ? (ntok + 7) / 8 : split;
+        const int kper = (ntok + split - 1) / split;
+        const dim3 grid(gx, gy, (ntok + kper - 1) / kper);
+        const int part0 = r0 / NR * gy;
+#define TAQ_SENS_MAIN(HT, R, EX)                                                                                              \
+    hipLaunchKernelGGL((sens_main_kernel<HT, R, NB, EX>), grid, dim3(256), 0, st, P, ab, va, bias, D, r0, kper, part, part0, W.npart)
+        if (H == 8) TAQ_SENS_MAIN(8, 8, true);
+        else if (H == 4) TAQ_SENS_MAIN(4, 8, true);
+        else if (H < 8) TAQ_SENS_MAIN(8, 8, false);
+        else if (H <= 16) TAQ_SENS_MAIN(16, 4, false);
+        else TAQ_SENS_MAIN(32, 2, false);
+#undef TAQ_SENS_MAIN
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(sens_reduce_kernel, dim3(ntok * NB), dim3(256), 0, st, part, W.npart, (double)s.B * s.N * s.C, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_token_sensitivity(const void* hidden, const void* context, const __half* Wk, const __half* Wv, const __half* Wq,
+                                    const __half* Wo, const float* bias, const int* tokens, int ntok, const int* bits, int nbits,
+                                    const taq_shape& s, double* out, uint8_t* ws, hipStream_t st) {
+    if (s.H > TAQ_SENS_MAX_H || ntok < 1 || ntok > s.T) return hipErrorInvalidValue;
+    if (nbits == 1) return sens_run<1>(hidden, context, Wk, Wv, Wq, Wo, bias, tokens, ntok, bits, s, out, ws, st);
+    if (nbits == 2) return sens_run<2>(hidden, context, Wk, Wv, Wq, Wo, bias, tokens, ntok, bits, s, out, ws, st);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace taq

@@ -7,8 +7,10 @@ the output y* obtained with every row protected,
 
     Delta_i(b) = MSE(y^(i,b), y*),      b in {8, 4}.
 
-Everything runs in the library's kernels, the squared-difference reduction included (taq_mse_f16);
-this module only builds the masks and loops over tokens. What "everything else" is computed at is
+Everything runs in the library's kernels, the squared-difference reduction included. In full
+precision the whole sweep is one call (taq_token_sensitivity), which updates the reference output by
+what the one changed row changes; for a quantized block this module builds the masks and loops over
+tokens (taq_quantize_kv, taq_cross_attn, taq_mse_f16). What "everything else" is computed at is
 the caller's choice through `shape`: with bits_q = bits_prob = bits_proj = 16 (Wq / Wo / Wk / Wv
 the fp16 matrices) all other parameters and activations stay in full precision, as Eq. (1) states;
 with the 8- or 4-bit widths the sweep isolates the effect of token i's rows inside the quantized
@@ -46,6 +48,15 @@ def token_sensitivity(hidden: torch.Tensor, context: torch.Tensor, Wk: torch.Ten
     for i in tokens:
         if not 0 <= i < Tn:
             raise ValueError("token index out of range")
+    widths = list(dict.fromkeys(bits))
+    if tokens and widths and shape.bits_q == 16 and shape.bits_prob == 16 and shape.bits_proj == 16 and shape.H <= 32:
+        # full precision: one call forms what all (token, width) pairs share once
+        distinct = list(dict.fromkeys(tokens))
+        delta = T.taq_token_sensitivity(hidden, context, Wk, Wv, wq, wo, scales, distinct, widths, shape).cpu()
+        if len(distinct) < len(tokens):
+            at = {t: k for k, t in enumerate(distinct)}
+            delta = delta[:, [at[t] for t in tokens]]
+        return {b: delta[j] for j, b in enumerate(widths)}
     dev = hidden.device
     ws = torch.empty(T.taq_workspace_bytes(shape), dtype=torch.uint8, device=dev)
     all_on = torch.ones((B, Tn), dtype=torch.uint8, device=dev)

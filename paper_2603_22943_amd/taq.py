@@ -41,6 +41,7 @@ EXPORTS = [
     "taq_quantize_kv",
     "taq_quantize_kv_w8",
     "taq_cross_attn", "taq_cross_attn_ex", "taq_cross_attn_static", "taq_cross_attn_batched", "taq_unpack_kv", "taq_mse_f16",
+    "taq_token_sensitivity_bytes", "taq_token_sensitivity",
     "taq_status_string",
 ]
 
@@ -101,6 +102,8 @@ def load() -> ctypes.CDLL:
     lib.taq_cross_attn_batched.argtypes = [ci, ctypes.POINTER(taq_request), shp, vp, vp]
     lib.taq_unpack_kv.argtypes = [vp, shp, vp, vp, vp, vp, vp, vp, vp]
     lib.taq_mse_f16.argtypes = [vp, vp, ctypes.c_size_t, vp, vp]
+    lib.taq_token_sensitivity_bytes.argtypes = [shp, ci, ci, sz]
+    lib.taq_token_sensitivity.argtypes = [vp, vp, vp, vp, vp, vp, vp, ctypes.POINTER(ci), ci, ctypes.POINTER(ci), ci, shp, vp, vp, vp]
     for name in EXPORTS:
         getattr(lib, name).restype = ctypes.c_char_p if name == "taq_status_string" else ci
     _lib = lib
@@ -267,6 +270,27 @@ def taq_mse_f16(x: torch.Tensor, y: torch.Tensor, out: Optional[torch.Tensor] = 
     if out is None:
         out = torch.empty(1, dtype=torch.float64, device=x.device)
     _check(load().taq_mse_f16(_ptr(x), _ptr(y), x.numel(), _ptr(out), _stream(stream)), "taq_mse_f16")
+    return out
+
+
+def taq_token_sensitivity_bytes(shape: taq_shape, ntok: int, nbits: int) -> int:
+    n = ctypes.c_size_t(0)
+    _check(load().taq_token_sensitivity_bytes(ctypes.byref(shape), ntok, nbits, ctypes.byref(n)), "taq_token_sensitivity_bytes")
+    return n.value
+
+
+def taq_token_sensitivity(hidden: torch.Tensor, context: torch.Tensor, Wk: torch.Tensor, Wv: torch.Tensor, Wq: torch.Tensor,
+                          Wo: torch.Tensor, scales: torch.Tensor, tokens: Sequence[int], bits: Sequence[int], shape: taq_shape,
+                          out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
+    """Eq. (1) in full precision for distinct text tokens and one or two widths -> float64 [len(bits), len(tokens)] on the GPU."""
+    dev, nt, nb = hidden.device, len(tokens), len(bits)
+    if out is None:
+        out = torch.empty((nb, nt), dtype=torch.float64, device=dev)
+    if workspace is None:
+        workspace = torch.empty(taq_token_sensitivity_bytes(shape, nt, nb), dtype=torch.uint8, device=dev)
+    _check(load().taq_token_sensitivity(_ptr(hidden), _ptr(context), _ptr(Wk), _ptr(Wv), _ptr(Wq), _ptr(Wo), _ptr(scales),
+                                        (ctypes.c_int * nt)(*tokens), nt, (ctypes.c_int * nb)(*bits), nb, ctypes.byref(shape),
+                                        _ptr(out), _ptr(workspace), _stream(stream)), "taq_token_sensitivity")
     return out
 
 
