@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void gemm_nt_seq_kernel(const __half* __restri
     const __half* wg0 = W + (size_t)(n0 + lr < N ? n0 + lr : N - 1) * K + 8 * ls;
     const __half* wg1 = W + (size_t)(n0 + 32 + lr < N ? n0 + 32 + lr : N - 1) * K + 8 * ls;
     uint4 av, w0, w1;
-    auto fetch = [&](int k0) {  // (K % 32 == 0: the last chunk may be half; what lies past the end becomes zero)
+    auto fetch = [&](int k0) {  // (K % 32 == 0: the last chunk may be half: what lies past the end is not read back)
         const int k = k0 + 8 * ls < K ? k0 : 0;
         av = *reinterpret_cast<const uint4*>(ag + k);
         w0 = *reinterpret_cast<const uint4*>(wg0 + k);

@@ -182,7 +182,7 @@ void to_out_tail_kernel(FusedTable tab, FusedDims dm) {
         const bool zero = amax == 0.f;
         const float sc = zero ? 1.f : amax / 127.f;
         const float safe = zero ? 1.f : amax;
-        const float cq = 127.f * __builtin_amdgcn_rcpf(safe);
+        const float cq = quant_mult(127.f, safe);
         const bool tap = blockIdx.z == 0 && nq < N;
         if (part == 0) s_o[tk] = sc;
         if (tap && dm.dbg.s_o && part == 0) dm.dbg.s_o[row] = sc;

@@ -21,29 +21,11 @@
 // Bit-exact steps (same float32 operation order as the definition): per-token codes of hidden,
 // the int32 accumulators, Qf = float(acc) * (s_h * s_wq), Q~ codes and scales.
 #pragma once
-#include "taq_internal.h"
+#include "taq_device.h"
 
 namespace taq {
 
-typedef int int32x4_t __attribute__((ext_vector_type(4)));
-typedef float floatx4_t __attribute__((ext_vector_type(4)));
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-
-#define TAQ_NEG_INF (-__builtin_inff())
 #define TAQ_MAX_REQ 16
-
-__device__ __forceinline__ int symq_code_f(float x, float qmaxf, float amax) {
-    float t = x * qmaxf;
-    float q = t / amax;  // correctly rounded float32 division
-    float r = __builtin_rintf(q);
-    r = fminf(fmaxf(r, -qmaxf), qmaxf);
-    return (int)r;
-}
-
-__device__ __forceinline__ unsigned pack4(int a, int b, int c, int d) {
-    return (unsigned)(a & 0xFF) | ((unsigned)(b & 0xFF) << 8) | ((unsigned)(c & 0xFF) << 16) | ((unsigned)(d & 0xFF) << 24);
-}
 
 // Buffer descriptor of a weight matrix: base address, no stride (raw byte offsets), `bytes` addressable, 32-bit data
 // format; out-of-range reads return zero.
@@ -114,85 +96,6 @@ struct FusedCfg {
     static constexpr int RING_MAX = DENSE ? 6 : NH <= 8 ? (NTT == 1 ? 32 : 24) : (NTT == 1 ? 12 : 8);
     static constexpr int RING = (!PREFETCH_W && NG == 1) ? (NF < RING_MAX ? NF : RING_MAX) : 0;
 };
-
-// Symmetric 8-bit codes of four values of one row, packed into a dword (low byte first).
-//   exact definition: code = rint((x * qmax) / amax) with IEEE float32 multiply and divide (qmax = 127, or 7 for
-//   4-bit Q~; the bounds below are stated for 127 and only shrink for 7).
-//   fast path: with c = qmax * rcp(amax) (rcp within 1 ulp, the product rounded once: c is within 1.5 * 2^-23 of
-//   qmax / amax, relatively), m = fma(x, c, 1.5 * 2^23) is the EXACT product x * c rounded half-to-even to an integer
-//   (plus the magic constant, whose low mantissa byte is then the code's byte), and e = fma(x, c, -(m - magic)) is the
-//   distance of that exact product from the integer. x * c lies within 1.5 * 2^-23 * 127 = 2.3e-5 of the exact ratio
-//   and the defined quotient within 2 * 2^-24 * 127 = 1.5e-5, so both round to the same integer unless x * c is
-//   within 3.8e-5 of a half-integer; lanes with |e| > 0.49995 redo their four values by the definition.
-__device__ __forceinline__ unsigned quant4_i8(float x0, float x1, float x2, float x3, float c, float amax,
-                                              float qmaxf = 127.f) {
-    const float magic = 12582912.0f;
-    const float m0 = __builtin_fmaf(x0, c, magic), m1 = __builtin_fmaf(x1, c, magic);
-    const float m2 = __builtin_fmaf(x2, c, magic), m3 = __builtin_fmaf(x3, c, magic);
-    const float e0 = __builtin_fmaf(x0, c, magic - m0), e1 = __builtin_fmaf(x1, c, magic - m1);
-    const float e2 = __builtin_fmaf(x2, c, magic - m2), e3 = __builtin_fmaf(x3, c, magic - m3);
-    const unsigned lo = __builtin_amdgcn_perm(__float_as_uint(m1), __float_as_uint(m0), 0x0c0c0400u);
-    const unsigned hi = __builtin_amdgcn_perm(__float_as_uint(m3), __float_as_uint(m2), 0x0c0c0400u);
-    unsigned pk = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-    if (fmaxf(fmaxf(fabsf(e0), fabsf(e1)), fmaxf(fabsf(e2), fabsf(e3))) > 0.49995f)
-        pk = pack4(symq_code_f(x0, qmaxf, amax), symq_code_f(x1, qmaxf, amax), symq_code_f(x2, qmaxf, amax),
-                   symq_code_f(x3, qmaxf, amax));
-    return pk;
-}
-
-// The same for values x_i * f whose products have not been formed yet (f > 0 common to the four): the fast path
-// rounds the exact product x * (f * c), f * c rounded once, which lies within 2.5 * 2^-23 * 127 = 3.8e-5 of the exact
-// ratio of y = fl(x * f) to amax (one more rounding in f * c, one in y itself); with the defined quotient's 1.5e-5 the
-// two agree unless the product is within 5.3e-5 of a half-integer. Flagged lanes form y and follow the definition.
-__device__ __forceinline__ unsigned quant4_i8_scaled(float x0, float x1, float x2, float x3, float f, float c, float amax) {
-    const float magic = 12582912.0f;
-    const float fc = f * c;
-    const float m0 = __builtin_fmaf(x0, fc, magic), m1 = __builtin_fmaf(x1, fc, magic);
-    const float m2 = __builtin_fmaf(x2, fc, magic), m3 = __builtin_fmaf(x3, fc, magic);
-    const float e0 = __builtin_fmaf(x0, fc, magic - m0), e1 = __builtin_fmaf(x1, fc, magic - m1);
-    const float e2 = __builtin_fmaf(x2, fc, magic - m2), e3 = __builtin_fmaf(x3, fc, magic - m3);
-    const unsigned lo = __builtin_amdgcn_perm(__float_as_uint(m1), __float_as_uint(m0), 0x0c0c0400u);
-    const unsigned hi = __builtin_amdgcn_perm(__float_as_uint(m3), __float_as_uint(m2), 0x0c0c0400u);
-    unsigned pk = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-    if (fmaxf(fmaxf(fabsf(e0), fabsf(e1)), fmaxf(fabsf(e2), fabsf(e3))) > 0.49994f)
-        pk = pack4(symq_code_f(x0 * f, 127.f, amax), symq_code_f(x1 * f, 127.f, amax), symq_code_f(x2 * f, 127.f, amax),
-                   symq_code_f(x3 * f, 127.f, amax));
-    return pk;
-}
-
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-
-// All-reduce over the four quarter-wave lanes that hold one image token (l, l^16, l^32, l^48) with the
-// gfx950 row / half-wave swaps: no LDS round trip.
-__device__ __forceinline__ float quad_allmax(float x) {
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float quad_allsum(float x) {
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-// Maximum over the 16 lanes of a row (DPP: xor 1, xor 2, mirror within 8, mirror within 16).
-__device__ __forceinline__ float row16_allmax(float x) {
-    x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0xB1, 0xF, 0xF, true)));
-    x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x4E, 0xF, 0xF, true)));
-    x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x141, 0xF, 0xF, true)));
-    x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x140, 0xF, 0xF, true)));
-    return x;
-}
-
-// Four biased bytes (code + 128) -> four fp16 codes: 0x6400 | byte is the fp16 number 1152 + code.
-__device__ __forceinline__ void biased4_to_half(unsigned w, half2_t& a, half2_t& b) {
-    const unsigned lo = __builtin_amdgcn_perm(0x64646464u, w, 0x04010400u);
-    const unsigned hi = __builtin_amdgcn_perm(0x64646464u, w, 0x04030402u);
-    const half2_t off = {(_Float16)1152.0f, (_Float16)1152.0f};
-    a = *reinterpret_cast<const half2_t*>(&lo) - off;
-    b = *reinterpret_cast<const half2_t*>(&hi) - off;
-}
 
 // TOK = 32 image tokens per workgroup. NTT = 2: one wavefront per head carrying two column tiles of 16 tokens
 // (A operands shared by both tiles). NTT = 1: two wavefronts per head, one tile each (16 wavefronts per CU
@@ -370,7 +273,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
         const bool zero0 = amax == 0.f;
         const float sc0 = zero0 ? 1.f : amax / 127.f;
         const float safe0 = zero0 ? 1.f : amax;
-        const float cq0 = 127.f * __builtin_amdgcn_rcpf(safe0);
+        const float cq0 = quant_mult(127.f, safe0);
         if (HOLDS && part0 == 0) s_h[tok0] = sc0;
     #pragma unroll
         for (int it = 0; it < KC; ++it) {
@@ -384,7 +287,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
             }
             if (HOLDS) {
                 const half2_t x01 = *reinterpret_cast<const half2_t*>(&xin[it].x), x23 = *reinterpret_cast<const half2_t*>(&xin[it].y);
-                const unsigned pk = quant4_i8((float)x01[0], (float)x01[1], (float)x23[0], (float)x23[1], cq0, safe0);
+                const unsigned pk = quant4_i8((float)x01[0], (float)x01[1], (float)x23[0], (float)x23[1], cq0, safe0, 127.f, TAQ_TIE_F16);
                 *reinterpret_cast<unsigned*>(tileq + tok0 * F::TILE_RS + (it * 16 + part0) * 4) = pk;
                 if (TAPS && dm.dbg.h_code && nq0 < N) *reinterpret_cast<unsigned*>(dm.dbg.h_code + row0 * C + (it * 16 + part0) * 4) = pk;
             }
@@ -436,7 +339,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
         const bool zero0 = amax == 0.f;
         const float sc0 = zero0 ? 1.f : amax / 127.f;
         const float safe0 = zero0 ? 1.f : amax;
-        const float cq0 = 127.f * __builtin_amdgcn_rcpf(safe0);
+        const float cq0 = quant_mult(127.f, safe0);
         if (tid < NH * D / 4) reinterpret_cast<float4*>(wsc)[tid] = swv;
         const bool tap = by == 0 && nq0 < N;
         if (part0 == 0) s_h[tok0] = sc0;
@@ -466,8 +369,8 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
             const float2 p0 = __half22float2(hh2[0]), p1 = __half22float2(hh2[1]);
             const float2 p2 = __half22float2(hh2[2]), p3 = __half22float2(hh2[3]);
             uint2 pk;
-            pk.x = quant4_i8(p0.x, p0.y, p1.x, p1.y, cq0, safe0);
-            pk.y = quant4_i8(p2.x, p2.y, p3.x, p3.y, cq0, safe0);
+            pk.x = quant4_i8(p0.x, p0.y, p1.x, p1.y, cq0, safe0, 127.f, TAQ_TIE_F16);
+            pk.y = quant4_i8(p2.x, p2.y, p3.x, p3.y, cq0, safe0, 127.f, TAQ_TIE_F16);
             *reinterpret_cast<uint2*>(tileq + tok0 * F::TILE_RS + (it * TPT + part0) * 8) = pk;
             if (TAPS && tap && dm.dbg.h_code) *reinterpret_cast<uint2*>(dm.dbg.h_code + row0 * C + (it * TPT + part0) * 8) = pk;
             __builtin_amdgcn_sched_barrier(0);
@@ -653,7 +556,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
         const bool qzero = qmax == 0.f;
         const float sQ = qzero ? 1.f : qmax / dm.qmaxq;
         const float qsafe = qzero ? 1.f : qmax;
-        const float cq = dm.qmaxq * __builtin_amdgcn_rcpf(qsafe);
+        const float cq = quant_mult(dm.qmaxq, qsafe);
 #pragma unroll
         for (int j = 0; j < TPH; ++j) qpk[nt][j] = quant4_i8(qf[j][0], qf[j][1], qf[j][2], qf[j][3], cq, qsafe, dm.qmaxq);
         if (TAPS && dm.dbg.q_code && nvalid[nt]) {
@@ -1073,7 +976,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
         const bool ozero = oamax == 0.f;
         so[nt] = ozero ? 1.f : oamax / 127.f;
         const float osafe = ozero ? 1.f : oamax;
-        const float cq = 127.f * __builtin_amdgcn_rcpf(osafe);
+        const float cq = quant_mult(127.f, osafe);
 #pragma unroll
         for (int jt = 0; jt < TPH; ++jt)
             if (16 * jt + 4 * q < D) {

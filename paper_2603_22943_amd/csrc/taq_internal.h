@@ -172,7 +172,7 @@ static inline KvLayout kv_layout(const taq_shape& s) {
 struct KvWorkspace {
     size_t w_code;  // i8  [2C][Cc]   Wk rows then Wv rows
     size_t s_w;     // f32 [2C]
-    size_t x_code;  // i8  [B*T][Cc]
+    size_t x_code;  // i8  [B*T][Cc], or (Cc % 64 == 0) tiles of 16 tokens in operand order
     size_t s_x;     // f32 [B*T]
     size_t rows_f;  // f32 [B*T][2C]  dequantised projection rows (K then V channels)
     size_t total;
@@ -185,7 +185,7 @@ static inline KvWorkspace kv_workspace(const taq_shape& s) {
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     W.w_code = take(C2 * Cc);
     W.s_w = take(C2 * 4);
-    W.x_code = take(M * Cc);
+    W.x_code = take((size_t)s.B * align_up(s.T, 16) * Cc);
     W.s_x = take(M * 4);
     W.rows_f = take(M * C2 * 4);
     W.total = off;

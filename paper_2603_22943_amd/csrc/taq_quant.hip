@@ -4,7 +4,7 @@
 // The symmetric quantizer is a fixed float32 sequence so that codes are reproducible
 // bit for bit:  amax = max|x|;  scale = amax/qmax;  code = clamp(rint((x*qmax)/amax)).
 // The build disables FMA contraction and keeps IEEE-correct float32 division.
-#include "taq_internal.h"
+#include "taq_device.h"
 
 namespace taq {
 
@@ -39,15 +39,61 @@ __device__ __forceinline__ unsigned pack4_i8(int a, int b, int c, int d) {
 }
 
 // ---------------------------------------------------------------- fp16 rows -> int8
-// One wavefront per row. K % 8 == 0.
-__global__ __launch_bounds__(256) void rowquant_f16_kernel(const __half* __restrict__ x, int M, int K,
-                                                           int8_t* __restrict__ code,
-                                                           float* __restrict__ scale) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + wave;
-    if (row >= M) return;
-    const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)row * K);
+// One wavefront per row, K % 8 == 0. Rows of up to 2048 values (every projection of the configured backbones) stay in
+// registers between the maximum and the codes: one pass over memory, all of a row's loads in flight at once; the maximum
+// is taken on the fp16 values, two per instruction (exact in any precision). Bound by the latency of that one round
+// trip: 1280 x 1280 weights 6.0 -> 3.8 us per launch with the two-pass loop and a division per value before.
+// `put(v, codes)` stores the eight codes of values 8v .. 8v+7.
+template <typename Put>
+__device__ __forceinline__ void rowquant_f16_exact(const uint4* __restrict__ xr, int nv, float amax, int lane, Put put) {
+#pragma unroll 1
+    for (int v = lane; v < nv; v += 64) {
+        const __half* x = reinterpret_cast<const __half*>(xr + v);
+        unsigned w[2] = {0u, 0u};
+#pragma unroll 1
+        for (int e = 0; e < 8; ++e) w[e >> 2] |= (unsigned)(symq_code_f(__half2float(x[e]), 127.f, amax) & 0xFF) << (8 * (e & 3));
+        put(v, make_uint2(w[0], w[1]));
+    }
+}
+
+template <int NV, typename Put>
+__device__ __forceinline__ void rowquant_f16_held(const uint4* __restrict__ xr, int nv, float* scale, int lane, Put put) {
+    uint4 u[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int v = lane + 64 * i;
+        u[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (v < nv) u[i] = xr[v];
+    }
+    half2_t am2 = {(_Float16)0.f, (_Float16)0.f};
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const unsigned w[4] = {u[i].x & 0x7fff7fffu, u[i].y & 0x7fff7fffu, u[i].z & 0x7fff7fffu, u[i].w & 0x7fff7fffu};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) am2 = __builtin_elementwise_max(am2, *reinterpret_cast<const half2_t*>(&w[e]));
+    }
+    const float amax = wave_allmax(fmaxf((float)am2[0], (float)am2[1]));
+    const bool zero = amax == 0.f;
+    const float safe = zero ? 1.f : amax;
+    const float c = quant_mult(127.f, safe);
+    if (lane == 0) *scale = zero ? 1.f : amax / 127.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int v = lane + 64 * i;
+        const half2_t* x = reinterpret_cast<const half2_t*>(&u[i]);
+        if (v < nv)
+            put(v, make_uint2(quant4_i8((float)x[0][0], (float)x[0][1], (float)x[1][0], (float)x[1][1], c, safe, 127.f, TAQ_TIE_F16),
+                              quant4_i8((float)x[2][0], (float)x[2][1], (float)x[3][0], (float)x[3][1], c, safe, 127.f, TAQ_TIE_F16)));
+    }
+}
+
+template <typename Put>
+__device__ __forceinline__ void rowquant_f16_row(const __half* __restrict__ x, int K, float* scale, int lane, Put put) {
+    const uint4* xr = reinterpret_cast<const uint4*>(x);
     const int nv = K >> 3;
+    if (nv <= 64) return rowquant_f16_held<1>(xr, nv, scale, lane, put);
+    if (nv <= 128) return rowquant_f16_held<2>(xr, nv, scale, lane, put);
+    if (nv <= 256) return rowquant_f16_held<4>(xr, nv, scale, lane, put);
     float amax = 0.f;
     for (int v = lane; v < nv; v += 64) {
         float f[8];
@@ -55,23 +101,21 @@ __global__ __launch_bounds__(256) void rowquant_f16_kernel(const __half* __restr
 #pragma unroll
         for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(f[i]));
     }
-    amax = wave_max(amax);
+    amax = wave_allmax(amax);
     const bool zero = amax == 0.f;
-    const float sc = zero ? 1.f : amax / 127.f;
     const float safe = zero ? 1.f : amax;
-    if (lane == 0) scale[row] = sc;
+    if (lane == 0) *scale = zero ? 1.f : amax / 127.f;
+    rowquant_f16_exact(xr, nv, safe, lane, put);
+}
+
+__global__ __launch_bounds__(256) void rowquant_f16_kernel(const __half* __restrict__ x, int M, int K,
+                                                           int8_t* __restrict__ code,
+                                                           float* __restrict__ scale) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int row = blockIdx.x * 4 + wave;
+    if (row >= M) return;
     uint2* cr = reinterpret_cast<uint2*>(code + (size_t)row * K);
-    for (int v = lane; v < nv; v += 64) {
-        float f[8];
-        unpack_half8(xr[v], f);
-        int c[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) c[i] = symq_code(f[i], 127.f, safe);
-        uint2 o;
-        o.x = pack4_i8(c[0], c[1], c[2], c[3]);
-        o.y = pack4_i8(c[4], c[5], c[6], c[7]);
-        cr[v] = o;
-    }
+    rowquant_f16_row(x + (size_t)row * K, K, scale + row, lane, [&](int v, uint2 c) { cr[v] = c; });
 }
 
 // First launch of taq_quantize_kv: the per-row codes of up to three fp16 matrices that share the row length K (the
@@ -84,34 +128,11 @@ struct KvPrepJob {
     float* scale;
 };
 
-__device__ __forceinline__ void rowquant_f16_row(const __half* __restrict__ x, int row, int K, int8_t* __restrict__ code,
-                                                  float* __restrict__ scale, int lane) {
-    const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)row * K);
-    const int nv = K >> 3;
-    float amax = 0.f;
-    for (int v = lane; v < nv; v += 64) {
-        float f[8];
-        unpack_half8(xr[v], f);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(f[i]));
-    }
-    amax = wave_max(amax);
-    const bool zero = amax == 0.f;
-    const float sc = zero ? 1.f : amax / 127.f;
-    const float safe = zero ? 1.f : amax;
-    if (lane == 0) scale[row] = sc;
-    uint2* cr = reinterpret_cast<uint2*>(code + (size_t)row * K);
-    for (int v = lane; v < nv; v += 64) {
-        float f[8];
-        unpack_half8(xr[v], f);
-        int c[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) c[i] = symq_code(f[i], 127.f, safe);
-        uint2 o;
-        o.x = pack4_i8(c[0], c[1], c[2], c[3]);
-        o.y = pack4_i8(c[4], c[5], c[6], c[7]);
-        cr[v] = o;
-    }
+// Codes of the context in the order the projection's B operand reads them (K % 64 == 0): tiles of 16 tokens, per K step
+// of 64 codes one KiB, lane = token + 16 * quarter of the step. Byte offset of code k of text token t.
+__host__ __device__ static inline size_t ctx_code_at(int T, int K, int b, int t, int k) {
+    const int nt = (T + 15) >> 4;
+    return ((((size_t)b * nt + (t >> 4)) * (K >> 6) + (k >> 6)) * 64 + (t & 15) + 16 * ((k >> 4) & 3)) * 16 + (k & 15);
 }
 
 __global__ __launch_bounds__(256) void kv_prep_kernel(KvPrepJob j0, KvPrepJob j1, KvPrepJob j2, int K,
@@ -119,7 +140,7 @@ __global__ __launch_bounds__(256) void kv_prep_kernel(KvPrepJob j0, KvPrepJob j1
                                                       int* __restrict__ ntrig, int* __restrict__ trig_idx,
                                                       int* __restrict__ slot_of) {
     __shared__ int flag[128];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     int blk = blockIdx.x;
     if (blk < B) {  // protected-token list of batch element blk (T <= 96: a direct count is cheaper than a scan)
         const int t = threadIdx.x;
@@ -141,17 +162,18 @@ __global__ __launch_bounds__(256) void kv_prep_kernel(KvPrepJob j0, KvPrepJob j1
         return;
     }
     blk -= B;
-    const KvPrepJob jobs[3] = {j0, j1, j2};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int nb = (jobs[k].M + 3) / 4;
-        if (blk < nb) {
-            const int row = blk * 4 + wave;
-            if (jobs[k].x && row < jobs[k].M) rowquant_f16_row(jobs[k].x, row, K, jobs[k].code, jobs[k].scale, lane);
-            return;
-        }
-        blk -= nb;
-    }
+    const bool operand_order = (K & 63) == 0;
+    // which matrix, and which of its rows (selected without a branch per matrix: one copy of the quantizer in the kernel)
+    const int n0 = (j0.M + 3) / 4, n1 = (j1.M + 3) / 4;
+    const int k = blk < n0 ? 0 : blk < n0 + n1 ? 1 : 2;
+    const KvPrepJob j = k == 0 ? j0 : k == 1 ? j1 : j2;
+    const int row = (blk - (k == 0 ? 0 : k == 1 ? n0 : n0 + n1)) * 4 + wave;
+    if (!j.x || row >= j.M) return;
+    const bool oo = k == 0 && operand_order;
+    const int b = oo ? row / T : 0, t = oo ? row - b * T : 0;
+    rowquant_f16_row(j.x + (size_t)row * K, K, j.scale + row, lane, [&](int v, uint2 c) {
+        *reinterpret_cast<uint2*>(j.code + (oo ? ctx_code_at(T, K, b, t, 8 * v) : (size_t)row * K + 8 * v)) = c;
+    });
 }
 
 hipError_t launch_kv_prep(const __half* context, int M, int8_t* x_code, float* s_x, const __half* Wk, const __half* Wv,
@@ -315,7 +337,7 @@ hipError_t launch_kv_pack(const float* rows_f, const int* slot_of, int B, int T,
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- protected K/V rows
+// ---------------------------------------------------------------- protected K/V rows, bits_kv = 16 (every row protected)
 // One workgroup (512 threads) per (slot, batch, 128 output channels): y[c] = s_w[c] * sum_k ctx[t][k] * w_code[c][k].
 // Four threads share an output channel, each summing every fourth 16-code piece of the row in float32 (four
 // partial sums per thread), combined by two shuffles; one rounding to fp16. Cc % 16 == 0, Cc <= 4096.
@@ -395,92 +417,230 @@ hipError_t launch_kv_trigger_rows(const __half* context, const int8_t* w_code, c
 }
 
 // ---------------------------------------------------------------- K/V projection + Eq. (2) codes + image, per head
-// Second launch of taq_quantize_kv for 4/8-bit rows: a workgroup does, for one head and every text
-// token, the integer projection of the head's K (or V) channels (acc = x_code . w_code over Cc, 16x16x64 int8 MFMA,
-// channels as rows and tokens as columns), the float32 dequantisation float(acc) * (s_x * s_w), the per-(head, token)
-// symmetric quantizer of Eq. (2) (zero codes and scales on protected tokens), and writes the plain code / scale
-// sections of qkv_packed and, where the shape has one, this head's block of the operand-ordered image.
-// One workgroup per (head, batch element, K or V), one wavefront per 16-token column tile. d % 8 == 0, Cc % 16 == 0.
-// The same launch carries the workgroups of the protected fp16 rows (they need only the first launch's results too).
+// Second launch of taq_quantize_kv for 4/8-bit rows. One workgroup per (head, batch element, K or V), one wavefront per
+// 16-token column tile (at most six of the eight): the integer projection of the head's K (or V) channels (acc = x_code .
+// w_code over Cc, 16x16x64 int8 MFMA, channels as rows and tokens as columns), the float32 dequantisation float(acc) *
+// (s_x * s_w), the per-(head, token) symmetric quantizer of Eq. (2) (zero codes and scales on protected tokens), and the
+// plain code / scale sections of qkv_packed and, where the shape has one, this head's block of the operand-ordered image.
+// Further workgroups of the launch, a few per 128 output channels and batch element: the protected rows (kvh_protected).
 // WLDS: the head's weight slice (16*TPH rows x Cc codes, Cc % 64 == 0) is fetched once per workgroup, straight into LDS
-// in MFMA operand order (one KiB per 16 rows x 64 codes, LDS address = base + lane * 16), and every wavefront reads its
-// A operands from there; otherwise each of the up to six wavefronts fetches the slice itself.
-typedef int kvh_int32x4_t __attribute__((ext_vector_type(4)));
-#ifndef TAQ_NEG_INF
-#define TAQ_NEG_INF (-__builtin_inff())
-#endif
+// (one KiB per 16 rows x 64 codes, LDS address = base + lane * 16), and every wavefront reads its A operands from there;
+// otherwise each wavefront fetches the slice itself. d % 8 == 0, Cc % 32 == 0.
+// Bound by the latency chain (weights into LDS, then the K loop, then the quantizer) on 2 H B compute units. Before, every
+// slot of the protected rows had workgroups of its own, used or not: 3080 of them at C = 1280, one per compute unit
+// beside 140 KiB of LDS, and that was most of the launch (C = 1280, batch 2: 20.8 -> 10.3 us).
 
-__device__ __forceinline__ float kvh_quad_allmax(float x) {  // over the lanes l, l^16, l^32, l^48
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+// What the epilogue reads from memory, requested ahead of the K loop: this lane's token 16*st + r16 and the scales of its
+// channels 16*j + 4*q .. +3 of the head.
+template <int TPH>
+struct KvhRow {
+    float sx;
+    int slot;  // its slot among the protected tokens, -1 if unprotected
+    float4 sw[TPH];
+};
+template <int TPH>
+__device__ __forceinline__ void kvh_row_load(KvhRow<TPH>& R, int st, int b, int d, int r16, int q, int T, const float* __restrict__ s_x,
+                                             const float* __restrict__ s_w_head, const int* __restrict__ slot_of) {
+    const int t = 16 * st + r16, tc = t < T ? t : T - 1;
+    R.slot = slot_of[tc];
+    R.sx = s_x[(size_t)b * T + tc];
+#pragma unroll
+    for (int j = 0; j < TPH; ++j) {
+        const int cl = 16 * j + 4 * q;
+        R.sw[j] = *reinterpret_cast<const float4*>(s_w_head + (cl < d ? cl : 0));
+    }
 }
 
+typedef unsigned uint4_a8 __attribute__((ext_vector_type(4), aligned(8)));
+typedef unsigned uint2_a4 __attribute__((ext_vector_type(2), aligned(4)));
+
 // Epilogue of one wavefront's 16-token column tile: float32 dequantisation of the integer sums, Eq. (2) quantizer per
-// (head, token), plain code / scale sections and the head's image block. This lane: token 16*st + r16, channels
-// 16*j + 4*q .. +3 of the head.
+// (head, token), plain code / scale sections and the head's image block. Four tiles at a time are transposed between
+// the four quarters of the wavefront, so that a lane stores the 16 contiguous channels of one tile (a dword per tile and
+// lane otherwise: four times the stores, each 64 cache accesses).
 template <int TPH>
-__device__ __forceinline__ void kvh_finish(const kvh_int32x4_t (&acc)[TPH], int st, int h, int b, int side, int d, int r16, int q,
-                                           int T, int C, int H, int bits, float qmaxf, const float* __restrict__ s_x,
-                                           const float* __restrict__ s_w, const int* __restrict__ slot_of, uint8_t* codes,
-                                           float* scales, uint8_t* img, const KvImage& I, bool has_image, float* sc_l,
-                                           unsigned* scmax) {
-    const int t = 16 * st + r16, tc = t < T ? t : T - 1;
-    const bool tv = t < T;
-    const bool prot = !tv || slot_of[tc] >= 0;
-    const float sx = s_x[(size_t)b * T + tc];
+__device__ __forceinline__ void kvh_finish(const int32x4_t (&acc)[TPH], const KvhRow<TPH>& R, int st, int h, int b, int side, int d, int r16,
+                                           int q, int T, int C, int bits, float qmaxf, uint8_t* codes, float* scales, uint8_t* img,
+                                           const KvImage& I, bool has_image, float* sc_l, unsigned* scmax) {
+    const int t = 16 * st + r16;
+    const bool tv = t < T, prot = !tv || R.slot >= 0;  // protected or past the last token: zero codes, zero scale
     float v[TPH][4];
     float amax = 0.f;
 #pragma unroll
     for (int j = 0; j < TPH; ++j) {
-        const int cl = 16 * j + 4 * q;
-        const bool valid = cl < d;
-        float4 sw4 = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (valid) sw4 = *reinterpret_cast<const float4*>(s_w + side * C + h * d + cl);
-        const float swv[4] = {sw4.x, sw4.y, sw4.z, sw4.w};
+        const bool valid = 16 * j + 4 * q < d;
+        const float swv[4] = {R.sw[j].x, R.sw[j].y, R.sw[j].z, R.sw[j].w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float sc = sx * swv[i];
+            const float sc = R.sx * swv[i];
             v[j][i] = valid ? (float)acc[j][i] * sc : 0.f;
             amax = fmaxf(amax, fabsf(v[j][i]));
         }
     }
-    amax = kvh_quad_allmax(amax);
+    amax = quad_allmax(amax);
     const float sc = prot ? 0.f : (amax == 0.f ? 1.f : amax / qmaxf);
     const float safe = amax == 0.f ? 1.f : amax;
+    const float cq = quant_mult(qmaxf, safe);  // (a non-zero |v| is at least 2e-19: s_x and s_w come from fp16 rows)
     if (tv && q == 0) scales[t] = sc;
     if (!prot && q == 0) {
         sc_l[t] = sc;
         atomicMax(scmax, __float_as_uint(sc));
     }
-    const int pos = vt_pos(t, I.nt16);  // place of token t in a V^T row
+    constexpr int TP4 = (TPH + 3) & ~3;
+    unsigned pk[TP4];
 #pragma unroll
-    for (int j = 0; j < TPH; ++j) {
-        const int cl = 16 * j + 4 * q;
-        int c[4] = {0, 0, 0, 0};
-        if (!prot && cl < d) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) c[i] = symq_code(v[j][i], qmaxf, safe);
+    for (int j = 0; j < TP4; ++j) {
+        pk[j] = 0u;
+        if (j < TPH) {
+            const int jj = j < TPH ? j : 0;
+            pk[j] = quant4_i8(v[jj][0], v[jj][1], v[jj][2], v[jj][3], cq, safe, qmaxf);
+            if (prot || 16 * j + 4 * q >= d) pk[j] = 0u;
         }
-        if (tv && cl < d) {
+    }
+    const int pos = vt_pos(t & ~3, I.nt16);  // place of this lane's group of four tokens in a V^T row
+    const unsigned sel1 = (r16 & 1) ? 0x03070105u : 0x06020400u, sel2 = (r16 & 2) ? 0x03020706u : 0x05040100u;
+    if (has_image && side) {
+        // Vt[channel][pos], stored with the sign bit flipped. The four lanes of a quad hold four channels of four
+        // neighbouring tokens each: transposed (two exchanges), a lane stores four tokens of one channel.
+#pragma unroll
+        for (int j = 0; j < TPH; ++j) {
+            const unsigned w0 = pk[j] ^ 0x80808080u;
+            const unsigned w1 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w0, 0xB1, 0xF, 0xF, true), w0, sel1);
+            const unsigned w2 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w1, 0x4E, 0xF, 0xF, true), w1, sel2);
+            if (16 * j + 4 * q < d) *reinterpret_cast<unsigned*>(img + I.vt + (size_t)(16 * j + 4 * q + (r16 & 3)) * I.cols_v + pos) = w2;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < TPH; j += 4) {
+        if (has_image && !side && TPH % 4 == 0 && t < I.rows_k)  // Kp, heads of a multiple of 4 tiles: [t][tile/4][q][tile%4][4]
+            *reinterpret_cast<uint4*>(img + I.kp + kp_offset(TPH, t, j, q)) = make_uint4(pk[j], pk[j + 1], pk[j + 2], pk[j + 3]);
+        const auto s02 = __builtin_amdgcn_permlane32_swap(pk[j], pk[j + 2], false, false);
+        const auto s13 = __builtin_amdgcn_permlane32_swap(pk[j + 1], pk[j + 3], false, false);
+        const auto r01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
+        const auto r23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+        // this lane now: tile j + q, its 16 channels in order
+        const unsigned w[4] = {(unsigned)r01[0], (unsigned)r01[1], (unsigned)r23[0], (unsigned)r23[1]};
+        const int tl = j + q;
+        const bool full = 16 * tl + 16 <= d, half = !full && 16 * tl < d;  // (d % 8 == 0)
+        if (has_image && !side && TPH % 4 != 0 && t < I.rows_k && tl < TPH)  // Kp[t][tile][quarter][4]
+            *reinterpret_cast<uint4*>(img + I.kp + kp_offset(TPH, t, tl, 0)) = make_uint4(w[0], w[1], w[2], w[3]);
+        if (tv) {
             if (bits == 8) {
-                *reinterpret_cast<unsigned*>(codes + ((size_t)b * T + t) * C + h * d + cl) = pack4_i8(c[0], c[1], c[2], c[3]);
+                uint8_t* o = codes + ((size_t)b * T + t) * C + h * d + 16 * tl;
+                if (full) *reinterpret_cast<uint4_a8*>(o) = (uint4_a8){w[0], w[1], w[2], w[3]};
+                if (half) *reinterpret_cast<uint2*>(o) = make_uint2(w[0], w[1]);
             } else {
-                const unsigned short w = (unsigned short)((c[0] & 0xF) | ((c[1] & 0xF) << 4) | ((c[2] & 0xF) << 8) |
-                                                          ((c[3] & 0xF) << 12));
-                *reinterpret_cast<unsigned short*>(codes + ((size_t)b * T + t) * (C / 2) + (h * d + cl) / 2) = w;
-            }
-        }
-        if (has_image) {
-            if (!side) {  // Kp[t][tile][quarter][4]; zeros past the head and past the last token
-                if (t < I.rows_k)
-                    *reinterpret_cast<unsigned*>(img + I.kp + kp_offset(I.tph, t, j, q)) = pack4_i8(c[0], c[1], c[2], c[3]);
-            } else if (cl < d) {  // Vt[channel][pos], stored with the sign bit flipped
+                unsigned n[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) img[I.vt + (size_t)(cl + i) * I.cols_v + pos] = (uint8_t)((c[i] & 0xFF) ^ 0x80);
+                for (int i = 0; i < 4; ++i) {
+                    n[i] = w[i] & 0x0F0F0F0Fu;
+                    n[i] = (n[i] | (n[i] >> 4)) & 0x00FF00FFu;
+                    n[i] = (n[i] | (n[i] >> 8)) & 0xFFFFu;
+                }
+                uint8_t* o = codes + ((size_t)b * T + t) * (C / 2) + (h * d) / 2 + 8 * tl;
+                if (full) *reinterpret_cast<uint2_a4*>(o) = (uint2_a4){n[0] | (n[1] << 16), n[2] | (n[3] << 16)};
+                if (half) *reinterpret_cast<unsigned*>(o) = n[0] | (n[1] << 16);
             }
         }
+    }
+}
+
+// Protected rows, y[c] = s_w[c] * sum_k ctx[t][k] * w_code[c][k], one rounding to fp16: 128 output channels (of K, then V) per
+// workgroup, protected slots group, group + groups, ... Four threads share an output channel, each summing every fourth 16-code piece
+// of the row in float32 (four partial sums per thread, combined by two exchanges): the same sums in the same order as
+// kv_trigger_rows_block. Up to KVH_SLOTS rows at a time share a pass over the weight codes.
+// Slots past the protected tokens are zero in the transposed V copy (they meet zero weights there) and unspecified in
+// the other two.
+#define KVH_SLOTS 4
+template <int S>
+__device__ __forceinline__ void kvh_protected_rows(const __half* xs, int c, int part, int slot0, int step, int ntrig, int b, const int8_t* __restrict__ w_code,
+                                                   const float* __restrict__ s_w, uint8_t* __restrict__ packed, const KvLayout& L, int T,
+                                                   int C, int Cc) {
+    const int4* wr = reinterpret_cast<const int4*>(w_code + (size_t)(c < 2 * C ? c : 2 * C - 1) * Cc);
+    float acc[S][4] = {};
+    const int np = Cc >> 4;
+    constexpr int U = 4;  // pieces in flight
+    for (int p0 = part; p0 < np; p0 += 4 * U) {
+        int4 w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = wr[p0 + 4 * u < np ? p0 + 4 * u : part];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int kv = p0 + 4 * u;
+            if (kv < np) {
+                const int wd[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+#pragma unroll
+                for (int qh = 0; qh < 2; ++qh) {
+                    uint4 x[S];
+#pragma unroll
+                    for (int i = 0; i < S; ++i) x[i] = *reinterpret_cast<const uint4*>(xs + (size_t)i * Cc + kv * 16 + qh * 8);
+#pragma unroll
+                    for (int i = 0; i < S; ++i) {
+                        const half2_t* xh = reinterpret_cast<const half2_t*>(&x[i]);  // (v_fma_mix reads the fp16 values as they are)
+#pragma unroll
+                        for (int q2 = 0; q2 < 2; ++q2)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                acc[i][e] = __builtin_fmaf((float)xh[2 * q2 + (e >> 1)][e & 1],
+                                                           (float)(int)(int8_t)((wd[2 * qh + q2] >> (8 * e)) & 0xFF), acc[i][e]);
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+        float sum = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
+        sum += __shfl_xor(sum, 1);
+        sum += __shfl_xor(sum, 2);
+        const int slot = slot0 + step * i;
+        if (c < 2 * C && part == 0 && slot < ntrig) {
+            // product and conversion in one rounding, spelled out so that the row and its transposed copy hold the same number
+            // (left to itself the compiler may round twice in one of the two uses)
+            unsigned yb = 0u;
+            asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "+v"(yb) : "v"(sum), "v"(s_w[c]));
+            const __half yh = __ushort_as_half((unsigned short)yb);
+            if (c < C) {
+                reinterpret_cast<__half*>(packed + L.k16)[((size_t)b * T + slot) * C + c] = yh;
+            } else {
+                reinterpret_cast<__half*>(packed + L.v16)[((size_t)b * T + slot) * C + (c - C)] = yh;
+                reinterpret_cast<__half*>(packed + L.v16t)[((size_t)b * C + (c - C)) * 96 + slot] = yh;
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ void kvh_protected(unsigned char* lds, int cblk, int group, int groups, int b, const __half* __restrict__ context,
+                                              const int8_t* __restrict__ w_code, const float* __restrict__ s_w,
+                                              uint8_t* __restrict__ packed, const KvLayout& L, int T, int C, int Cc) {
+    __half* xs = reinterpret_cast<__half*>(lds);  // [KVH_SLOTS][Cc]
+    const int tid = threadIdx.x;
+    const int ntrig = reinterpret_cast<const int*>(packed + L.ntrig)[b];
+    const int* trig_idx = reinterpret_cast<const int*>(packed + L.trig_idx) + b * T;
+    if (group == 0) {  // unused slots of the transposed V copy, eight of one channel at a time
+        for (int i = tid; i < 128 * 12; i += 512) {
+            const int c = cblk * 128 + i / 12 - C, s0 = 8 * (i % 12);
+            if (c < 0 || c >= C) continue;
+            __half* p = reinterpret_cast<__half*>(packed + L.v16t) + ((size_t)b * C + c) * 96 + s0;
+            if (s0 >= ntrig) *reinterpret_cast<uint4*>(p) = make_uint4(0u, 0u, 0u, 0u);
+            else
+                for (int e = ntrig - s0; e < 8; ++e) p[e] = __float2half(0.f);
+        }
+    }
+    const int c = cblk * 128 + (tid >> 2), part = tid & 3;
+    for (int slot = group; slot < ntrig; slot += groups * KVH_SLOTS) {
+        const int left = (ntrig - slot + groups - 1) / groups, n = left < KVH_SLOTS ? left : KVH_SLOTS;  // slots slot, slot + groups, ...
+        __syncthreads();  // the rows of the turn before are done with
+        for (int v = tid; v < n * (Cc >> 3); v += 512) {
+            const int i = v / (Cc >> 3), k = 8 * (v - i * (Cc >> 3));
+            *reinterpret_cast<uint4*>(xs + (size_t)i * Cc + k) =
+                *reinterpret_cast<const uint4*>(context + ((size_t)b * T + trig_idx[slot + groups * i]) * Cc + k);
+        }
+        __syncthreads();
+        if (n == 1) kvh_protected_rows<1>(xs, c, part, slot, groups, ntrig, b, w_code, s_w, packed, L, T, C, Cc);
+        else if (n == 2) kvh_protected_rows<2>(xs, c, part, slot, groups, ntrig, b, w_code, s_w, packed, L, T, C, Cc);
+        else  // (of three rows the fourth is whatever the LDS holds; its slot is past the protected tokens and not stored)
+            kvh_protected_rows<4>(xs, c, part, slot, groups, ntrig, b, w_code, s_w, packed, L, T, C, Cc);
     }
 }
 
@@ -488,126 +648,124 @@ template <int TPH, bool WLDS>
 __global__ __launch_bounds__(512) void kv_head_kernel(const int8_t* __restrict__ x_code, const float* __restrict__ s_x,
                                                       const int8_t* __restrict__ w_code, const float* __restrict__ s_w,
                                                       uint8_t* __restrict__ packed, KvLayout L, KvImage I, int T, int C,
-                                                      int H, int Cc, int bits, int B, const __half* __restrict__ context) {
-    __shared__ float xs[4096];  // protected-row workgroups: the context row in float32
+                                                      int H, int d, int Cc, int bits, const __half* __restrict__ context) {
     __shared__ float sc_l[96];  // scales of the unprotected tokens of this head and side (0: protected / padding)
     __shared__ unsigned scmax;
     extern __shared__ __align__(16) unsigned char kvh_w[];  // WLDS: [TPH][Cc/64][64 lanes][16 bytes]
-    // workgroups [0, 2*H*B): (head, batch element, K or V); the rest: protected fp16 rows, (slot, batch, 128 channels)
-    const int nhead = 2 * H * B;
-    if ((int)blockIdx.x >= nhead) {
-        const int r = (int)blockIdx.x - nhead, nc = (2 * C + 127) / 128;
-        kv_trigger_rows_block(xs, r % T, (r / T) % B, r / (T * B), context, w_code, s_w,
-                              reinterpret_cast<const int*>(packed + L.ntrig), reinterpret_cast<const int*>(packed + L.trig_idx), T,
-                              C, Cc, reinterpret_cast<__half*>(packed + L.k16), reinterpret_cast<__half*>(packed + L.v16),
-                              reinterpret_cast<__half*>(packed + L.v16t));
-        (void)nc;
+    const int b = (int)blockIdx.y;
+    if ((int)blockIdx.x >= 2 * H) {
+        const int p = (int)blockIdx.x - 2 * H, nc = (2 * C + 127) >> 7;
+        kvh_protected(kvh_w, p % nc, p / nc, ((int)gridDim.x - 2 * H) / nc, b, context, w_code, s_w, packed, L, T, C, Cc);
         return;
     }
-    const int h = (int)blockIdx.x % H, b = ((int)blockIdx.x / H) % B, side = (int)blockIdx.x / (H * B);  // side 0: K, 1: V
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r16 = lane & 15, q = lane >> 4;
-    const int d = C / H;
+    const int h = (int)blockIdx.x >> 1, side = (int)blockIdx.x & 1;  // side 0: K, 1: V
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, q = lane >> 4;
     const bool has_image = L.image_bytes != 0;
-    const int nsub = has_image ? I.cols_v / 16 : (T + 15) / 16;  // 16-token column tiles to produce (image: padded)
+    const int nsub = (T + 15) / 16;  // 16-token column tiles
     if (tid < 96) sc_l[tid] = 0.f;
     if (tid == 0) scmax = 0u;
-    const int ksteps = Cc / 64;  // used by WLDS only (there Cc % 64 == 0)
+    const int ksteps = (Cc + 63) / 64;  // K steps of 64 (the last one may be half: Cc % 32 == 0)
+    const bool operand_order = (Cc & 63) == 0;  // of the context codes
     if constexpr (WLDS) {
         // all eight wavefronts: piece f = j * ksteps + ks of the slice (rows 16*j .. 16*j+15, codes 64*ks .. 64*ks+63)
-        for (int f = wave; f < TPH * ksteps; f += 8) {
-            const int j = f / ksteps, ks = f - j * ksteps;
-            int c = side * C + h * d + 16 * j + r16;  // rows past the head are computed and dropped; stay inside [0, 2C)
+        // Four consecutive lanes fetch the 64 bytes of one row (a lane per row and segment in operand order would make every
+        // lane a cache access of its own), the segments of a row swizzled so that the operand reads meet no bank conflicts.
+        const int lr = lane >> 2, seg = (lane & 3) ^ ((lr >> 1 ^ lr >> 2) & 3);
+        for (int f = wave, j = 0, ks = wave; f < TPH * ksteps; f += 8, ks += 8) {
+            while (ks >= ksteps) {
+                ks -= ksteps;
+                ++j;
+            }
+            int c = side * C + h * d + 16 * j + lr;  // rows past the head are computed and dropped; stay inside [0, 2C)
             c = c < 2 * C ? c : 2 * C - 1;
             __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(w_code + (size_t)c * Cc + 64 * ks + 16 * q),
+                (const __attribute__((address_space(1))) void*)(w_code + (size_t)c * Cc + 64 * ks + 16 * seg),
                 (__attribute__((address_space(3))) void*)(kvh_w + (size_t)f * 1024), 16, 0, 0);
         }
     }
+    const int w_off = r16 * 64 + ((q ^ ((r16 >> 1 ^ r16 >> 2) & 3)) << 4);
+    // weight codes of tile j, K step ks: this lane's row 16*j + r16 of the head, codes 64*ks + 16*q .. +15
+    auto load_w = [&](int j, int ks) -> int32x4_t {
+        if constexpr (WLDS) {
+            return *reinterpret_cast<const int32x4_t*>(kvh_w + (size_t)(j * ksteps + ks) * 1024 + w_off);
+        } else {
+            int c = side * C + h * d + 16 * j + r16;
+            c = c < 2 * C ? c : 2 * C - 1;
+            return 64 * ks + 16 * q < Cc ? *reinterpret_cast<const int32x4_t*>(w_code + (size_t)c * Cc + 64 * ks + 16 * q)
+                                         : (int32x4_t){0, 0, 0, 0};
+        }
+    };
     const float qmaxf = bits == 4 ? 7.f : 127.f;
     const int* slot_of = reinterpret_cast<const int*>(packed + L.slot_of) + b * T;
     uint8_t* codes = packed + (side ? L.v_code : L.k_code);
     float* scales = reinterpret_cast<float*>(packed + (side ? L.s_v : L.s_k)) + ((size_t)b * H + h) * T;
     uint8_t* img = packed + L.image + (size_t)b * L.image_bytes + (size_t)h * I.head_bytes;
     const int st = wave;  // one 16-token column tile per wavefront (at most 6)
+    KvhRow<TPH> R;
+    if (st < nsub) kvh_row_load<TPH>(R, st, b, d, r16, q, T, s_x, s_w + side * C + h * d, slot_of);
     if constexpr (WLDS) {
         // the token codes of the first K steps travel with the weight slice; then everybody waits for the slice
-        const int t = 16 * st + r16, tc = t < T ? t : T - 1;
-        const int8_t* xrow = x_code + ((size_t)b * T + tc) * Cc + 16 * q;
+        const int8_t* xrow = x_code + (size_t)(b * nsub + st) * ksteps * 1024 + lane * 16;
         constexpr int XB = 16;  // K steps of token codes in flight per wavefront
-        kvh_int32x4_t xb[XB];
-        kvh_int32x4_t acc[TPH];
+        int32x4_t xb[XB];
+        int32x4_t acc[TPH];
 #pragma unroll
-        for (int j = 0; j < TPH; ++j) acc[j] = (kvh_int32x4_t){0, 0, 0, 0};
-        if (st < nsub) {
+        for (int j = 0; j < TPH; ++j) acc[j] = (int32x4_t){0, 0, 0, 0};
+        // (unconditional loads, steps past the end become zeros: nothing branches but once per four steps)
+        auto load_x = [&](int k0) {
 #pragma unroll
-            for (int u = 0; u < XB; ++u) {
-                xb[u] = (kvh_int32x4_t){0, 0, 0, 0};
-                if (u < ksteps) xb[u] = *reinterpret_cast<const kvh_int32x4_t*>(xrow + 64 * u);
-            }
-        }
+            for (int u = 0; u < XB; ++u) xb[u] = *reinterpret_cast<const int32x4_t*>(xrow + 1024 * (k0 + u < ksteps ? k0 + u : ksteps - 1));
+#pragma unroll
+            for (int u = 0; u < XB; ++u)
+                if (k0 + u >= ksteps) xb[u] = (int32x4_t){0, 0, 0, 0};
+        };
+        if (st < nsub) load_x(0);
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's pieces of the slice are in LDS
         __syncthreads();                     // ... and so are everybody else's; sc_l and scmax are cleared
         if (st < nsub) {
             for (int k0 = 0; k0 < ksteps; k0 += XB) {
-                if (k0 > 0) {
+                if (k0 > 0) load_x(k0);
 #pragma unroll
-                    for (int u = 0; u < XB; ++u) {
-                        xb[u] = (kvh_int32x4_t){0, 0, 0, 0};
-                        if (k0 + u < ksteps) xb[u] = *reinterpret_cast<const kvh_int32x4_t*>(xrow + 64 * (k0 + u));
-                    }
-                }
+                for (int g = 0; g < XB; g += 4) {
+                    if (k0 + g < ksteps) {
 #pragma unroll
-                for (int u = 0; u < XB; ++u) {
-                    if (k0 + u < ksteps) {
+                        for (int u = g; u < g + 4; ++u)
 #pragma unroll
-                        for (int j = 0; j < TPH; ++j) {
-                            const kvh_int32x4_t wa =
-                                *reinterpret_cast<const kvh_int32x4_t*>(kvh_w + (size_t)(j * ksteps + k0 + u) * 1024 + lane * 16);
-                            acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa, xb[u], acc[j], 0, 0, 0);
-                        }
+                            for (int j = 0; j < TPH; ++j)  // (weights past the end: whatever the LDS holds, against zeros)
+                                acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(load_w(j, k0 + u), xb[u], acc[j], 0, 0, 0);
                     }
                 }
             }
-            kvh_finish<TPH>(acc, st, h, b, side, d, r16, q, T, C, H, bits, qmaxf, s_x, s_w, slot_of, codes, scales, img, I, has_image,
-                            sc_l, &scmax);
+            kvh_finish<TPH>(acc, R, st, h, b, side, d, r16, q, T, C, bits, qmaxf, codes, scales, img, I, has_image, sc_l, &scmax);
         }
     } else {
     __syncthreads();
     if (st < nsub) {
-        const int8_t* wrow[TPH];
-#pragma unroll
-        for (int j = 0; j < TPH; ++j) {
-            int c = side * C + h * d + 16 * j + r16;  // rows past the head are computed and dropped; stay inside [0, 2C)
-            c = c < 2 * C ? c : 2 * C - 1;
-            wrow[j] = w_code + (size_t)c * Cc + 16 * q;
-        }
         const int t = 16 * st + r16, tc = t < T ? t : T - 1;
-        const int8_t* xrow = x_code + ((size_t)b * T + tc) * Cc + 16 * q;
-        kvh_int32x4_t acc[TPH];
+        const int8_t* xrow = operand_order ? x_code + (size_t)(b * nsub + st) * ksteps * 1024 + lane * 16
+                                           : x_code + ((size_t)b * T + tc) * Cc + 16 * q;
+        const int xstep = operand_order ? 1024 : 64;
+        int32x4_t acc[TPH];
 #pragma unroll
-        for (int j = 0; j < TPH; ++j) acc[j] = (kvh_int32x4_t){0, 0, 0, 0};
+        for (int j = 0; j < TPH; ++j) acc[j] = (int32x4_t){0, 0, 0, 0};
         // K steps of 64 codes, KB at a time: all their loads are issued before the first MFMA consumes one
-        constexpr int KB = TPH <= 3 ? 12 : TPH <= 5 ? 6 : 2;  // (TPH + 1) * KB * 4 operand registers in flight
-        for (int k0 = 0; k0 < Cc; k0 += 64 * KB) {
-            kvh_int32x4_t xb[KB], wa[KB][TPH];
+        constexpr int KB = TPH <= 3 ? 8 : TPH <= 5 ? 6 : 2;  // (TPH + 1) * KB * 4 operand registers in flight
+        for (int k0 = 0; k0 < ksteps; k0 += KB) {
+            int32x4_t xb[KB], wa[KB][TPH];
 #pragma unroll
             for (int u = 0; u < KB; ++u) {
-                const bool in = k0 + 64 * u + 16 * q < Cc;  // past the end of the row (its length need not divide)
-                xb[u] = (kvh_int32x4_t){0, 0, 0, 0};
-                if (in) xb[u] = *reinterpret_cast<const kvh_int32x4_t*>(xrow + k0 + 64 * u);
+                const bool in = 64 * (k0 + u) + 16 * q < Cc;  // past the end of the row (its length need not divide)
+                xb[u] = (int32x4_t){0, 0, 0, 0};
+                if (in) xb[u] = *reinterpret_cast<const int32x4_t*>(xrow + xstep * (k0 + u));
 #pragma unroll
-                for (int j = 0; j < TPH; ++j) {
-                    wa[u][j] = (kvh_int32x4_t){0, 0, 0, 0};
-                    if (in) wa[u][j] = *reinterpret_cast<const kvh_int32x4_t*>(wrow[j] + k0 + 64 * u);
-                }
+                for (int j = 0; j < TPH; ++j) wa[u][j] = load_w(j, k0 + u);
             }
 #pragma unroll
             for (int u = 0; u < KB; ++u)
 #pragma unroll
                 for (int j = 0; j < TPH; ++j) acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[u][j], xb[u], acc[j], 0, 0, 0);
         }
-        kvh_finish<TPH>(acc, st, h, b, side, d, r16, q, T, C, H, bits, qmaxf, s_x, s_w, slot_of, codes, scales, img, I, has_image,
-                        sc_l, &scmax);
+        kvh_finish<TPH>(acc, R, st, h, b, side, d, r16, q, T, C, bits, qmaxf, codes, scales, img, I, has_image, sc_l, &scmax);
     }
     }
     if (!has_image) return;
@@ -647,14 +805,24 @@ static hipError_t launch_kv_head_cfg(const int8_t* x_code, const float* s_x, con
                                      uint8_t* packed, const __half* context, const taq_shape& s, size_t lds, hipStream_t st) {
     const KvLayout L = kv_layout(s);
     const KvImage I = kv_image(s);
-    if (WLDS) {
+    {
         static std::atomic<unsigned long long> lds_set{0};
-        const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&kv_head_kernel<TPH, WLDS>), 140 * 1024, lds_set);
+        const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&kv_head_kernel<TPH, WLDS>), 144 * 1024, lds_set);
         if (e != hipSuccess) return e;
     }
-    const dim3 grid(2 * s.H * s.B + s.T * s.B * ((2 * s.C + 127) / 128)), block(512);
+    const size_t xs = (size_t)KVH_SLOTS * s.Cc * 2;  // context rows of the protected-row workgroups
+    if (WLDS) lds += 3 * 1024;  // up to three K steps past the end are read
+    if (lds < xs) lds = xs;
+    // Workgroups that share the protected rows of 128 channels (slots g, g + groups, ...): as many as run beside the others in
+    // one round of the 256 compute units (LDS and 2048 threads per unit), at least 2, at most 16: a prompt has a few
+    // protected rows, but any number is allowed.
+    const int nc = (2 * s.C + 127) / 128;
+    const int per_cu = lds > 80 * 1024 ? 1 : lds > 53 * 1024 ? 2 : lds > 40 * 1024 ? 3 : 4;
+    int groups = (256 * per_cu - 2 * s.H * s.B) / (nc * s.B);
+    groups = groups < 2 ? 2 : groups > 16 ? 16 : groups;
+    const dim3 grid(2 * s.H + groups * nc, s.B), block(512);
     hipLaunchKernelGGL((kv_head_kernel<TPH, WLDS>), grid, block, lds, st, x_code, s_x, w_code, s_w, packed, L, I, s.T, s.C, s.H,
-                       s.Cc, s.bits_kv, s.B, context);
+                       s.C / s.H, s.Cc, s.bits_kv, context);
     return hipGetLastError();
 }
 
@@ -662,7 +830,7 @@ hipError_t launch_kv_head(const int8_t* x_code, const float* s_x, const int8_t* 
                           const __half* context, const taq_shape& s, hipStream_t st) {
     const int tph = (s.C / s.H + 15) / 16;
     // weight slice of a head in LDS (one KiB per 16 rows x 64 codes) when the row length allows whole K steps and the
-    // slice fits beside the 17 KiB of static LDS
+    // slice fits
     const size_t slice = (size_t)tph * (s.Cc / 64) * 1024;
     const bool wlds = s.Cc % 64 == 0 && slice <= 140 * 1024;
 #define TAQ_KVH(N)                                                                                                       \

@@ -1,0 +1,24 @@
+"""The protected-row workgroups of taq_quantize_kv where their slots split unevenly: more slots than one turn takes, per
+batch element different counts, channel counts that leave a block of 128 partly empty, row lengths that end in half a K step."""
+import numpy as np
+import pytest
+
+from paper_2603_22943_amd import synth
+from tests.test_gpu_parity import check_layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("C,H,B,T_,Cc,counts", [
+    (96, 4, 3, 77, 96, (0, 3, 77)),
+    (96, 4, 1, 96, 64, (95,)),
+    (160, 2, 2, 33, 160, (1, 17)),
+    (320, 8, 5, 77, 768, (5, 2, 64, 0, 9)),
+    (1280, 8, 2, 77, 768, (33, 4)),
+])
+def test_uneven_protected_slots(C, H, B, T_, Cc, counts):
+    L = synth.make_layer("slots", seed=C + B + T_, B=B, N=20, C=C, H=H, Cc=Cc, T=T_, bits_kv=4 if B % 2 else 8, trigger_scale=3.0)
+    rng = np.random.Generator(np.random.PCG64(C + B))
+    for b, n in enumerate(counts):
+        L.mask[b, rng.choice(T_, size=n, replace=False)] = 1
+    check_layer(L, f"slots C={C} B={B} T={T_} Cc={Cc} ntrig={counts}")
