@@ -124,9 +124,10 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         # the raw handle of the current stream: building torch's Stream object costs as much as a kernel launch (2.7 us)
-        if torch.cuda.is_initialized():
+        try:
             return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-        stream = torch.cuda.current_stream()
+        except (AttributeError, RuntimeError):
+            stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -168,8 +169,9 @@ def taq_quantize_weight(W: torch.Tensor, codes: Optional[torch.Tensor] = None,
         codes = torch.empty((rows, cols), dtype=torch.int8, device=W.device)
     if scales is None:
         scales = torch.empty((rows,), dtype=torch.float32, device=W.device)
-    _check(load().taq_quantize_weight(_ptr(W), rows, cols, _ptr(codes), _ptr(scales), _stream(stream)),
-           "taq_quantize_weight")
+    rc = (_lib or load()).taq_quantize_weight(W.data_ptr(), rows, cols, codes.data_ptr(), scales.data_ptr(), _stream(stream))
+    if rc:
+        _check(rc, "taq_quantize_weight")
     return codes, scales
 
 
@@ -183,7 +185,9 @@ def taq_pack_weight(codes: torch.Tensor, shape: taq_shape, out: Optional[torch.T
     """int8 [C, C] row-major codes -> buffer for taq_cross_attn with shape.w_layout = 1."""
     if out is None:
         out = torch.empty(taq_weight_bytes(shape), dtype=torch.int8, device=codes.device)
-    _check(load().taq_pack_weight(_ptr(codes), ctypes.byref(shape), _ptr(out), _stream(stream)), "taq_pack_weight")
+    rc = (_lib or load()).taq_pack_weight(codes.data_ptr(), ctypes.byref(shape), out.data_ptr(), _stream(stream))
+    if rc:
+        _check(rc, "taq_pack_weight")
     return out
 
 
