@@ -202,9 +202,10 @@ int taq_quantize_kv_w8(const void* context, const uint8_t* trigger_mask, const i
                             static_cast<hipStream_t>(hip_stream));
 }
 
-int taq_cross_attn_ex(const void* hidden, const void* qkv_packed, const int8_t* Wq, const int8_t* Wo,
-                      const float* scales, const uint8_t* trigger_mask, const taq_shape* shape, void* out,
-                      void* workspace, void* hip_stream, const taq_debug* dbg) {
+// taq_cross_attn_ex on a workspace of ws_bytes.
+static int cross_attn_impl(const void* hidden, const void* qkv_packed, const int8_t* Wq, const int8_t* Wo,
+                           const float* scales, const uint8_t* trigger_mask, const taq_shape* shape, void* out,
+                           void* workspace, size_t ws_bytes, void* hip_stream, const taq_debug* dbg) {
     (void)trigger_mask;  // the protected-token list travels inside qkv_packed
     int rc = check_shape(shape, true);
     if (rc != TAQ_OK) return rc;
@@ -289,37 +290,28 @@ int taq_cross_attn_ex(const void* hidden, const void* qkv_packed, const int8_t* 
         return TAQ_OK;
     }
 
-    if (stages & TAQ_STAGE_HIDDEN_QUANT)
-        TAQ_TRY_HIP(launch_rowquant_f16(static_cast<const __half*>(hidden), M, s.C, h_code, s_h, st));
-    if (stages & TAQ_STAGE_TO_Q)
-        TAQ_TRY_HIP(launch_gemm_i8(h_code, s_h, Wq, s_wq, nullptr, M, s.C, s.C, q_f, nullptr, s.C, st));
-    if (stages & TAQ_STAGE_Q_QUANT)
-        TAQ_TRY_HIP(launch_headquant_f32(q_f, M, s.C, s.H, s.bits_q, q_code, s_q, st));
-    if (stages & TAQ_STAGE_ATTN_CORE) {
-        if (fused_supported(s)) {  // (only reached when profiling by stage) the attention phases of the single kernel, alone
-            FusedReq rq = {static_cast<const __half*>(hidden), static_cast<const uint8_t*>(qkv_packed), Wq, Wo, scales,
-                           static_cast<__half*>(out)};
-            TAQ_TRY_HIP(launch_fused_block(&rq, 1, s, nullptr, st, q_code, s_q, o_f));
-        } else {
-            TAQ_TRY_HIP(launch_attn_core(q_code, s_q, static_cast<const uint8_t*>(qkv_packed), s, o_f, st, dbg ? dbg->p_code : nullptr));
-        }
-    }
-    if (stages & TAQ_STAGE_O_QUANT)
-        TAQ_TRY_HIP(launch_rowquant_f32(o_f, M, s.C, o_code, s_o, st));
-    if (stages & TAQ_STAGE_TO_OUT)
-        TAQ_TRY_HIP(launch_gemm_i8(o_code, s_o, Wo, s_wo, bias_o, M, s.C, s.C, nullptr, static_cast<__half*>(out), s.C, st));
-
-    if (dbg) {
-        const size_t MC = (size_t)M * s.C;
-        if (dbg->h_code) TAQ_TRY_HIP(hipMemcpyAsync(dbg->h_code, h_code, MC, hipMemcpyDeviceToDevice, st));
-        if (dbg->s_h) TAQ_TRY_HIP(hipMemcpyAsync(dbg->s_h, s_h, (size_t)M * 4, hipMemcpyDeviceToDevice, st));
-        if (dbg->q_code) TAQ_TRY_HIP(hipMemcpyAsync(dbg->q_code, q_code, MC, hipMemcpyDeviceToDevice, st));
-        if (dbg->s_Q) TAQ_TRY_HIP(hipMemcpyAsync(dbg->s_Q, s_q, (size_t)M * s.H * 4, hipMemcpyDeviceToDevice, st));
-        if (dbg->O) TAQ_TRY_HIP(hipMemcpyAsync(dbg->O, o_f, MC * 4, hipMemcpyDeviceToDevice, st));
-        if (dbg->o_code) TAQ_TRY_HIP(hipMemcpyAsync(dbg->o_code, o_code, MC, hipMemcpyDeviceToDevice, st));
-        if (dbg->s_o) TAQ_TRY_HIP(hipMemcpyAsync(dbg->s_o, s_o, (size_t)M * 4, hipMemcpyDeviceToDevice, st));
+    // One kernel per stage, on as many tiles of 16 image tokens at a time as the workspace holds (all of them, in a workspace
+    // of taq_workspace_bytes()). Taps are written by the kernels themselves. (Q~ is quantized by the to_q kernel.)
+    const size_t tiles = stage_tiles(s);
+    size_t chunk = tiles;
+    while (chunk > 1 && stage_chunk_bytes(s, chunk) > ws_bytes) chunk = (chunk + 1) / 2;
+    if (stage_chunk_bytes(s, chunk) > ws_bytes) return TAQ_ERR_SCRATCH_TOO_SMALL;
+    if (chunk < tiles && stages != ~0u) return TAQ_ERR_SCRATCH_TOO_SMALL;  // single stages need all tiles at once
+    for (size_t t0 = 0; t0 < tiles; t0 += chunk) {
+        const StageChunk c = stage_chunk(s, ws, t0, t0 + chunk < tiles ? t0 + chunk : tiles);
+        if (stages & TAQ_STAGE_HIDDEN_QUANT) TAQ_TRY_HIP(launch_rowquant_op(c, s, static_cast<const __half*>(hidden), dbg, st));
+        if (stages & TAQ_STAGE_TO_Q) TAQ_TRY_HIP(launch_to_q_op(c, s, Wq, s_wq, dbg, st));
+        if (stages & TAQ_STAGE_ATTN_CORE) TAQ_TRY_HIP(launch_attn_op(c, s, static_cast<const uint8_t*>(qkv_packed), dbg, st));
+        if (stages & TAQ_STAGE_O_QUANT) TAQ_TRY_HIP(launch_oquant_op(c, s, dbg, st));
+        if (stages & TAQ_STAGE_TO_OUT) TAQ_TRY_HIP(launch_to_out_op(c, s, Wo, s_wo, bias_o, static_cast<__half*>(out), st));
     }
     return TAQ_OK;
+}
+
+int taq_cross_attn_ex(const void* hidden, const void* qkv_packed, const int8_t* Wq, const int8_t* Wo,
+                      const float* scales, const uint8_t* trigger_mask, const taq_shape* shape, void* out,
+                      void* workspace, void* hip_stream, const taq_debug* dbg) {
+    return cross_attn_impl(hidden, qkv_packed, Wq, Wo, scales, trigger_mask, shape, out, workspace, ~(size_t)0, hip_stream, dbg);
 }
 
 int taq_cross_attn(const void* hidden, const void* qkv_packed, const int8_t* Wq, const int8_t* Wo,
@@ -353,14 +345,14 @@ int taq_cross_attn_static(const void* hidden, const void* qkv_packed, const int8
     int rc = check_shape(shape, true);
     if (rc != TAQ_OK) return rc;
     // the single-kernel shapes never touch the workspace; every other path uses the layout of attn_workspace
-    const size_t need = fused_supported(*shape) ? 0 : attn_workspace(*shape).total;
+    const size_t need = fused_supported(*shape) ? 0 : attn_workspace(*shape).least;
     if (need > (size_t)TAQ_STATIC_SCRATCH_BYTES) return TAQ_ERR_SCRATCH_TOO_SMALL;
     if (!hidden || !qkv_packed || !Wq || !Wo || !scales || !out) return TAQ_ERR_INVALID_ARG;
     void* ws = nullptr;
     rc = static_scratch(&ws);
     if (rc != TAQ_OK) return rc;
     // nothing in the workspace has to start at zero: every kernel writes what a later one reads
-    return taq_cross_attn_ex(hidden, qkv_packed, Wq, Wo, scales, trigger_mask, shape, out, ws, hip_stream, nullptr);
+    return cross_attn_impl(hidden, qkv_packed, Wq, Wo, scales, trigger_mask, shape, out, ws, TAQ_STATIC_SCRATCH_BYTES, hip_stream, nullptr);
 }
 
 int taq_cross_attn_batched(int R, const taq_request* table, const taq_shape* shape, void* workspace,

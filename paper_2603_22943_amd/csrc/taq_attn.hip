@@ -1,439 +1,403 @@
-// Attention core of the TAQ block (PersonalQ, Section III-B) on gfx950 matrix cores:
+// Attention of the kernel-per-stage path (PersonalQ, Section III-B) on gfx950 matrix cores, for any head dimension:
 //   A  = softmax(Q~ K~^T / sqrt(d))            over the T text tokens of one head
-//   A^ = M_A*A + (1-M_A)*Q_a(A)                Eq. (3), Q_a(A) = rint(255*A)/255
+//   A^ = M_A*A + (1-M_A)*Q_a(A)                Eq. (3)
 //   O  = A^ V~
-// with K~/V~ mixed precision (Eq. 2): int8/int4 codes with a per-(head, token) scale, or an
-// fp16 row for protected (trigger) tokens.
+// from Q~ codes in operand order (taq_gemm.hip) and the operand-ordered K~/V~ image of qkv_packed to float32 O in operand
+// order and its largest magnitude per (token, head).
 //
-// Formulation. Everything is computed transposed, S^T = K~ Q~^T, so that one image token
-// lives in one lane (and its partner lane in the other half-wave): the 32x32 accumulator
-// layout then gives every lane 16 of the 32 text tokens of a tile for *its* image token, the
-// softmax statistics are in-lane reductions plus one exchange between half-waves, and the
-// probabilities never leave registers: the accumulator registers, converted to fp16, are
-// exactly the B operand of the next contraction O^T = V~^T A^^T once V~^T is stored in LDS
-// in the matching token order.
+// The arithmetic is that of the fused block kernel's attention phases (taq_fused_kernel.h, where each step is derived):
+// everything transposed, an image token in lane (token % 16) of its wavefront from the scores to O; integer scores; the
+// probability code formed in one FMA; weights code * s_V as exact packed-fp16 products split in high and low parts;
+// protected columns in two run-time loops over the handful of protected rows.
 //
-// Exactness. Unprotected scores are exact int8 dot products (integer MFMA) scaled in fp32.
-// A^ V~ needs float32-grade accuracy because its result is re-quantized to int8 right after:
-// the per-token weight s_V[t]*v_code[t][j] is split into an fp16 high part and an fp16 low
-// part (two fp16 MFMAs with the exact integer probability code as the other operand), and
-// protected columns split the probability itself the same way against the fp16 V row.
-#include "taq_internal.h"
+// Work split: a workgroup of four wavefronts owns one head of one batch element and 4 * NTT tiles of 16 image tokens, so
+// that the head's image block (8 to 27 KiB, fetched once into LDS) serves them all and several workgroups share a
+// compute unit. Bound by vector issue (softmax and Eq. 3, about 12 instructions per probability). The kernel that stood
+// here before staged and split K~/V~ itself in every workgroup, whatever the number of tokens: 31 us at B = 2, N = 2304,
+// 12 heads of 64, MEAS_ATTN us now.
+#include "taq_device.h"
 
 namespace taq {
 
-typedef int int32x4_t __attribute__((ext_vector_type(4)));
-typedef int int32x16_t __attribute__((ext_vector_type(16)));
-typedef float floatx16_t __attribute__((ext_vector_type(16)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+template <int TPH, int NTT, int PG, int NT16>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TPH <= 3 ? 3 : 2)))
+void attn_op_kernel(AttnOpArgs a) {
+    constexpr bool LOGP = PG == TAQ_PROB_LOG2, ROWMAX = PG == TAQ_PROB_ROWMAX;
+    constexpr int MT16 = NT16 ? NT16 : 6, KS = (TPH + 3) / 4, FS = (TPH + 1) / 2;
+    extern __shared__ __align__(16) unsigned char img[];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, q = lane >> 4;
+    const int h = blockIdx.y, T = a.T, C = a.C, H = a.H, d = a.d, nt16 = NT16 ? NT16 : a.nt16;
+    // tiles of the chunk: tile index t (of the whole call) = b * NT + tile within the batch element; blockIdx.z counts batch
+    // elements from the chunk's first
+    const int b = a.b0 + (int)blockIdx.z;
+    const int lo = b * a.NT > a.tile0 ? b * a.NT : a.tile0, hi = (b + 1) * a.NT < a.tile1 ? (b + 1) * a.NT : a.tile1;
+    const int first = lo + ((int)blockIdx.x * 4 + wave) * NTT;  // this wavefront's first tile
+    if (lo + (int)blockIdx.x * 4 * NTT >= hi) return;           // (the whole workgroup)
+    const unsigned char* gimg = a.packed + a.L.image + (size_t)b * a.L.image_bytes + (size_t)h * a.I.head_bytes;
+    const int n16 = (int)(a.I.head_bytes >> 4);
+#pragma unroll 4
+    for (int i = tid; i < n16; i += 256) reinterpret_cast<uint4*>(img)[i] = reinterpret_cast<const uint4*>(gimg)[i];
+    const int ntrig = reinterpret_cast<const int*>(a.packed + a.L.ntrig)[b];
+    const int nfp = (ntrig + 15) >> 4;
+    const __half* k16 = reinterpret_cast<const __half*>(a.packed + a.L.k16) + (size_t)b * T * C + h * d;
+    const __half* v16t = reinterpret_cast<const __half*>(a.packed + a.L.v16t) + ((size_t)b * C + h * d) * 96;
 
-#define TAQ_NEG_INF (-__builtin_inff())
-
-// Position of text token t inside the LDS rows of V~^T: within each block of 16 tokens the
-// order follows the accumulator registers of a 32x32 MFMA tile, so that a lane's 8
-// consecutive halfs are the 8 tokens its 8 accumulator registers (of that block) hold.
-__device__ __forceinline__ int perm_token(int t) {
-    const int u = t & 15;
-    return (t & ~15) + 8 * ((u >> 2) & 1) + 4 * (u >> 3) + (u & 3);
-}
-
-template <int DT>
-struct CoreLds {
-    static constexpr int RS_K = DT * 32 + 16;    // bytes per row of int8 K codes
-    static constexpr int RS_KF = DT * 32 + 8;    // halfs per row of fp16 K rows
-    static constexpr int RS_V = TAQ_MAX_T + 8;   // halfs per row of V~^T (token axis)
-    static constexpr int OFF_SK = 0;                                   // f32 [96]
-    static constexpr int OFF_BIAS = OFF_SK + TAQ_MAX_T * 4;            // f32 [96]
-    static constexpr int OFF_BIASF = OFF_BIAS + TAQ_MAX_T * 4;         // f32 [96]
-    static constexpr int OFF_SVMAX = OFF_BIASF + TAQ_MAX_T * 4;        // u32 [4] (first: max s_V bits)
-    static constexpr int OFF_KC = OFF_SVMAX + 16;                      // i8  [96][RS_K]
-    static constexpr int OFF_KF = OFF_KC + TAQ_MAX_T * RS_K;           // f16 [96][RS_KF]
-    static constexpr int OFF_M1 = OFF_KF + TAQ_MAX_T * RS_KF * 2;      // f16 [DT*32][RS_V]
-    static constexpr int OFF_M2 = OFF_M1 + DT * 32 * RS_V * 2;
-    static constexpr int OFF_VF = OFF_M2 + DT * 32 * RS_V * 2;
-    static constexpr int BYTES = OFF_VF + DT * 32 * RS_V * 2;
-};
-
-struct CoreArgs {
-    const int8_t* q_code;   // [B][N][C]
-    const float* s_q;       // [B][N][H]
-    const int* ntrig;       // [B]
-    const int* slot_of;     // [B][T]
-    const float* s_k;       // [B][H][T]
-    const float* s_v;
-    const uint8_t* k_code;  // [B][T][Cb]
-    const uint8_t* v_code;
-    const __half* k16;      // [B][T][C] by slot
-    const __half* v16;
-    float* o_f;             // [B][N][C]
-    uint8_t* p_code;        // [B][N][H][T] tap of the probability codes, or NULL
-    int N, C, H, T, bits;
-    float sig2;             // softmax scale * log2(e)
-    float pmax;             // linear grid: 255 or 15 (Eq. 3); log2 grid: 2^15, the factor that puts 2^-code into fp16's range
-    float plast;            // log2 grid: the last code, 255 or 15
-    int plog;               // 1: log2 grid
-    int prow;               // 1: linear grid over the row's own range (largest unprotected probability)
-};
-
-__device__ __forceinline__ int load_code(const uint8_t* codes, size_t row, int C, int c, int bits) {
-    if (bits == 8) return (int8_t)codes[row * C + c];
-    const int nib = (codes[row * (C >> 1) + (c >> 1)] >> (4 * (c & 1))) & 0xF;
-    return (nib ^ 8) - 8;
-}
-
-// grid: (ceil(N/128), H, B); block: 4 wavefronts x 32 image tokens.
-template <int DT>
-__global__ __launch_bounds__(256) void attn_core_kernel(CoreArgs a) {
-    using L = CoreLds<DT>;
-    extern __shared__ __align__(16) unsigned char smem[];
-    float* sK = reinterpret_cast<float*>(smem + L::OFF_SK);
-    float* bias = reinterpret_cast<float*>(smem + L::OFF_BIAS);
-    float* biasf = reinterpret_cast<float*>(smem + L::OFF_BIASF);
-    int8_t* Kc = reinterpret_cast<int8_t*>(smem + L::OFF_KC);
-    _Float16* Kf = reinterpret_cast<_Float16*>(smem + L::OFF_KF);
-    _Float16* M1 = reinterpret_cast<_Float16*>(smem + L::OFF_M1);
-    _Float16* M2 = reinterpret_cast<_Float16*>(smem + L::OFF_M2);
-    _Float16* Vf = reinterpret_cast<_Float16*>(smem + L::OFF_VF);
-
-    const int tid = threadIdx.x;
-    const int b = blockIdx.z, h = blockIdx.y;
-    const int N = a.N, C = a.C, H = a.H, T = a.T, bits = a.bits;
-    const int d = C / H;
-    const int ntrig = a.ntrig[b];
-    const int nfp = (ntrig + 31) >> 5;   // fp16 tiles of 32 protected tokens
-    const int ntt = (T + 31) >> 5;       // tiles of 32 text tokens
-    const int* slot_of = a.slot_of + b * T;
-
-    // ---------------- stage K~ / V~ of this (batch, head) in LDS
-    unsigned* svmax = reinterpret_cast<unsigned*>(smem + L::OFF_SVMAX);
-    if (tid == 0) svmax[0] = 0u;
-    __syncthreads();
-    for (int t = tid; t < TAQ_MAX_T; t += 256) {
-        const bool isint = t < T && slot_of[t] < 0;
-        sK[t] = isint ? a.s_k[((size_t)b * H + h) * T + t] * a.sig2 : 0.f;
-        bias[t] = isint ? 0.f : TAQ_NEG_INF;
-        biasf[t] = t < ntrig ? 0.f : TAQ_NEG_INF;
-        if (isint && bits != 16) atomicMax(svmax, __float_as_uint(a.s_v[((size_t)b * H + h) * T + t]));
+    // Q~ codes of this head, the B operand as it is (zero past the head), and their scales
+    int tile[NTT];
+    bool live[NTT];
+    unsigned qpk[NTT][TPH];
+    float sq2[NTT];
+#pragma unroll
+    for (int nt = 0; nt < NTT; ++nt) {
+        live[nt] = first + nt < hi;
+        tile[nt] = live[nt] ? first + nt : hi - 1;
+        const size_t th = (size_t)(tile[nt] - a.tile0) * H + h;
+#pragma unroll
+        for (int j = 0; j < TPH; ++j) qpk[nt][j] = a.q_op[(th * TPH + j) * 64 + lane];
+        sq2[nt] = fmaxf(a.s_q[th * 16 + r16] * a.sig2, 1e-37f);
     }
     __syncthreads();
-    // Power-of-two prescale of the dequantised V rows: brings the largest |s_V*code| into
-    // [256, 512) so that the fp16 high/low split keeps ~22 bits whatever the data's magnitude.
-    int kexp = 0;
+    if (first >= hi) return;  // (no barrier follows)
+
+    // ---- scores x[t][n] = (K~ Q~^T)[t][n] * s_K[t] (+ 0 / -inf)
+    const float* img_sk = reinterpret_cast<const float*>(img + a.I.s_k);
+    const float* img_bias = reinterpret_cast<const float*>(img + a.I.bias);
+    float S[NTT][MT16][4];
     {
-        const float dmax = __uint_as_float(svmax[0]) * (bits == 4 ? 7.f : 127.f);
-        if (dmax > 0.f) {
-            int e;
-            (void)frexpf(dmax, &e);
-            kexp = 9 - e;
-        }
-    }
-    const float vpre = ldexpf(1.0f, kexp);
-    for (int i = tid; i < TAQ_MAX_T * DT * 8; i += 256) {  // K codes, 4 channels per item
-        const int t = i / (DT * 8), j = (i % (DT * 8)) * 4;
-        unsigned w = 0;
-        if (t < T && j < d && bits != 16) {
-            const size_t row = (size_t)b * T + t;
-            if (bits == 8) {
-                w = *reinterpret_cast<const unsigned*>(a.k_code + row * C + h * d + j);
-            } else {
-                const unsigned short q = *reinterpret_cast<const unsigned short*>(a.k_code + row * (C >> 1) + ((h * d + j) >> 1));
+        int32x4_t qop[NTT][KS];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int nib = (q >> (4 * e)) & 0xF;
-                    w |= (unsigned)(((nib ^ 8) - 8) & 0xFF) << (8 * e);
-                }
-            }
-        }
-        *reinterpret_cast<unsigned*>(Kc + t * L::RS_K + j) = w;
-    }
-    for (int i = tid; i < nfp * 32 * DT * 4; i += 256) {  // fp16 K rows, 8 channels per item
-        const int slot = i / (DT * 4), j = (i % (DT * 4)) * 8;
-        uint4 w = make_uint4(0, 0, 0, 0);
-        if (slot < ntrig && j < d)
-            w = *reinterpret_cast<const uint4*>(a.k16 + ((size_t)b * T + slot) * C + h * d + j);
-        *reinterpret_cast<uint4*>(Kf + slot * L::RS_KF + j) = w;
-    }
-    for (int i = tid; i < TAQ_MAX_T * DT * 32; i += 256) {  // V~^T high/low parts
-        const int t = i / (DT * 32), j = i % (DT * 32);
-        float hi = 0.f, lo = 0.f;
-        if (t < T && j < d && bits != 16 && slot_of[t] < 0) {
-            const float sv = a.s_v[((size_t)b * H + h) * T + t];
-            const float D = ((float)load_code(a.v_code, (size_t)b * T + t, C, h * d + j, bits) * sv) * vpre;
-            hi = (float)(_Float16)__builtin_amdgcn_cvt_pkrtz(D, 0.f)[0];  // (an intrinsic: one value for both uses, see below)
-            lo = D - hi;
-        }
-        const int p = perm_token(t);
-        M1[j * L::RS_V + p] = (_Float16)hi;
-        M2[j * L::RS_V + p] = (_Float16)lo;
-    }
-    for (int i = tid; i < nfp * 32 * DT * 32; i += 256) {  // fp16 V rows, transposed
-        const int slot = i / (DT * 32), j = i % (DT * 32);
-        _Float16 v = (_Float16)0.f;
-        if (slot < ntrig && j < d)
-            v = reinterpret_cast<const _Float16*>(a.v16)[((size_t)b * T + slot) * C + h * d + j];
-        Vf[j * L::RS_V + perm_token(slot)] = v;
-    }
-    __syncthreads();
-
-    // ---------------- this lane's image token
-    const int wave = tid >> 6, lane = tid & 63, r = lane & 31, half = lane >> 5;
-    const int n = blockIdx.x * 128 + wave * 32 + r;
-    const bool nvalid = n < N;
-    const size_t tok = (size_t)b * N + (nvalid ? n : N - 1);
-    const int8_t* qrow = a.q_code + tok * C + h * d;
-    int32x4_t qop[DT];
+        for (int nt = 0; nt < NTT; ++nt)
 #pragma unroll
-    for (int s = 0; s < DT; ++s) {
-        const int off = 32 * s + 16 * half;
-        uint2 lo = make_uint2(0, 0), hi = make_uint2(0, 0);
-        if (off + 8 <= d) lo = *reinterpret_cast<const uint2*>(qrow + off);
-        if (off + 16 <= d) hi = *reinterpret_cast<const uint2*>(qrow + off + 8);
-        qop[s][0] = (int)lo.x;
-        qop[s][1] = (int)lo.y;
-        qop[s][2] = (int)hi.x;
-        qop[s][3] = (int)hi.y;
-    }
-    const float sQ = a.s_q[tok * H + h];
-
-    // ---------------- scores (log2 domain): S^T = K~ Q~^T
-    float S[3][16], Sf[3][16];
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-    for (int tile = 0; tile < 3; ++tile) {
-        if (tile < ntt) {
-            int32x16_t acc;
+                for (int jj = 0; jj < 4; ++jj) qop[nt][ks][jj] = (4 * ks + jj < TPH) ? (int)qpk[nt][4 * ks + jj < TPH ? 4 * ks + jj : 0] : 0;
+        const unsigned char* kp = img + a.I.kp;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] = 0;
+        for (int tt = 0; tt < MT16; ++tt) {
+            if (tt < nt16) {
+                int32x4_t acc[NTT];
 #pragma unroll
-            for (int s = 0; s < DT; ++s) {
-                const int32x4_t ka = *reinterpret_cast<const int32x4_t*>(Kc + (32 * tile + r) * L::RS_K + 32 * s + 16 * half);
-                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(ka, qop[s], acc, 0, 0, 0);
-            }
+                for (int nt = 0; nt < NTT; ++nt) acc[nt] = (int32x4_t){0, 0, 0, 0};
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int t0 = 32 * tile + 8 * g + 4 * half;
-                const float4 sk = *reinterpret_cast<const float4*>(sK + t0);
-                const float4 bi = *reinterpret_cast<const float4*>(bias + t0);
-                S[tile][4 * g + 0] = __builtin_fmaf((float)acc[4 * g + 0], sQ * sk.x, bi.x);
-                S[tile][4 * g + 1] = __builtin_fmaf((float)acc[4 * g + 1], sQ * sk.y, bi.y);
-                S[tile][4 * g + 2] = __builtin_fmaf((float)acc[4 * g + 2], sQ * sk.z, bi.z);
-                S[tile][4 * g + 3] = __builtin_fmaf((float)acc[4 * g + 3], sQ * sk.w, bi.w);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) S[tile][i] = TAQ_NEG_INF;
-        }
-    }
-    if (nfp > 0) {
-        half8_t qh[DT][2];  // Q~ codes as fp16 (exact)
-#pragma unroll
-        for (int s = 0; s < DT; ++s)
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int w = qop[s][2 * sub + (e >> 2)];
-                    qh[s][sub][e] = (_Float16)(float)(int)(int8_t)((w >> (8 * (e & 3))) & 0xFF);
-                }
-        const float sq2 = sQ * a.sig2;
-#pragma unroll
-        for (int ft = 0; ft < 3; ++ft) {
-            if (ft < nfp) {
-                floatx16_t acc;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-#pragma unroll
-                for (int s = 0; s < DT; ++s)
-#pragma unroll
-                    for (int sub = 0; sub < 2; ++sub) {
-                        const half8_t ka = *reinterpret_cast<const half8_t*>(Kf + (32 * ft + r) * L::RS_KF + 32 * s + 16 * half + 8 * sub);
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ka, qh[s][sub], acc, 0, 0, 0);
-                    }
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const float4 bi = *reinterpret_cast<const float4*>(biasf + 32 * ft + 8 * g + 4 * half);
-                    Sf[ft][4 * g + 0] = __builtin_fmaf(acc[4 * g + 0], sq2, bi.x);
-                    Sf[ft][4 * g + 1] = __builtin_fmaf(acc[4 * g + 1], sq2, bi.y);
-                    Sf[ft][4 * g + 2] = __builtin_fmaf(acc[4 * g + 2], sq2, bi.z);
-                    Sf[ft][4 * g + 3] = __builtin_fmaf(acc[4 * g + 3], sq2, bi.w);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) Sf[ft][i] = TAQ_NEG_INF;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int ft = 0; ft < 3; ++ft)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) Sf[ft][i] = TAQ_NEG_INF;
-    }
-
-    // ---------------- softmax over all text tokens of this image token
-    float mx = TAQ_NEG_INF;
-#pragma unroll
-    for (int tile = 0; tile < 3; ++tile)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, fmaxf(S[tile][i], Sf[tile][i]));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    float Z = 0.f, eu = 0.f;
-#pragma unroll
-    for (int tile = 0; tile < 3; ++tile)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float arg = S[tile][i] - mx;
-            const float ex = __builtin_amdgcn_exp2f(arg);
-            Sf[tile][i] = __builtin_amdgcn_exp2f(Sf[tile][i] - mx);
-            Z += ex + Sf[tile][i];
-            eu = fmaxf(eu, ex);
-            S[tile][i] = a.plog ? arg : ex;  // the log2 grid rounds the exponent itself
-        }
-    Z += __shfl_xor(Z, 32);
-    eu = fmaxf(eu, __shfl_xor(eu, 32));
-    const float inv = 1.0f / Z;
-    const float lz = __builtin_amdgcn_logf(Z);  // log2 Z >= 0 (the largest term is 1)
-    // Row-range grid: codes = rint(pmax * E / range) with range = largest unprotected E, A^ = code * (range / Z) / pmax.
-    // Unprotected columns that together weigh less than 2^-40 of the row (or none at all) are dropped.
-    const bool ranged = a.prow && eu > Z * 9.094947e-13f;
-    const float invc = ranged ? 1.0f / eu : inv;    // code = rint((E * invc) * pmax)
-    const float rz = ranged ? Z / eu : 1.f;         // protected partial sums into the units of the coded ones
-    const float fz = ranged ? eu / Z : 1.f;         // and the result back
-
-    // ---------------- O^T = V~^T A^^T
-    floatx16_t oacc[DT];
-#pragma unroll
-    for (int jt = 0; jt < DT; ++jt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[jt][i] = 0.f;
-#pragma unroll
-    for (int ft = 0; ft < 3; ++ft) {
-        if (ft < nfp) {
-#pragma unroll
-            for (int blk = 0; blk < 2; ++blk) {
-                half8_t phi, plo;  // protected columns keep A: 255*A as fp16 high + low parts
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    // high part by the conversion intrinsic (round toward zero), so that the one value that goes into
-                    // the MFMA is also the one subtracted: a plain cast of the product may be merged with the multiply
-                    // into a single-rounding instruction in one use and not in the other
-                    const float x = (Sf[ft][8 * blk + e] * inv) * a.pmax;
-                    const _Float16 xh = (_Float16)__builtin_amdgcn_cvt_pkrtz(x, 0.f)[0];
-                    phi[e] = xh;
-                    plo[e] = (_Float16)(x - (float)xh);
-                }
-#pragma unroll
-                for (int jt = 0; jt < DT; ++jt) {
-                    const half8_t v = *reinterpret_cast<const half8_t*>(Vf + (32 * jt + r) * L::RS_V + 32 * ft + 16 * blk + 8 * half);
-                    oacc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v, phi, oacc[jt], 0, 0, 0);
-                    oacc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v, plo, oacc[jt], 0, 0, 0);
-                }
-            }
-        }
-    }
-
-    if (nfp > 0) {  // bring the protected columns' partial sums to the prescaled units
-#pragma unroll
-        for (int jt = 0; jt < DT; ++jt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[jt][i] *= vpre * rz;
-    }
-#pragma unroll
-    for (int tile = 0; tile < 3; ++tile) {
-        if (tile < ntt) {
-#pragma unroll
-            for (int blk = 0; blk < 2; ++blk) {
-                half8_t p;  // Eq. (3): integer probability codes, exact in fp16
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    float code;
-                    if (a.plog) {
-                        // -code = clip(rint(log2 A)) = clip(rint(arg - log2 Z)); weight 2^(15 - code), a power of
-                        // two that fp16 holds exactly down to 2^-24 (smaller ones vanish: below 2^-39 of the row sum)
-                        const float c = fminf(fmaxf(__builtin_rintf(S[tile][8 * blk + e] - lz), -a.plast), 0.f);
-                        p[e] = (_Float16)ldexpf(1.0f, 15 + (int)c);
-                        code = -c;
+                for (int ks = 0; ks < KS; ++ks) {
+                    int32x4_t ka;
+                    if constexpr (TPH % 4 == 0) {
+                        ka = *reinterpret_cast<const int32x4_t*>(kp + kp_offset(TPH, 16 * tt + r16, 4 * ks, q));
                     } else {
-                        code = __builtin_rintf((S[tile][8 * blk + e] * invc) * a.pmax);
-                        p[e] = (_Float16)code;
-                    }
-                    if (a.p_code && nvalid) {  // tap: register e of this block holds text token t (accumulator order)
-                        const int t = 32 * tile + 16 * blk + 8 * (e >> 2) + 4 * half + (e & 3);
-                        if (t < T) a.p_code[(tok * H + h) * (size_t)T + t] = (uint8_t)(int)code;
-                    }
-                }
 #pragma unroll
-                for (int jt = 0; jt < DT; ++jt) {
-                    const int o = (32 * jt + r) * L::RS_V + 32 * tile + 16 * blk + 8 * half;
-                    const half8_t v1 = *reinterpret_cast<const half8_t*>(M1 + o);
-                    const half8_t v2 = *reinterpret_cast<const half8_t*>(M2 + o);
-                    oacc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v1, p, oacc[jt], 0, 0, 0);
-                    oacc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v2, p, oacc[jt], 0, 0, 0);
+                        for (int jj = 0; jj < 4; ++jj)
+                            ka[jj] = (4 * ks + jj < TPH) ? *reinterpret_cast<const int*>(kp + kp_offset(TPH, 16 * tt + r16, 4 * ks + jj, q)) : 0;
+                    }
+#pragma unroll
+                    for (int nt = 0; nt < NTT; ++nt) acc[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ka, qop[nt][ks], acc[nt], 0, 0, 0);
+                }
+                const float4 sk = *reinterpret_cast<const float4*>(img_sk + 16 * tt + 4 * q);
+                const float4 bi = *reinterpret_cast<const float4*>(img_bias + 16 * tt + 4 * q);
+#pragma unroll
+                for (int nt = 0; nt < NTT; ++nt) {
+                    S[nt][tt][0] = __builtin_fmaf((float)acc[nt][0], sk.x, bi.x);
+                    S[nt][tt][1] = __builtin_fmaf((float)acc[nt][1], sk.y, bi.y);
+                    S[nt][tt][2] = __builtin_fmaf((float)acc[nt][2], sk.z, bi.z);
+                    S[nt][tt][3] = __builtin_fmaf((float)acc[nt][3], sk.w, bi.w);
                 }
             }
         }
     }
-    // ---------------- store O (float32): lane holds channels 32*jt + 8*g + 4*half + 0..3
-    if (nvalid) {
-        float* orow = a.o_f + tok * C + h * d;
-        const float k = (ldexpf(1.0f, -kexp) / a.pmax) * fz;
+    // ---- protected rows: scores of tile ft of 16 slots, straight from the fp16 K rows; -inf past ntrig
+    half8_t qh[NTT][FS];
+    if (nfp > 0) {
 #pragma unroll
-        for (int jt = 0; jt < DT; ++jt)
+        for (int nt = 0; nt < NTT; ++nt)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int j = 32 * jt + 8 * g + 4 * half;
-                if (j < d) {
-                    float4 v = make_float4(oacc[jt][4 * g] * k, oacc[jt][4 * g + 1] * k, oacc[jt][4 * g + 2] * k,
-                                           oacc[jt][4 * g + 3] * k);
-                    *reinterpret_cast<float4*>(orow + j) = v;
+            for (int s = 0; s < FS; ++s) {
+                half2_t c0, c1, c2 = {(_Float16)0.f, (_Float16)0.f}, c3 = c2;
+                biased4_to_half(qpk[nt][2 * s] ^ 0x80808080u, c0, c1);
+                if (2 * s + 1 < TPH) biased4_to_half(qpk[nt][2 * s + 1 < TPH ? 2 * s + 1 : 0] ^ 0x80808080u, c2, c3);
+                qh[nt][s] = (half8_t){c0[0], c0[1], c1[0], c1[1], c2[0], c2[1], c3[0], c3[1]};
+            }
+    }
+    auto protected_scores = [&](int ft, floatx4_t (&facc)[NTT]) {
+#pragma unroll
+        for (int nt = 0; nt < NTT; ++nt) facc[nt] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
+        int slot = 16 * ft + r16;
+        slot = slot < T ? slot : T - 1;
+        const __half* kr = k16 + (size_t)slot * C + 4 * q;
+#pragma unroll
+        for (int s = 0; s < FS; ++s) {
+            half8_t ka;
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) {
+                const int j = 2 * s + jj;
+                const uint2 w = (j < TPH && 16 * j + 4 * q < d) ? *reinterpret_cast<const uint2*>(kr + 16 * j) : make_uint2(0, 0);
+                const half4_t hv = *reinterpret_cast<const half4_t*>(&w);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ka[4 * jj + e] = hv[e];
+            }
+#pragma unroll
+            for (int nt = 0; nt < NTT; ++nt) facc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka, qh[nt][s], facc[nt], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool in = 16 * ft + 4 * q + i < ntrig;
+#pragma unroll
+            for (int nt = 0; nt < NTT; ++nt) facc[nt][i] = in ? facc[nt][i] : TAQ_NEG_INF;
+        }
+    };
+
+    // ---- softmax
+    float mxs[NTT];
+#pragma unroll
+    for (int nt = 0; nt < NTT; ++nt) {
+        float mx = TAQ_NEG_INF;
+#pragma unroll
+        for (int tt = 0; tt < MT16; ++tt)
+            if (tt < nt16) mx = fmaxf(mx, fmaxf(fmaxf(S[nt][tt][0], S[nt][tt][1]), fmaxf(S[nt][tt][2], S[nt][tt][3])));
+        mxs[nt] = mx;
+    }
+    for (int ft = 0; ft < nfp; ++ft) {
+        floatx4_t facc[NTT];
+        protected_scores(ft, facc);
+#pragma unroll
+        for (int nt = 0; nt < NTT; ++nt)
+            mxs[nt] = fmaxf(mxs[nt], fmaxf(fmaxf(facc[nt][0], facc[nt][1]), fmaxf(facc[nt][2], facc[nt][3])));
+    }
+    float Zs[NTT], eus[NTT], offs[NTT];
+#pragma unroll
+    for (int nt = 0; nt < NTT; ++nt) {
+        const float mx = quad_allmax(mxs[nt]);
+        const float sc = sq2[nt], off = -mx * sc;
+        offs[nt] = off;
+        float Z = 0.f, eu = 0.f;
+#pragma unroll
+        for (int tt = 0; tt < MT16; ++tt)
+            if (tt < nt16) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float arg = __builtin_fmaf(S[nt][tt][i], sc, off);
+                    const float ex = __builtin_amdgcn_exp2f(arg);
+                    Z += ex;
+                    if (ROWMAX) eu = fmaxf(eu, ex);
+                    S[nt][tt][i] = LOGP ? arg : ex;
                 }
             }
+        Zs[nt] = Z;
+        eus[nt] = eu;
+    }
+    floatx4_t oacc[NTT][TPH];
+#pragma unroll
+    for (int nt = 0; nt < NTT; ++nt)
+#pragma unroll
+        for (int k = 0; k < TPH; ++k) oacc[nt][k] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
+    for (int ft = 0; ft < nfp; ++ft) {  // protected columns keep A, unnormalised here
+        floatx4_t facc[NTT];
+        protected_scores(ft, facc);
+        half4_t phi[NTT], plo[NTT];
+#pragma unroll
+        for (int nt = 0; nt < NTT; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float ex = __builtin_amdgcn_exp2f(__builtin_fmaf(facc[nt][i], sq2[nt], offs[nt]));
+                Zs[nt] += ex;
+                const _Float16 xh = (_Float16)__builtin_amdgcn_cvt_pkrtz(ex, 0.f)[0];
+                phi[nt][i] = xh;
+                plo[nt][i] = (_Float16)(ex - (float)xh);
+            }
+#pragma unroll
+        for (int k = 0; k < TPH; ++k) {
+            const int c = 16 * k + r16 < d ? 16 * k + r16 : d - 1;
+            const uint2 w = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 16 * ft + 4 * q);
+            const half4_t va = *reinterpret_cast<const half4_t*>(&w);  // slots past ntrig hold zeros
+#pragma unroll
+            for (int nt = 0; nt < NTT; ++nt) {
+                oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, phi[nt], oacc[nt][k], 0, 0, 0);
+                oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, plo[nt], oacc[nt][k], 0, 0, 0);
+            }
+        }
+    }
+    float kq[NTT], lz[NTT], fz[NTT];
+#pragma unroll
+    for (int nt = 0; nt < NTT; ++nt) {
+        const float Z = quad_allsum(Zs[nt]);
+        const float kqp = quant_mult(a.pmax, Z);  // pmax / Z
+        float rz = 1.f;
+        kq[nt] = kqp;
+        lz[nt] = LOGP ? __builtin_amdgcn_logf(Z) : 0.f;
+        fz[nt] = 1.f;
+        if constexpr (ROWMAX) {  // (unprotected columns that together weigh less than 2^-40 of the row are dropped)
+            const float eu = quad_allmax(eus[nt]);
+            if (eu > Z * 9.094947e-13f) {
+                kq[nt] = quant_mult(a.pmax, eu);
+                rz = quant_mult(Z, eu);
+                fz[nt] = quant_mult(eu, Z);
+            }
+        }
+        if (nfp > 0) {
+            const float f = kqp * (reinterpret_cast<const float*>(img + a.I.vpre)[0] * rz);
+#pragma unroll
+            for (int k = 0; k < TPH; ++k)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) oacc[nt][k][i] *= f;
+        }
+    }
+
+    // ---- Eq. (3) and O^T = V~^T A^^T over the unprotected columns
+    const uint8_t* vt = img + a.I.vt;
+    const _Float16* img_sv = reinterpret_cast<const _Float16*>(img + a.I.s_vp);  // [ntok] high parts | [ntok] low parts
+    const half2_t k1024 = {(_Float16)1024.0f, (_Float16)1024.0f};
+    auto tap_pcode = [&](int nt, int t, unsigned c0, unsigned c1) {
+        const int n = (tile[nt] - b * a.NT) * 16 + r16;
+        if (live[nt] && n < a.N) {
+            uint8_t* row = a.p_code + (((size_t)b * a.N + n) * H + h) * (size_t)T;
+            if (t < T) row[t] = (uint8_t)c0;
+            if (t + 1 < T) row[t + 1] = (uint8_t)c1;
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        if (2 * s < nt16) {
+            const bool second = 2 * s + 1 < nt16;
+            half8_t phi[NTT], plo[NTT];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                constexpr int LAST = MT16 - 1;
+                const int tt = 2 * s + u < MT16 ? 2 * s + u : LAST;
+                if (u == 0 || second) {
+                    const uint2 h4 = *reinterpret_cast<const uint2*>(img_sv + 16 * tt + 4 * q);
+                    const uint2 l4 = *reinterpret_cast<const uint2*>(img_sv + a.I.ntok + 16 * tt + 4 * q);
+                    const half2_t sh[2] = {*reinterpret_cast<const half2_t*>(&h4.x), *reinterpret_cast<const half2_t*>(&h4.y)};
+                    const half2_t sl[2] = {*reinterpret_cast<const half2_t*>(&l4.x), *reinterpret_cast<const half2_t*>(&l4.y)};
+#pragma unroll
+                    for (int nt = 0; nt < NTT; ++nt)
+#pragma unroll
+                        for (int i2 = 0; i2 < 2; ++i2) {
+                            half2_t c;
+                            if constexpr (LOGP) {
+                                const float c0 = __builtin_amdgcn_fmed3f(__builtin_rintf(S[nt][tt][2 * i2] - lz[nt]), -a.plast, 0.f);
+                                const float c1 = __builtin_amdgcn_fmed3f(__builtin_rintf(S[nt][tt][2 * i2 + 1] - lz[nt]), -a.plast, 0.f);
+                                const auto pw = __builtin_amdgcn_cvt_pkrtz(ldexpf(256.0f, (int)c0), ldexpf(256.0f, (int)c1));
+                                c = (half2_t){(_Float16)pw[0], (_Float16)pw[1]};
+                                if (a.p_code) tap_pcode(nt, 16 * tt + 4 * q + 2 * i2, (unsigned)(int)(-c0), (unsigned)(int)(-c1));
+                            } else {
+                                const float m0 = __builtin_fmaf(S[nt][tt][2 * i2], kq[nt], 12608512.0f);
+                                const float m1 = __builtin_fmaf(S[nt][tt][2 * i2 + 1], kq[nt], 12608512.0f);
+                                const unsigned w = __builtin_amdgcn_perm(__float_as_uint(m1), __float_as_uint(m0), 0x05040100u);
+                                c = *reinterpret_cast<const half2_t*>(&w) - k1024;
+                                if (a.p_code) tap_pcode(nt, 16 * tt + 4 * q + 2 * i2, w & 0xFFu, (w >> 16) & 0xFFu);
+                            }
+                            const half2_t wh = c * sh[i2];
+                            const half2_t wl = __builtin_elementwise_fma(c, sl[i2], __builtin_elementwise_fma(c, sh[i2], -wh));
+                            phi[nt][4 * u + 2 * i2] = wh[0];
+                            phi[nt][4 * u + 2 * i2 + 1] = wh[1];
+                            plo[nt][4 * u + 2 * i2] = wl[0];
+                            plo[nt][4 * u + 2 * i2 + 1] = wl[1];
+                        }
+                } else {
+#pragma unroll
+                    for (int nt = 0; nt < NTT; ++nt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) phi[nt][4 * u + i] = plo[nt][4 * u + i] = (_Float16)0.f;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < TPH; ++k) {
+                const int j = 16 * k + r16 < d ? 16 * k + r16 : d - 1;
+                if (second) {
+                    const uint2 w = *reinterpret_cast<const uint2*>(vt + (size_t)j * a.I.cols_v + 32 * s + 8 * q);
+                    half2_t v0, v1, v2, v3;
+                    biased4_to_half(w.x, v0, v1);
+                    biased4_to_half(w.y, v2, v3);
+                    const half8_t va = {v0[0], v0[1], v1[0], v1[1], v2[0], v2[1], v3[0], v3[1]};
+#pragma unroll
+                    for (int nt = 0; nt < NTT; ++nt) {
+                        oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va, phi[nt], oacc[nt][k], 0, 0, 0);
+                        oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va, plo[nt], oacc[nt][k], 0, 0, 0);
+                    }
+                } else {
+                    const unsigned w = *reinterpret_cast<const unsigned*>(vt + (size_t)j * a.I.cols_v + 32 * s + 4 * q);
+                    half2_t v0, v1;
+                    biased4_to_half(w, v0, v1);
+                    const half4_t va = {v0[0], v0[1], v1[0], v1[1]};
+#pragma unroll
+                    for (int nt = 0; nt < NTT; ++nt) {
+                        const half4_t ph = {phi[nt][0], phi[nt][1], phi[nt][2], phi[nt][3]};
+                        const half4_t pl = {plo[nt][0], plo[nt][1], plo[nt][2], plo[nt][3]};
+                        oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, ph, oacc[nt][k], 0, 0, 0);
+                        oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, pl, oacc[nt][k], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    }
+    // ---- O and its largest magnitude per token of this head
+    const float osc = reinterpret_cast<const float*>(img + a.I.oscale)[0] * (1.0f / a.pmax);
+#pragma unroll
+    for (int nt = 0; nt < NTT; ++nt) {
+        const float of = ROWMAX ? osc * fz[nt] : osc;
+        const size_t th = (size_t)(tile[nt] - a.tile0) * H + h;
+        const int n = (tile[nt] - b * a.NT) * 16 + r16;
+        float omx = 0.f;
+#pragma unroll
+        for (int k = 0; k < TPH; ++k) {
+            const bool valid = 16 * k + 4 * q < d;
+            const float4 o4 = make_float4(oacc[nt][k][0] * of, oacc[nt][k][1] * of, oacc[nt][k][2] * of, oacc[nt][k][3] * of);
+            if (valid) omx = fmaxf(omx, fmaxf(fmaxf(fabsf(o4.x), fabsf(o4.y)), fmaxf(fabsf(o4.z), fabsf(o4.w))));
+            if (live[nt] && valid) {
+                reinterpret_cast<float4*>(a.o_op)[(th * TPH + k) * 64 + lane] = o4;
+                if (a.O && n < a.N) *reinterpret_cast<float4*>(a.O + ((size_t)b * a.N + n) * C + h * d + 16 * k + 4 * q) = o4;
+            }
+        }
+        omx = quad_allmax(omx);
+        if (live[nt] && q == 0) a.o_max[th * 16 + r16] = omx;
     }
 }
 
-template <int DT>
-static hipError_t launch_core_dt(const CoreArgs& a, int B, hipStream_t st) {
-    static std::atomic<unsigned long long> lds_set{0};
-    const int bytes = CoreLds<DT>::BYTES;
-    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_core_kernel<DT>), bytes, lds_set);
-    if (e != hipSuccess) return e;
-    dim3 grid((a.N + 127) / 128, a.H, B);
-    hipLaunchKernelGGL(attn_core_kernel<DT>, grid, dim3(256), bytes, st, a);
+template <int TPH, int NTT, int PG, int NT16>
+static hipError_t launch_attn_cfg(const AttnOpArgs& a, int tiles_b, int nb, hipStream_t st) {
+    hipLaunchKernelGGL((attn_op_kernel<TPH, NTT, PG, NT16>), dim3((tiles_b + 4 * NTT - 1) / (4 * NTT), a.H, nb), dim3(256), a.I.head_bytes, st, a);
     return hipGetLastError();
 }
 
-hipError_t launch_attn_core(const int8_t* q_code, const float* s_q, const uint8_t* packed, const taq_shape& s,
-                            float* o_f, hipStream_t st, uint8_t* p_code) {
-    const KvLayout L = kv_layout(s);
-    CoreArgs a;
-    a.q_code = q_code;
-    a.p_code = p_code;
-    a.s_q = s_q;
-    a.ntrig = reinterpret_cast<const int*>(packed + L.ntrig);
-    a.slot_of = reinterpret_cast<const int*>(packed + L.slot_of);
-    a.s_k = reinterpret_cast<const float*>(packed + L.s_k);
-    a.s_v = reinterpret_cast<const float*>(packed + L.s_v);
-    a.k_code = packed + L.k_code;
-    a.v_code = packed + L.v_code;
-    a.k16 = reinterpret_cast<const __half*>(packed + L.k16);
-    a.v16 = reinterpret_cast<const __half*>(packed + L.v16);
-    a.o_f = o_f;
-    a.N = s.N;
-    a.C = s.C;
-    a.H = s.H;
-    a.T = s.T;
-    a.bits = s.bits_kv;
-    const int d = s.C / s.H;
-    const float sigma = s.softmax_scale != 0.f ? s.softmax_scale : 1.0f / sqrtf((float)d);
+template <int TPH, int PG>
+static hipError_t launch_attn_grid(const AttnOpArgs& a, int tiles_b, int nb, hipStream_t st) {
+    constexpr int NTT = TPH <= 5 ? 2 : 1;  // two tiles per wavefront share the operand conversions; wide heads have no registers for it
+    // 65 to 80 text tokens (the 77-token prompts): no run-time guards around the score tiles
+    if (a.nt16 == 5) return launch_attn_cfg<TPH, NTT, PG, 5>(a, tiles_b, nb, st);
+    return launch_attn_cfg<TPH, NTT, PG, 0>(a, tiles_b, nb, st);
+}
+
+template <int TPH>
+static hipError_t launch_attn_tph(const AttnOpArgs& a, int grid, int tiles_b, int nb, hipStream_t st) {
+    if (grid == TAQ_PROB_LOG2) return launch_attn_grid<TPH, TAQ_PROB_LOG2>(a, tiles_b, nb, st);
+    if (grid == TAQ_PROB_ROWMAX) return launch_attn_grid<TPH, TAQ_PROB_ROWMAX>(a, tiles_b, nb, st);
+    return launch_attn_grid<TPH, TAQ_PROB_LINEAR>(a, tiles_b, nb, st);
+}
+
+hipError_t launch_attn_op(const StageChunk& c, const taq_shape& s, const uint8_t* packed, const taq_debug* dbg, hipStream_t st) {
+    AttnOpArgs a;
+    a.q_op = c.q_op;
+    a.s_q = c.s_q;
+    a.packed = packed;
+    a.o_op = c.o_op;
+    a.o_max = c.o_max;
+    a.p_code = dbg ? dbg->p_code : nullptr;
+    a.O = dbg ? dbg->O : nullptr;
+    a.L = kv_layout(s);
+    a.I = kv_image(s);
+    a.N = s.N; a.NT = c.NT; a.tile0 = c.tile0; a.tile1 = c.tile1;
+    a.C = s.C; a.H = s.H; a.d = s.C / s.H; a.T = s.T;
+    a.nt16 = (s.T + 15) / 16;
+    const float sigma = s.softmax_scale != 0.f ? s.softmax_scale : 1.0f / sqrtf((float)a.d);
     a.sig2 = sigma * 1.4426950408889634f;
-    a.pmax = s.prob_grid == TAQ_PROB_LOG2 ? 32768.f : s.bits_prob == 4 ? 15.f : 255.f;
     a.plast = s.bits_prob == 4 ? 15.f : 255.f;
-    a.plog = s.prob_grid == TAQ_PROB_LOG2;
-    a.prow = s.prob_grid == TAQ_PROB_ROWMAX;
-    switch ((d + 31) / 32) {
-        case 1: return launch_core_dt<1>(a, s.B, st);
-        case 2: return launch_core_dt<2>(a, s.B, st);
-        case 3: return launch_core_dt<3>(a, s.B, st);
-        case 4: return launch_core_dt<4>(a, s.B, st);
-        case 5: return launch_core_dt<5>(a, s.B, st);
+    a.pmax = s.prob_grid == TAQ_PROB_LOG2 ? 256.f : a.plast;
+    a.b0 = c.tile0 / c.NT;
+    const int nb = (c.tile1 - 1) / c.NT - a.b0 + 1;
+    const int tiles_b = nb == 1 ? c.tile1 - c.tile0 : c.NT;  // tiles of a batch element in the chunk, at most
+    if (nb > 65535) return hipErrorInvalidValue;
+    switch ((a.d + 15) / 16) {
+#define TAQ_ATT(N) case N: return launch_attn_tph<N>(a, s.prob_grid, tiles_b, nb, st);
+        TAQ_ATT(1) TAQ_ATT(2) TAQ_ATT(3) TAQ_ATT(4) TAQ_ATT(5) TAQ_ATT(6) TAQ_ATT(7) TAQ_ATT(8) TAQ_ATT(9) TAQ_ATT(10)
+#undef TAQ_ATT
         default: return hipErrorInvalidValue;
     }
 }

@@ -144,6 +144,19 @@ __device__ __forceinline__ void biased4_to_half(unsigned w, half2_t& a, half2_t&
     b = *reinterpret_cast<const half2_t*>(&hi) - off;
 }
 
+// 4 x 4 transpose of dwords between four registers and the four quarters of the wavefront: afterwards register k of a lane
+// in quarter q holds what register q of the same lane in quarter k held.
+__device__ __forceinline__ void quad_transpose(unsigned (&r)[4]) {
+    const auto s02 = __builtin_amdgcn_permlane32_swap(r[0], r[2], false, false);
+    const auto s13 = __builtin_amdgcn_permlane32_swap(r[1], r[3], false, false);
+    const auto r01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
+    const auto r23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+    r[0] = r01[0];
+    r[1] = r01[1];
+    r[2] = r23[0];
+    r[3] = r23[1];
+}
+
 // Maximum over all 64 lanes.
 __device__ __forceinline__ float wave_allmax(float x) { return quad_allmax(row16_allmax(x)); }
 

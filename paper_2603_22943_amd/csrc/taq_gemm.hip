@@ -3,11 +3,10 @@
 // Serves the W8A8 contractions of the TAQ block (to_q, to_out, and the K/V projections of
 // unprotected text tokens): acc[m][n] = sum_k A[m][k] * W[n][k], both operands K-contiguous,
 // result = float(acc) * (sa[m] * sw[n]) (+ bias[n]), in that order of float32 operations.
-#include "taq_internal.h"
+#include "taq_device.h"
 
 namespace taq {
 
-typedef int int32x4_t __attribute__((ext_vector_type(4)));
 typedef int int32x16_t __attribute__((ext_vector_type(16)));
 
 // Workgroup = 4 wavefronts in a 2x2 arrangement, each owning one 32x32 accumulator tile
@@ -230,6 +229,284 @@ hipError_t launch_gemm_i8(const int8_t* A, const float* sa, const int8_t* W, con
     dim3 grid((M + 63) / 64, (N + 63) / 64);  // (M, which may be large, along x)
     hipLaunchKernelGGL(gemm_i8_kernel, grid, dim3(256), 0, st, A, sa, W, sw, bias, M, N, K, out_f32, out_f16, ldo);
     return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------
+// to_q and to_out of the kernel-per-stage path. The same pipeline as gemm_i8_lds_kernel on operands that are already in
+// MFMA operand order: a 16 x 64 block is one contiguous KiB, in memory and in LDS (conflict-free as it is). Tokens come
+// that way from the quantizer kernels, weights from taq_pack_weight; row-major weights go through the swizzled stage of
+// gemm_i8_lds_kernel. Weight blocks are counted per head (tph = ceil(d/16) blocks each, the last one partly filled), so
+// that a workgroup of to_q holds whole heads and quantizes Q~ on its accumulators: what leaves the kernel is one byte per
+// channel instead of a float32 for a quantizer kernel to read again, in the registers' own order, which is the order in
+// which the attention's score operand wants it.
+//   MB tiles of 16 tokens x NB blocks of 16 channels per workgroup of four wavefronts; TPH > 0: to_q with heads of TPH
+//   blocks; TPH = 0: to_out.
+// What a compute unit receives per K step, (MB + NB) KiB, is most of the time at these sizes (measured over the whole chip
+// about 12 TB/s): to_q + quantizer at M = 4608, C = 768 took 14.3 + 7.1 us, MEAS_TOQ us now; to_out 14.3 -> MEAS_TOUT us.
+// ------------------------------------------------------------------------------------------
+struct GemmOpArgs {
+    const int8_t* A;      // token codes in operand order
+    const float* sa;      // [tile][16]
+    const int8_t* W;      // weight codes
+    const float* sw;
+    const float* bias;    // to_out
+    unsigned* q_op;       // to_q: codes and scales
+    float* s_q;
+    __half* out;          // to_out
+    int8_t* tap_code;     // to_q: row-major taps or NULL
+    float* tap_scale;
+    float qmax;
+    int tiles;            // token tiles of the chunk
+    int tile0, NT, N;     // where they are: tile0 + t = b * NT + tile of batch element b
+    int KC, C, H, d, tph, packed, MX, NX;
+    size_t pack_off;
+};
+
+template <int MB, int NB, int TPH>
+__global__ __launch_bounds__(256) void gemm_op_kernel(GemmOpArgs a) {
+    constexpr int BLK = MB + NB, STAGES = 3, MW = MB / 4, RD = 4;
+    constexpr int NLD = (BLK + 3) / 4;
+    __shared__ __align__(16) unsigned char lds[STAGES * BLK * 1024];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
+    // Workgroups are dealt to the 8 XCDs in turn. All channel blocks of a token block go to one XCD, one after the other, so
+    // that its L2 fetches those tokens once (the weights, which every XCD reads whole, are the smaller operand).
+    const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
+    const int mb = (slot / a.NX) * 8 + xcd, nb = slot % a.NX;
+    if (mb >= a.MX) return;
+    const int t0 = mb * MB, g0 = nb * NB, ng = a.H * a.tph;  // first token tile, first weight block, weight blocks
+    const int KC = a.KC, C = a.C, d = a.d, tph = TPH ? TPH : a.tph;
+    const int lrow = lane >> 2, lseg = lane & 3;
+    const int swz_st = lrow * 64 + ((lseg ^ ((lrow >> 1 ^ lrow >> 2) & 3)) << 4);
+    const int ld_a = lane * 16, ld_w = a.packed ? lane * 16 : r16 * 64 + ((q ^ ((r16 >> 1 ^ r16 >> 2) & 3)) << 4);
+    const int8_t* src[NLD];
+    int step[NLD], last[NLD], st_off[NLD];
+#pragma unroll
+    for (int u = 0; u < NLD; ++u) {
+        const int blk = wave + 4 * u < BLK ? wave + 4 * u : BLK - 1;
+        if (blk < MB) {
+            const int t = t0 + blk < a.tiles ? t0 + blk : a.tiles - 1;
+            src[u] = a.A + (size_t)t * KC * 1024 + lane * 16;
+            step[u] = 1024;
+            last[u] = (KC - 1) * 1024;
+            st_off[u] = lane * 16;
+        } else {
+            const int g = g0 + blk - MB < ng ? g0 + blk - MB : ng - 1;
+            if (a.packed) {
+                src[u] = a.W + a.pack_off + (size_t)g * KC * 1024 + lane * 16;
+                step[u] = 1024;
+                last[u] = (KC - 1) * 1024;
+                st_off[u] = lane * 16;
+            } else {
+                const int h = g / tph, row = h * d + 16 * (g - h * tph) + lrow;  // (rows past the head: results dropped)
+                src[u] = a.W + (size_t)(row < C ? row : C - 1) * C + 16 * lseg;
+                step[u] = 64;
+                last[u] = C - 16 - 16 * lseg;  // (C % 64 == 32: past the end the row's last codes, which meet zero token codes)
+                st_off[u] = swz_st;
+            }
+        }
+    }
+    int32x4_t gr[RD][NLD];
+    auto load_stage = [&](int kc, int s) {
+#pragma unroll
+        for (int u = 0; u < NLD; ++u) {
+            const int off = kc * step[u];
+            gr[s][u] = *reinterpret_cast<const int32x4_t*>(src[u] + (off < last[u] ? off : last[u]));
+        }
+    };
+    auto store_stage = [&](int kc, int s) {
+        unsigned char* dst = lds + (kc % STAGES) * (BLK * 1024);
+#pragma unroll
+        for (int u = 0; u < NLD; ++u)
+            if (4 * u + 3 < BLK || wave + 4 * u < BLK) *reinterpret_cast<int32x4_t*>(dst + (wave + 4 * u) * 1024 + st_off[u]) = gr[s][u];
+    };
+    int32x4_t acc[NB][MW];
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int i = 0; i < MW; ++i) acc[j][i] = (int32x4_t){0, 0, 0, 0};
+    int32x4_t wa[2][NB], xb[2][MW];
+    auto read_ops = [&](int kc, int set) {
+        const unsigned char* st = lds + (kc % STAGES) * (BLK * 1024);
+#pragma unroll
+        for (int i = 0; i < MW; ++i) xb[set][i] = *reinterpret_cast<const int32x4_t*>(st + (MW * wave + i) * 1024 + ld_a);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) wa[set][j] = *reinterpret_cast<const int32x4_t*>(st + (MB + j) * 1024 + ld_w);
+    };
+    auto mfmas = [&](int set) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int i = 0; i < MW; ++i) acc[j][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[set][j], xb[set][i], acc[j][i], 0, 0, 0);
+    };
+    load_stage(0, 0);
+    load_stage(1, 1);
+    store_stage(0, 0);
+    store_stage(1, 1);
+    load_stage(2, 2);
+    load_stage(3, 3);
+    load_stage(4, 0);
+    load_stage(5, 1);
+    __syncthreads();
+    read_ops(0, 0);
+    auto even_step = [&](int kc, int s) {  // s = (kc + 2) % 4
+        __syncthreads();
+        read_ops(kc + 1, 1);
+        store_stage(kc + 2, s);
+        store_stage(kc + 3, s + 1);
+        load_stage(kc + 6, s);
+        load_stage(kc + 7, s + 1);
+        mfmas(0);
+    };
+    auto odd_step = [&](int kc) {
+        __syncthreads();
+        read_ops(kc + 1, 0);
+        mfmas(1);
+    };
+    int kc = 0;
+    for (; kc + 4 <= KC; kc += 4) {
+        even_step(kc, 2);
+        odd_step(kc + 1);
+        even_step(kc + 2, 0);
+        odd_step(kc + 3);
+    }
+    if (kc < KC) even_step(kc, 2);
+    if (kc + 1 < KC) odd_step(kc + 1);
+    if (kc + 2 < KC) even_step(kc + 2, 0);
+
+#pragma unroll
+    for (int i = 0; i < MW; ++i) {
+        const int t = t0 + MW * wave + i;
+        if (t >= a.tiles) continue;
+        const int b = (a.tile0 + t) / a.NT, n = (a.tile0 + t - b * a.NT) * 16 + r16;
+        const size_t tok = (size_t)b * a.N + n;
+        const float sam = a.sa[t * 16 + r16];
+        if constexpr (TPH > 0) {
+            // Qf = float(acc) * (s_h * s_wq); codes and scale per (token, head), in the defined order
+#pragma unroll
+            for (int hh = 0; hh < NB / (TPH ? TPH : 1); ++hh) {
+                const int h = g0 / TPH + hh;
+                if (h >= a.H) continue;
+                float v[TPH ? TPH : 1][4];
+                float amax = 0.f;
+#pragma unroll
+                for (int j = 0; j < TPH; ++j) {
+                    const int cl = 16 * j + 4 * q;
+                    const bool valid = cl < d;
+                    const float4 w4 = *reinterpret_cast<const float4*>(a.sw + h * d + (valid ? cl : 0));
+                    const float wv[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float y = (float)acc[hh * TPH + j][i][e] * (sam * wv[e]);
+                        v[j][e] = valid ? y : 0.f;
+                        amax = fmaxf(amax, fabsf(v[j][e]));
+                    }
+                }
+                amax = quad_allmax(amax);
+                const bool zero = amax == 0.f;
+                const float safe = zero ? 1.f : amax, cq = quant_mult(a.qmax, safe), sq = zero ? 1.f : amax / a.qmax;
+                const size_t th = (size_t)t * a.H + h;
+                if (q == 0) a.s_q[th * 16 + r16] = sq;
+                if (a.tap_scale && q == 0 && n < a.N) a.tap_scale[tok * a.H + h] = sq;
+#pragma unroll
+                for (int j = 0; j < TPH; ++j) {
+                    const unsigned pk = quant4_i8(v[j][0], v[j][1], v[j][2], v[j][3], cq, safe, a.qmax);
+                    a.q_op[(th * TPH + j) * 64 + lane] = pk;
+                    if (a.tap_code && n < a.N && 16 * j + 4 * q < d) *reinterpret_cast<unsigned*>(a.tap_code + tok * C + h * d + 16 * j + 4 * q) = pk;
+                }
+            }
+        } else {
+            // fp16(float(acc) * (s_o * s_wo) + bias); four blocks are exchanged between the quarters of the wavefront, which
+            // leaves a lane with the 16 channels of one block: 32 contiguous bytes
+#pragma unroll
+            for (int j = 0; j < NB; j += 4) {
+                unsigned p0[4], p1[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int g = g0 + j + u < ng ? g0 + j + u : ng - 1, h = g / tph, cl = 16 * (g - h * tph) + 4 * q;
+                    const int c = h * d + (cl < d ? cl : 0);
+                    const float4 w4 = *reinterpret_cast<const float4*>(a.sw + c);
+                    const float4 b4 = *reinterpret_cast<const float4*>(a.bias + c);
+                    // (converted by the intrinsic: a plain cast may be merged with the addition into one rounding)
+                    const __half2 y01 = __floats2half2_rn((float)acc[j + u][i][0] * (sam * w4.x) + b4.x, (float)acc[j + u][i][1] * (sam * w4.y) + b4.y);
+                    const __half2 y23 = __floats2half2_rn((float)acc[j + u][i][2] * (sam * w4.z) + b4.z, (float)acc[j + u][i][3] * (sam * w4.w) + b4.w);
+                    p0[u] = *reinterpret_cast<const unsigned*>(&y01);
+                    p1[u] = *reinterpret_cast<const unsigned*>(&y23);
+                }
+                quad_transpose(p0);
+                quad_transpose(p1);
+                const int g = g0 + j + q, h = g / tph, cl = 16 * (g - h * tph);
+                if (g < ng && n < a.N) {
+                    uint4* o = reinterpret_cast<uint4*>(a.out + tok * C + h * d + cl);  // (d % 8 == 0: 16-byte aligned)
+                    o[0] = make_uint4(p0[0], p1[0], p0[1], p1[1]);
+                    if (cl + 16 <= d) o[1] = make_uint4(p0[2], p1[2], p0[3], p1[3]);
+                }
+            }
+        }
+    }
+}
+
+template <int NB, int TPH>
+static hipError_t launch_gemm_op(GemmOpArgs a, hipStream_t st) {
+    const int ng = a.H * a.tph;
+    a.NX = (ng + NB - 1) / NB;
+    // While 128-token blocks would give every compute unit at most one workgroup, 64-token blocks: two workgroups per unit,
+    // each hiding the other's waits.
+    const bool small = (long)((a.tiles + 7) / 8) * a.NX <= 256;
+    a.MX = small ? (a.tiles + 3) / 4 : (a.tiles + 7) / 8;
+    const dim3 grid(8 * ((a.MX + 7) / 8) * a.NX);
+    if (small) hipLaunchKernelGGL((gemm_op_kernel<4, NB, TPH>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((gemm_op_kernel<8, NB, TPH>), grid, dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+static GemmOpArgs gemm_op_args(const StageChunk& c, const taq_shape& s, const int8_t* W, const float* sw) {
+    GemmOpArgs a = {};
+    a.A = c.code;
+    a.sa = c.s;
+    a.W = W;
+    a.sw = sw;
+    a.tiles = c.tile1 - c.tile0;
+    a.tile0 = c.tile0;
+    a.NT = c.NT;
+    a.N = s.N;
+    a.KC = (s.C + 63) / 64;
+    a.C = s.C;
+    a.H = s.H;
+    a.d = s.C / s.H;
+    a.tph = (a.d + 15) / 16;
+    a.packed = s.w_layout == 1 && s.C % 64 == 0;
+    a.pack_off = weight_pack_offset(s);
+    return a;
+}
+
+hipError_t launch_to_q_op(const StageChunk& c, const taq_shape& s, const int8_t* Wq, const float* s_wq, const taq_debug* dbg, hipStream_t st) {
+    GemmOpArgs a = gemm_op_args(c, s, Wq, s_wq);
+    a.q_op = c.q_op;
+    a.s_q = c.s_q;
+    a.qmax = s.bits_q == 4 ? 7.f : 127.f;
+    a.tap_code = dbg ? dbg->q_code : nullptr;
+    a.tap_scale = dbg ? dbg->s_Q : nullptr;
+    switch (a.tph) {
+        case 1: return launch_gemm_op<8, 1>(a, st);
+        case 2: return launch_gemm_op<8, 2>(a, st);
+        case 3: return launch_gemm_op<6, 3>(a, st);
+        case 4: return launch_gemm_op<8, 4>(a, st);
+        case 5: return launch_gemm_op<10, 5>(a, st);
+        case 6: return launch_gemm_op<6, 6>(a, st);
+        case 7: return launch_gemm_op<7, 7>(a, st);
+        case 8: return launch_gemm_op<8, 8>(a, st);
+        case 9: return launch_gemm_op<9, 9>(a, st);
+        case 10: return launch_gemm_op<10, 10>(a, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_to_out_op(const StageChunk& c, const taq_shape& s, const int8_t* Wo, const float* s_wo, const float* bias, __half* out,
+                            hipStream_t st) {
+    GemmOpArgs a = gemm_op_args(c, s, Wo, s_wo);
+    a.bias = bias;
+    a.out = out;
+    return launch_gemm_op<8, 0>(a, st);
 }
 
 }  // namespace taq

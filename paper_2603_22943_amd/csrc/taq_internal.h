@@ -30,13 +30,13 @@ struct KvLayout {
     size_t k16;       // f16 [B][T][C]  protected rows, compacted by slot
     size_t v16;
     size_t v16t;      // f16 [B][C][96] protected V rows transposed (slot along the last axis)
-    size_t image;     // [B][image_bytes] LDS-ready K~/V~ image for the fused block kernel (may be empty)
+    size_t image;     // [B][image_bytes] operand-ordered K~/V~ image of the attention kernels
     size_t image_bytes;
     size_t total;
     int Cb;
 };
 
-// LDS-ready image of the integer part of K~/V~ for one batch element (fused block kernel): one
+// LDS-ready image of the integer part of K~/V~ for one batch element (with bits_kv = 16: no integer rows at all): one
 // self-contained block per head, so that the wavefront that owns a head copies and waits for its own
 // block only. Offsets are relative to the head block; head_bytes is a multiple of 1 KiB (the unit of
 // the direct-to-LDS copy).
@@ -162,7 +162,7 @@ static inline KvLayout kv_layout(const taq_shape& s) {
     L.k16 = take(B * T * C * 2);
     L.v16 = take(B * T * C * 2);
     L.v16t = take(B * C * 96 * 2);
-    L.image_bytes = (fused_supported(s) || mid_supported(s)) ? align_up(kv_image(s).bytes, 256) : 0;
+    L.image_bytes = align_up(kv_image(s).bytes, 256);
     L.image = take(B * L.image_bytes);
     L.total = off;
     return L;
@@ -192,7 +192,66 @@ static inline KvWorkspace kv_workspace(const taq_shape& s) {
     return W;
 }
 
-// Workspace of taq_cross_attn (per request).
+// Kernel-per-stage path: its buffers hold tiles of 16 image tokens (NT = ceil(N/16) per batch element) in the order in
+// which the next kernel's matrix operands are read, so that every access is a contiguous KiB or 256 bytes. One tile:
+struct StageTile {
+    size_t code;   // i8  [ceil(C/64)][64 lanes][16]  codes of hidden, later of A^ V~ (lane = token + 16 * quarter of the K step)
+    size_t s;      // f32 [16]                        their scales
+    size_t q;      // u32 [H][tph][64 lanes]          Q~ codes as the to_q accumulators leave them, zero past the head
+    size_t s_q;    // f32 [H][16]
+    size_t o;      // f32 [H][tph][64 lanes][4]       A^ V~
+    size_t o_max;  // f32 [H][16]                     largest |A^ V~| of each (head, token)
+    size_t total;
+};
+static inline StageTile stage_tile(const taq_shape& s) {
+    StageTile t;
+    const size_t H = s.H, tph = (s.C / s.H + 15) / 16, kc = (s.C + 63) / 64;
+    t.code = kc * 1024;
+    t.s = 64;
+    t.q = H * tph * 256;
+    t.s_q = H * 64;
+    t.o = H * tph * 1024;
+    t.o_max = H * 64;
+    t.total = t.code + t.s + t.q + t.s_q + t.o + t.o_max;
+    return t;
+}
+static inline size_t stage_tiles(const taq_shape& s) { return (size_t)s.B * ((s.N + 15) / 16); }
+
+// Tiles [tile0, tile1) of the call (tile = b * NT + tile within the batch element) and their buffers.
+struct StageChunk {
+    int NT, tile0, tile1;
+    int8_t* code;
+    float* s;
+    unsigned* q_op;
+    float* s_q;
+    float* o_op;
+    float* o_max;
+};
+// How many tiles fit `bytes` of workspace (sections 256-byte aligned), and the buffers of a chunk of `n` tiles in it.
+static inline size_t stage_chunk_bytes(const taq_shape& s, size_t n) {
+    const StageTile t = stage_tile(s);
+    return align_up(n * t.code, 256) + align_up(n * t.s, 256) + align_up(n * t.q, 256) + align_up(n * t.s_q, 256) + align_up(n * t.o, 256) +
+           align_up(n * t.o_max, 256);
+}
+static inline StageChunk stage_chunk(const taq_shape& s, uint8_t* ws, size_t tile0, size_t tile1) {
+    const StageTile t = stage_tile(s);
+    const size_t n = tile1 - tile0;
+    StageChunk c;
+    c.NT = (s.N + 15) / 16;
+    c.tile0 = (int)tile0;
+    c.tile1 = (int)tile1;
+    auto take = [&](size_t bytes) { uint8_t* p = ws; ws += align_up(bytes, 256); return p; };
+    c.code = reinterpret_cast<int8_t*>(take(n * t.code));
+    c.s = reinterpret_cast<float*>(take(n * t.s));
+    c.q_op = reinterpret_cast<unsigned*>(take(n * t.q));
+    c.s_q = reinterpret_cast<float*>(take(n * t.s_q));
+    c.o_op = reinterpret_cast<float*>(take(n * t.o));
+    c.o_max = reinterpret_cast<float*>(take(n * t.o_max));
+    return c;
+}
+
+// Workspace of taq_cross_attn (per request): the head-group path and the full-precision modes use these sections, the
+// kernel-per-stage path lays its tiles out in the same memory.
 struct AttnWorkspace {
     size_t h_code;  // i8  [B*N][C]
     size_t s_h;     // f32 [B*N]
@@ -202,7 +261,8 @@ struct AttnWorkspace {
     size_t o_f;     // f32 [B*N][C]
     size_t o_code;  // i8  [B*N][C]
     size_t s_o;     // f32 [B*N]
-    size_t total;
+    size_t least;   // what the calls cannot do without (the stage path goes through fewer tiles at a time)
+    size_t total;   // with all tiles of the stage path at once
 };
 
 static inline AttnWorkspace attn_workspace(const taq_shape& s) {
@@ -218,7 +278,9 @@ static inline AttnWorkspace attn_workspace(const taq_shape& s) {
     W.o_f = take(M * C * 4);
     W.o_code = take(M * C);
     W.s_o = take(M * 4);
-    W.total = off;
+    const size_t one = stage_chunk_bytes(s, 1), all = stage_chunk_bytes(s, stage_tiles(s));
+    W.least = off > one ? off : one;
+    W.total = W.least > all ? W.least : all;
     return W;
 }
 
@@ -339,8 +401,32 @@ hipError_t launch_fused_mid(const FusedReq& rq, const taq_shape& s, float* o_f, 
 hipError_t launch_to_out_tail(const FusedReq& rq, const taq_shape& s, const float* o_f, const float* o_max,
                               const int8_t* o_code, const float* s_o, const taq_debug* dbg, hipStream_t st);
 
-// Attention core: scores, softmax, Eq. (3), A^ V~ for all (batch, head, token).
-hipError_t launch_attn_core(const int8_t* q_code, const float* s_q, const uint8_t* packed,
-                            const taq_shape& s, float* o_f, hipStream_t st, uint8_t* p_code = nullptr);
+// ---- kernel-per-stage path, on a chunk of tiles (StageChunk); taps in `dbg` are written by the kernel that computes them
+// per-token codes of hidden
+hipError_t launch_rowquant_op(const StageChunk& c, const taq_shape& s, const __half* hidden, const taq_debug* dbg, hipStream_t st);
+// to_q with the per-(token, head) quantizer of Eq. (2), third line
+hipError_t launch_to_q_op(const StageChunk& c, const taq_shape& s, const int8_t* Wq, const float* s_wq, const taq_debug* dbg, hipStream_t st);
+// scores, softmax, Eq. (3), A^ V~
+struct AttnOpArgs {
+    const unsigned* q_op;
+    const float* s_q;
+    const uint8_t* packed;
+    float* o_op;
+    float* o_max;
+    uint8_t* p_code;  // taps or NULL
+    float* O;
+    KvLayout L;
+    KvImage I;
+    int N, NT, tile0, tile1, b0, C, H, d, T, nt16;
+    float sig2;   // softmax scale * log2(e)
+    float pmax;   // linear grid: 255 or 15; log2 grid: 256 (brings 2^-code * s_V to the linear grid's magnitudes)
+    float plast;  // log2 grid: the last code, 255 or 15
+};
+hipError_t launch_attn_op(const StageChunk& c, const taq_shape& s, const uint8_t* packed, const taq_debug* dbg, hipStream_t st);
+// per-token codes of A^ V~ (over the codes of hidden, which are done with)
+hipError_t launch_oquant_op(const StageChunk& c, const taq_shape& s, const taq_debug* dbg, hipStream_t st);
+// to_out, bias, fp16
+hipError_t launch_to_out_op(const StageChunk& c, const taq_shape& s, const int8_t* Wo, const float* s_wo, const float* bias, __half* out,
+                            hipStream_t st);
 
 }  // namespace taq

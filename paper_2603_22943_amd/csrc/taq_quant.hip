@@ -118,6 +118,76 @@ __global__ __launch_bounds__(256) void rowquant_f16_kernel(const __half* __restr
     rowquant_f16_row(x + (size_t)row * K, K, scale + row, lane, [&](int v, uint2 c) { cr[v] = c; });
 }
 
+// Kernel-per-stage path: per-token codes of hidden in the order to_q's token operand is read (tiles of 16 tokens, per K step
+// of 64 codes one KiB, lane = token + 16 * quarter). C % 64 == 32: the second half of the last step is cleared.
+__global__ __launch_bounds__(256) void rowquant_op_kernel(const __half* __restrict__ x, StageChunk c, int N, int C,
+                                                          int8_t* __restrict__ tap_code, float* __restrict__ tap_scale) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int lt = blockIdx.x >> 2, r = ((int)blockIdx.x & 3) * 4 + wave;  // tile of the chunk, token of the tile
+    const int tile = c.tile0 + lt, b = tile / c.NT, n = (tile - b * c.NT) * 16 + r;
+    if (n >= N) return;  // (codes past the last token are never used)
+    const int KC = (C + 63) >> 6;
+    const size_t row = (size_t)b * N + n;
+    int8_t* code = c.code + (size_t)lt * KC * 1024 + r * 16;
+    rowquant_f16_row(x + row * C, C, c.s + lt * 16 + r, lane, [&](int v, uint2 w) {
+        *reinterpret_cast<uint2*>(code + (size_t)(v >> 3) * 1024 + ((v >> 1) & 3) * 256 + (v & 1) * 8) = w;
+        if (tap_code) *reinterpret_cast<uint2*>(tap_code + row * C + 8 * v) = w;
+    });
+    if ((C & 63) && lane < 4) {
+        const int v = (C >> 3) + lane;
+        *reinterpret_cast<uint2*>(code + (size_t)(v >> 3) * 1024 + ((v >> 1) & 3) * 256 + (v & 1) * 8) = make_uint2(0u, 0u);
+    }
+    if (tap_scale && lane == 0) tap_scale[row] = c.s[lt * 16 + r];
+}
+
+hipError_t launch_rowquant_op(const StageChunk& c, const taq_shape& s, const __half* hidden, const taq_debug* dbg, hipStream_t st) {
+    hipLaunchKernelGGL(rowquant_op_kernel, dim3(4 * (c.tile1 - c.tile0)), dim3(256), 0, st, hidden, c, s.N, s.C, dbg ? dbg->h_code : nullptr,
+                       dbg ? dbg->s_h : nullptr);
+    return hipGetLastError();
+}
+
+// Kernel-per-stage path: per-token codes of A^ V~ from its float32 values in accumulator order and the largest magnitudes
+// per head (one pass: the row maximum is there already). A workgroup per tile of 16 tokens; a lane forms the 16 codes of one
+// token and 16-channel segment, four groups of four channels, each a 16-byte load of a contiguous 256-byte piece.
+__global__ __launch_bounds__(256) void oquant_op_kernel(StageChunk c, int N, int C, int H, int d, int tph, int8_t* __restrict__ tap_code,
+                                                        float* __restrict__ tap_scale) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
+    const int lt = blockIdx.x, tile = c.tile0 + lt, b = tile / c.NT, n = (tile - b * c.NT) * 16 + r16;
+    const int KC = (C + 63) >> 6;
+    float amax = 0.f;
+    for (int h = q; h < H; h += 4) amax = fmaxf(amax, c.o_max[((size_t)lt * H + h) * 16 + r16]);
+    amax = quad_allmax(amax);
+    const bool zero = amax == 0.f;
+    const float safe = zero ? 1.f : amax, cq = quant_mult(127.f, safe), sc = zero ? 1.f : amax / 127.f;
+    if (wave == 0 && q == 0) {
+        c.s[lt * 16 + r16] = sc;
+        if (tap_scale && n < N) tap_scale[(size_t)b * N + n] = sc;
+    }
+    const float4* o = reinterpret_cast<const float4*>(c.o_op) + (size_t)lt * H * tph * 64 + r16;
+    for (int ks = wave; ks < KC; ks += 4) {
+        const int c0 = 64 * ks + 16 * q;
+        float4 x[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int ch = c0 + 4 * g < C ? c0 + 4 * g : 0;
+            const int h = ch / d, cl = ch - h * d;
+            x[g] = o[(size_t)(h * tph + (cl >> 4)) * 64 + 16 * ((cl >> 2) & 3)];
+        }
+        unsigned w[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) w[g] = c0 < C ? quant4_i8(x[g].x, x[g].y, x[g].z, x[g].w, cq, safe) : 0u;
+        const uint4 w4 = make_uint4(w[0], w[1], w[2], w[3]);
+        *reinterpret_cast<uint4*>(c.code + ((size_t)lt * KC + ks) * 1024 + lane * 16) = w4;
+        if (tap_code && n < N && c0 < C) *reinterpret_cast<uint4*>(tap_code + ((size_t)b * N + n) * C + c0) = w4;
+    }
+}
+
+hipError_t launch_oquant_op(const StageChunk& c, const taq_shape& s, const taq_debug* dbg, hipStream_t st) {
+    hipLaunchKernelGGL(oquant_op_kernel, dim3(c.tile1 - c.tile0), dim3(256), 0, st, c, s.N, s.C, s.H, s.C / s.H, (s.C / s.H + 15) / 16,
+                       dbg ? dbg->o_code : nullptr, dbg ? dbg->s_o : nullptr);
+    return hipGetLastError();
+}
+
 // First launch of taq_quantize_kv: the per-row codes of up to three fp16 matrices that share the row length K (the
 // context rows and, unless cached, the rows of Wk and Wv), and the protected-token list, each part on workgroups of
 // its own: one launch instead of four.
@@ -514,12 +584,8 @@ __device__ __forceinline__ void kvh_finish(const int32x4_t (&acc)[TPH], const Kv
     for (int j = 0; j < TPH; j += 4) {
         if (has_image && !side && TPH % 4 == 0 && t < I.rows_k)  // Kp, heads of a multiple of 4 tiles: [t][tile/4][q][tile%4][4]
             *reinterpret_cast<uint4*>(img + I.kp + kp_offset(TPH, t, j, q)) = make_uint4(pk[j], pk[j + 1], pk[j + 2], pk[j + 3]);
-        const auto s02 = __builtin_amdgcn_permlane32_swap(pk[j], pk[j + 2], false, false);
-        const auto s13 = __builtin_amdgcn_permlane32_swap(pk[j + 1], pk[j + 3], false, false);
-        const auto r01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
-        const auto r23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
-        // this lane now: tile j + q, its 16 channels in order
-        const unsigned w[4] = {(unsigned)r01[0], (unsigned)r01[1], (unsigned)r23[0], (unsigned)r23[1]};
+        unsigned w[4] = {pk[j], pk[j + 1], pk[j + 2], pk[j + 3]};
+        quad_transpose(w);  // this lane now: tile j + q, its 16 channels in order
         const int tl = j + q;
         const bool full = 16 * tl + 16 <= d, half = !full && 16 * tl < d;  // (d % 8 == 0)
         if (has_image && !side && TPH % 4 != 0 && t < I.rows_k && tl < TPH)  // Kp[t][tile][quarter][4]
