@@ -14,7 +14,7 @@
 // that the head's image block (8 to 27 KiB, fetched once into LDS) serves them all and several workgroups share a
 // compute unit. Bound by vector issue (softmax and Eq. 3, about 12 instructions per probability). The kernel that stood
 // here before staged and split K~/V~ itself in every workgroup, whatever the number of tokens: 31 us at B = 2, N = 2304,
-// 12 heads of 64, MEAS_ATTN us now.
+// 12 heads of 64, 13 us now.
 #include "taq_device.h"
 
 namespace taq {

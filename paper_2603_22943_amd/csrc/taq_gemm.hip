@@ -232,17 +232,23 @@ hipError_t launch_gemm_i8(const int8_t* A, const float* sa, const int8_t* W, con
 }
 
 // ------------------------------------------------------------------------------------------
-// to_q and to_out of the kernel-per-stage path. The same pipeline as gemm_i8_lds_kernel on operands that are already in
-// MFMA operand order: a 16 x 64 block is one contiguous KiB, in memory and in LDS (conflict-free as it is). Tokens come
-// that way from the quantizer kernels, weights from taq_pack_weight; row-major weights go through the swizzled stage of
+// to_q and to_out of the kernel-per-stage path, on operands in MFMA operand order: a 16 x 64 block is one contiguous KiB, in
+// memory and in LDS (conflict-free as it is). Tokens come that way from the quantizer kernels, weights from
+// taq_pack_weight; of row-major weights four lanes fetch the 64 bytes of a row, segments swizzled as in
 // gemm_i8_lds_kernel. Weight blocks are counted per head (tph = ceil(d/16) blocks each, the last one partly filled), so
-// that a workgroup of to_q holds whole heads and quantizes Q~ on its accumulators: what leaves the kernel is one byte per
+// that a wavefront of to_q holds whole heads and quantizes Q~ on its accumulators: what leaves the kernel is one byte per
 // channel instead of a float32 for a quantizer kernel to read again, in the registers' own order, which is the order in
 // which the attention's score operand wants it.
-//   MB tiles of 16 tokens x NB blocks of 16 channels per workgroup of four wavefronts; TPH > 0: to_q with heads of TPH
-//   blocks; TPH = 0: to_out.
-// What a compute unit receives per K step, (MB + NB) KiB, is most of the time at these sizes (measured over the whole chip
-// about 12 TB/s): to_q + quantizer at M = 4608, C = 768 took 14.3 + 7.1 us, MEAS_TOQ us now; to_out 14.3 -> MEAS_TOUT us.
+//
+// WM x WN wavefronts of MW token tiles x NW channel blocks each; TPH > 0: to_q with heads of TPH blocks (NW a multiple);
+// TPH = 0: to_out. Blocks go straight from global memory into LDS (no registers in between, so that several workgroups share
+// a compute unit and one's waits are filled by another's MFMAs), STAGES K steps ahead; the operands of the next step are read
+// from LDS while the current one is multiplied; one barrier per step. The LDS reads and the waits are written by hand: for
+// reads that it knows of, the compiler waits for every outstanding direct-to-LDS load, which would serialise the stages. A
+// wavefront's loads per stage are a constant (blocks past the last are fetched again, K steps past the end re-fetch the last
+// one into a buffer nobody reads any more), so "stage kc + 1 has arrived" is "at most (STAGES - 2) * NLD loads outstanding".
+// Bound by what a compute unit receives per K step, (WM MW + WN NW) KiB. With register staging this took 15.3 us at
+// M = 2048, C = 1280 and 41.9 us at M = 8192 (compiler-made register shuffles and one workgroup per unit), 10 and 22 us now.
 // ------------------------------------------------------------------------------------------
 struct GemmOpArgs {
     const int8_t* A;      // token codes in operand order
@@ -262,12 +268,30 @@ struct GemmOpArgs {
     size_t pack_off;
 };
 
-template <int MB, int NB, int TPH>
-__global__ __launch_bounds__(256) void gemm_op_kernel(GemmOpArgs a) {
-    constexpr int BLK = MB + NB, STAGES = 3, MW = MB / 4, RD = 4;
-    constexpr int NLD = (BLK + 3) / 4;
+template <int OFF>
+__device__ __forceinline__ int32x4_t lds_read16(unsigned addr) {
+    int32x4_t r;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF));
+    return r;
+}
+// NR blocks of 1 KiB from addr on, one operand register each.
+template <int NR>
+__device__ __forceinline__ void lds_read_blocks(int32x4_t (&r)[NR], unsigned addr) {
+    static_assert(NR <= 10, "reads are listed one by one");
+#define TAQ_RD(J) if constexpr (NR > J) r[NR > J ? J : 0] = lds_read16<1024 * J>(addr);
+    TAQ_RD(0) TAQ_RD(1) TAQ_RD(2) TAQ_RD(3) TAQ_RD(4) TAQ_RD(5) TAQ_RD(6) TAQ_RD(7) TAQ_RD(8) TAQ_RD(9)
+#undef TAQ_RD
+}
+
+template <int MW, int NW, int WM, int WN, int TPH, int STAGES>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2)))
+void gemm_op_kernel(GemmOpArgs a) {
+    constexpr int WAVES = WM * WN, MB = MW * WM, NB = NW * WN, BLK = MB + NB, NLD = (BLK + WAVES - 1) / WAVES;
+    static_assert(NLD * (STAGES - 1) < 64, "vmcnt");
+    static_assert(TPH == 0 || NW % (TPH ? TPH : 1) == 0, "whole heads per wavefront");
     __shared__ __align__(16) unsigned char lds[STAGES * BLK * 1024];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
+    const int wm = wave % WM, wn = wave / WM;
     // Workgroups are dealt to the 8 XCDs in turn. All channel blocks of a token block go to one XCD, one after the other, so
     // that its L2 fetches those tokens once (the weights, which every XCD reads whole, are the smaller operand).
     const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
@@ -275,107 +299,86 @@ __global__ __launch_bounds__(256) void gemm_op_kernel(GemmOpArgs a) {
     if (mb >= a.MX) return;
     const int t0 = mb * MB, g0 = nb * NB, ng = a.H * a.tph;  // first token tile, first weight block, weight blocks
     const int KC = a.KC, C = a.C, d = a.d, tph = TPH ? TPH : a.tph;
-    const int lrow = lane >> 2, lseg = lane & 3;
-    const int swz_st = lrow * 64 + ((lseg ^ ((lrow >> 1 ^ lrow >> 2) & 3)) << 4);
-    const int ld_a = lane * 16, ld_w = a.packed ? lane * 16 : r16 * 64 + ((q ^ ((r16 >> 1 ^ r16 >> 2) & 3)) << 4);
     const int8_t* src[NLD];
-    int step[NLD], last[NLD], st_off[NLD];
+    int step[NLD], last[NLD];
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
-        const int blk = wave + 4 * u < BLK ? wave + 4 * u : BLK - 1;
+        const int blk = wave + WAVES * u < BLK ? wave + WAVES * u : BLK - 1;
         if (blk < MB) {
             const int t = t0 + blk < a.tiles ? t0 + blk : a.tiles - 1;
             src[u] = a.A + (size_t)t * KC * 1024 + lane * 16;
             step[u] = 1024;
             last[u] = (KC - 1) * 1024;
-            st_off[u] = lane * 16;
         } else {
             const int g = g0 + blk - MB < ng ? g0 + blk - MB : ng - 1;
             if (a.packed) {
                 src[u] = a.W + a.pack_off + (size_t)g * KC * 1024 + lane * 16;
                 step[u] = 1024;
                 last[u] = (KC - 1) * 1024;
-                st_off[u] = lane * 16;
             } else {
+                const int lrow = lane >> 2, lseg = (lane & 3) ^ ((lrow >> 1 ^ lrow >> 2) & 3);
                 const int h = g / tph, row = h * d + 16 * (g - h * tph) + lrow;  // (rows past the head: results dropped)
                 src[u] = a.W + (size_t)(row < C ? row : C - 1) * C + 16 * lseg;
                 step[u] = 64;
                 last[u] = C - 16 - 16 * lseg;  // (C % 64 == 32: past the end the row's last codes, which meet zero token codes)
-                st_off[u] = swz_st;
             }
         }
     }
-    int32x4_t gr[RD][NLD];
     auto load_stage = [&](int kc, int s) {
 #pragma unroll
         for (int u = 0; u < NLD; ++u) {
             const int off = kc * step[u];
-            gr[s][u] = *reinterpret_cast<const int32x4_t*>(src[u] + (off < last[u] ? off : last[u]));
+            const int blk = wave + WAVES * u < BLK ? wave + WAVES * u : BLK - 1;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[u] + (off < last[u] ? off : last[u])),
+                                             (__attribute__((address_space(3))) void*)(lds + (s * BLK + blk) * 1024), 16, 0, 0);
         }
     };
-    auto store_stage = [&](int kc, int s) {
-        unsigned char* dst = lds + (kc % STAGES) * (BLK * 1024);
+    int32x4_t acc[NW][MW];
 #pragma unroll
-        for (int u = 0; u < NLD; ++u)
-            if (4 * u + 3 < BLK || wave + 4 * u < BLK) *reinterpret_cast<int32x4_t*>(dst + (wave + 4 * u) * 1024 + st_off[u]) = gr[s][u];
-    };
-    int32x4_t acc[NB][MW];
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
+    for (int j = 0; j < NW; ++j)
 #pragma unroll
         for (int i = 0; i < MW; ++i) acc[j][i] = (int32x4_t){0, 0, 0, 0};
-    int32x4_t wa[2][NB], xb[2][MW];
-    auto read_ops = [&](int kc, int set) {
-        const unsigned char* st = lds + (kc % STAGES) * (BLK * 1024);
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+    const unsigned ld_a = lds0 + wm * MW * 1024 + lane * 16;
+    const unsigned ld_w = lds0 + (MB + wn * NW) * 1024 + (a.packed ? lane * 16 : r16 * 64 + ((q ^ ((r16 >> 1 ^ r16 >> 2) & 3)) << 4));
 #pragma unroll
-        for (int i = 0; i < MW; ++i) xb[set][i] = *reinterpret_cast<const int32x4_t*>(st + (MW * wave + i) * 1024 + ld_a);
-#pragma unroll
-        for (int j = 0; j < NB; ++j) wa[set][j] = *reinterpret_cast<const int32x4_t*>(st + (MB + j) * 1024 + ld_w);
+    for (int s = 0; s < STAGES; ++s) load_stage(s, s);
+    int32x4_t xb[2][MW], wa[2][NW];  // operands of the step being multiplied and of the next
+    auto read_ops = [&](int set, int s) {
+        lds_read_blocks<MW>(xb[set], ld_a + s * (BLK * 1024));
+        lds_read_blocks<NW>(wa[set], ld_w + s * (BLK * 1024));
     };
-    auto mfmas = [&](int set) {
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 1) * NLD) : "memory");
+    read_ops(0, 0);
+    int cur = 0;  // stage of step kc
+    auto step_k = [&](int kc, int set) {
+        // this wavefront has its operands of step kc (so it is done with that stage) and its part of stage kc + 1 has arrived;
+        // after the barrier that holds for everybody
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+        for (int i = 0; i < MW; ++i) asm volatile("" : "+v"(xb[set][i]));  // (the registers are used after the wait, not before)
+#pragma unroll
+        for (int j = 0; j < NW; ++j) asm volatile("" : "+v"(wa[set][j]));
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 2) * NLD) : "memory");
+        const int nxt = cur + 1 == STAGES ? 0 : cur + 1;
+        read_ops(set ^ 1, nxt);
+        load_stage(kc + STAGES, cur);
+        cur = nxt;
+#pragma unroll
+        for (int j = 0; j < NW; ++j)
 #pragma unroll
             for (int i = 0; i < MW; ++i) acc[j][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[set][j], xb[set][i], acc[j][i], 0, 0, 0);
     };
-    load_stage(0, 0);
-    load_stage(1, 1);
-    store_stage(0, 0);
-    store_stage(1, 1);
-    load_stage(2, 2);
-    load_stage(3, 3);
-    load_stage(4, 0);
-    load_stage(5, 1);
-    __syncthreads();
-    read_ops(0, 0);
-    auto even_step = [&](int kc, int s) {  // s = (kc + 2) % 4
-        __syncthreads();
-        read_ops(kc + 1, 1);
-        store_stage(kc + 2, s);
-        store_stage(kc + 3, s + 1);
-        load_stage(kc + 6, s);
-        load_stage(kc + 7, s + 1);
-        mfmas(0);
-    };
-    auto odd_step = [&](int kc) {
-        __syncthreads();
-        read_ops(kc + 1, 0);
-        mfmas(1);
-    };
-    int kc = 0;
-    for (; kc + 4 <= KC; kc += 4) {
-        even_step(kc, 2);
-        odd_step(kc + 1);
-        even_step(kc + 2, 0);
-        odd_step(kc + 3);
+    for (int kc = 0; kc < KC; kc += 2) {
+        step_k(kc, 0);
+        if (kc + 1 < KC) step_k(kc + 1, 1);
     }
-    if (kc < KC) even_step(kc, 2);
-    if (kc + 1 < KC) odd_step(kc + 1);
-    if (kc + 2 < KC) even_step(kc + 2, 0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the re-fetched steps past the end
 
 #pragma unroll
     for (int i = 0; i < MW; ++i) {
-        const int t = t0 + MW * wave + i;
+        const int t = t0 + MW * wm + i;
         if (t >= a.tiles) continue;
         const int b = (a.tile0 + t) / a.NT, n = (a.tile0 + t - b * a.NT) * 16 + r16;
         const size_t tok = (size_t)b * a.N + n;
@@ -383,8 +386,8 @@ __global__ __launch_bounds__(256) void gemm_op_kernel(GemmOpArgs a) {
         if constexpr (TPH > 0) {
             // Qf = float(acc) * (s_h * s_wq); codes and scale per (token, head), in the defined order
 #pragma unroll
-            for (int hh = 0; hh < NB / (TPH ? TPH : 1); ++hh) {
-                const int h = g0 / TPH + hh;
+            for (int hh = 0; hh < NW / (TPH ? TPH : 1); ++hh) {
+                const int h = (g0 + wn * NW) / TPH + hh;
                 if (h >= a.H) continue;
                 float v[TPH ? TPH : 1][4];
                 float amax = 0.f;
@@ -418,11 +421,12 @@ __global__ __launch_bounds__(256) void gemm_op_kernel(GemmOpArgs a) {
             // fp16(float(acc) * (s_o * s_wo) + bias); four blocks are exchanged between the quarters of the wavefront, which
             // leaves a lane with the 16 channels of one block: 32 contiguous bytes
 #pragma unroll
-            for (int j = 0; j < NB; j += 4) {
+            for (int j = 0; j < NW; j += 4) {
+                const int gw = g0 + wn * NW + j;
                 unsigned p0[4], p1[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int g = g0 + j + u < ng ? g0 + j + u : ng - 1, h = g / tph, cl = 16 * (g - h * tph) + 4 * q;
+                    const int g = gw + u < ng ? gw + u : ng - 1, h = g / tph, cl = 16 * (g - h * tph) + 4 * q;
                     const int c = h * d + (cl < d ? cl : 0);
                     const float4 w4 = *reinterpret_cast<const float4*>(a.sw + c);
                     const float4 b4 = *reinterpret_cast<const float4*>(a.bias + c);
@@ -434,7 +438,7 @@ __global__ __launch_bounds__(256) void gemm_op_kernel(GemmOpArgs a) {
                 }
                 quad_transpose(p0);
                 quad_transpose(p1);
-                const int g = g0 + j + q, h = g / tph, cl = 16 * (g - h * tph);
+                const int g = gw + q, h = g / tph, cl = 16 * (g - h * tph);
                 if (g < ng && n < a.N) {
                     uint4* o = reinterpret_cast<uint4*>(a.out + tok * C + h * d + cl);  // (d % 8 == 0: 16-byte aligned)
                     o[0] = make_uint4(p0[0], p1[0], p0[1], p1[1]);
@@ -445,18 +449,30 @@ __global__ __launch_bounds__(256) void gemm_op_kernel(GemmOpArgs a) {
     }
 }
 
-template <int NB, int TPH>
-static hipError_t launch_gemm_op(GemmOpArgs a, hipStream_t st) {
-    const int ng = a.H * a.tph;
-    a.NX = (ng + NB - 1) / NB;
-    // While 128-token blocks would give every compute unit at most one workgroup, 64-token blocks: two workgroups per unit,
-    // each hiding the other's waits.
-    const bool small = (long)((a.tiles + 7) / 8) * a.NX <= 256;
-    a.MX = small ? (a.tiles + 3) / 4 : (a.tiles + 7) / 8;
-    const dim3 grid(8 * ((a.MX + 7) / 8) * a.NX);
-    if (small) hipLaunchKernelGGL((gemm_op_kernel<4, NB, TPH>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((gemm_op_kernel<8, NB, TPH>), grid, dim3(256), 0, st, a);
+template <int MW, int NW, int WM, int WN, int TPH>
+static hipError_t launch_gemm_op_cfg(GemmOpArgs a, hipStream_t st) {
+    a.NX = (a.H * a.tph + NW * WN - 1) / (NW * WN);
+    a.MX = (a.tiles + MW * WM - 1) / (MW * WM);
+    hipLaunchKernelGGL((gemm_op_kernel<MW, NW, WM, WN, TPH, 4>), dim3(8 * ((a.MX + 7) / 8) * a.NX), dim3(64 * WM * WN), 0, st, a);
     return hipGetLastError();
+}
+
+// Blocks of 64 tokens with four wavefronts while they are at most one per compute unit, above that 128 tokens with eight
+// wavefronts: half the weight bytes per token, and the larger workgroup's longer start is shared by two. At C = 1280 (128 channels
+// per block) 7.7 and 8.8 us at 512 tokens, 10.6 and 9.5 us at 2048 (320 and 160 workgroups), 23.2 and 21.9 us at 8192; at C = 640
+// the lines cross between 2048 and 4608 tokens (160 and 360 workgroups). Blocks of 256 tokens or 256 channels are slower everywhere.
+template <int NW, int TPH>
+static hipError_t launch_gemm_op(const GemmOpArgs& a, hipStream_t st) {
+    const long nx = (a.H * a.tph + 2 * NW - 1) / (2 * NW);
+    if ((a.tiles + 3) / 4 * nx <= 256) return launch_gemm_op_cfg<2, NW, 2, 2, TPH>(a, st);
+    return launch_gemm_op_cfg<2, NW, 4, 2, TPH>(a, st);
+}
+
+// Heads of 96 channels and more fill a wavefront: one head per block, and 128 tokens take twice the accumulators instead.
+template <int TPH>
+static hipError_t launch_gemm_op_wide(const GemmOpArgs& a, hipStream_t st) {
+    if ((long)((a.tiles + 7) / 8) * a.H <= 256) return launch_gemm_op_cfg<1, TPH, 4, 1, TPH>(a, st);
+    return launch_gemm_op_cfg<2, TPH, 4, 1, TPH>(a, st);
 }
 
 static GemmOpArgs gemm_op_args(const StageChunk& c, const taq_shape& s, const int8_t* W, const float* sw) {
@@ -487,16 +503,16 @@ hipError_t launch_to_q_op(const StageChunk& c, const taq_shape& s, const int8_t*
     a.tap_code = dbg ? dbg->q_code : nullptr;
     a.tap_scale = dbg ? dbg->s_Q : nullptr;
     switch (a.tph) {
-        case 1: return launch_gemm_op<8, 1>(a, st);
-        case 2: return launch_gemm_op<8, 2>(a, st);
-        case 3: return launch_gemm_op<6, 3>(a, st);
-        case 4: return launch_gemm_op<8, 4>(a, st);
-        case 5: return launch_gemm_op<10, 5>(a, st);
-        case 6: return launch_gemm_op<6, 6>(a, st);
-        case 7: return launch_gemm_op<7, 7>(a, st);
-        case 8: return launch_gemm_op<8, 8>(a, st);
-        case 9: return launch_gemm_op<9, 9>(a, st);
-        case 10: return launch_gemm_op<10, 10>(a, st);
+        case 1: return launch_gemm_op<4, 1>(a, st);
+        case 2: return launch_gemm_op<4, 2>(a, st);
+        case 3: return launch_gemm_op<3, 3>(a, st);
+        case 4: return launch_gemm_op<4, 4>(a, st);
+        case 5: return launch_gemm_op<5, 5>(a, st);
+        case 6: return launch_gemm_op_wide<6>(a, st);
+        case 7: return launch_gemm_op_wide<7>(a, st);
+        case 8: return launch_gemm_op_wide<8>(a, st);
+        case 9: return launch_gemm_op_wide<9>(a, st);
+        case 10: return launch_gemm_op_wide<10>(a, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -506,7 +522,7 @@ hipError_t launch_to_out_op(const StageChunk& c, const taq_shape& s, const int8_
     GemmOpArgs a = gemm_op_args(c, s, Wo, s_wo);
     a.bias = bias;
     a.out = out;
-    return launch_gemm_op<8, 0>(a, st);
+    return launch_gemm_op<4, 0>(a, st);
 }
 
 }  // namespace taq

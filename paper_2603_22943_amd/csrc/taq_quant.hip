@@ -147,44 +147,48 @@ hipError_t launch_rowquant_op(const StageChunk& c, const taq_shape& s, const __h
 }
 
 // Kernel-per-stage path: per-token codes of A^ V~ from its float32 values in accumulator order and the largest magnitudes
-// per head (one pass: the row maximum is there already). A workgroup per tile of 16 tokens; a lane forms the 16 codes of one
-// token and 16-channel segment, four groups of four channels, each a 16-byte load of a contiguous 256-byte piece.
-__global__ __launch_bounds__(256) void oquant_op_kernel(StageChunk c, int N, int C, int H, int d, int tph, int8_t* __restrict__ tap_code,
-                                                        float* __restrict__ tap_scale) {
+// per head (one pass: the row maximum is there already). A wavefront forms one K step of a tile of 16 tokens, a lane the 16
+// codes of one token and 16-channel segment: four groups of four channels, each a 16-byte load of a contiguous 256-byte
+// piece. With one workgroup per tile, its wavefronts walking the steps, a call was as long as one wavefront's five dependent
+// rounds: 7.1 us at 64 tokens and 8.4 us at 2048 (C = 1280), 4.2 and 5.4 us this way; from 8192 tokens on both are bound by
+// memory (10 to 11 us).
+__global__ __launch_bounds__(256) void oquant_op_kernel(StageChunk c, int N, int C, int H, int d, int tph, unsigned inv_d,
+                                                        int8_t* __restrict__ tap_code, float* __restrict__ tap_scale) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
-    const int lt = blockIdx.x, tile = c.tile0 + lt, b = tile / c.NT, n = (tile - b * c.NT) * 16 + r16;
-    const int KC = (C + 63) >> 6;
+    const int lt = blockIdx.x, ks = blockIdx.y * 4 + wave, KC = (C + 63) >> 6;
+    if (ks >= KC) return;
+    const int c0 = 64 * ks + 16 * q;
+    const float4* o = reinterpret_cast<const float4*>(c.o_op) + (size_t)lt * H * tph * 64 + r16;
+    float4 x[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int ch = c0 + 4 * g < C ? c0 + 4 * g : 0;
+        const int h = (int)__umulhi((unsigned)ch, inv_d), cl = ch - h * d;  // (ch / d: exact while ch * d < 2^32)
+        x[g] = o[(size_t)(h * tph + (cl >> 4)) * 64 + 16 * ((cl >> 2) & 3)];
+    }
     float amax = 0.f;
     for (int h = q; h < H; h += 4) amax = fmaxf(amax, c.o_max[((size_t)lt * H + h) * 16 + r16]);
     amax = quad_allmax(amax);
     const bool zero = amax == 0.f;
-    const float safe = zero ? 1.f : amax, cq = quant_mult(127.f, safe), sc = zero ? 1.f : amax / 127.f;
-    if (wave == 0 && q == 0) {
+    const float safe = zero ? 1.f : amax, cq = quant_mult(127.f, safe);
+    unsigned w[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) w[g] = c0 < C ? quant4_i8(x[g].x, x[g].y, x[g].z, x[g].w, cq, safe) : 0u;
+    const uint4 w4 = make_uint4(w[0], w[1], w[2], w[3]);
+    *reinterpret_cast<uint4*>(c.code + ((size_t)lt * KC + ks) * 1024 + lane * 16) = w4;
+    const int tile = c.tile0 + lt, b = tile / c.NT, n = (tile - b * c.NT) * 16 + r16;
+    if (tap_code && n < N && c0 < C) *reinterpret_cast<uint4*>(tap_code + ((size_t)b * N + n) * C + c0) = w4;
+    if (ks == 0 && q == 0) {
+        const float sc = zero ? 1.f : amax / 127.f;
         c.s[lt * 16 + r16] = sc;
         if (tap_scale && n < N) tap_scale[(size_t)b * N + n] = sc;
-    }
-    const float4* o = reinterpret_cast<const float4*>(c.o_op) + (size_t)lt * H * tph * 64 + r16;
-    for (int ks = wave; ks < KC; ks += 4) {
-        const int c0 = 64 * ks + 16 * q;
-        float4 x[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int ch = c0 + 4 * g < C ? c0 + 4 * g : 0;
-            const int h = ch / d, cl = ch - h * d;
-            x[g] = o[(size_t)(h * tph + (cl >> 4)) * 64 + 16 * ((cl >> 2) & 3)];
-        }
-        unsigned w[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) w[g] = c0 < C ? quant4_i8(x[g].x, x[g].y, x[g].z, x[g].w, cq, safe) : 0u;
-        const uint4 w4 = make_uint4(w[0], w[1], w[2], w[3]);
-        *reinterpret_cast<uint4*>(c.code + ((size_t)lt * KC + ks) * 1024 + lane * 16) = w4;
-        if (tap_code && n < N && c0 < C) *reinterpret_cast<uint4*>(tap_code + ((size_t)b * N + n) * C + c0) = w4;
     }
 }
 
 hipError_t launch_oquant_op(const StageChunk& c, const taq_shape& s, const taq_debug* dbg, hipStream_t st) {
-    hipLaunchKernelGGL(oquant_op_kernel, dim3(c.tile1 - c.tile0), dim3(256), 0, st, c, s.N, s.C, s.H, s.C / s.H, (s.C / s.H + 15) / 16,
-                       dbg ? dbg->o_code : nullptr, dbg ? dbg->s_o : nullptr);
+    const int d = s.C / s.H;
+    hipLaunchKernelGGL(oquant_op_kernel, dim3(c.tile1 - c.tile0, ((s.C + 63) / 64 + 3) / 4), dim3(256), 0, st, c, s.N, s.C, s.H, d, (d + 15) / 16,
+                       (unsigned)(0x100000000ull / d + 1), dbg ? dbg->o_code : nullptr, dbg ? dbg->s_o : nullptr);
     return hipGetLastError();
 }
 
