@@ -78,10 +78,11 @@ typedef struct taq_shape {
                                 TAQ_PROB_ROWMAX (2) : the affine quantizer with the row's own range:
                                                       amax = largest unprotected A of the (token, head) row,
                                                       code = rint(pmax*A/amax), A^ = code*amax/pmax     */
-    int tok_tile;            /* image tokens per workgroup of the single-kernel and head-group paths: 0 = the library
-                                picks (16 when 32-token tiles would fill at most half of the GPU's compute units;
-                                head-group path: when they would give at most four workgroups per compute unit);
-                                32 or 16 forces one (tests and tuning). Results do not depend on it.              */
+    int tok_tile;            /* 0 = the library picks by the number of tokens and compute units. Single-kernel shapes: image
+                                tokens per workgroup, 16 when 32-token tiles would fill at most half of the GPU's compute
+                                units. C = 1280 shapes: 16 = two kernels, a workgroup per 16 tokens and head group (few
+                                tokens), 32 = one kernel per stage (many). 32 or 16 forces one (tests and tuning).
+                                Results do not depend on it.                                                              */
 } taq_shape;
 
 enum { TAQ_PROB_LINEAR = 0, TAQ_PROB_LOG2 = 1, TAQ_PROB_ROWMAX = 2 };

@@ -272,21 +272,12 @@ static int cross_attn_impl(const void* hidden, const void* qkv_packed, const int
         return TAQ_OK;
     }
 
-    if (mid_supported(s) && !(dbg && dbg->stage_mask)) {
-        // C = 1280 layers, two kernels: hidden codes + to_q + Q~ + attention per head group, then the per-token codes of
-        // A^ V~ + to_out; A^ V~ (float32) and its partial row maxima pass through the workspace (the q_f region holds the
-        // maxima). Taps are written by the kernels themselves.
+    if (mid_supported(s) && mid_preferred(s) && !(dbg && dbg->stage_mask)) {
+        // C = 1280 layers of few tokens, two kernels; A^ V~ (float32) and its partial row maxima pass through the workspace
+        // (the q_f region holds the maxima).
         FusedReq rq = {static_cast<const __half*>(hidden), static_cast<const uint8_t*>(qkv_packed), Wq, Wo, scales,
                        static_cast<__half*>(out)};
         TAQ_TRY_HIP(launch_fused_mid(rq, s, o_f, q_f, dbg, st));
-        if (M <= 1024) {  // few token tiles: every to_out workgroup quantizes its 16 rows of A^ V~ itself
-            TAQ_TRY_HIP(launch_to_out_tail(rq, s, o_f, q_f, nullptr, nullptr, dbg, st));
-        } else {          // many: quantize each row once, in a kernel of its own
-            TAQ_TRY_HIP(launch_rowquant_f32(o_f, M, s.C, o_code, s_o, st));
-            TAQ_TRY_HIP(launch_to_out_tail(rq, s, o_f, q_f, o_code, s_o, dbg, st));
-            if (dbg && dbg->o_code) TAQ_TRY_HIP(hipMemcpyAsync(dbg->o_code, o_code, (size_t)M * s.C, hipMemcpyDeviceToDevice, st));
-            if (dbg && dbg->s_o) TAQ_TRY_HIP(hipMemcpyAsync(dbg->s_o, s_o, (size_t)M * 4, hipMemcpyDeviceToDevice, st));
-        }
         return TAQ_OK;
     }
 

@@ -38,8 +38,9 @@ __device__ __forceinline__ float byte_to_float(unsigned w, int e) { return (floa
 // ------------------------------------------------------------------------------------------
 // Fused block kernel
 // ------------------------------------------------------------------------------------------
+template <int R>
 struct FusedTable {
-    FusedReq req[TAQ_MAX_REQ];
+    FusedReq req[R];
 };
 
 struct FusedDims {
@@ -59,10 +60,6 @@ struct FusedDims {
     float* ws_of;            // f32 [B*N][C]
     float* ws_omax;          // f32 [B*N][omax_n]  max |A^ V~| over each wavefront's share of a token's row
     int omax_n;              // partial maxima per token (heads x wavefronts per head and token group)
-    const int8_t* core_qcode;  // i8  [B*N][C]  Q~ codes (attention-core-only variant)
-    const float* core_sq;      // f32 [B*N][H]  ... and their scales
-    const int8_t* ws_ocode;  // i8  [B*N][C]  per-token codes of A^ V~ when a separate kernel formed them (else NULL)
-    const float* ws_so;      // f32 [B*N]     ... and their scales
 };
 
 template <int D, int NH, int NTT, int NG, int TOK = 32, bool DENSE = false>
@@ -101,22 +98,20 @@ struct FusedCfg {
 // (A operands shared by both tiles). NTT = 1: two wavefronts per head, one tile each (16 wavefronts per CU
 // instead of 8: more latency hiding for twice the A-operand traffic). TOK = 16 (with NTT = 1): one wavefront per
 // head and half the tokens, for layers whose 32-token tiles would leave most compute units without a workgroup.
-// CORE: only the attention core (profiling by stage): Q~ codes and scales come from the workspace instead of the
-// hidden tile and to_q, and the kernel stops after writing A^ V~ as float32.
-// NG > 1 (layers too wide for one workgroup's LDS): the workgroup owns one head group (NH of the NH*NG
-// heads), takes the per-token codes of `hidden` from the workspace, and stops after A^ V~, which it writes to
-// the workspace as float32; the per-token quantization of that result and to_out run as separate kernels.
+// NG > 1 (layers too wide for one workgroup's LDS; TOK = 16): the workgroup owns one head group (NH of the NH*NG
+// heads), forms the per-token codes of `hidden` itself, and stops after A^ V~, which it writes to the workspace as
+// float32; the per-token quantization of that result and to_out are a second kernel.
 // NT16 > 0: the number of 16-token score tiles, ceil(T / 16), is this compile-time constant (5 for the 77 text tokens
 // of every configured workload: no run-time guards around the tiles) and the taps on intermediate results are
 // compiled out; NT16 = 0: any T up to 96, guards at run time, taps where the caller asks for them.
-template <int D, int NH, int NTT, int NG, int PG, int TOK = 32, bool CORE = false, int NT16 = 0, bool DENSE = false>
+template <int D, int NH, int NTT, int NG, int PG, int TOK = 32, int NT16 = 0, bool DENSE = false>
 __global__ __launch_bounds__(NG > 1 ? 512 : 64 * NH * (TOK / (16 * NTT)))
 __attribute__((amdgpu_waves_per_eu(DENSE ? 4 : 1, DENSE ? 4 : NG > 1 ? 2 : (NH * (TOK / (16 * NTT)) + 3) / 4)))
-void fused_block_kernel(FusedTable tab, FusedDims dm) {
+void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm) {
     using F = FusedCfg<D, NH, NTT, NG, TOK, DENSE>;
-    static_assert(!DENSE || (NG == 1 && !CORE && NH * (TOK / (16 * NTT)) == 8), "two 8-wavefront workgroups per compute unit");
+    static_assert(!DENSE || (NG == 1 && NH * (TOK / (16 * NTT)) == 8), "two 8-wavefront workgroups per compute unit");
     static_assert(TOK == 32 || (TOK == 16 && NTT == 1), "a workgroup owns 32 image tokens, or 16 with one tile per wavefront");
-    static_assert(!CORE || NG == 1, "the attention-core-only variant exists for the single-kernel shapes");
+    static_assert(NG == 1 || TOK == 16, "head groups: one tile of 16 image tokens");
     constexpr int C = F::C, H = F::H, TPH = F::TPH, KS = F::KS, FS = F::FS, KC = F::KC, NT = F::NT;
     constexpr int SUB = F::SUB, TPS = F::TPS;
     constexpr bool LOGP = PG == TAQ_PROB_LOG2, ROWMAX = PG == TAQ_PROB_ROWMAX;  // grid of the probabilities, Eq. (3)
@@ -144,7 +139,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     // ---- The hidden tile's loads are issued before anything else: they are the head of the kernel's one unavoidable
     // latency chain (HBM), and everything below (scalar loads of layout fields, of the protected-token count from
     // global memory, address arithmetic for the weights) would otherwise sit in front of them.
-    constexpr bool HQ1 = NG == 1 && !CORE;         // single-kernel variant: 16 threads per token, 8-byte loads
+    constexpr bool HQ1 = NG == 1;                  // single-kernel variant: 16 threads per token, 8-byte loads
     constexpr int TPT = NG > 1 ? NT / TOK : 16;    // threads per token
     constexpr int CH = NG > 1 ? C / (8 * TPT) : 1; // head-group variant: 16-byte pieces of a hidden row per thread
     const int tok0 = tid / TPT, part0 = tid % TPT;
@@ -174,7 +169,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     float* wsc = reinterpret_cast<float*>(smem + img_bytes + TOK * F::TILE_RS);  // s_wq | s_wo | bias_o  [3C]
     float* s_h = wsc + (NG == 1 ? 3 * C : NH * D);               // [TOK]  (NG > 1: only s_wq of the workgroup's heads)
     unsigned* omax = reinterpret_cast<unsigned*>(s_h + TOK);     // [TOK][NH]  (NG == 1)
-    int* qacc = reinterpret_cast<int*>(s_h + TOK);               // [K ranges][TOK/16][NH*TPH][64][4] partial to_q sums (NG > 1)
+    int* qacc = reinterpret_cast<int*>(s_h + TOK);               // [K ranges][NH*TPH][64][4] partial to_q sums (NG > 1)
 
     const uint8_t* packed = rq.packed;
     const int ntrig = reinterpret_cast<const int*>(packed + dm.L.ntrig)[b];
@@ -202,7 +197,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
         return (int32x4_t)__builtin_amdgcn_raw_buffer_load_b128(rs, wrow[j], off, 0);
     };
     int32x4_t wreg[F::PREFETCH_W ? TPH : 1][F::PREFETCH_W ? KC : 1];
-    constexpr int RING = CORE ? 0 : F::RING, NF = F::NF;
+    constexpr int RING = F::RING, NF = F::NF;
     constexpr int RPS = RING ? (RING + KC - 1) / KC : 0;  // ring loads issued per step of the hidden quantizer
     int32x4_t wring[RING ? RING : 1];
     const float* swq = wsc;
@@ -239,7 +234,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
         }
     };
 
-    if constexpr (NG == 1 && !CORE) {
+    if constexpr (NG == 1) {
         // ---- phase 0: issue every global read up front, oldest first in the order of use (loads return in
         // order): hidden tile, weight scales, this head's to_q weight slice, the K~/V~ image
         // (16 threads per token, 4 channels per load: the first 16*TOK threads hold the tile, requested above)
@@ -305,7 +300,6 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     // the order of use: the hidden tile, this wavefront's share of the to_q weights, the K~/V~ image blocks
     constexpr int TW = NH * TPH;                       // weight tiles (16 output channels) of this workgroup
     constexpr int KP = NG > 1 ? NT / 128 : 1;          // the wavefronts split to_q into two tile groups x KP K ranges
-    constexpr int N2 = TOK / 16;                       // token groups of 16, all covered by every wavefront's share
     constexpr int TJ = NG > 1 ? TW / 2 : 1;            // weight tiles per tile group
     constexpr int KW = NG > 1 ? KC / KP : 1;           // K steps per K range
     constexpr int IMV = NG > 1 ? (NH * F::IMGC * 64 + NT - 1) / NT : 1;
@@ -390,7 +384,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
 
     // ================= to_q for this head: Qf^T[c][n]
     int32x4_t hb[NTT][NG == 1 && RING == 0 ? KC : 1];
-    if constexpr (NG == 1 && !CORE && RING == 0) {
+    if constexpr (NG == 1 && RING == 0) {
 #pragma unroll
         for (int nt = 0; nt < NTT; ++nt)
 #pragma unroll
@@ -398,9 +392,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
                 hb[nt][ks] = *reinterpret_cast<const int32x4_t*>(tileq + (tbase + 16 * nt + r16) * F::TILE_RS + 64 * ks + 16 * q);
     }
     int32x4_t pacc[NTT][TPH];
-    if constexpr (CORE) {
-        // no projection: Q~ comes from the workspace
-    } else if constexpr (F::PREFETCH_W) {
+    if constexpr (F::PREFETCH_W) {
         // K step outermost: the order in which the weight loads were issued, so that the MFMAs follow the weights as they
         // arrive and only one step's worth is left to do after the last load
 #pragma unroll
@@ -450,28 +442,20 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
         }
     } else {
         // Head-group variant: the wavefronts split the workgroup's to_q by weight tile group (js) and K range (kp),
-        // each for all of the workgroup's tokens; every wavefront leaves its int32 partial sums in a slot of its own
-        // in LDS, and then adds up the KP partial sums of its own (head, token group): integer adds, exact in any order.
+        // each for the workgroup's 16 tokens; every wavefront leaves its int32 partial sums in a slot of its own
+        // in LDS, and then adds up the KP partial sums of its own head: integer adds, exact in any order.
         const int wv = tid >> 6, js = wv & 1, kp = wv >> 1;
         if (sub < SUB) load_protected();  // needed only after the second barrier: they travel during the MFMAs
-        int32x4_t hb2[N2][KW];
+        int32x4_t hb2[KW];
 #pragma unroll
-        for (int n2 = 0; n2 < N2; ++n2)
-#pragma unroll
-            for (int kk = 0; kk < KW; ++kk)
-                hb2[n2][kk] = *reinterpret_cast<const int32x4_t*>(tileq + (16 * n2 + r16) * F::TILE_RS + 64 * (kp * KW + kk) + 16 * q);
+        for (int kk = 0; kk < KW; ++kk)
+            hb2[kk] = *reinterpret_cast<const int32x4_t*>(tileq + r16 * F::TILE_RS + 64 * (kp * KW + kk) + 16 * q);
 #pragma unroll
         for (int jj = 0; jj < TJ; ++jj) {
-            int32x4_t a2[N2];
+            int32x4_t a2 = (int32x4_t){0, 0, 0, 0};
 #pragma unroll
-            for (int n2 = 0; n2 < N2; ++n2) a2[n2] = (int32x4_t){0, 0, 0, 0};
-#pragma unroll
-            for (int kk = 0; kk < KW; ++kk)
-#pragma unroll
-                for (int n2 = 0; n2 < N2; ++n2) a2[n2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wpre[jj][kk], hb2[n2][kk], a2[n2], 0, 0, 0);
-#pragma unroll
-            for (int n2 = 0; n2 < N2; ++n2)
-                *reinterpret_cast<int32x4_t*>(qacc + (((kp * N2 + n2) * TW + js * TJ + jj) * 64 + lane) * 4) = a2[n2];
+            for (int kk = 0; kk < KW; ++kk) a2 = __builtin_amdgcn_mfma_i32_16x16x64_i8(wpre[jj][kk], hb2[kk], a2, 0, 0, 0);
+            *reinterpret_cast<int32x4_t*>(qacc + ((kp * TW + js * TJ + jj) * 64 + lane) * 4) = a2;
         }
         {   // the K~/V~ image blocks (read into registers in phase 0) go to LDS
             const int img16 = (int)((NH * dm.I.head_bytes) >> 4);
@@ -482,28 +466,25 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
             }
         }
         __syncthreads();
-        if (sub >= SUB) return;  // 16-token variant: only ROLES of the eight wavefronts carry on (no barrier follows)
+        if (sub >= SUB) return;  // only ROLES of the eight wavefronts carry on (no barrier follows)
 #pragma unroll
         for (int j = 0; j < TPH; ++j) {
-            pacc[0][j] = *reinterpret_cast<const int32x4_t*>(qacc + (((tbase >> 4) * TW + hl * TPH + j) * 64 + lane) * 4);
+            pacc[0][j] = *reinterpret_cast<const int32x4_t*>(qacc + ((hl * TPH + j) * 64 + lane) * 4);
 #pragma unroll
-            for (int p = 1; p < KP; ++p)
-                pacc[0][j] += *reinterpret_cast<const int32x4_t*>(qacc + (((p * N2 + (tbase >> 4)) * TW + hl * TPH + j) * 64 + lane) * 4);
+            for (int p = 1; p < KP; ++p) pacc[0][j] += *reinterpret_cast<const int32x4_t*>(qacc + ((p * TW + hl * TPH + j) * 64 + lane) * 4);
         }
     }
     // Everything the Q~ step reads from LDS is fetched now, so that no LDS access sits between the issue of the
     // image copy below and the wait for it (the compiler orders LDS accesses after outstanding direct-to-LDS loads).
     float4 wq4[TPH];
     float shv[NTT];
-    if constexpr (!CORE) {
 #pragma unroll
-        for (int j = 0; j < TPH; ++j) {
-            const int cl = 16 * j + 4 * q;
-            wq4[j] = *reinterpret_cast<const float4*>((NG == 1 ? swq + h * D : wsc + hl * D) + (((16 * j + 16 <= D) || cl < D) ? cl : 0));
-        }
-#pragma unroll
-        for (int nt = 0; nt < NTT; ++nt) shv[nt] = s_h[tbase + 16 * nt + r16];
+    for (int j = 0; j < TPH; ++j) {
+        const int cl = 16 * j + 4 * q;
+        wq4[j] = *reinterpret_cast<const float4*>((NG == 1 ? swq + h * D : wsc + hl * D) + (((16 * j + 16 <= D) || cl < D) ? cl : 0));
     }
+#pragma unroll
+    for (int nt = 0; nt < NTT; ++nt) shv[nt] = s_h[tbase + 16 * nt + r16];
     // This head's block of the K~/V~ image: straight into LDS, 1 KiB per wavefront-wide load (LDS address =
     // base + lane * 16), no registers in between; it travels while to_q and Q~ are computed, and only this
     // wavefront reads it, so only this wavefront waits for it. The last piece may be fetched more than once.
@@ -527,15 +508,6 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     float sq2[NTT];
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) {
-        if constexpr (CORE) {  // Q~ codes (one per byte) and per-(token, head) scales as a separate kernel formed them
-#pragma unroll
-            for (int j = 0; j < TPH; ++j) {
-                const int cl = 16 * j + 4 * q;
-                qpk[nt][j] = cl < D ? *reinterpret_cast<const unsigned*>(dm.core_qcode + tok[nt] * C + h * D + cl) : 0u;
-            }
-            sq2[nt] = fmaxf(dm.core_sq[tok[nt] * H + h] * dm.sig2, 1e-37f);
-            continue;
-        }
         const float sh = shv[nt];
         float qf[TPH][4];
         float qmax = 0.f;
@@ -786,7 +758,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) {
         const float Z = quad_allsum(Zs[nt]);
-        kqp[nt] = dm.pmax * __builtin_amdgcn_rcpf(Z);
+        kqp[nt] = quant_mult(dm.pmax, Z);  // pmax / Z, as the stage path forms it: the same codes from either
         kq[nt] = kqp[nt];
         lz[nt] = LOGP ? __builtin_amdgcn_logf(Z) : 0.f;  // log2 Z >= 0: the largest term of Z is 1
         rz[nt] = 1.f;
@@ -796,10 +768,9 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
             // less than 2^-40 of the row (or none at all) are dropped: their codes would scale a vanishing range.
             const float eu = quad_allmax(eus[nt]);
             if (eu > Z * 9.094947e-13f) {
-                const float re = __builtin_amdgcn_rcpf(eu);
-                kq[nt] = dm.pmax * re;
-                rz[nt] = Z * re;
-                fz[nt] = eu * __builtin_amdgcn_rcpf(Z);
+                kq[nt] = quant_mult(dm.pmax, eu);
+                rz[nt] = quant_mult(Z, eu);
+                fz[nt] = quant_mult(eu, Z);
             }
         }
     }
@@ -923,7 +894,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
         }
     }
 
-    if (F::PREFETCH_W && !CORE) {  // to_out's weight slice travels while A^ V~ is quantized (two barriers away from its use)
+    if (F::PREFETCH_W) {  // to_out's weight slice travels while A^ V~ is quantized (two barriers away from its use)
 #pragma unroll
         for (int j = 0; j < TPH; ++j)
 #pragma unroll
@@ -937,7 +908,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     // O = oacc * of, of = 2^-kexp / pmax (times range / Z on the row-range grid). Where nobody needs O itself (no tap, no
     // workspace copy) the products are not formed: the row maximum is max|oacc| * of (a product with a positive
     // constant is monotone, so this IS the maximum of the products), and the quantizer takes oacc and of apart.
-    constexpr bool KEEP_O = NG > 1 || CORE || TAPS;
+    constexpr bool KEEP_O = NG > 1 || TAPS;
     const float osc = reinterpret_cast<const float*>(imgh + dm.I.oscale)[0] * (1.0f / dm.pmax);
     float of[NTT];
 #pragma unroll
@@ -956,16 +927,16 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
             if (KEEP_O && nvalid[nt] && valid) {
                 const float4 o4 = make_float4(oacc[nt][k][0], oacc[nt][k][1], oacc[nt][k][2], oacc[nt][k][3]);
                 if (TAPS && dm.dbg.O) *reinterpret_cast<float4*>(dm.dbg.O + tok[nt] * C + h * D + 16 * jt + 4 * q) = o4;
-                if constexpr (NG > 1 || CORE) *reinterpret_cast<float4*>(dm.ws_of + tok[nt] * C + h * D + 16 * jt + 4 * q) = o4;
+                if constexpr (NG > 1) *reinterpret_cast<float4*>(dm.ws_of + tok[nt] * C + h * D + 16 * jt + 4 * q) = o4;
             }
         }
         if constexpr (!KEEP_O) omx *= of[nt];
         omx = quad_allmax(omx);
-        if (NG == 1 && !CORE && q == 0) omax[(tbase + 16 * nt + r16) * NH + hl] = __float_as_uint(omx);
+        if (NG == 1 && q == 0) omax[(tbase + 16 * nt + r16) * NH + hl] = __float_as_uint(omx);
         // head-group variant: this wavefront's share of the token's row maximum, for the kernel that quantizes the row
         if (NG > 1 && q == 0 && nvalid[nt]) dm.ws_omax[tok[nt] * (H * SUB) + h * SUB + sub] = omx;
     }
-    if constexpr (NG > 1 || CORE) return;  // the per-token quantization of A^ V~ and to_out are separate kernels
+    if constexpr (NG > 1) return;  // the per-token quantization of A^ V~ and to_out are separate kernels
     __syncthreads();  // every wavefront is past its reads of the hidden codes
     float so[NTT];
 #pragma unroll
@@ -1065,46 +1036,45 @@ static inline int device_cu_count() {
     return n;
 }
 
-template <int D, int NH, int NTT, int NG, int PG, int TOK, bool CORE, int NT16 = 0, bool DENSE = false>
-static hipError_t launch_fused_grid(const FusedTable& tab, const FusedDims& dm, hipStream_t st) {
+template <int D, int NH, int NTT, int NG, int PG, int TOK, int NT16 = 0, bool DENSE = false>
+static hipError_t launch_fused_grid(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& tab, const FusedDims& dm, hipStream_t st) {
     if constexpr (NT16 == 0) {  // 65 to 80 text tokens: the instantiation without run-time guards around the score tiles
         const bool taps = dm.dbg.h_code || dm.dbg.s_h || dm.dbg.q_code || dm.dbg.s_Q || dm.dbg.O || dm.dbg.o_code || dm.dbg.s_o || dm.dbg.p_code;
-        if (dm.nt16 == 5 && !taps) return launch_fused_grid<D, NH, NTT, NG, PG, TOK, CORE, 5>(tab, dm, st);
+        if (dm.nt16 == 5 && !taps) return launch_fused_grid<D, NH, NTT, NG, PG, TOK, 5>(tab, dm, st);
     }
     using F = FusedCfg<D, NH, NTT, NG, TOK, DENSE>;
     static std::atomic<unsigned long long> lds_set{0};
     const size_t bytes = NG == 1 ? dm.I.bytes + TOK * F::TILE_RS + 3 * F::C * 4 + TOK * 4 + TOK * NH * 4  // = fused_lds_bytes
                                  : (size_t)NH * dm.I.head_bytes + TOK * F::TILE_RS + NH * D * 4 + TOK * 4 +
-                                       (F::NT / 128) * (TOK / 16) * NH * F::TPH * 1024;  // = mid_lds_bytes at TOK = 32
+                                       (F::NT / 128) * NH * F::TPH * 1024;  // = mid_lds_bytes
     if (bytes > 160 * 1024 || dm.I.head_bytes > (size_t)F::IMGC * 1024) return hipErrorInvalidValue;
-    if constexpr (!DENSE && NT16 == 5 && D == 40 && NH == 8 && NTT == 2 && NG == 1 && !CORE) {
+    if constexpr (!DENSE && NT16 == 5 && D == 40 && NH == 8 && NTT == 2 && NG == 1) {
         // More token tiles than compute units and a working set of at most half a compute unit's LDS: the instantiation
         // of which two workgroups share a compute unit (one is in its arithmetic while the other waits for memory).
         if ((dm.N + TOK - 1) / TOK * dm.R * dm.B > device_cu_count() && bytes <= 80 * 1024)
-            return launch_fused_grid<D, NH, NTT, NG, PG, TOK, CORE, NT16, true>(tab, dm, st);
+            return launch_fused_grid<D, NH, NTT, NG, PG, TOK, NT16, true>(tab, dm, st);
     }
-    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&fused_block_kernel<D, NH, NTT, NG, PG, TOK, CORE, NT16, DENSE>), 160 * 1024, lds_set);
+    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&fused_block_kernel<D, NH, NTT, NG, PG, TOK, NT16, DENSE>), 160 * 1024, lds_set);
     if (e != hipSuccess) return e;
     const int tiles = (dm.N + TOK - 1) / TOK;
     if (tiles > 65535 || dm.R > 65535 || (NG > 1 && dm.R != 1)) return hipErrorInvalidValue;
     const dim3 grid = NG > 1 ? dim3(dm.B, tiles, NG) : dim3(dm.B, dm.R, tiles);
-    hipLaunchKernelGGL((fused_block_kernel<D, NH, NTT, NG, PG, TOK, CORE, NT16, DENSE>), grid, dim3(F::NT), bytes, st, tab, dm);
+    hipLaunchKernelGGL((fused_block_kernel<D, NH, NTT, NG, PG, TOK, NT16, DENSE>), grid, dim3(F::NT), bytes, st, tab, dm);
     return hipGetLastError();
 }
 
-template <int D, int NH, int NTT, int NG, int TOK = 32, bool CORE = false>
-static hipError_t launch_fused_cfg(const FusedTable& tab, const FusedDims& dm, int grid, hipStream_t st) {
-    if (grid == TAQ_PROB_LOG2) return launch_fused_grid<D, NH, NTT, NG, TAQ_PROB_LOG2, TOK, CORE>(tab, dm, st);
-    if (grid == TAQ_PROB_ROWMAX) return launch_fused_grid<D, NH, NTT, NG, TAQ_PROB_ROWMAX, TOK, CORE>(tab, dm, st);
-    return launch_fused_grid<D, NH, NTT, NG, TAQ_PROB_LINEAR, TOK, CORE>(tab, dm, st);
+template <int D, int NH, int NTT, int NG, int TOK>
+static hipError_t launch_fused_cfg(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& tab, const FusedDims& dm, int grid, hipStream_t st) {
+    if (grid == TAQ_PROB_LOG2) return launch_fused_grid<D, NH, NTT, NG, TAQ_PROB_LOG2, TOK>(tab, dm, st);
+    if (grid == TAQ_PROB_ROWMAX) return launch_fused_grid<D, NH, NTT, NG, TAQ_PROB_ROWMAX, TOK>(tab, dm, st);
+    return launch_fused_grid<D, NH, NTT, NG, TAQ_PROB_LINEAR, TOK>(tab, dm, st);
 }
 
-// Family launchers, one translation unit each. tok = 32 or 16 image tokens per workgroup; core: the attention core
-// alone (single-kernel families only).
-hipError_t launch_fused_d40(const FusedTable& tab, const FusedDims& dm, int grid, int tok, bool core, hipStream_t st);   // (d, H) = (40, 8)
-hipError_t launch_fused_d80(const FusedTable& tab, const FusedDims& dm, int grid, int tok, bool core, hipStream_t st);   // (80, 8)
-hipError_t launch_fused_d64(const FusedTable& tab, const FusedDims& dm, int grid, int tok, bool core, hipStream_t st);   // (64, 10)
-hipError_t launch_fused_mid160(const FusedTable& tab, const FusedDims& dm, int grid, int tok, hipStream_t st);           // (160, 8): 8 groups of 1 head
-hipError_t launch_fused_mid64(const FusedTable& tab, const FusedDims& dm, int grid, int tok, hipStream_t st);            // (64, 20): 10 groups of 2 heads
+// Family launchers, one translation unit each. tok = 32 or 16 image tokens per workgroup (head groups: 16).
+hipError_t launch_fused_d40(const FusedTable<TAQ_MAX_REQ>& tab, const FusedDims& dm, int grid, int tok, hipStream_t st);   // (d, H) = (40, 8)
+hipError_t launch_fused_d80(const FusedTable<TAQ_MAX_REQ>& tab, const FusedDims& dm, int grid, int tok, hipStream_t st);   // (80, 8)
+hipError_t launch_fused_d64(const FusedTable<TAQ_MAX_REQ>& tab, const FusedDims& dm, int grid, int tok, hipStream_t st);   // (64, 10)
+hipError_t launch_fused_mid160(const FusedTable<1>& tab, const FusedDims& dm, int grid, hipStream_t st);         // (160, 8): 8 groups of 1 head
+hipError_t launch_fused_mid64(const FusedTable<1>& tab, const FusedDims& dm, int grid, hipStream_t st);          // (64, 20): 10 groups of 2 heads
 
 }  // namespace taq

@@ -3,8 +3,8 @@
 
 namespace taq {
 
-hipError_t launch_fused_mid160(const FusedTable& tab, const FusedDims& dm, int grid, int tok, hipStream_t st) {
-    return tok == 16 ? launch_fused_cfg<160, 1, 1, 8, 16>(tab, dm, grid, st) : launch_fused_cfg<160, 1, 1, 8>(tab, dm, grid, st);
+hipError_t launch_fused_mid160(const FusedTable<1>& tab, const FusedDims& dm, int grid, hipStream_t st) {
+    return launch_fused_cfg<160, 1, 1, 8, 16>(tab, dm, grid, st);
 }
 
 }  // namespace taq

@@ -130,11 +130,12 @@ static inline bool fused_supported(const taq_shape& s) {
 
 // Shapes of the head-group variant (to_q + Q~ + attention per head group; C = 1280 layers):
 // (d, H) = (160, 8) with one head per workgroup, (64, 20) with two.
+static inline int mid_groups(const taq_shape& s) { return s.C / s.H == 160 ? 8 : 10; }
 static inline size_t mid_lds_bytes(const taq_shape& s) {
     const int d = s.C / s.H;
     const size_t nh = d == 160 ? 1 : 2;
-    // image blocks | 32 token rows of codes | s_wq of the heads | s_h | partial to_q sums [4 K ranges][2 token groups][tiles][1 KiB]
-    return nh * kv_image(s).head_bytes + 32 * ((size_t)s.C + 16) + nh * d * 4 + 32 * 4 + 8 * nh * (size_t)((d + 15) / 16) * 1024;
+    // image blocks | 16 token rows of codes | s_wq of the heads | s_h | partial to_q sums [4 K ranges][tiles][1 KiB]
+    return nh * kv_image(s).head_bytes + 16 * ((size_t)s.C + 16) + nh * d * 4 + 16 * 4 + 4 * nh * (size_t)((d + 15) / 16) * 1024;
 }
 static inline bool mid_supported(const taq_shape& s) {
     if (fp_mode(s)) return false;
@@ -144,6 +145,16 @@ static inline bool mid_supported(const taq_shape& s) {
     if (!((d == 160 && s.H == 8) || (d == 64 && s.H == 20))) return false;
     if (s.N > 16 * 65535) return false;  // token tiles are a y dimension of the grid
     return mid_lds_bytes(s) <= 160 * 1024;
+}
+// Whether the head-group path takes such a layer, or the kernel-per-stage path. Head groups save three launches and every
+// pass over the workspace but one, but each workgroup reads its share of Wq for 16 tokens only and fills a compute unit, so
+// the time goes with the rounds of 256 workgroups: 14 us + 12 us per further round at d = 160, 13 + 8 us at d = 64, half as
+// much again with row-major weights, against 33 to 38 us for the five stage kernels at these sizes (2048 tokens, d = 160:
+// 56.6 and 40.9 us; 8192: 159 and 87 us). shape.tok_tile = 16 or 32 forces head groups or stages (tests and tuning).
+static inline bool mid_preferred(const taq_shape& s) {
+    if (s.tok_tile) return s.tok_tile == 16;
+    const long rounds = ((long)s.B * ((s.N + 15) / 16) * mid_groups(s) + 255) / 256;
+    return rounds <= (s.C / s.H == 160 ? 2 : 3) - (s.w_layout ? 0 : 1);
 }
 
 static inline KvLayout kv_layout(const taq_shape& s) {
@@ -388,18 +399,12 @@ struct FusedReq {
     const float* scales;
     __half* out;
 };
-// Whole block in one kernel (shapes of fused_supported only). dbg may be NULL. With core_qcode != NULL (R == 1) the
-// kernel runs the attention core alone: Q~ codes i8 [B*N][C] and scales f32 [B*N][H] in, float32 A^ V~ [B*N][C] out.
-hipError_t launch_fused_block(const FusedReq* reqs, int R, const taq_shape& s, const taq_debug* dbg, hipStream_t st,
-                              const int8_t* core_qcode = nullptr, const float* core_sq = nullptr, float* core_of = nullptr);
+// Whole block in one kernel (shapes of fused_supported only). dbg may be NULL.
+hipError_t launch_fused_block(const FusedReq* reqs, int R, const taq_shape& s, const taq_debug* dbg, hipStream_t st);
 // Head-group path (shapes of mid_supported), two kernels: (1) per-token codes of `hidden`, to_q, Q~ and the attention
 // per head group, writing float32 A^ V~ [B*N][C] and partial row maxima [B*N][<= 40] to the workspace; (2) per-token
-// codes of A^ V~ and to_out (with o_code != NULL the codes come from the row quantizer kernel instead). Taps in `dbg`
-// are written by the kernel that computes them.
-hipError_t launch_fused_mid(const FusedReq& rq, const taq_shape& s, float* o_f, float* o_max, const taq_debug* dbg,
-                            hipStream_t st);
-hipError_t launch_to_out_tail(const FusedReq& rq, const taq_shape& s, const float* o_f, const float* o_max,
-                              const int8_t* o_code, const float* s_o, const taq_debug* dbg, hipStream_t st);
+// codes of A^ V~ and to_out. Taps in `dbg` are written by the kernel that computes them.
+hipError_t launch_fused_mid(const FusedReq& rq, const taq_shape& s, float* o_f, float* o_max, const taq_debug* dbg, hipStream_t st);
 
 // ---- kernel-per-stage path, on a chunk of tiles (StageChunk); taps in `dbg` are written by the kernel that computes them
 // per-token codes of hidden
