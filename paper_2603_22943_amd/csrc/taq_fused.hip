@@ -121,7 +121,7 @@ hipError_t launch_pack_weight(const int8_t* codes, const taq_shape& s, int8_t* o
 // one kernel less. Same operand layout and epilogue as the last phase of the fused kernel.
 // (At most 128 registers per lane, so that two 8-wavefront workgroups share a compute unit: the 256-token layers have
 // 320 workgroups, and with one per compute unit the last 64 of them ran as a second round after the first had finished.)
-template <int C, int OT>
+template <int C, int OT, bool ROWMAJ>
 __global__ __launch_bounds__(64 * OT) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void to_out_tail_kernel(FusedReq rq, FusedDims dm) {
     constexpr int KC = C / 64, NT = 64 * OT, TILE_RS = C + 16;
@@ -135,11 +135,11 @@ void to_out_tail_kernel(FusedReq rq, FusedDims dm) {
     const int N = dm.N, n0 = tile * TOKS;
     int8_t* tileq = reinterpret_cast<int8_t*>(smem);               // [TOKS][C+16]
     float* s_o = reinterpret_cast<float*>(smem + TOKS * TILE_RS);  // [TOKS]
+    unsigned char* slot = smem + TOKS * (TILE_RS + 4) + wave * 1024;  // row-major weights only
     // The rows of the tile are requested first: they are needed first (quantizer), and loads return in order; the
     // weights, needed only after the barrier, travel while the rows are quantized.
-    const int cr = 16 * gt + r16;
-    const int wrow = dm.w_layout ? (int)dm.w_pack_off + (gt * KC) * 1024 + lane * 16 : cr * C + 16 * q;
-    const int wstep = dm.w_layout ? 1024 : 64;
+    const int wrow = !ROWMAJ ? (int)dm.w_pack_off + (gt * KC) * 1024 + lane * 16 : (16 * gt + (lane >> 2)) * C + 16 * (lane & 3);
+    constexpr int wstep = ROWMAJ ? 64 : 1024;
     int32x4_t wa[KC];
     {
         const int tk = tid >> 5, part = tid & 31;  // token of the tile, piece of its row
@@ -178,6 +178,10 @@ void to_out_tail_kernel(FusedReq rq, FusedDims dm) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int ks = KPRE; ks < KC; ++ks) wa[ks] = *reinterpret_cast<const int32x4_t*>(rq.wo + wrow + wstep * ks);
+    }
+    if constexpr (ROWMAJ) {
+#pragma unroll
+        for (int ks = 0; ks < KC; ++ks) wa[ks] = exchange_rows(wa[ks], slot, lane);
     }
     __syncthreads();
     int32x4_t acc = (int32x4_t){0, 0, 0, 0};
@@ -257,9 +261,10 @@ hipError_t launch_fused_mid(const FusedReq& rq, const taq_shape& s, float* o_f, 
     if (e != hipSuccess) return e;
     dm.dbg = all;
     constexpr int C = 1280, OT = 8;
-    static_assert(16 * (C + 16) + 16 * 4 <= 64 * 1024, "LDS without an attribute");
-    if (s.C != C) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((to_out_tail_kernel<C, OT>), dim3(dm.B, (dm.N + 15) / 16, C / 16 / OT), dim3(64 * OT), 16 * (C + 16) + 16 * 4, st, rq, dm);
+    const unsigned lds = 16 * (C + 16) + 16 * 4;  // (below 64 KiB, the exchange of row-major weights included: needs no attribute)
+    const dim3 grid(dm.B, (dm.N + 15) / 16, C / 16 / OT);
+    if (s.w_layout) hipLaunchKernelGGL((to_out_tail_kernel<C, OT, false>), grid, dim3(64 * OT), lds, st, rq, dm);
+    else hipLaunchKernelGGL((to_out_tail_kernel<C, OT, true>), grid, dim3(64 * OT), lds + OT * 1024, st, rq, dm);
     return hipGetLastError();
 }
 

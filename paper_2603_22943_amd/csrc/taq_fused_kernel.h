@@ -33,7 +33,21 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rsrc(const int8_t* p, u
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(p), 0, (int)bytes, 0x00020000);
 }
 
-__device__ __forceinline__ float byte_to_float(unsigned w, int e) { return (float)(int)(int8_t)((w >> (8 * e)) & 0xFF); }
+// A 16 x 64 block of row-major codes, fetched with four neighbouring lanes per row (lane = 4 * row + segment), in MFMA operand
+// order (lane = row + 16 * segment): through the KiB at `slot`, which is this wavefront's alone. The segments of a row are
+// swizzled, so that neither access has bank conflicts; LDS serves a wavefront in order, so that blocks can follow one another
+// without a wait.
+__device__ __forceinline__ int32x4_t exchange_rows(int32x4_t w, unsigned char* slot, int lane) {
+    const int lr = lane >> 2, ls = lane & 3, r16 = lane & 15, q = lane >> 4;
+    *reinterpret_cast<int32x4_t*>(slot + lr * 64 + ((ls ^ ((lr >> 1 ^ lr >> 2) & 3)) << 4)) = w;
+    return *reinterpret_cast<const int32x4_t*>(slot + r16 * 64 + ((q ^ ((r16 >> 1 ^ r16 >> 2) & 3)) << 4));
+}
+
+// x, and the compiler does not know it: what is computed from it is computed here and not kept from elsewhere.
+__device__ __forceinline__ int opaque(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
 
 // ------------------------------------------------------------------------------------------
 // Fused block kernel
@@ -89,8 +103,10 @@ struct FusedCfg {
     // only one step's B operands are live); left to itself the compiler keeps one to ten loads ahead and the loop
     // waits on latency.
     static constexpr int NF = TPH * KC;  // weight loads (16 rows x 64 bytes) of one projection per wavefront
-    // two wavefronts per SIMD (256 registers each), or three at ten heads (168)
-    static constexpr int RING_MAX = DENSE ? 6 : NH <= 8 ? (NTT == 1 ? 32 : 24) : (NTT == 1 ? 12 : 8);
+    // As many as the registers take: two wavefronts per SIMD (256 registers each), three at ten heads (168), four DENSE (128).
+    // (DENSE 6 -> 12: 65.3 -> 63.4 us for 16 requests of 4096 tokens; 24 and 8 -> 32 and 16 of two token tiles: 20.6 -> 19.9 us
+    // at eight heads of 80 and 8192 tokens, 21.6 -> 20.9 us at ten of 64; one more step up spills.)
+    static constexpr int RING_MAX = DENSE ? 12 : NH <= 8 ? 32 : 16;
     static constexpr int RING = (!PREFETCH_W && NG == 1) ? (NF < RING_MAX ? NF : RING_MAX) : 0;
 };
 
@@ -104,7 +120,7 @@ struct FusedCfg {
 // NT16 > 0: the number of 16-token score tiles, ceil(T / 16), is this compile-time constant (5 for the 77 text tokens
 // of every configured workload: no run-time guards around the tiles) and the taps on intermediate results are
 // compiled out; NT16 = 0: any T up to 96, guards at run time, taps where the caller asks for them.
-template <int D, int NH, int NTT, int NG, int PG, int TOK = 32, int NT16 = 0, bool DENSE = false>
+template <int D, int NH, int NTT, int NG, int PG, int TOK = 32, int NT16 = 0, bool DENSE = false, bool ROWMAJ = false>
 __global__ __launch_bounds__(NG > 1 ? 512 : 64 * NH * (TOK / (16 * NTT)))
 __attribute__((amdgpu_waves_per_eu(DENSE ? 4 : 1, DENSE ? 4 : NG > 1 ? 2 : (NH * (TOK / (16 * NTT)) + 3) / 4)))
 void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm) {
@@ -119,7 +135,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     constexpr bool TAPS = NT16 == 0;       // taps of intermediate codes and scales (tests, profiling)
     extern __shared__ __align__(16) unsigned char smem[];
 
-    const int tid = threadIdx.x, hl = (tid >> 6) % NH, lane = tid & 63, r16 = lane & 15, q = lane >> 4;
+    const int tid = threadIdx.x, hl = (tid >> 6) % NH, lane = tid & 63, r16 = lane & 15, q = DENSE ? opaque(lane >> 4) : lane >> 4;
     // Grid: x = batch element, y = request, z = token tile; head-group variant (one request): x = batch element,
     // y = token tile, z = head group. Workgroups are dispatched x fastest, so consecutive ones (which round-robin over
     // the 8 XCDs) share a token tile index and differ in the batch element / request: one XCD, few K~/V~ images. The
@@ -180,15 +196,18 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     // one contiguous KiB, otherwise 16 rows x 64 bytes)
     int wrow[TPH];
     const int wstep = dm.w_layout ? 1024 : 64;
+    auto set_wrow = [&](int ln) {
 #pragma unroll
-    for (int j = 0; j < TPH; ++j) {
-        const int c = h * D + 16 * j + r16;
-        wrow[j] = dm.w_layout ? (int)dm.w_pack_off + ((h * TPH + j) * KC) * 1024 + lane * 16 : (c < C ? c : C - 1) * C + 16 * q;
-        // Weight rows past the head (the upper lanes of a partly filled last tile) are not fetched: their products are
-        // dropped anyway, and at d = 40 they are a sixth of the bytes every CU pulls through its L2. Their lanes carry
-        // an offset past the end of the buffer, for which a buffer load returns zero without a memory access.
-        if (!((D % 16 == 0) || 16 * j + 16 <= D || r16 < D - 16 * j)) wrow[j] = 0x7fffffff;
-    }
+        for (int j = 0; j < TPH; ++j) {
+            const int row = ln & 15, c = h * D + 16 * j + row;
+            wrow[j] = dm.w_layout ? (int)dm.w_pack_off + ((h * TPH + j) * KC) * 1024 + ln * 16 : (c < C ? c : C - 1) * C + 16 * (ln >> 4);
+            // Weight rows past the head (the upper lanes of a partly filled last tile) are not fetched: their products are
+            // dropped anyway, and at d = 40 they are a sixth of the bytes every CU pulls through its L2. Their lanes carry
+            // an offset past the end of the buffer, for which a buffer load returns zero without a memory access.
+            if (!((D % 16 == 0) || 16 * j + 16 <= D || row < D - 16 * j)) wrow[j] = 0x7fffffff;
+        }
+    };
+    set_wrow(lane);
     // Buffer loads: the descriptor (base, size) and the step sit in scalar registers and the lane's part is a 32-bit
     // offset, so a load costs no vector address arithmetic (a 64-bit vector add per load otherwise) and the lanes
     // without a row need neither a branch nor registers cleared by hand.
@@ -198,6 +217,18 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     };
     int32x4_t wreg[F::PREFETCH_W ? TPH : 1][F::PREFETCH_W ? KC : 1];
     constexpr int RING = F::RING, NF = F::NF;
+    // ROWMAJ: row-major weights through the ring. Fetched as the MFMA wants them (lane = row + 16 * quarter), such a load
+    // touches 64 separate 16-byte pieces, which the texture path serves one per clock: 29.4 us at C = 640 and 2048 tokens.
+    // Here four neighbouring lanes take the 64 contiguous bytes of a row, the two halves of a 128-byte line one after the
+    // other (23.5 -> 19.5 us at 4096 tokens), and the lanes are exchanged through LDS: 18.3 us (operand-ordered weights: 15.0;
+    // an exchange by DPP selects in registers: 21.2). The KiB for it is the start of the head's K~/V~ block: to_q is done
+    // before the image arrives there, and to_out begins when the attention is through with it.
+    static_assert(!ROWMAJ || (D % 16 == 0 && KC % 2 == 0), "whole tiles, whole 128-byte lines");
+    const int rm_off = (h * D + (lane >> 2)) * C + 16 * (lane & 3);
+    auto ring_load = [&](const __amdgpu_buffer_rsrc_t rs, int f) -> int32x4_t {  // the f-th load of a projection
+        if constexpr (ROWMAJ) return (int32x4_t)__builtin_amdgcn_raw_buffer_load_b128(rs, rm_off, 16 * ((f / 2) % TPH) * C + 64 * (f / (2 * TPH) * 2 + f % 2), 0);
+        return load_w(rs, f % TPH, wstep * (f / TPH));
+    };
     constexpr int RPS = RING ? (RING + KC - 1) / KC : 0;  // ring loads issued per step of the hidden quantizer
     int32x4_t wring[RING ? RING : 1];
     const float* swq = wsc;
@@ -278,7 +309,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             }
             if constexpr (RING > 0) {  // the first RING loads of to_q, in the order the MFMAs use them
     #pragma unroll
-                for (int f = it * RPS; f < (it + 1) * RPS && f < RING; ++f) wring[f] = load_w(rs_wq, f % TPH, wstep * (f / TPH));
+                for (int f = it * RPS; f < (it + 1) * RPS && f < RING; ++f) wring[f] = ring_load(rs_wq, f);
             }
             if (HOLDS) {
                 const half2_t x01 = *reinterpret_cast<const half2_t*>(&xin[it].x), x23 = *reinterpret_cast<const half2_t*>(&xin[it].y);
@@ -306,7 +337,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     int32x4_t wpre[TJ][KW];
     int32x4_t imv[IMV];
     if constexpr (NG > 1) {
-        static_assert(NG == 1 || (TW % 2 == 0 && KC % KP == 0 && C % (8 * TPT) == 0 && (TPT == 16 || TPT == 32)), "head-group split");
+        static_assert(NG == 1 || (D % 16 == 0 && TW % 2 == 0 && KC % KP == 0 && C % (8 * TPT) == 0 && (TPT == 16 || TPT == 32)), "head-group split");
         const int wv = tid >> 6, js = wv & 1, kp = wv >> 1;
         float4 swv = make_float4(0.f, 0.f, 0.f, 0.f);  // s_wq of this workgroup's heads: NH*D floats
         if (tid < NH * D / 4) swv = reinterpret_cast<const float4*>(rq.scales + (size_t)by * NH * D)[tid];
@@ -350,10 +381,9 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
                     const int jj = f / KW, kk = f % KW;
                     const int tw = js * TJ + jj;                       // weight tile within the workgroup
                     const int hh = by * NH + tw / TPH;    // its head and tile within the head
-                    const int c = hh * D + 16 * (tw % TPH) + r16;
-                    const int off = dm.w_layout ? (int)dm.w_pack_off + ((hh * TPH + tw % TPH) * KC) * 1024 + lane * 16
-                                                : (c < C ? c : C - 1) * C + 16 * q;
-                    wpre[jj][kk] = *reinterpret_cast<const int32x4_t*>(rq.wq + off + wstep * (kp * KW + kk));
+                    const int off = !ROWMAJ ? (int)dm.w_pack_off + ((hh * TPH + tw % TPH) * KC) * 1024 + lane * 16
+                                                : (hh * D + 16 * (tw % TPH) + (lane >> 2)) * C + 16 * (lane & 3);  // (exchanged below)
+                    wpre[jj][kk] = *reinterpret_cast<const int32x4_t*>(rq.wq + off + (ROWMAJ ? 64 : 1024) * (kp * KW + kk));
                 } else {            // the K~/V~ image blocks of this workgroup's heads
                     const int i = tid + (f - TJ * KW) * NT;
                     imv[f - TJ * KW] = gimg[i < img16 ? i : img16 - 1];
@@ -382,6 +412,49 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         tok[nt] = (size_t)b * N + (n < N ? n : N - 1);
     }
 
+    // A projection whose first RING weight loads are on their way: acc^T[c][n] over the codes in `tileq`; every slot of the
+    // ring is refilled as soon as its MFMAs are issued.
+    auto ring_project = [&](const __amdgpu_buffer_rsrc_t rs, int32x4_t (&acc)[NTT][TPH], int ln) {
+#pragma unroll
+        for (int j = 0; j < TPH; ++j)
+#pragma unroll
+            for (int nt = 0; nt < NTT; ++nt) acc[nt][j] = (int32x4_t){0, 0, 0, 0};
+        constexpr int RD = RING ? RING : 1;
+        const int8_t* xrow = tileq + (tbase + (ln & 15)) * F::TILE_RS + 16 * (ln >> 4);
+        constexpr int AHEAD = ROWMAJ ? 4 : 0;  // operands on their way through LDS
+        int32x4_t op[AHEAD + 1];
+        auto operand = [&](int f) {
+            if constexpr (ROWMAJ) op[f % (AHEAD + 1)] = exchange_rows(wring[f % RD], imgh, lane);
+            else op[0] = wring[f % RD];
+        };
+#pragma unroll
+        for (int f = 0; f < AHEAD; ++f) operand(f);
+        constexpr int KG = ROWMAJ ? 2 : 1;  // (the two halves of a 128-byte line of a row one after the other)
+#pragma unroll
+        for (int ks = 0; ks < KC; ks += KG) {
+            int32x4_t hbk[NTT][KG];
+#pragma unroll
+            for (int nt = 0; nt < NTT; ++nt)
+#pragma unroll
+                for (int k = 0; k < KG; ++k) hbk[nt][k] = *reinterpret_cast<const int32x4_t*>(xrow + 16 * nt * F::TILE_RS + 64 * (ks + k));
+#pragma unroll
+            for (int jk = 0; jk < TPH * KG; ++jk) {
+                const int j = jk / KG, k = jk % KG, f = ks * TPH + jk, g = f + AHEAD;
+                if (g < NF) operand(g);
+#pragma unroll
+                for (int nt = 0; nt < NTT; ++nt) acc[nt][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(op[f % (AHEAD + 1)], hbk[nt][k], acc[nt][j], 0, 0, 0);
+                // the slot is free again: the load RING places ahead takes it
+                if (ROWMAJ && f == 0) {
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u)
+                        if (u + RING < NF) wring[u % RD] = ring_load(rs, u + RING);
+                }
+                if (g + RING < NF) wring[g % RD] = ring_load(rs, g + RING);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+
     // ================= to_q for this head: Qf^T[c][n]
     int32x4_t hb[NTT][NG == 1 && RING == 0 ? KC : 1];
     if constexpr (NG == 1 && RING == 0) {
@@ -406,46 +479,23 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
 #pragma unroll
                 for (int nt = 0; nt < NTT; ++nt)
                     pacc[nt][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wreg[j][ks], hb[nt][ks], pacc[nt][j], 0, 0, 0);
-    } else if constexpr (NG == 1 && RING > 0) {
-#pragma unroll
-        for (int j = 0; j < TPH; ++j)
-#pragma unroll
-            for (int nt = 0; nt < NTT; ++nt) pacc[nt][j] = (int32x4_t){0, 0, 0, 0};
-#pragma unroll
-        for (int ks = 0; ks < KC; ++ks) {
-            int32x4_t hbk[NTT];
-#pragma unroll
-            for (int nt = 0; nt < NTT; ++nt)
-                hbk[nt] = *reinterpret_cast<const int32x4_t*>(tileq + (tbase + 16 * nt + r16) * F::TILE_RS + 64 * ks + 16 * q);
-#pragma unroll
-            for (int j = 0; j < TPH; ++j) {
-                const int f = ks * TPH + j;
-                const int32x4_t wa = wring[f % RING];
-#pragma unroll
-                for (int nt = 0; nt < NTT; ++nt) pacc[nt][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa, hbk[nt], pacc[nt][j], 0, 0, 0);
-                // the slot is free again: the load RING places ahead takes it
-                if (f + RING < NF) wring[f % RING] = load_w(rs_wq, (f + RING) % TPH, wstep * ((f + RING) / TPH));
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
     } else if constexpr (NG == 1) {
-#pragma unroll
-        for (int j = 0; j < TPH; ++j) {
-#pragma unroll
-            for (int nt = 0; nt < NTT; ++nt) pacc[nt][j] = (int32x4_t){0, 0, 0, 0};
-#pragma unroll
-            for (int ks = 0; ks < KC; ++ks) {
-                const int32x4_t wa = load_w(rs_wq, j, wstep * ks);
-#pragma unroll
-                for (int nt = 0; nt < NTT; ++nt) pacc[nt][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa, hb[nt][ks], pacc[nt][j], 0, 0, 0);
-            }
-        }
+        ring_project(rs_wq, pacc, lane);
     } else {
         // Head-group variant: the wavefronts split the workgroup's to_q by weight tile group (js) and K range (kp),
         // each for the workgroup's 16 tokens; every wavefront leaves its int32 partial sums in a slot of its own
         // in LDS, and then adds up the KP partial sums of its own head: integer adds, exact in any order.
         const int wv = tid >> 6, js = wv & 1, kp = wv >> 1;
         if (sub < SUB) load_protected();  // needed only after the second barrier: they travel during the MFMAs
+        if constexpr (ROWMAJ) {  // row-major weights: the lanes are exchanged through a KiB of LDS (as under ROWMAJ above), the
+                             // place of this wavefront's last partial sum: 26.5 -> 21.1 us at 512 tokens, d = 160
+                             // (with the same in the to_out kernel; operand-ordered weights: 19.5)
+            unsigned char* slot = reinterpret_cast<unsigned char*>(qacc) + (kp * TW + js * TJ + TJ - 1) * 1024;
+#pragma unroll
+            for (int jj = 0; jj < TJ; ++jj)
+#pragma unroll
+                for (int kk = 0; kk < KW; ++kk) wpre[jj][kk] = exchange_rows(wpre[jj][kk], slot, lane);
+        }
         int32x4_t hb2[KW];
 #pragma unroll
         for (int kk = 0; kk < KW; ++kk)
@@ -544,7 +594,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     __builtin_amdgcn_s_waitcnt(0x0F70);
     if constexpr (RING > 0 && NTT == 1) {  // ... or its first RING loads
 #pragma unroll
-        for (int f = 0; f < RING; ++f) wring[f] = load_w(rs_wo, f % TPH, wstep * (f / TPH));
+        for (int f = 0; f < RING; ++f) wring[f] = ring_load(rs_wo, f);
     }
 
     // ================= scores: x[t][n] = (K~ Q~^T)[t][n] * s_K[t]   (times sQ * sigma * log2 e later)
@@ -671,9 +721,8 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
 
     // ================= softmax over the text tokens; Eq. (3); weights of O^T = V~^T A^^T
     float kq[NTT];   // code = rint(E * kq): pmax / Z per image token (row-range grid: pmax / largest unprotected E)
-    float kqp[NTT];  // protected columns: weight = E * kqp = pmax * A
     float lz[NTT];   // log2 Z (log2 grid only)
-    float rz[NTT], fz[NTT];  // row-range grid only: Z / range and range / Z, which move between the two units
+    float fz[NTT];   // row-range grid only: range / Z
     float mxs[NTT];  // row maximum of the raw scores
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) {
@@ -755,13 +804,14 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             }
         }
     }
+    const float vpre = nfp > 0 ? reinterpret_cast<const float*>(imgh + dm.I.vpre)[0] : 0.f;
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) {
         const float Z = quad_allsum(Zs[nt]);
-        kqp[nt] = quant_mult(dm.pmax, Z);  // pmax / Z, as the stage path forms it: the same codes from either
-        kq[nt] = kqp[nt];
+        const float kqp = quant_mult(dm.pmax, Z);  // pmax / Z, as the stage path forms it: the same codes from either
+        float f = kqp * vpre;                      // protected columns: weight = E * kqp = pmax * A
+        kq[nt] = kqp;
         lz[nt] = LOGP ? __builtin_amdgcn_logf(Z) : 0.f;  // log2 Z >= 0: the largest term of Z is 1
-        rz[nt] = 1.f;
         fz[nt] = 1.f;
         if constexpr (ROWMAX) {
             // codes = rint(pmax * E / range), A^ = code * (range / Z) / pmax. Unprotected columns that together weigh
@@ -769,16 +819,11 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             const float eu = quad_allmax(eus[nt]);
             if (eu > Z * 9.094947e-13f) {
                 kq[nt] = quant_mult(dm.pmax, eu);
-                rz[nt] = quant_mult(Z, eu);
+                f = kqp * (vpre * quant_mult(Z, eu));
                 fz[nt] = quant_mult(eu, Z);
             }
         }
-    }
-    if (nfp > 0) {
-        const float vpre = reinterpret_cast<const float*>(imgh + dm.I.vpre)[0];
-#pragma unroll
-        for (int nt = 0; nt < NTT; ++nt) {
-            const float f = kqp[nt] * (ROWMAX ? vpre * rz[nt] : vpre);
+        if (nfp > 0) {
 #pragma unroll
             for (int k = 0; k < TPS; ++k)
 #pragma unroll
@@ -894,6 +939,10 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         }
     }
 
+    // DENSE has no register to spare across the attention: addresses are formed again instead of kept (four registers
+    // spilled otherwise, and their reloads wait for the weights on their way: 19.0 us at 16384 tokens, 18.3 without)
+    const int lane2 = DENSE ? opaque(lane) : lane;
+    if constexpr (DENSE) set_wrow(lane2);
     if (F::PREFETCH_W) {  // to_out's weight slice travels while A^ V~ is quantized (two barriers away from its use)
 #pragma unroll
         for (int j = 0; j < TPH; ++j)
@@ -902,7 +951,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     }
     if constexpr (RING > 0 && NTT == 2) {  // two token tiles per wavefront: the attention needs the registers; the first
 #pragma unroll                         // RING loads of to_out travel while A^ V~ is quantized
-        for (int f = 0; f < RING; ++f) wring[f] = load_w(rs_wo, f % TPH, wstep * (f / TPH));
+        for (int f = 0; f < RING; ++f) wring[f] = ring_load(rs_wo, f);
     }
     // ================= per-token int8 codes of O over all heads
     // O = oacc * of, of = 2^-kexp / pmax (times range / Z on the row-range grid). Where nobody needs O itself (no tap, no
@@ -938,23 +987,24 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     }
     if constexpr (NG > 1) return;  // the per-token quantization of A^ V~ and to_out are separate kernels
     __syncthreads();  // every wavefront is past its reads of the hidden codes
+    const int r2 = lane2 & 15, q2 = lane2 >> 4;
     float so[NTT];
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) {
         float oamax = 0.f;
 #pragma unroll
-        for (int w = 0; w < NH; ++w) oamax = fmaxf(oamax, __uint_as_float(omax[(tbase + 16 * nt + r16) * NH + w]));
+        for (int w = 0; w < NH; ++w) oamax = fmaxf(oamax, __uint_as_float(omax[(tbase + 16 * nt + r2) * NH + w]));
         const bool ozero = oamax == 0.f;
         so[nt] = ozero ? 1.f : oamax / 127.f;
         const float osafe = ozero ? 1.f : oamax;
         const float cq = quant_mult(127.f, osafe);
 #pragma unroll
         for (int jt = 0; jt < TPH; ++jt)
-            if (16 * jt + 4 * q < D) {
+            if (16 * jt + 4 * q2 < D) {
                 const unsigned pk = KEEP_O ? quant4_i8(oacc[nt][jt][0], oacc[nt][jt][1], oacc[nt][jt][2], oacc[nt][jt][3], cq, osafe)
                                            : quant4_i8_scaled(oacc[nt][jt][0], oacc[nt][jt][1], oacc[nt][jt][2], oacc[nt][jt][3], of[nt], cq, osafe);
-                const int c = h * D + 16 * jt + 4 * q;
-                *reinterpret_cast<unsigned*>(tileq + (tbase + 16 * nt + r16) * F::TILE_RS + c) = pk;
+                const int c = h * D + 16 * jt + 4 * q2;
+                *reinterpret_cast<unsigned*>(tileq + (tbase + 16 * nt + r2) * F::TILE_RS + c) = pk;
                 if (TAPS && dm.dbg.o_code && nvalid[nt]) *reinterpret_cast<unsigned*>(dm.dbg.o_code + tok[nt] * C + c) = pk;
             }
         if (TAPS && dm.dbg.s_o && nvalid[nt] && q == 0 && h == 0) dm.dbg.s_o[tok[nt]] = so[nt];
@@ -963,26 +1013,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
 
     // ================= to_out: Y^T[c][n] for this head's D output channels
     if constexpr (RING > 0) {
-#pragma unroll
-        for (int j = 0; j < TPH; ++j)
-#pragma unroll
-            for (int nt = 0; nt < NTT; ++nt) pacc[nt][j] = (int32x4_t){0, 0, 0, 0};
-#pragma unroll
-        for (int ks = 0; ks < KC; ++ks) {
-            int32x4_t hbk[NTT];
-#pragma unroll
-            for (int nt = 0; nt < NTT; ++nt)
-                hbk[nt] = *reinterpret_cast<const int32x4_t*>(tileq + (tbase + 16 * nt + r16) * F::TILE_RS + 64 * ks + 16 * q);
-#pragma unroll
-            for (int j = 0; j < TPH; ++j) {
-                const int f = ks * TPH + j;
-                const int32x4_t wa = wring[f % RING];
-#pragma unroll
-                for (int nt = 0; nt < NTT; ++nt) pacc[nt][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa, hbk[nt], pacc[nt][j], 0, 0, 0);
-                if (f + RING < NF) wring[f % RING] = load_w(rs_wo, (f + RING) % TPH, wstep * ((f + RING) / TPH));
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
+        ring_project(rs_wo, pacc, lane2);
     } else {
 #pragma unroll
         for (int nt = 0; nt < NTT; ++nt)
@@ -995,7 +1026,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             for (int nt = 0; nt < NTT; ++nt) pacc[nt][j] = (int32x4_t){0, 0, 0, 0};
 #pragma unroll
             for (int ks = 0; ks < KC; ++ks) {
-                const int32x4_t wa = F::PREFETCH_W ? wreg[j][ks] : load_w(rs_wo, j, wstep * ks);
+                const int32x4_t wa = wreg[j][ks];
 #pragma unroll
                 for (int nt = 0; nt < NTT; ++nt) pacc[nt][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa, hb[nt][ks], pacc[nt][j], 0, 0, 0);
             }
@@ -1003,7 +1034,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     }
 #pragma unroll
     for (int j = 0; j < TPH; ++j) {
-        const int cl = 16 * j + 4 * q;
+        const int cl = 16 * j + 4 * q2;
         if (cl < D) {
             const int c = h * D + cl;
             const float4 w4 = *reinterpret_cast<const float4*>(swo + c);
@@ -1014,9 +1045,10 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
                 const float y1 = (float)pacc[nt][j][1] * (so[nt] * w4.y) + b4.y;
                 const float y2 = (float)pacc[nt][j][2] * (so[nt] * w4.z) + b4.z;
                 const float y3 = (float)pacc[nt][j][3] * (so[nt] * w4.w) + b4.w;
-                if (nvalid[nt]) {
+                const int n = n0 + tbase + 16 * nt + r2;
+                if (n < N) {
                     const half4_t y = {(_Float16)y0, (_Float16)y1, (_Float16)y2, (_Float16)y3};
-                    *reinterpret_cast<half4_t*>(rq.out + tok[nt] * C + c) = y;
+                    *reinterpret_cast<half4_t*>(rq.out + ((size_t)b * N + n) * C + c) = y;
                 }
             }
         }
@@ -1036,38 +1068,50 @@ static inline int device_cu_count() {
     return n;
 }
 
-template <int D, int NH, int NTT, int NG, int PG, int TOK, int NT16 = 0, bool DENSE = false>
-static hipError_t launch_fused_grid(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& tab, const FusedDims& dm, hipStream_t st) {
-    if constexpr (NT16 == 0) {  // 65 to 80 text tokens: the instantiation without run-time guards around the score tiles
-        const bool taps = dm.dbg.h_code || dm.dbg.s_h || dm.dbg.q_code || dm.dbg.s_Q || dm.dbg.O || dm.dbg.o_code || dm.dbg.s_o || dm.dbg.p_code;
-        if (dm.nt16 == 5 && !taps) return launch_fused_grid<D, NH, NTT, NG, PG, TOK, 5>(tab, dm, st);
-    }
-    using F = FusedCfg<D, NH, NTT, NG, TOK, DENSE>;
+template <int D, int NH, int NTT, int NG, int PG, int TOK, int NT16, bool DENSE, bool ROWMAJ>
+static hipError_t launch_fused_one(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& tab, const FusedDims& dm, size_t bytes, hipStream_t st) {
     static std::atomic<unsigned long long> lds_set{0};
-    const size_t bytes = NG == 1 ? dm.I.bytes + TOK * F::TILE_RS + 3 * F::C * 4 + TOK * 4 + TOK * NH * 4  // = fused_lds_bytes
-                                 : (size_t)NH * dm.I.head_bytes + TOK * F::TILE_RS + NH * D * 4 + TOK * 4 +
-                                       (F::NT / 128) * NH * F::TPH * 1024;  // = mid_lds_bytes
-    if (bytes > 160 * 1024 || dm.I.head_bytes > (size_t)F::IMGC * 1024) return hipErrorInvalidValue;
-    if constexpr (!DENSE && NT16 == 5 && D == 40 && NH == 8 && NTT == 2 && NG == 1) {
-        // More token tiles than compute units and a working set of at most half a compute unit's LDS: the instantiation
-        // of which two workgroups share a compute unit (one is in its arithmetic while the other waits for memory).
-        if ((dm.N + TOK - 1) / TOK * dm.R * dm.B > device_cu_count() && bytes <= 80 * 1024)
-            return launch_fused_grid<D, NH, NTT, NG, PG, TOK, NT16, true>(tab, dm, st);
-    }
-    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&fused_block_kernel<D, NH, NTT, NG, PG, TOK, NT16, DENSE>), 160 * 1024, lds_set);
+    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&fused_block_kernel<D, NH, NTT, NG, PG, TOK, NT16, DENSE, ROWMAJ>), 160 * 1024, lds_set);
     if (e != hipSuccess) return e;
     const int tiles = (dm.N + TOK - 1) / TOK;
     if (tiles > 65535 || dm.R > 65535 || (NG > 1 && dm.R != 1)) return hipErrorInvalidValue;
     const dim3 grid = NG > 1 ? dim3(dm.B, tiles, NG) : dim3(dm.B, dm.R, tiles);
-    hipLaunchKernelGGL((fused_block_kernel<D, NH, NTT, NG, PG, TOK, NT16, DENSE>), grid, dim3(F::NT), bytes, st, tab, dm);
+    hipLaunchKernelGGL((fused_block_kernel<D, NH, NTT, NG, PG, TOK, NT16, DENSE, ROWMAJ>), grid, dim3(FusedCfg<D, NH, NTT, NG, TOK, DENSE>::NT), bytes, st, tab, dm);
     return hipGetLastError();
+}
+
+template <int D, int NH, int NTT, int NG, int PG, int TOK, int NT16>
+static hipError_t launch_fused_grid(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& tab, const FusedDims& dm, hipStream_t st) {
+    using F = FusedCfg<D, NH, NTT, NG, TOK>;
+    const size_t bytes = NG == 1 ? dm.I.bytes + TOK * F::TILE_RS + 3 * F::C * 4 + TOK * 4 + TOK * NH * 4  // = fused_lds_bytes
+                                 : (size_t)NH * dm.I.head_bytes + TOK * F::TILE_RS + NH * D * 4 + TOK * 4 +
+                                       (F::NT / 128) * NH * F::TPH * 1024;  // = mid_lds_bytes
+    if (bytes > 160 * 1024 || dm.I.head_bytes > (size_t)F::IMGC * 1024) return hipErrorInvalidValue;
+    if constexpr (NT16 == 5 && D == 40 && NH == 8 && NTT == 2 && NG == 1) {
+        // More token tiles than compute units and a working set of at most half a compute unit's LDS: the instantiation
+        // of which two workgroups share a compute unit (one is in its arithmetic while the other waits for memory).
+        if ((dm.N + TOK - 1) / TOK * dm.R * dm.B > device_cu_count() && bytes <= 80 * 1024)
+            return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, true, false>(tab, dm, bytes, st);
+    }
+    if constexpr ((F::RING > 0 || NG > 1) && D % 16 == 0) {
+        if (!dm.w_layout) return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, false, true>(tab, dm, bytes, st);
+    }
+    return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, false, false>(tab, dm, bytes, st);
+}
+
+template <int D, int NH, int NTT, int NG, int PG, int TOK>
+static hipError_t launch_fused_tiles(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& tab, const FusedDims& dm, hipStream_t st) {
+    // 65 to 80 text tokens: the instantiation without run-time guards around the score tiles
+    const bool taps = dm.dbg.h_code || dm.dbg.s_h || dm.dbg.q_code || dm.dbg.s_Q || dm.dbg.O || dm.dbg.o_code || dm.dbg.s_o || dm.dbg.p_code;
+    if (dm.nt16 == 5 && !taps) return launch_fused_grid<D, NH, NTT, NG, PG, TOK, 5>(tab, dm, st);
+    return launch_fused_grid<D, NH, NTT, NG, PG, TOK, 0>(tab, dm, st);
 }
 
 template <int D, int NH, int NTT, int NG, int TOK>
 static hipError_t launch_fused_cfg(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& tab, const FusedDims& dm, int grid, hipStream_t st) {
-    if (grid == TAQ_PROB_LOG2) return launch_fused_grid<D, NH, NTT, NG, TAQ_PROB_LOG2, TOK>(tab, dm, st);
-    if (grid == TAQ_PROB_ROWMAX) return launch_fused_grid<D, NH, NTT, NG, TAQ_PROB_ROWMAX, TOK>(tab, dm, st);
-    return launch_fused_grid<D, NH, NTT, NG, TAQ_PROB_LINEAR, TOK>(tab, dm, st);
+    if (grid == TAQ_PROB_LOG2) return launch_fused_tiles<D, NH, NTT, NG, TAQ_PROB_LOG2, TOK>(tab, dm, st);
+    if (grid == TAQ_PROB_ROWMAX) return launch_fused_tiles<D, NH, NTT, NG, TAQ_PROB_ROWMAX, TOK>(tab, dm, st);
+    return launch_fused_tiles<D, NH, NTT, NG, TAQ_PROB_LINEAR, TOK>(tab, dm, st);
 }
 
 // Family launchers, one translation unit each. tok = 32 or 16 image tokens per workgroup (head groups: 16).

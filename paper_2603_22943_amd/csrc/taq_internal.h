@@ -148,13 +148,13 @@ static inline bool mid_supported(const taq_shape& s) {
 }
 // Whether the head-group path takes such a layer, or the kernel-per-stage path. Head groups save three launches and every
 // pass over the workspace but one, but each workgroup reads its share of Wq for 16 tokens only and fills a compute unit, so
-// the time goes with the rounds of 256 workgroups: 14 us + 12 us per further round at d = 160, 13 + 8 us at d = 64, half as
-// much again with row-major weights, against 33 to 38 us for the five stage kernels at these sizes (2048 tokens, d = 160:
-// 56.6 and 40.9 us; 8192: 159 and 87 us). shape.tok_tile = 16 or 32 forces head groups or stages (tests and tuning).
+// the time goes with the rounds of 256 workgroups: 16 us + 12 us per further round at d = 160, 14 + 8 us at d = 64 (2 to 5 us
+// more with row-major weights), against 33 to 38 us for the five stage kernels at these sizes (2048 tokens, d = 160: 56.6 and
+// 40.9 us; 8192: 159 and 87 us). shape.tok_tile = 16 or 32 forces head groups or stages (tests and tuning).
 static inline bool mid_preferred(const taq_shape& s) {
     if (s.tok_tile) return s.tok_tile == 16;
     const long rounds = ((long)s.B * ((s.N + 15) / 16) * mid_groups(s) + 255) / 256;
-    return rounds <= (s.C / s.H == 160 ? 2 : 3) - (s.w_layout ? 0 : 1);
+    return rounds <= (s.C / s.H == 160 ? 2 : 3);
 }
 
 static inline KvLayout kv_layout(const taq_shape& s) {
