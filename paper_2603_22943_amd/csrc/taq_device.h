@@ -8,6 +8,7 @@ namespace taq {
 typedef int int32x4_t __attribute__((ext_vector_type(4)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 
 #define TAQ_NEG_INF (-__builtin_inff())
@@ -24,37 +25,24 @@ __device__ __forceinline__ unsigned pack4(int a, int b, int c, int d) {
     return (unsigned)(a & 0xFF) | ((unsigned)(b & 0xFF) << 8) | ((unsigned)(c & 0xFF) << 16) | ((unsigned)(d & 0xFF) << 24);
 }
 
-// Symmetric 8-bit codes of four values of one row, packed into a dword (low byte first).
-//   exact definition: code = rint((x * qmax) / amax) with IEEE float32 multiply and divide (qmax = 127, or 7 for
-//   4-bit Q~; the bounds below are stated for 127 and only shrink for 7).
-//   fast path: with c = quant_mult(qmax, amax) (within 0.5 ulp and a little of qmax / amax: 6.1e-8, relatively),
-//   m = fma(x, c, 1.5 * 2^23) is the EXACT product x * c rounded half-to-even to an integer (plus the magic constant,
-//   whose low mantissa byte is then the code's byte), and e = fma(x, c, -(m - magic)) is the distance of that exact
-//   product from the integer. x * c lies within 7.7e-6 of the exact ratio (|ratio| <= 127), the defined quotient within
-//   7.6e-6 (its product, rounded once; exact where x is fp16 and qmax 127) + 3.8e-6 (half a last place below 128), so
-//   both round to the same integer unless x * c is within 1.9e-5 (fp16 rows: 1.15e-5) of a half-integer; values beyond
-//   TAQ_TIE (TAQ_TIE_F16) are settled by quant4_ties.
-#define TAQ_TIE 0.49997f
-#define TAQ_TIE_F16 0.49998f
-
-__device__ __forceinline__ float quant_mult(float qmaxf, float amax) {  // qmax / amax, refined once
+// qmax / amax, refined once: within 0.5 ulp and a little (6.1e-8, relatively).
+__device__ __forceinline__ float quant_mult(float qmaxf, float amax) {
     const float r = __builtin_amdgcn_rcpf(amax), c = qmaxf * r;
     return __builtin_fmaf(__builtin_fmaf(-c, amax, qmaxf), r, c);
 }
 
-// Settles the flagged values of four by the definition code = rint(fl(t / amax)), t = fl(y * qmax), without the division:
-// such a quotient lies beside H = n + copysign(0.5, e) (n: the fast path's integer), so only its side of H matters, or
-// whether it rounds to H itself, in which case the even neighbour is taken. s = fma(-H, amax, t) has the exact sign of
+// Settles the values of four whose bytes are flagged by the definition code = rint(fl(t / amax)), t = fl(y * qmax), without the
+// division: such a quotient lies beside H = n + copysign(0.5, e) (n: the inner candidate, in pk), so only its side of H matters,
+// or whether it rounds to H itself, in which case the even neighbour is taken. s = fma(-H, amax, t) has the exact sign of
 // t / amax - H, and the quotient rounds to H while |s| <= amax * (half a unit in the last place of H; half of that on
 // the inner side of a power of two, here only 0.5; the end points round to H too, whose last bit is 0).
-// A value in 2 * 10^4 gets here, but then its whole wavefront waits. One value after the other, in a loop (a lane rarely has
+// A value in 10^5 gets here, but then its whole wavefront waits. One value after the other, in a loop (a lane rarely has
 // two at once), keeps the code small.
-__device__ __forceinline__ unsigned quant4_ties(unsigned pk, bool f0, bool f1, bool f2, bool f3, float x0, float x1, float x2, float x3,
-                                                float f, float fc, float amax, float qmaxf) {
-    unsigned flags = (f0 ? 1u : 0u) | (f1 ? 2u : 0u) | (f2 ? 4u : 0u) | (f3 ? 8u : 0u);
+__device__ __forceinline__ unsigned quant4_ties(unsigned pk, unsigned flags, float x0, float x1, float x2, float x3, float f, float fc, float amax,
+                                                float qmaxf) {
 #pragma unroll 1
     do {
-        const int i = __builtin_ctz(flags);
+        const int i = __builtin_ctz(flags) >> 3;
         const float x = i & 2 ? (i & 1 ? x3 : x2) : (i & 1 ? x1 : x0);
         const float n = (float)((int)(pk << (24 - 8 * i)) >> 24);
         const float e = __builtin_fmaf(x, fc, -n);
@@ -71,43 +59,34 @@ __device__ __forceinline__ unsigned quant4_ties(unsigned pk, bool f0, bool f1, b
         code = h < 0.f ? -code : code;
         const unsigned m = 0xFFu << (8 * i);
         pk = (pk & ~m) | (((unsigned)code << (8 * i)) & m);
-        flags &= flags - 1;
+        flags &= ~m;
     } while (flags);
     return pk;
 }
 
-__device__ __forceinline__ unsigned quant4_i8(float x0, float x1, float x2, float x3, float c, float amax,
-                                              float qmaxf = 127.f, float tie = TAQ_TIE) {
+// Symmetric 8-bit codes of four values y = x * f of one row, packed into a dword (low byte first).
+//   exact definition: code = rint((y * qmax) / amax) with IEEE float32 operations (qmax = 127, or 7 for 4-bit Q~).
+//   fast path: the defined quotient is within 3 * 2^-24 of y * qmax / amax, relatively (y, where f is not 1, its product and
+//   the division, rounded once each), x times fc = f * quant_mult(qmax, amax) within 2^-23 and a little: together less than
+//   3.1e-7. The FMAs fma(x, fc (1 -+ 2^-21), 1.5 * 2^23) round two exact products, 4.1e-7 and more to either side, half-to-even
+//   to integers (the constant's low mantissa bytes); rounding is monotone, so where they agree the quotient rounds to the same.
+//   Where they differ, quant4_ties decides. (Both products cost two instructions per four values less than one product and its
+//   distance from the integer, and the doubtful zone narrows with the magnitude: a fourth of the visits there.)
+__device__ __forceinline__ unsigned quant4_i8_scaled(float x0, float x1, float x2, float x3, float f, float c, float amax, float qmaxf = 127.f) {
     const float magic = 12582912.0f;
-    const float m0 = __builtin_fmaf(x0, c, magic), m1 = __builtin_fmaf(x1, c, magic);
-    const float m2 = __builtin_fmaf(x2, c, magic), m3 = __builtin_fmaf(x3, c, magic);
-    const float e0 = __builtin_fmaf(x0, c, magic - m0), e1 = __builtin_fmaf(x1, c, magic - m1);
-    const float e2 = __builtin_fmaf(x2, c, magic - m2), e3 = __builtin_fmaf(x3, c, magic - m3);
-    const unsigned lo = __builtin_amdgcn_perm(__float_as_uint(m1), __float_as_uint(m0), 0x0c0c0400u);
-    const unsigned hi = __builtin_amdgcn_perm(__float_as_uint(m3), __float_as_uint(m2), 0x0c0c0400u);
-    unsigned pk = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-    if (fmaxf(fmaxf(fabsf(e0), fabsf(e1)), fmaxf(fabsf(e2), fabsf(e3))) > tie)
-        pk = quant4_ties(pk, fabsf(e0) > tie, fabsf(e1) > tie, fabsf(e2) > tie, fabsf(e3) > tie, x0, x1, x2, x3, 1.f, c, amax, qmaxf);
+    const float fc = f * c, in = __builtin_fmaf(fc, -4.76837158203125e-07f, fc), out = __builtin_fmaf(fc, 4.76837158203125e-07f, fc);
+    auto pack = [&](float m) {
+        const unsigned lo = __builtin_amdgcn_perm(__float_as_uint(__builtin_fmaf(x1, m, magic)), __float_as_uint(__builtin_fmaf(x0, m, magic)), 0x0c0c0400u);
+        const unsigned hi = __builtin_amdgcn_perm(__float_as_uint(__builtin_fmaf(x3, m, magic)), __float_as_uint(__builtin_fmaf(x2, m, magic)), 0x0c0c0400u);
+        return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+    };
+    unsigned pk = pack(in);
+    const unsigned other = pack(out);
+    if (pk != other) pk = quant4_ties(pk, pk ^ other, x0, x1, x2, x3, f, fc, amax, qmaxf);
     return pk;
 }
-
-// The same for values x_i * f whose products have not been formed yet (f > 0 common to the four): the fast path rounds
-// the exact product x * (f * c), f * c rounded once, which adds 7.6e-6, as does the rounding in y = fl(x * f): the two
-// agree unless the product is within 3.5e-5 of a half-integer.
-__device__ __forceinline__ unsigned quant4_i8_scaled(float x0, float x1, float x2, float x3, float f, float c, float amax) {
-    constexpr float tie = 0.49996f;
-    const float magic = 12582912.0f;
-    const float fc = f * c;
-    const float m0 = __builtin_fmaf(x0, fc, magic), m1 = __builtin_fmaf(x1, fc, magic);
-    const float m2 = __builtin_fmaf(x2, fc, magic), m3 = __builtin_fmaf(x3, fc, magic);
-    const float e0 = __builtin_fmaf(x0, fc, magic - m0), e1 = __builtin_fmaf(x1, fc, magic - m1);
-    const float e2 = __builtin_fmaf(x2, fc, magic - m2), e3 = __builtin_fmaf(x3, fc, magic - m3);
-    const unsigned lo = __builtin_amdgcn_perm(__float_as_uint(m1), __float_as_uint(m0), 0x0c0c0400u);
-    const unsigned hi = __builtin_amdgcn_perm(__float_as_uint(m3), __float_as_uint(m2), 0x0c0c0400u);
-    unsigned pk = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-    if (fmaxf(fmaxf(fabsf(e0), fabsf(e1)), fmaxf(fabsf(e2), fabsf(e3))) > tie)
-        pk = quant4_ties(pk, fabsf(e0) > tie, fabsf(e1) > tie, fabsf(e2) > tie, fabsf(e3) > tie, x0, x1, x2, x3, f, fc, amax, 127.f);
-    return pk;
+__device__ __forceinline__ unsigned quant4_i8(float x0, float x1, float x2, float x3, float c, float amax, float qmaxf = 127.f) {
+    return quant4_i8_scaled(x0, x1, x2, x3, 1.f, c, amax, qmaxf);
 }
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
@@ -133,6 +112,25 @@ __device__ __forceinline__ float row16_allmax(float x) {
     x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x141, 0xF, 0xF, true)));
     x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x140, 0xF, 0xF, true)));
     return x;
+}
+
+// x, and the compiler does not know it: what is computed from it is computed here and not kept from elsewhere.
+__device__ __forceinline__ int opaque(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// Two values in [0, 1] as fp16 high parts (truncated) and remainders, at i and i + 1 of two operands. (High parts by the conversion
+// intrinsic: the value that enters the MFMA is the one subtracted, whatever the compiler would pick for a plain cast.)
+__device__ __forceinline__ void split_half2(float e0, float e1, half4_t& hi, half4_t& lo, int i) {
+    const auto w = __builtin_amdgcn_cvt_pkrtz(e0, e1);
+    const _Float16 h0 = (_Float16)w[0], h1 = (_Float16)w[1];
+    typedef float float2_t __attribute__((ext_vector_type(2)));
+    const half2_t l = __builtin_convertvector((float2_t){e0 - (float)h0, e1 - (float)h1}, half2_t);
+    hi[i] = h0;
+    hi[i + 1] = h1;
+    lo[i] = l[0];
+    lo[i + 1] = l[1];
 }
 
 // Four biased bytes (code + 128) -> four fp16 codes: 0x6400 | byte is the fp16 number 1152 + code.

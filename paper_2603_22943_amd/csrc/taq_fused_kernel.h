@@ -43,12 +43,6 @@ __device__ __forceinline__ int32x4_t exchange_rows(int32x4_t w, unsigned char* s
     return *reinterpret_cast<const int32x4_t*>(slot + r16 * 64 + ((q ^ ((r16 >> 1 ^ r16 >> 2) & 3)) << 4));
 }
 
-// x, and the compiler does not know it: what is computed from it is computed here and not kept from elsewhere.
-__device__ __forceinline__ int opaque(int x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
-
 // ------------------------------------------------------------------------------------------
 // Fused block kernel
 // ------------------------------------------------------------------------------------------
@@ -313,7 +307,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             }
             if (HOLDS) {
                 const half2_t x01 = *reinterpret_cast<const half2_t*>(&xin[it].x), x23 = *reinterpret_cast<const half2_t*>(&xin[it].y);
-                const unsigned pk = quant4_i8((float)x01[0], (float)x01[1], (float)x23[0], (float)x23[1], cq0, safe0, 127.f, TAQ_TIE_F16);
+                const unsigned pk = quant4_i8((float)x01[0], (float)x01[1], (float)x23[0], (float)x23[1], cq0, safe0);
                 *reinterpret_cast<unsigned*>(tileq + tok0 * F::TILE_RS + (it * 16 + part0) * 4) = pk;
                 if (TAPS && dm.dbg.h_code && nq0 < N) *reinterpret_cast<unsigned*>(dm.dbg.h_code + row0 * C + (it * 16 + part0) * 4) = pk;
             }
@@ -393,8 +387,8 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             const float2 p0 = __half22float2(hh2[0]), p1 = __half22float2(hh2[1]);
             const float2 p2 = __half22float2(hh2[2]), p3 = __half22float2(hh2[3]);
             uint2 pk;
-            pk.x = quant4_i8(p0.x, p0.y, p1.x, p1.y, cq0, safe0, 127.f, TAQ_TIE_F16);
-            pk.y = quant4_i8(p2.x, p2.y, p3.x, p3.y, cq0, safe0, 127.f, TAQ_TIE_F16);
+            pk.x = quant4_i8(p0.x, p0.y, p1.x, p1.y, cq0, safe0);
+            pk.y = quant4_i8(p2.x, p2.y, p3.x, p3.y, cq0, safe0);
             *reinterpret_cast<uint2*>(tileq + tok0 * F::TILE_RS + (it * TPT + part0) * 8) = pk;
             if (TAPS && tap && dm.dbg.h_code) *reinterpret_cast<uint2*>(dm.dbg.h_code + row0 * C + (it * TPT + part0) * 8) = pk;
             __builtin_amdgcn_sched_barrier(0);
@@ -639,24 +633,11 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             }
         }
     }
-    // protected rows: fp16 K rows (the first 16 from registers, further ones straight from global memory: a handful of
-    // rows). Their scores are formed twice by a run-time loop over tiles of 16 protected tokens, once for the row
-    // maximum and once more for the exponentials, which go straight into the MFMAs against the fp16 V rows: only
-    // one tile of protected scores is ever held in registers.
-    half8_t qh[NTT][FS];  // Q~ codes as fp16: step s covers tiles 2s, 2s+1
-    if (nfp > 0) {
-#pragma unroll
-        for (int nt = 0; nt < NTT; ++nt)
-#pragma unroll
-            for (int s = 0; s < FS; ++s) {
-                half2_t c0 = {(_Float16)0.f, (_Float16)0.f}, c1 = c0, c2 = c0, c3 = c0;
-                biased4_to_half(qpk[nt][2 * s] ^ 0x80808080u, c0, c1);
-                if (2 * s + 1 < TPH) biased4_to_half(qpk[nt][2 * s + 1 < TPH ? 2 * s + 1 : 0] ^ 0x80808080u, c2, c3);
-                qh[nt][s] = (half8_t){c0[0], c0[1], c1[0], c1[1], c2[0], c2[1], c3[0], c3[1]};
-            }
-    }
-    // scores of protected tile ft (tokens of slots 16*ft .. 16*ft+15) for this lane's image tokens; -inf past ntrig
-    auto protected_scores = [&](int ft, floatx4_t (&facc)[NTT]) {
+    // protected rows: fp16 K rows, the first 16 from registers, further ones (rare) straight from global memory. Scores of
+    // protected tile ft (tokens of slots 16*ft .. 16*ft+15) for this lane's image tokens; -inf past ntrig. Only the first
+    // tile's scores are held in registers; those of further ones are formed once for the row maximum and once more for the
+    // exponentials.
+    auto protected_scores = [&](auto first, int ft, const unsigned (&code)[NTT][TPH], floatx4_t (&facc)[NTT]) {
 #pragma unroll
         for (int nt = 0; nt < NTT; ++nt) facc[nt] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
         int slot = 16 * ft + r16;
@@ -669,7 +650,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             for (int jj = 0; jj < 2; ++jj) {
                 const int j = 2 * s + jj;
                 uint2 w = k16r[s][jj];
-                if (ft > 0) w = (j < TPH && 16 * j + 4 * q < D) ? *reinterpret_cast<const uint2*>(kr + 16 * j) : make_uint2(0, 0);
+                if constexpr (!decltype(first)::value) w = (j < TPH && 16 * j + 4 * q < D) ? *reinterpret_cast<const uint2*>(kr + 16 * j) : make_uint2(0, 0);
                 const half4_t hv = *reinterpret_cast<const half4_t*>(&w);
                 ka[4 * jj + 0] = hv[0];
                 ka[4 * jj + 1] = hv[1];
@@ -677,7 +658,13 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
                 ka[4 * jj + 3] = hv[3];
             }
 #pragma unroll
-            for (int nt = 0; nt < NTT; ++nt) facc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka, qh[nt][s], facc[nt], 0, 0, 0);
+            for (int nt = 0; nt < NTT; ++nt) {
+                half2_t c0, c1, c2 = {(_Float16)0.f, (_Float16)0.f}, c3 = c2;  // Q~ codes of tiles 2s and 2s + 1 as fp16
+                biased4_to_half(code[nt][2 * s] ^ 0x80808080u, c0, c1);
+                if (2 * s + 1 < TPH) biased4_to_half(code[nt][2 * s + 1 < TPH ? 2 * s + 1 : 0] ^ 0x80808080u, c2, c3);
+                const half8_t qh = {c0[0], c0[1], c1[0], c1[1], c2[0], c2[1], c3[0], c3[1]};
+                facc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka, qh, facc[nt], 0, 0, 0);
+            }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -685,6 +672,14 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
 #pragma unroll
             for (int nt = 0; nt < NTT; ++nt) facc[nt][i] = live ? facc[nt][i] : TAQ_NEG_INF;
         }
+    };
+    auto further_scores = [&](int ft, floatx4_t (&facc)[NTT]) {  // (codes as fp16 are not kept for them)
+        unsigned code[NTT][TPH];
+#pragma unroll
+        for (int nt = 0; nt < NTT; ++nt)
+#pragma unroll
+            for (int j = 0; j < TPH; ++j) code[nt][j] = (unsigned)opaque((int)qpk[nt][j]);
+        protected_scores(std::false_type{}, ft, code, facc);
     };
 
     // The LDS operands of O^T = V~^T A^^T (this wavefront's V~ codes and the split V scales) are read now, into
@@ -732,12 +727,18 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             if (tt < nt16) mx = fmaxf(mx, fmaxf(fmaxf(S[nt][tt][0], S[nt][tt][1]), fmaxf(S[nt][tt][2], S[nt][tt][3])));
         mxs[nt] = mx;
     }
-    for (int ft = 0; ft < nfp; ++ft) {  // first pass over the protected tiles: their share of the row maximum
-        floatx4_t facc[NTT];
-        protected_scores(ft, facc);
+    floatx4_t fsc[NTT];  // scores of the first protected tile
+    if (nfp > 0) {
+        protected_scores(std::true_type{}, 0, qpk, fsc);
 #pragma unroll
-        for (int nt = 0; nt < NTT; ++nt)
-            mxs[nt] = fmaxf(mxs[nt], fmaxf(fmaxf(facc[nt][0], facc[nt][1]), fmaxf(facc[nt][2], facc[nt][3])));
+        for (int nt = 0; nt < NTT; ++nt) mxs[nt] = fmaxf(mxs[nt], fmaxf(fmaxf(fsc[nt][0], fsc[nt][1]), fmaxf(fsc[nt][2], fsc[nt][3])));
+        for (int ft = 1; ft < nfp; ++ft) {
+            floatx4_t facc[NTT];
+            further_scores(ft, facc);
+#pragma unroll
+            for (int nt = 0; nt < NTT; ++nt)
+                mxs[nt] = fmaxf(mxs[nt], fmaxf(fmaxf(facc[nt][0], facc[nt][1]), fmaxf(facc[nt][2], facc[nt][3])));
+        }
     }
     float Zs[NTT], eus[NTT], offs[NTT];
 #pragma unroll
@@ -769,24 +770,20 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     for (int nt = 0; nt < NTT; ++nt)
 #pragma unroll
         for (int k = 0; k < TPS; ++k) oacc[nt][k] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
-    // protected columns keep A (Eq. 3). Second pass over the protected tiles: E = exp2(score - max), not yet divided
-    // by Z, as fp16 high + low parts against the fp16 V rows; the accumulators are brought to the unit of the
-    // unprotected columns' weights (pmax * A * 2^kexp) once Z is known.
-    for (int ft = 0; ft < nfp; ++ft) {
-        floatx4_t facc[NTT];
-        protected_scores(ft, facc);
+    // protected columns keep A (Eq. 3): E = exp2(score - max), not yet divided by Z, as fp16 high + low parts against the
+    // fp16 V rows; the accumulators are brought to the unit of the unprotected columns' weights (pmax * A * 2^kexp) once Z
+    // is known.
+    auto protected_values = [&](auto first, int ft, const floatx4_t (&facc)[NTT]) {
         half4_t phi[NTT], plo[NTT];
 #pragma unroll
         for (int nt = 0; nt < NTT; ++nt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float ex = __builtin_amdgcn_exp2f(__builtin_fmaf(facc[nt][i], sq2[nt], offs[nt]));
-                Zs[nt] += ex;
-                // (high part by the conversion intrinsic: the value that enters the MFMA is the one subtracted, whatever
-                // instruction the compiler would pick for a plain cast in either place)
-                const _Float16 xh = (_Float16)__builtin_amdgcn_cvt_pkrtz(ex, 0.f)[0];
-                phi[nt][i] = xh;
-                plo[nt][i] = (_Float16)(ex - (float)xh);
+            for (int i = 0; i < 4; i += 2) {
+                const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(facc[nt][i], sq2[nt], offs[nt]));
+                const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(facc[nt][i + 1], sq2[nt], offs[nt]));
+                Zs[nt] += e0;
+                Zs[nt] += e1;
+                split_half2(e0, e1, phi[nt], plo[nt], i);
             }
 #pragma unroll
         for (int k = 0; k < TPS; ++k) {
@@ -795,13 +792,21 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             int c = h * D + 16 * jt + r16;
             c = c < C ? c : C - 1;
             uint2 w = v16r[k];
-            if (ft > 0) w = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 16 * ft + 4 * q);
+            if constexpr (!decltype(first)::value) w = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 16 * ft + 4 * q);
             const half4_t va = *reinterpret_cast<const half4_t*>(&w);  // slots past ntrig hold zeros
 #pragma unroll
             for (int nt = 0; nt < NTT; ++nt) {
                 oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, phi[nt], oacc[nt][k], 0, 0, 0);
                 oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, plo[nt], oacc[nt][k], 0, 0, 0);
             }
+        }
+    };
+    if (nfp > 0) {
+        protected_values(std::true_type{}, 0, fsc);
+        for (int ft = 1; ft < nfp; ++ft) {
+            floatx4_t facc[NTT];
+            further_scores(ft, facc);
+            protected_values(std::false_type{}, ft, facc);
         }
     }
     const float vpre = nfp > 0 ? reinterpret_cast<const float*>(imgh + dm.I.vpre)[0] : 0.f;
@@ -1032,25 +1037,25 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             }
         }
     }
+    // Stores through a buffer descriptor of this batch element's rows of `out`: one 32-bit offset per token instead of a 64-bit
+    // address per store, and rows past the last (and channels past the head, whose offset is set past the end) are dropped by
+    // the bounds check.
+    const __amdgpu_buffer_rsrc_t rs_out = __builtin_amdgcn_make_buffer_rsrc(rq.out + (size_t)b * N * C, 0, N * C * 2, 0x00020000);
 #pragma unroll
     for (int j = 0; j < TPH; ++j) {
-        const int cl = 16 * j + 4 * q2;
-        if (cl < D) {
-            const int c = h * D + cl;
-            const float4 w4 = *reinterpret_cast<const float4*>(swo + c);
-            const float4 b4 = *reinterpret_cast<const float4*>(bo + c);
+        const int cl = 16 * j + 4 * q2, c = h * D + cl;
+        const float4 w4 = *reinterpret_cast<const float4*>(swo + c);
+        const float4 b4 = *reinterpret_cast<const float4*>(bo + c);
 #pragma unroll
-            for (int nt = 0; nt < NTT; ++nt) {
-                const float y0 = (float)pacc[nt][j][0] * (so[nt] * w4.x) + b4.x;
-                const float y1 = (float)pacc[nt][j][1] * (so[nt] * w4.y) + b4.y;
-                const float y2 = (float)pacc[nt][j][2] * (so[nt] * w4.z) + b4.z;
-                const float y3 = (float)pacc[nt][j][3] * (so[nt] * w4.w) + b4.w;
-                const int n = n0 + tbase + 16 * nt + r2;
-                if (n < N) {
-                    const half4_t y = {(_Float16)y0, (_Float16)y1, (_Float16)y2, (_Float16)y3};
-                    *reinterpret_cast<half4_t*>(rq.out + ((size_t)b * N + n) * C + c) = y;
-                }
-            }
+        for (int nt = 0; nt < NTT; ++nt) {
+            const float y0 = (float)pacc[nt][j][0] * (so[nt] * w4.x) + b4.x;
+            const float y1 = (float)pacc[nt][j][1] * (so[nt] * w4.y) + b4.y;
+            const float y2 = (float)pacc[nt][j][2] * (so[nt] * w4.z) + b4.z;
+            const float y3 = (float)pacc[nt][j][3] * (so[nt] * w4.w) + b4.w;
+            const half4_t y = {(_Float16)y0, (_Float16)y1, (_Float16)y2, (_Float16)y3};
+            int off = ((n0 + tbase + 16 * nt + r2) * C + h * D + 4 * q2) * 2 + 32 * j;
+            if (!(16 * j + 16 <= D || cl < D)) off = 0x7fffff00;
+            __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const uint2_t*>(&y), rs_out, off, 0, 0);
         }
     }
 }

@@ -82,8 +82,8 @@ __device__ __forceinline__ void rowquant_f16_held(const uint4* __restrict__ xr, 
         const int v = lane + 64 * i;
         const half2_t* x = reinterpret_cast<const half2_t*>(&u[i]);
         if (v < nv)
-            put(v, make_uint2(quant4_i8((float)x[0][0], (float)x[0][1], (float)x[1][0], (float)x[1][1], c, safe, 127.f, TAQ_TIE_F16),
-                              quant4_i8((float)x[2][0], (float)x[2][1], (float)x[3][0], (float)x[3][1], c, safe, 127.f, TAQ_TIE_F16)));
+            put(v, make_uint2(quant4_i8((float)x[0][0], (float)x[0][1], (float)x[1][0], (float)x[1][1], c, safe),
+                              quant4_i8((float)x[2][0], (float)x[2][1], (float)x[3][0], (float)x[3][1], c, safe)));
     }
 }
 
