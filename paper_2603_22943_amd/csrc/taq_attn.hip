@@ -34,9 +34,11 @@ void attn_op_kernel(AttnOpArgs a) {
     const int first = lo + ((int)blockIdx.x * 4 + wave) * NTT;  // this wavefront's first tile
     if (lo + (int)blockIdx.x * 4 * NTT >= hi) return;           // (the whole workgroup)
     const unsigned char* gimg = a.packed + a.L.image + (size_t)b * a.L.image_bytes + (size_t)h * a.I.head_bytes;
-    const int n16 = (int)(a.I.head_bytes >> 4);
-#pragma unroll 4
-    for (int i = tid; i < n16; i += 256) reinterpret_cast<uint4*>(img)[i] = reinterpret_cast<const uint4*>(gimg)[i];
+    // straight into LDS in pieces of 1 KiB, all under way at once (of the last one the lanes inside the block)
+    for (int o = wave * 1024; o < (int)a.I.head_bytes; o += 4096)
+        if (o + lane * 16 < (int)a.I.head_bytes)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gimg + o + lane * 16),
+                                             (__attribute__((address_space(3))) void*)(img + o), 16, 0, 0);
     const int ntrig = reinterpret_cast<const int*>(a.packed + a.L.ntrig)[b];
     const int nfp = (ntrig + 15) >> 4;
     const __half* k16 = reinterpret_cast<const __half*>(a.packed + a.L.k16) + (size_t)b * T * C + h * d;
@@ -55,6 +57,22 @@ void attn_op_kernel(AttnOpArgs a) {
 #pragma unroll
         for (int j = 0; j < TPH; ++j) qpk[nt][j] = a.q_op[(th * TPH + j) * 64 + lane];
         sq2[nt] = fmaxf(a.s_q[th * 16 + r16] * a.sig2, 1e-37f);
+    }
+    // the first 16 protected K rows and V columns, operands as they are, whether there are any or not: their number is still
+    // on its way (scores of rows past it are dropped, such V columns hold zeros)
+    uint2 k16r[FS][2], v16r[TPH];
+    {
+        const __half* kr = k16 + (size_t)(r16 < T ? r16 : T - 1) * C + 4 * q;
+#pragma unroll
+        for (int s = 0; s < FS; ++s)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+                k16r[s][jj] = (2 * s + jj < TPH && 16 * (2 * s + jj) + 4 * q < d) ? *reinterpret_cast<const uint2*>(kr + 16 * (2 * s + jj)) : make_uint2(0, 0);
+#pragma unroll
+        for (int k = 0; k < TPH; ++k) {
+            const int c = 16 * k + r16 < d ? 16 * k + r16 : d - 1;
+            v16r[k] = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 4 * q);
+        }
     }
     __syncthreads();
     if (first >= hi) return;  // (no barrier follows)
@@ -103,20 +121,9 @@ void attn_op_kernel(AttnOpArgs a) {
             }
         }
     }
-    // ---- protected rows: scores of tile ft of 16 slots, straight from the fp16 K rows; -inf past ntrig
-    half8_t qh[NTT][FS];
-    if (nfp > 0) {
-#pragma unroll
-        for (int nt = 0; nt < NTT; ++nt)
-#pragma unroll
-            for (int s = 0; s < FS; ++s) {
-                half2_t c0, c1, c2 = {(_Float16)0.f, (_Float16)0.f}, c3 = c2;
-                biased4_to_half(qpk[nt][2 * s] ^ 0x80808080u, c0, c1);
-                if (2 * s + 1 < TPH) biased4_to_half(qpk[nt][2 * s + 1 < TPH ? 2 * s + 1 : 0] ^ 0x80808080u, c2, c3);
-                qh[nt][s] = (half8_t){c0[0], c0[1], c1[0], c1[1], c2[0], c2[1], c3[0], c3[1]};
-            }
-    }
-    auto protected_scores = [&](int ft, floatx4_t (&facc)[NTT]) {
+    // ---- protected rows: scores of tile ft of 16 slots, the first from registers, further ones (rare) straight from the fp16
+    // K rows; -inf past ntrig
+    auto protected_scores = [&](auto head, int ft, floatx4_t (&facc)[NTT]) {
 #pragma unroll
         for (int nt = 0; nt < NTT; ++nt) facc[nt] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
         int slot = 16 * ft + r16;
@@ -128,13 +135,25 @@ void attn_op_kernel(AttnOpArgs a) {
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj) {
                 const int j = 2 * s + jj;
-                const uint2 w = (j < TPH && 16 * j + 4 * q < d) ? *reinterpret_cast<const uint2*>(kr + 16 * j) : make_uint2(0, 0);
+                uint2 w = k16r[s][jj];
+                if constexpr (!decltype(head)::value) w = (j < TPH && 16 * j + 4 * q < d) ? *reinterpret_cast<const uint2*>(kr + 16 * j) : make_uint2(0, 0);
                 const half4_t hv = *reinterpret_cast<const half4_t*>(&w);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) ka[4 * jj + e] = hv[e];
             }
 #pragma unroll
-            for (int nt = 0; nt < NTT; ++nt) facc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka, qh[nt][s], facc[nt], 0, 0, 0);
+            for (int nt = 0; nt < NTT; ++nt) {
+                unsigned c01 = qpk[nt][2 * s], c23 = qpk[nt][2 * s + 1 < TPH ? 2 * s + 1 : 0];
+                if constexpr (!decltype(head)::value) {  // (codes as fp16 are not kept for them)
+                    c01 = (unsigned)opaque((int)c01);
+                    c23 = (unsigned)opaque((int)c23);
+                }
+                half2_t c0, c1, c2 = {(_Float16)0.f, (_Float16)0.f}, c3 = c2;
+                biased4_to_half(c01 ^ 0x80808080u, c0, c1);
+                if (2 * s + 1 < TPH) biased4_to_half(c23 ^ 0x80808080u, c2, c3);
+                const half8_t qh = {c0[0], c0[1], c1[0], c1[1], c2[0], c2[1], c3[0], c3[1]};
+                facc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka, qh, facc[nt], 0, 0, 0);
+            }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -154,12 +173,18 @@ void attn_op_kernel(AttnOpArgs a) {
             if (tt < nt16) mx = fmaxf(mx, fmaxf(fmaxf(S[nt][tt][0], S[nt][tt][1]), fmaxf(S[nt][tt][2], S[nt][tt][3])));
         mxs[nt] = mx;
     }
-    for (int ft = 0; ft < nfp; ++ft) {
-        floatx4_t facc[NTT];
-        protected_scores(ft, facc);
+    floatx4_t fsc[NTT];  // scores of the first protected tile; those of further ones are formed again for the exponentials
+    if (nfp > 0) {
+        protected_scores(std::true_type{}, 0, fsc);
 #pragma unroll
-        for (int nt = 0; nt < NTT; ++nt)
-            mxs[nt] = fmaxf(mxs[nt], fmaxf(fmaxf(facc[nt][0], facc[nt][1]), fmaxf(facc[nt][2], facc[nt][3])));
+        for (int nt = 0; nt < NTT; ++nt) mxs[nt] = fmaxf(mxs[nt], fmaxf(fmaxf(fsc[nt][0], fsc[nt][1]), fmaxf(fsc[nt][2], fsc[nt][3])));
+        for (int ft = 1; ft < nfp; ++ft) {
+            floatx4_t facc[NTT];
+            protected_scores(std::false_type{}, ft, facc);
+#pragma unroll
+            for (int nt = 0; nt < NTT; ++nt)
+                mxs[nt] = fmaxf(mxs[nt], fmaxf(fmaxf(facc[nt][0], facc[nt][1]), fmaxf(facc[nt][2], facc[nt][3])));
+        }
     }
     float Zs[NTT], eus[NTT], offs[NTT];
 #pragma unroll
@@ -188,30 +213,37 @@ void attn_op_kernel(AttnOpArgs a) {
     for (int nt = 0; nt < NTT; ++nt)
 #pragma unroll
         for (int k = 0; k < TPH; ++k) oacc[nt][k] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
-    for (int ft = 0; ft < nfp; ++ft) {  // protected columns keep A, unnormalised here
-        floatx4_t facc[NTT];
-        protected_scores(ft, facc);
+    auto protected_values = [&](auto head, int ft, const floatx4_t (&facc)[NTT]) {  // protected columns keep A, unnormalised here
         half4_t phi[NTT], plo[NTT];
 #pragma unroll
         for (int nt = 0; nt < NTT; ++nt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float ex = __builtin_amdgcn_exp2f(__builtin_fmaf(facc[nt][i], sq2[nt], offs[nt]));
-                Zs[nt] += ex;
-                const _Float16 xh = (_Float16)__builtin_amdgcn_cvt_pkrtz(ex, 0.f)[0];
-                phi[nt][i] = xh;
-                plo[nt][i] = (_Float16)(ex - (float)xh);
+            for (int i = 0; i < 4; i += 2) {
+                const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(facc[nt][i], sq2[nt], offs[nt]));
+                const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(facc[nt][i + 1], sq2[nt], offs[nt]));
+                Zs[nt] += e0;
+                Zs[nt] += e1;
+                split_half2(e0, e1, phi[nt], plo[nt], i);
             }
 #pragma unroll
         for (int k = 0; k < TPH; ++k) {
             const int c = 16 * k + r16 < d ? 16 * k + r16 : d - 1;
-            const uint2 w = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 16 * ft + 4 * q);
+            uint2 w = v16r[k];
+            if constexpr (!decltype(head)::value) w = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 16 * ft + 4 * q);
             const half4_t va = *reinterpret_cast<const half4_t*>(&w);  // slots past ntrig hold zeros
 #pragma unroll
             for (int nt = 0; nt < NTT; ++nt) {
                 oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, phi[nt], oacc[nt][k], 0, 0, 0);
                 oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, plo[nt], oacc[nt][k], 0, 0, 0);
             }
+        }
+    };
+    if (nfp > 0) {
+        protected_values(std::true_type{}, 0, fsc);
+        for (int ft = 1; ft < nfp; ++ft) {
+            floatx4_t facc[NTT];
+            protected_scores(std::false_type{}, ft, facc);
+            protected_values(std::false_type{}, ft, facc);
         }
     }
     float kq[NTT], lz[NTT], fz[NTT];
