@@ -457,14 +457,14 @@ static hipError_t launch_gemm_op_cfg(GemmOpArgs a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Blocks of 64 tokens with four wavefronts while they are at most one per compute unit, above that 128 tokens with eight
-// wavefronts: half the weight bytes per token, and the larger workgroup's longer start is shared by two. At C = 1280 (128 channels
-// per block) 7.7 and 8.8 us at 512 tokens, 10.6 and 9.5 us at 2048 (320 and 160 workgroups), 23.2 and 21.9 us at 8192; at C = 640
-// the lines cross between 2048 and 4608 tokens (160 and 360 workgroups). Blocks of 256 tokens or 256 channels are slower everywhere.
+// Blocks of 64 tokens x 64 channels (four wavefronts over the tokens) while there are at most three per compute unit: the more
+// units fetch the weights, the sooner they are there. Above, 128 x 128 with eight wavefronts: half the bytes per product. At
+// C = 1280 5.4 and 8.4 us at 64 tokens, 7.1 and 8.9 us at 1024, 9.4 and 9.3 us at 2048, 24.8 and 20.6 us at 8192; at C = 768 the
+// lines cross between 3072 and 4608 tokens (576 and 864 blocks), at 640 above 4608 (720), at 320 above 8192 (640). Blocks of
+// 64 x 128 lie between the two at most sizes and win nowhere by more than 3 %; 256 tokens or channels are slower everywhere.
 template <int NW, int TPH>
 static hipError_t launch_gemm_op(const GemmOpArgs& a, hipStream_t st) {
-    const long nx = (a.H * a.tph + 2 * NW - 1) / (2 * NW);
-    if ((a.tiles + 3) / 4 * nx <= 256) return launch_gemm_op_cfg<2, NW, 2, 2, TPH>(a, st);
+    if ((long)((a.tiles + 3) / 4) * ((a.H * a.tph + NW - 1) / NW) <= 768) return launch_gemm_op_cfg<1, NW, 4, 1, TPH>(a, st);
     return launch_gemm_op_cfg<2, NW, 4, 2, TPH>(a, st);
 }
 
