@@ -105,11 +105,15 @@ __device__ __forceinline__ float quad_allsum(float x) {
     const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
-// Maximum over the 16 lanes of a row (DPP: xor 1, xor 2, mirror within 8, mirror within 16).
-__device__ __forceinline__ float row16_allmax(float x) {
+// Maximum over 8 neighbouring lanes (DPP: xor 1, xor 2, mirror within 8), and over the 16 of a row (mirror within 16).
+__device__ __forceinline__ float row8_allmax(float x) {
     x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0xB1, 0xF, 0xF, true)));
     x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x4E, 0xF, 0xF, true)));
     x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x141, 0xF, 0xF, true)));
+    return x;
+}
+__device__ __forceinline__ float row16_allmax(float x) {
+    x = row8_allmax(x);
     x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x140, 0xF, 0xF, true)));
     return x;
 }

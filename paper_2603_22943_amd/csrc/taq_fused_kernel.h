@@ -97,10 +97,11 @@ struct FusedCfg {
     // only one step's B operands are live); left to itself the compiler keeps one to ten loads ahead and the loop
     // waits on latency.
     static constexpr int NF = TPH * KC;  // weight loads (16 rows x 64 bytes) of one projection per wavefront
-    // As many as the registers take: two wavefronts per SIMD (256 registers each), three at ten heads (168), four DENSE (128).
-    // (DENSE 6 -> 12: 65.3 -> 63.4 us for 16 requests of 4096 tokens; 24 and 8 -> 32 and 16 of two token tiles: 20.6 -> 19.9 us
-    // at eight heads of 80 and 8192 tokens, 21.6 -> 20.9 us at ten of 64; one more step up spills.)
-    static constexpr int RING_MAX = DENSE ? 12 : NH <= 8 ? 32 : 16;
+    // As many as the registers take: two wavefronts per SIMD (256 registers each), three at ten heads (168), four DENSE (128);
+    // fewer with three or four token tiles, whose accumulators take the rest. (DENSE 6 -> 12: 65.3 -> 63.4 us for 16 requests
+    // of 4096 tokens; 24 and 8 -> 32 and 16 with two token tiles: 20.6 -> 19.9 us at eight heads of 80 and 8192 tokens,
+    // 21.6 -> 20.9 us at ten of 64; one more step up spills.)
+    static constexpr int RING_MAX = DENSE ? 12 : NH > 8 ? (NTT > 2 ? 8 : 16) : NTT == 4 ? 20 : NTT == 3 ? 28 : 32;
     static constexpr int RING = (!PREFETCH_W && NG == 1) ? (NF < RING_MAX ? NF : RING_MAX) : 0;
 };
 
@@ -120,16 +121,17 @@ __attribute__((amdgpu_waves_per_eu(DENSE ? 4 : 1, DENSE ? 4 : NG > 1 ? 2 : (NH *
 void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm) {
     using F = FusedCfg<D, NH, NTT, NG, TOK, DENSE>;
     static_assert(!DENSE || (NG == 1 && NH * (TOK / (16 * NTT)) == 8), "two 8-wavefront workgroups per compute unit");
-    static_assert(TOK == 32 || (TOK == 16 && NTT == 1), "a workgroup owns 32 image tokens, or 16 with one tile per wavefront");
+    static_assert(TOK == 16 * NTT || TOK == 32, "one wavefront per head, or two of one tile each");
     static_assert(NG == 1 || TOK == 16, "head groups: one tile of 16 image tokens");
     constexpr int C = F::C, H = F::H, TPH = F::TPH, KS = F::KS, FS = F::FS, KC = F::KC, NT = F::NT;
     constexpr int SUB = F::SUB, TPS = F::TPS;
+    constexpr bool LEAN = DENSE || (NTT > 2 && NH <= 8);  // no register to spare
     constexpr bool LOGP = PG == TAQ_PROB_LOG2, ROWMAX = PG == TAQ_PROB_ROWMAX;  // grid of the probabilities, Eq. (3)
     constexpr int MT16 = NT16 ? NT16 : 6;  // score tiles the code is unrolled for
     constexpr bool TAPS = NT16 == 0;       // taps of intermediate codes and scales (tests, profiling)
     extern __shared__ __align__(16) unsigned char smem[];
 
-    const int tid = threadIdx.x, hl = (tid >> 6) % NH, lane = tid & 63, r16 = lane & 15, q = DENSE ? opaque(lane >> 4) : lane >> 4;
+    const int tid = threadIdx.x, hl = (tid >> 6) % NH, lane = tid & 63, r16 = lane & 15, q = LEAN ? opaque(lane >> 4) : lane >> 4;
     // Grid: x = batch element, y = request, z = token tile; head-group variant (one request): x = batch element,
     // y = token tile, z = head group. Workgroups are dispatched x fastest, so consecutive ones (which round-robin over
     // the 8 XCDs) share a token tile index and differ in the batch element / request: one XCD, few K~/V~ images. The
@@ -149,20 +151,29 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     // ---- The hidden tile's loads are issued before anything else: they are the head of the kernel's one unavoidable
     // latency chain (HBM), and everything below (scalar loads of layout fields, of the protected-token count from
     // global memory, address arithmetic for the weights) would otherwise sit in front of them.
-    constexpr bool HQ1 = NG == 1;                  // single-kernel variant: 16 threads per token, 8-byte loads
-    constexpr int TPT = NG > 1 ? NT / TOK : 16;    // threads per token
+    // threads per token, with 16-byte loads (single-kernel variant with at least 16 threads for each: 16, with 8-byte loads)
+    constexpr int TPT = NG > 1 ? NT / TOK : 16 * TOK <= NT ? 16 : 8;
+    constexpr int XW = 16 / TPT;                   // single-kernel variant: 8-byte pieces per load
     constexpr int CH = NG > 1 ? C / (8 * TPT) : 1; // head-group variant: 16-byte pieces of a hidden row per thread
     const int tok0 = tid / TPT, part0 = tid % TPT;
     const int nq0 = n0 + tok0;
     const size_t row0 = (size_t)b * N + (nq0 < N ? nq0 : N - 1);
-    const bool HOLDS = NT == 16 * TOK || tid < 16 * TOK;  // this thread holds a piece of the tile (all do, at 8 heads)
-    uint2 xin[HQ1 ? KC : 1];
+    const bool HOLDS = NT == TPT * TOK || tid < TPT * TOK;  // this thread holds a piece of the tile (all do, at 8 heads)
+    uint2 xin[NG == 1 ? KC : 1][NG == 1 ? XW : 1];
     uint4 xin4[NG > 1 ? CH : 1];
-    if constexpr (HQ1) {
+    if constexpr (NG == 1) {
         if (HOLDS) {
-            const uint2* xr = reinterpret_cast<const uint2*>(rq.hidden + row0 * C);
+            const uint2* xr = reinterpret_cast<const uint2*>(rq.hidden + row0 * C) + part0 * XW;
 #pragma unroll
-            for (int it = 0; it < KC; ++it) xin[it] = xr[it * 16 + part0];
+            for (int it = 0; it < KC; ++it) {
+                if constexpr (XW == 1) {
+                    xin[it][0] = xr[it * 16];
+                } else {
+                    const uint4 w = *reinterpret_cast<const uint4*>(xr + it * 16);
+                    xin[it][0] = make_uint2(w.x, w.y);
+                    xin[it][XW - 1] = make_uint2(w.z, w.w);
+                }
+            }
         }
     }
     if constexpr (NG > 1) {
@@ -262,7 +273,6 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     if constexpr (NG == 1) {
         // ---- phase 0: issue every global read up front, oldest first in the order of use (loads return in
         // order): hidden tile, weight scales, this head's to_q weight slice, the K~/V~ image
-        // (16 threads per token, 4 channels per load: the first 16*TOK threads hold the tile, requested above)
         constexpr int SCV = (3 * C / 4 + NT - 1) / NT;
         float4 scv[SCV];
     #pragma unroll
@@ -276,11 +286,13 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         if (HOLDS) {
             half2_t am2 = {(_Float16)0.f, (_Float16)0.f};
     #pragma unroll
-            for (int it = 0; it < KC; ++it) {
-                const unsigned a0 = xin[it].x & 0x7fff7fffu, a1 = xin[it].y & 0x7fff7fffu;
-                am2 = __builtin_elementwise_max(am2, __builtin_elementwise_max(*reinterpret_cast<const half2_t*>(&a0),
-                                                                                 *reinterpret_cast<const half2_t*>(&a1)));
-            }
+            for (int it = 0; it < KC; ++it)
+    #pragma unroll
+                for (int u = 0; u < XW; ++u) {
+                    const unsigned a0 = xin[it][u].x & 0x7fff7fffu, a1 = xin[it][u].y & 0x7fff7fffu;
+                    am2 = __builtin_elementwise_max(am2, __builtin_elementwise_max(*reinterpret_cast<const half2_t*>(&a0),
+                                                                                     *reinterpret_cast<const half2_t*>(&a1)));
+                }
             amax = fmaxf((float)am2[0], (float)am2[1]);
         }
         // The hidden tile has arrived (the unpacking above waited for it). Only now are the 10x larger weight reads
@@ -289,7 +301,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         // The weight slice is fetched a few loads at a time between pieces of arithmetic: a wavefront stalls at a
         // vector-memory instruction while the texture unit's queue is full (it coalesces 64 B per clock, and every
         // CU pulls ~300 KB of weights and image per launch), so the requests are spread under the ALU work.
-        amax = row16_allmax(amax);
+        amax = TPT == 16 ? row16_allmax(amax) : row8_allmax(amax);
         const bool zero0 = amax == 0.f;
         const float sc0 = zero0 ? 1.f : amax / 127.f;
         const float safe0 = zero0 ? 1.f : amax;
@@ -306,10 +318,18 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
                 for (int f = it * RPS; f < (it + 1) * RPS && f < RING; ++f) wring[f] = ring_load(rs_wq, f);
             }
             if (HOLDS) {
-                const half2_t x01 = *reinterpret_cast<const half2_t*>(&xin[it].x), x23 = *reinterpret_cast<const half2_t*>(&xin[it].y);
-                const unsigned pk = quant4_i8((float)x01[0], (float)x01[1], (float)x23[0], (float)x23[1], cq0, safe0);
-                *reinterpret_cast<unsigned*>(tileq + tok0 * F::TILE_RS + (it * 16 + part0) * 4) = pk;
-                if (TAPS && dm.dbg.h_code && nq0 < N) *reinterpret_cast<unsigned*>(dm.dbg.h_code + row0 * C + (it * 16 + part0) * 4) = pk;
+                unsigned pk[XW];
+    #pragma unroll
+                for (int u = 0; u < XW; ++u) {
+                    const half2_t x01 = *reinterpret_cast<const half2_t*>(&xin[it][u].x), x23 = *reinterpret_cast<const half2_t*>(&xin[it][u].y);
+                    pk[u] = quant4_i8((float)x01[0], (float)x01[1], (float)x23[0], (float)x23[1], cq0, safe0);
+                }
+                int8_t* dst = tileq + tok0 * F::TILE_RS + it * 64 + part0 * (4 * XW);
+                if constexpr (XW == 1) *reinterpret_cast<unsigned*>(dst) = pk[0];
+                else *reinterpret_cast<uint2*>(dst) = make_uint2(pk[0], pk[XW - 1]);
+                if (TAPS && dm.dbg.h_code && nq0 < N)
+    #pragma unroll
+                    for (int u = 0; u < XW; ++u) *reinterpret_cast<unsigned*>(dm.dbg.h_code + row0 * C + it * 64 + part0 * (4 * XW) + 4 * u) = pk[u];
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -944,17 +964,17 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         }
     }
 
-    // DENSE has no register to spare across the attention: addresses are formed again instead of kept (four registers
-    // spilled otherwise, and their reloads wait for the weights on their way: 19.0 us at 16384 tokens, 18.3 without)
-    const int lane2 = DENSE ? opaque(lane) : lane;
-    if constexpr (DENSE) set_wrow(lane2);
+    // LEAN: addresses are formed again instead of kept across the attention (DENSE spilled four registers otherwise, and their
+    // reloads wait for the weights on their way: 19.0 us at 16384 tokens, 18.3 without)
+    const int lane2 = LEAN ? opaque(lane) : lane;
+    if constexpr (LEAN) set_wrow(lane2);
     if (F::PREFETCH_W) {  // to_out's weight slice travels while A^ V~ is quantized (two barriers away from its use)
 #pragma unroll
         for (int j = 0; j < TPH; ++j)
 #pragma unroll
             for (int ks = 0; ks < KC; ++ks) wreg[j][ks] = load_w(rs_wo, j, wstep * ks);
     }
-    if constexpr (RING > 0 && NTT == 2) {  // two token tiles per wavefront: the attention needs the registers; the first
+    if constexpr (RING > 0 && NTT >= 2) {  // several token tiles per wavefront: the attention needs the registers; the first
 #pragma unroll                         // RING loads of to_out travel while A^ V~ is quantized
         for (int f = 0; f < RING; ++f) wring[f] = ring_load(rs_wo, f);
     }
@@ -1085,6 +1105,15 @@ static hipError_t launch_fused_one(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& 
     return hipGetLastError();
 }
 
+// The instantiation for the layout of the weights.
+template <int D, int NH, int NTT, int NG, int PG, int TOK, int NT16>
+static hipError_t launch_fused_layout(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& tab, const FusedDims& dm, size_t bytes, hipStream_t st) {
+    if constexpr ((FusedCfg<D, NH, NTT, NG, TOK>::RING > 0 || NG > 1) && D % 16 == 0) {
+        if (!dm.w_layout) return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, false, true>(tab, dm, bytes, st);
+    }
+    return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, false, false>(tab, dm, bytes, st);
+}
+
 template <int D, int NH, int NTT, int NG, int PG, int TOK, int NT16>
 static hipError_t launch_fused_grid(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& tab, const FusedDims& dm, hipStream_t st) {
     using F = FusedCfg<D, NH, NTT, NG, TOK>;
@@ -1098,10 +1127,18 @@ static hipError_t launch_fused_grid(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>&
         if ((dm.N + TOK - 1) / TOK * dm.R * dm.B > device_cu_count() && bytes <= 80 * 1024)
             return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, true, false>(tab, dm, bytes, st);
     }
-    if constexpr ((F::RING > 0 || NG > 1) && D % 16 == 0) {
-        if (!dm.w_layout) return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, false, true>(tab, dm, bytes, st);
+    if constexpr (F::RING > 0 && NT16 == 5 && NTT == 2) {
+        // Workgroups that fill a compute unit run in rounds of one per unit; of 48 or 64 tokens each, instead of 32, they take
+        // longer (at d = 80 26 and 33 us, against 20; at d = 64 28), but there may be fewer rounds: 12288 tokens
+        // 37.2 -> 26.3 us, 16384 tokens 38.2 -> 33.1 us.
+        const long cu = device_cu_count(), mul = (long)dm.R * dm.B;
+        auto rounds = [&](int tok) { return ((dm.N + tok - 1) / tok * mul + cu - 1) / cu; };
+        auto fits = [&](int tok) { return bytes + (tok - TOK) * (F::TILE_RS + 4 + NH * 4) <= 160 * 1024; };
+        const long cost2 = 20 * rounds(32), cost3 = fits(48) ? (NH <= 8 ? 26 : 28) * rounds(48) : cost2, cost4 = fits(64) ? 33 * rounds(64) : cost2;
+        if constexpr (NH <= 8) if (cost4 < cost2 && cost4 < cost3) return launch_fused_layout<D, NH, 4, NG, PG, 64, NT16>(tab, dm, bytes + 32 * (F::TILE_RS + 4 + NH * 4), st);
+        if (cost3 < cost2) return launch_fused_layout<D, NH, 3, NG, PG, 48, NT16>(tab, dm, bytes + 16 * (F::TILE_RS + 4 + NH * 4), st);
     }
-    return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, false, false>(tab, dm, bytes, st);
+    return launch_fused_layout<D, NH, NTT, NG, PG, TOK, NT16>(tab, dm, bytes, st);
 }
 
 template <int D, int NH, int NTT, int NG, int PG, int TOK>
