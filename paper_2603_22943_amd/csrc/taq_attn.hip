@@ -389,12 +389,22 @@ static hipError_t launch_attn_cfg(const AttnOpArgs& a, int tiles_b, int nb, hipS
     return hipGetLastError();
 }
 
-template <int TPH, int PG>
-static hipError_t launch_attn_grid(const AttnOpArgs& a, int tiles_b, int nb, hipStream_t st) {
-    constexpr int NTT = TPH <= 5 ? 2 : 1;  // two tiles per wavefront share the operand conversions; wide heads have no registers for it
+template <int TPH, int PG, int NTT>
+static hipError_t launch_attn_text(const AttnOpArgs& a, int tiles_b, int nb, hipStream_t st) {
     // 65 to 80 text tokens (the 77-token prompts): no run-time guards around the score tiles
     if (a.nt16 == 5) return launch_attn_cfg<TPH, NTT, PG, 5>(a, tiles_b, nb, st);
     return launch_attn_cfg<TPH, NTT, PG, 0>(a, tiles_b, nb, st);
+}
+
+// Two tiles per wavefront share the operand conversions, one is done sooner: at 20 heads of 64 5.2 and 6.3 us with 64 tokens, 9.0
+// and 9.5 us with 2048 (320 workgroups of two tiles per wavefront), 19.6 and 18.2 us with 8192; at 12 heads 12.3 and 11.4 us with
+// 4608 tokens (432 workgroups). Wide heads have no registers for two.
+template <int TPH, int PG>
+static hipError_t launch_attn_grid(const AttnOpArgs& a, int tiles_b, int nb, hipStream_t st) {
+    if constexpr (TPH <= 5) {
+        if ((long)((tiles_b + 7) / 8) * a.H * nb > 384) return launch_attn_text<TPH, PG, 2>(a, tiles_b, nb, st);
+    }
+    return launch_attn_text<TPH, PG, 1>(a, tiles_b, nb, st);
 }
 
 template <int TPH>
