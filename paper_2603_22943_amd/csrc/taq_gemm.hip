@@ -268,6 +268,11 @@ struct GemmOpArgs {
     size_t pack_off;
 };
 
+// The compiler takes the result of this read to be there at once; it knows nothing of the data still on its way into these
+// registers. Rule: on every path the destinations pass through `arrived` below (a wait, then an empty asm that takes and gives
+// back each of them) before they are used and before the kernel goes on without them. Until then they are alive to the
+// compiler, so it places nothing else there; a read whose result nobody takes would leave it free to, with only timing to keep
+// the late data from overwriting what it placed. tests/test_inflight_registers.py checks the generated code of every kernel.
 template <int OFF>
 __device__ __forceinline__ int32x4_t lds_read16(unsigned addr) {
     int32x4_t r;
@@ -351,14 +356,17 @@ void gemm_op_kernel(GemmOpArgs a) {
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 1) * NLD) : "memory");
     read_ops(0, 0);
     int cur = 0;  // stage of step kc
+    auto arrived = [&](int set) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < MW; ++i) asm volatile("" : "+v"(xb[set][i]));
+#pragma unroll
+        for (int j = 0; j < NW; ++j) asm volatile("" : "+v"(wa[set][j]));
+    };
     auto step_k = [&](int kc, int set) {
         // this wavefront has its operands of step kc (so it is done with that stage) and its part of stage kc + 1 has arrived;
         // after the barrier that holds for everybody
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int i = 0; i < MW; ++i) asm volatile("" : "+v"(xb[set][i]));  // (the registers are used after the wait, not before)
-#pragma unroll
-        for (int j = 0; j < NW; ++j) asm volatile("" : "+v"(wa[set][j]));
+        arrived(set);
         asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 2) * NLD) : "memory");
         const int nxt = cur + 1 == STAGES ? 0 : cur + 1;
         read_ops(set ^ 1, nxt);
@@ -369,11 +377,15 @@ void gemm_op_kernel(GemmOpArgs a) {
 #pragma unroll
             for (int i = 0; i < MW; ++i) acc[j][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[set][j], xb[set][i], acc[j][i], 0, 0, 0);
     };
-    for (int kc = 0; kc < KC; kc += 2) {
+    // (left from the middle, not by a guarded second half: no path leads from a half whose reads are in flight to its own start)
+    for (int kc = 0;;) {
         step_k(kc, 0);
-        if (kc + 1 < KC) step_k(kc + 1, 1);
+        if (++kc >= KC) break;
+        step_k(kc, 1);
+        if (++kc >= KC) break;
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    arrived(0);  // the last step's reads, which nobody multiplies, are in one set or the other
+    arrived(1);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the re-fetched steps past the end
 
 #pragma unroll
