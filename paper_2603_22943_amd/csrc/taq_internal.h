@@ -377,6 +377,9 @@ struct SensWorkspace {
     size_t o;       // f32 [chunk][C]            reference attention output
     size_t p;       // f32 [chunk][H][C]         ... through each head's slice of to_out
     size_t ab;      // f32 [chunk][ntok][nb][H][2]
+    size_t dom;     // i32 [chunk][H]            swept token whose change is taken from md, or -1
+    size_t dcoef;   // f32 [chunk][H][nb]        its factors
+    size_t md;      // f32 [chunk][C]            mean of the other tokens' V rows minus its own
     size_t part;    // f64 [nb][ntok][npart]     partial sums of squares
     size_t total;
     int np, chunk, npart;

@@ -2,14 +2,22 @@
 // token i and bit width b, the mean squared change of the block output when only the K and V rows of token i are
 // quantized to b bits and everything else stays in full precision.
 //
-// Running the block once per (i, b) repeats almost all of its work. With p = A[n, i] of head h, r = exp(sigma q.(k' - k))
-// and g = 1 + p (r - 1), replacing row i by (k', v') moves the head's attention output by
+// Running the block once per (i, b) repeats almost all of its work. With p = A[n, i] of head h, u = 1 - p as the sum of the other
+// tokens' weights (a difference from 1 would be all rounding where token i dominates), r = exp(sigma q.(k' - k)) and
+// g = u + p r, replacing row i by (k', v') moves the head's attention output by
 //     dO = alpha (O - v) + beta (v' - v),      alpha = p (1 - r) / g,   beta = p r / g
 // (1 - r taken from expm1: no cancellation), and to_out is linear, so with P[n, h] = Wo_h O[n, h], a[i, h] = Wo_h v and
 // D[i, h] = Wo_h (v' - v), each formed once,
 //     y'(i, b)[n] = y[n] + sum_h ( alpha (P[n, h] - a[i, h]) + beta D[i, h] ),
 // H multiply-adds per output element and term instead of the whole block. Everything is float32 (float64 in the sums of
 // squares); the outputs are rounded to fp16 on both sides before the difference is taken, as the block stores them.
+//
+// Where token i dominates its row and its score falls, alpha is large (up to p / u) and O - v = u (m - v) is small, m being the
+// mean of V over the other tokens by their weights: a difference of nearly equal numbers, enlarged. From alpha = 16 on, where
+// the 2^-24 of O would be 2^-20 in dO (a 512th of the fp16 rounding of y'), the row's term is taken from m itself,
+//     dO = (p - beta) (m - v) + beta (v' - v).
+// alpha > 16 needs u < 1/16, so it is one token of a (row, head) at most, the one of the largest score: `dom` says which swept
+// token that is, md holds m - v and dcoef p - beta, and sens_main_kernel adds that term apart from the others.
 #include "taq_internal.h"
 
 namespace taq {
@@ -104,12 +112,14 @@ __device__ __forceinline__ float sens_quad_sum(float x) {
 // of them idle): S^T = K Q^T and the score changes (k' - k) Q^T of every text token, softmax, O^T = V^T A^T, all with
 // V_MFMA_F32_16X16X4_F32 (text tokens or channels along the rows, image tokens along the columns: the accumulator
 // registers of the scores are the B operand of the last product). A chain of latencies: each step's operands are
-// requested while the step before is multiplied. o [row][C], ab [row][nk][NB][H]{alpha, beta}, rows counted from row0
-// over all batch elements, D.Np of them each. MT: tiles of 16 text tokens.
+// requested while the step before is multiplied. o, md [row][C], ab [row][nk][NB][H]{alpha, beta}, dom [row][H] (swept token
+// or -1), dcoef [row][H][NB], rows counted from row0 over all batch elements, D.Np of them each; md is written by wavefronts
+// with a dom >= 0 only. MT: tiles of 16 text tokens.
 template <int NB, int MT>
 __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__ q_f, const float* __restrict__ kx,
                                                         const float* __restrict__ vx, SensDims D, int row0,
-                                                        float* __restrict__ o, float* __restrict__ ab) {
+                                                        float* __restrict__ o, float* __restrict__ ab, int* __restrict__ dom,
+                                                        float* __restrict__ dcoef, float* __restrict__ md) {
     const int lane = threadIdx.x, r16 = lane & 15, q = lane >> 4;
     const int tile = blockIdx.x, h = blockIdx.y;
     const int row = tile * 16 + r16;  // of the chunk
@@ -156,34 +166,88 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
             mx = fmaxf(mx, S[0][tt][i]);
         }
     mx = sens_quad_max(mx);
-    float Z = 0.f;
+    int top = TAQ_MAX_T;  // the first token of the largest score
 #pragma unroll
     for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            S[0][tt][i] = __expf(S[0][tt][i] - mx);
-            Z += S[0][tt][i];
+            const int t = 16 * tt + 4 * q + i;
+            if (S[0][tt][i] == mx && t < top) top = t;
+        }
+    top = min(top, __shfl_xor(top, 16));
+    top = min(top, __shfl_xor(top, 32));
+    float mr = -__builtin_inff();  // the largest of the others
+#pragma unroll
+    for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (16 * tt + 4 * q + i != top) mr = fmaxf(mr, S[0][tt][i]);
+    const bool alone = T == 1;
+    mr = alone ? mx : sens_quad_max(mr);
+    float Z = 0.f, R2 = 0.f;  // sum over all tokens beside the largest score, over the others beside theirs (>= 1 both)
+#pragma unroll
+    for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            Z += __expf(S[0][tt][i] - mx);
+            R2 += 16 * tt + 4 * q + i == top ? 0.f : __expf(S[0][tt][i] - mr);
         }
     Z = sens_quad_sum(Z);
+    R2 = sens_quad_sum(R2);
+    const float inv_z = 1.f / Z, u_top = R2 * __expf(mr - mx) * inv_z;
+    int flagged = -1;
 #pragma unroll
     for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float p = S[0][tt][i] / Z;
-            S[0][tt][i] = p;
             const int t = 16 * tt + 4 * q + i;
+            const float e = __expf(S[0][tt][i] - mx), p = e / Z;
             const int k = t < T ? D.slot[t] : -1;
             if (k >= 0) {
+                const bool is_top = t == top;
+                const float R = is_top ? R2 : Z - e;                     // the others' sum, >= 1 but for rounding ...
+                const float lead = S[0][tt][i] - (is_top ? mr : mx);    // ... and this token's score beside the same reference
+                const float u = is_top ? u_top : R * inv_z;
+                float al[NB], be[NB], w[NB], Rc[NB];
+                bool hv[NB], heavy = false;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    const float em = expm1f(S[1 + j][tt][i] * D.sigma), g = 1.f + p * em;  // r - 1, Z' / Z
-                    float2 f;
-                    f.x = -(p * em) / g;
-                    f.y = p * (1.f + em) / g;
-                    reinterpret_cast<float2*>(ab)[(((size_t)row * D.nk + k) * NB + j) * D.H + h] = f;
+                    const float dl = alone ? 0.f : S[1 + j][tt][i] * D.sigma;
+                    const float x = lead + dl, c = fmaxf(x, 0.f);
+                    w[j] = __expf(x - c);
+                    Rc[j] = R * __expf(-c);
+                    be[j] = w[j] * __builtin_amdgcn_rcpf(w[j] + Rc[j]);  // (the sum is between 1 and T + 1)
+                    const float em = expm1f(-fabsf(dl));               // e^-|dl| - 1
+                    const float num = -p * em, g = u + p * (1.f + em);  // (of a score that falls)
+                    hv[j] = dl <= 0.f && num > 16.f * g;
+                    heavy |= hv[j];
+                    al[j] = dl > 0.f ? be[j] * em : num / g;           // (p (1 - r) / g = beta (1 - r) / r)
                 }
+                if (heavy) {
+                    flagged = k;
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {  // p - beta
+                        dcoef[((size_t)row * D.H + h) * NB + j] = hv[j] ? Rc[j] / (w[j] + Rc[j]) - u : al[j] * u;
+                        al[j] = 0.f;
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+                    reinterpret_cast<float2*>(ab)[(((size_t)row * D.nk + k) * NB + j) * D.H + h] = make_float2(al[j], be[j]);
             }
+            S[1][tt][i] = p;
         }
+    flagged = max(flagged, __shfl_xor(flagged, 16));
+    flagged = max(flagged, __shfl_xor(flagged, 32));
+    if (q == 0) dom[(size_t)row * D.H + h] = flagged;
+    const bool sharp = __any(flagged >= 0);
+    if (sharp) {  // m - v as weights of the V rows
+        const float inv = 1.f / R2;
+#pragma unroll
+        for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) S[0][tt][i] = 16 * tt + 4 * q + i == top ? -1.f : __expf(S[0][tt][i] - mr) * inv;
+    }
     float va[MT][4];
     auto fetch_v = [&](int j0) {
         const int c = j0 + r16 < d ? j0 + r16 : d - 1;
@@ -207,10 +271,36 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
 #pragma unroll
         for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[tt][i], S[0][tt][i], acc, 0, 0, 0);
+            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[tt][i], S[1][tt][i], acc, 0, 0, 0);
         if (j0 + 4 * q < d)
             *reinterpret_cast<float4*>(o + (size_t)row * C + h * d + j0 + 4 * q) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        if (sharp) {
+            sens_floatx4_t m = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) m = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[tt][i], S[0][tt][i], m, 0, 0, 0);
+            if (j0 + 4 * q < d)
+                *reinterpret_cast<float4*>(md + (size_t)row * C + h * d + j0 + 4 * q) = make_float4(m[0], m[1], m[2], m[3]);
+        }
     }
+}
+
+// One output channel's slice of a head (d % 8 == 0, 16-byte aligned) times a row's vector.
+__device__ __forceinline__ float sens_dot(const __half* w, const float* m, int d) {
+    float t = 0.f;
+#pragma unroll 2
+    for (int c = 0; c < d; c += 8) {
+        const uint4 v = *reinterpret_cast<const uint4*>(w + c);
+        const unsigned x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float2 f = __half22float2(*reinterpret_cast<const __half2*>(&x[i]));
+            t = __builtin_fmaf(f.x, m[c + 2 * i], t);
+            t = __builtin_fmaf(f.y, m[c + 2 * i + 1], t);
+        }
+    }
+    return t;
 }
 
 // ---------------------------------------------------------------- outputs of every (token, width) and their squared changes
@@ -219,9 +309,13 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
 // wavefronts of a workgroup take neighbouring rows of the same channels, so that those loads meet in the compute unit's
 // cache. Bound by vector issue: HT * (1 + 2 NB) multiply-adds per output element and swept token.
 // Sums of squares in float64: per lane over the rows, then across lanes through LDS, 16 (token, width) pairs at a time.
+// Workgroups with a row whose largest token needs its own term (dom) take a second form of the loop; the term is one dot
+// product over the head's channels, for one token of a (row, head) at most.
 template <int HT, int NR, int NB, bool EXACT>
-__global__ __launch_bounds__(256) void sens_main_kernel(const float* __restrict__ P, const float* __restrict__ ab,
-                                                        const float* __restrict__ va, const float* __restrict__ bias, SensDims D,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HT <= 8 ? 4 : 2))) void sens_main_kernel(const float* __restrict__ P, const float* __restrict__ ab,
+                                                        const float* __restrict__ va, const float* __restrict__ bias,
+                                                        const int* __restrict__ dom, const float* __restrict__ dcoef,
+                                                        const float* __restrict__ md, const __half* __restrict__ Wo, SensDims D,
                                                         int row0, int kper, double* __restrict__ part, int part0, int npart) {
     constexpr int CHUNK = 16;
     __shared__ double red[4][CHUNK][65];
@@ -230,80 +324,118 @@ __global__ __launch_bounds__(256) void sens_main_kernel(const float* __restrict_
     const int c = blockIdx.y * 64 + lane, cc = c < C ? c : C - 1;
     const int row = ((int)blockIdx.x * 4 + wave) * NR;  // first row of this wavefront, within the chunk
     const int b = (row0 + row) / D.Np, np0 = (row0 + row) % D.Np;
-    float p[NR][HT], ys[NR];
-    float y16[NR];
     const float bc = bias[cc];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        float y = 0.f;
-#pragma unroll
-        for (int h = 0; h < HT; ++h) {
-            p[r][h] = (EXACT || h < H) ? P[((size_t)(row + r) * H + h) * C + cc] : 0.f;
-            y += p[r][h];
-        }
-        ys[r] = y + bc;
-        y16[r] = __half2float(__float2half_rn(ys[r]));
-    }
     const int k0 = blockIdx.z * kper, k1 = k0 + kper < D.nk ? k0 + kper : D.nk;
     const size_t plane = (size_t)D.B * D.T * H * C;
     const bool cin = c < C;
-    for (int kb = k0; kb < k1; kb += CHUNK / NB) {
+    bool sharp = false;  // of the workgroup's rows
+    for (int i = threadIdx.x; i < 4 * NR * H; i += 256) sharp |= dom[(size_t)blockIdx.x * (4 * NR) * H + i] >= 0;
+    sharp = __syncthreads_or(sharp);
+    // sums(k, a, dl, s): squared changes of token k over this wavefront's rows, given its a and D
+    auto sweep = [&](auto sums) {
+        for (int kb = k0; kb < k1; kb += CHUNK / NB) {
 #pragma unroll 1
-        for (int kk = 0; kk < CHUNK / NB && kb + kk < k1; ++kk) {
-            const int k = kb + kk;
-            const float* vr = va + ((size_t)b * D.T + D.tok[k]) * H * C + cc;
-            float a[HT], dl[NB][HT];
+            for (int kk = 0; kk < CHUNK / NB && kb + kk < k1; ++kk) {
+                const int k = kb + kk;
+                const float* vr = va + ((size_t)b * D.T + D.tok[k]) * H * C + cc;
+                float a[HT], dl[NB][HT];
 #pragma unroll
-            for (int h = 0; h < HT; ++h) {
-                const bool in = EXACT || h < H;
-                a[h] = in ? vr[(size_t)h * C] : 0.f;
+                for (int h = 0; h < HT; ++h) {
+                    const bool in = EXACT || h < H;
+                    a[h] = in ? vr[(size_t)h * C] : 0.f;
 #pragma unroll
-                for (int j = 0; j < NB; ++j) dl[j][h] = in ? vr[(size_t)(1 + j) * plane + (size_t)h * C] : 0.f;
+                    for (int j = 0; j < NB; ++j) dl[j][h] = in ? vr[(size_t)(1 + j) * plane + (size_t)h * C] : 0.f;
+                }
+                double s[NB];
+#pragma unroll
+                for (int j = 0; j < NB; ++j) s[j] = 0.0;
+                sums(k, a, dl, s);
+#pragma unroll
+                for (int j = 0; j < NB; ++j) red[wave][kk * NB + j][lane] = s[j];
             }
-            double s[NB];
+            __syncthreads();
+            {
+                int e = lane >> 2;  // four lanes per (token, width) pair
+                asm volatile("" : "+v"(e));  // (addresses formed here, not held in registers over the loop)
+                const int k = kb + e / NB;
+                double t = 0.0;
 #pragma unroll
-            for (int j = 0; j < NB; ++j) s[j] = 0.0;
-            const float* f = ab + ((size_t)row * D.nk + k) * NB * H * 2;
+                for (int u = 0; u < 16; ++u) t += red[wave][e][(lane & 3) * 16 + u];
+                t += __shfl_xor(t, 1);
+                t += __shfl_xor(t, 2);
+                if ((lane & 3) == 0 && k < k1)
+                    part[((size_t)(e % NB) * D.nk + k) * npart + part0 + ((int)blockIdx.x * 4 + wave) * (int)gridDim.y + (int)blockIdx.y] = t;
+            }
+            __syncthreads();
+        }
+    };
+    auto row_of_p = [&](int r, float (&p)[HT], float& y, float& y16) {
+        y = 0.f;
+#pragma unroll
+        for (int h = 0; h < HT; ++h) {
+            p[h] = (EXACT || h < H) ? P[((size_t)(row + r) * H + h) * C + cc] : 0.f;
+            y += p[h];
+        }
+        y += bc;
+        y16 = __half2float(__float2half_rn(y));
+    };
+    auto changed = [&](int r, int k, const float (&p)[HT], const float (&a)[HT], const float (&dl)[NB][HT], float (&y)[NB]) {
+        const float* fr = ab + ((size_t)(row + r) * D.nk + k) * NB * H * 2;
+#pragma unroll
+        for (int h = 0; h < HT; ++h) {
+            if (EXACT || h < H) {
+                const float pm = p[h] - a[h];
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    y[j] = __builtin_fmaf(fr[(j * H + h) * 2], pm, y[j]);
+                    y[j] = __builtin_fmaf(fr[(j * H + h) * 2 + 1], dl[j][h], y[j]);
+                }
+            }
+        }
+    };
+    auto square = [&](int r, const float (&y)[NB], float y16, double (&s)[NB]) {
+        if (np0 + r < D.N && cin) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const double df = (double)(__half2float(__float2half_rn(y[j])) - y16);  // (exact: both are fp16 numbers)
+                s[j] = __builtin_fma(df, df, s[j]);
+            }
+        }
+    };
+    if (!sharp) {
+        float p[NR][HT], ys[NR], y16[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) row_of_p(r, p[r], ys[r], y16[r]);
+        sweep([&](int k, const float (&a)[HT], const float (&dl)[NB][HT], double (&s)[NB]) {
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
-                const float* fr = f + (size_t)r * D.nk * NB * H * 2;
                 float y[NB];
 #pragma unroll
                 for (int j = 0; j < NB; ++j) y[j] = ys[r];
-#pragma unroll
-                for (int h = 0; h < HT; ++h) {
-                    if (EXACT || h < H) {
-                        const float pm = p[r][h] - a[h];
-#pragma unroll
-                        for (int j = 0; j < NB; ++j) {
-                            y[j] = __builtin_fmaf(fr[(j * H + h) * 2], pm, y[j]);
-                            y[j] = __builtin_fmaf(fr[(j * H + h) * 2 + 1], dl[j][h], y[j]);
-                        }
-                    }
-                }
-                if (np0 + r < D.N && cin) {
-#pragma unroll
-                    for (int j = 0; j < NB; ++j) {
-                        const double df = (double)(__half2float(__float2half_rn(y[j])) - y16[r]);  // (exact: both are fp16 numbers)
-                        s[j] = __builtin_fma(df, df, s[j]);
-                    }
-                }
+                changed(r, k, p[r], a, dl, y);
+                square(r, y, y16[r], s);
             }
+        });
+    } else {  // a row at a time, P read again for each token: with the rows' P in registers this form would spill
+        sweep([&](int k, const float (&a)[HT], const float (&dl)[NB][HT], double (&s)[NB]) {
+#pragma unroll 1
+            for (int r = 0; r < NR; ++r) {
+                float p[HT], ref, y16, y[NB];
+                row_of_p(r, p, ref, y16);
 #pragma unroll
-            for (int j = 0; j < NB; ++j) red[wave][kk * NB + j][lane] = s[j];
-        }
-        __syncthreads();
-        {
-            const int e = lane >> 2, k = kb + e / NB;  // four lanes per (token, width) pair
-            double t = 0.0;
+                for (int j = 0; j < NB; ++j) y[j] = ref;
+                changed(r, k, p, a, dl, y);
+#pragma unroll 1
+                for (int h = 0; h < H; ++h) {
+                    const size_t rh = (size_t)(row + r) * H + h;
+                    if (dom[rh] != k) continue;
+                    const float t = sens_dot(Wo + (size_t)cc * C + h * D.d, md + (size_t)(row + r) * C + h * D.d, D.d);
 #pragma unroll
-            for (int u = 0; u < 16; ++u) t += red[wave][e][(lane & 3) * 16 + u];
-            t += __shfl_xor(t, 1);
-            t += __shfl_xor(t, 2);
-            if ((lane & 3) == 0 && k < k1)
-                part[((size_t)(e % NB) * D.nk + k) * npart + part0 + ((int)blockIdx.x * 4 + wave) * (int)gridDim.y + (int)blockIdx.y] = t;
-        }
-        __syncthreads();
+                    for (int j = 0; j < NB; ++j) y[j] = __builtin_fmaf(dcoef[rh * NB + j], t, y[j]);
+                }
+                square(r, y, y16, s);
+            }
+        });
     }
 }
 
@@ -334,7 +466,7 @@ SensWorkspace sens_workspace(const taq_shape& s, int ntok, int nbits) {
     W.np = (int)align_up(s.N, 32);
     const size_t rows = (size_t)s.B * W.np;
     // rows per pass: P and the factors of a chunk stay within 128 MiB (whole 64-row GEMM tiles)
-    const size_t per_row = (H * C + C + (size_t)ntok * nbits * H * 2) * 4;
+    const size_t per_row = (H * C + 2 * C + (size_t)ntok * nbits * H * 2 + H * (1 + nbits)) * 4;
     size_t chunk = ((size_t)128 << 20) / per_row / 64 * 64;
     chunk = chunk < 64 ? 64 : chunk;
     W.chunk = (int)(chunk < rows ? chunk : rows);
@@ -346,6 +478,9 @@ SensWorkspace sens_workspace(const taq_shape& s, int ntok, int nbits) {
     W.o = take((size_t)W.chunk * C * 4);
     W.p = take((size_t)W.chunk * H * C * 4);
     W.ab = take((size_t)W.chunk * ntok * nbits * H * 2 * 4);
+    W.dom = take((size_t)W.chunk * H * 4);
+    W.dcoef = take((size_t)W.chunk * H * nbits * 4);
+    W.md = take((size_t)W.chunk * C * 4);
     W.npart = (int)(rows / rows_per_wave(s.H) * ((C + 63) / 64));
     W.part = take((size_t)W.npart * ntok * nbits * 8);
     W.total = off;
@@ -376,6 +511,9 @@ static hipError_t sens_run(const void* hidden, const void* context, const __half
     float* o = reinterpret_cast<float*>(ws + W.o);
     float* P = reinterpret_cast<float*>(ws + W.p);
     float* ab = reinterpret_cast<float*>(ws + W.ab);
+    int* dom = reinterpret_cast<int*>(ws + W.dom);
+    float* dcoef = reinterpret_cast<float*>(ws + W.dcoef);
+    float* md = reinterpret_cast<float*>(ws + W.md);
     double* part = reinterpret_cast<double*>(ws + W.part);
     const int BT = s.B * s.T, C = s.C, H = s.H, rows = s.B * W.np, NR = rows_per_wave(H);
     hipError_t e;
@@ -387,7 +525,7 @@ static hipError_t sens_run(const void* hidden, const void* context, const __half
     for (int r0 = 0; r0 < rows; r0 += W.chunk) {
         const int nr = rows - r0 < W.chunk ? rows - r0 : W.chunk;  // a multiple of 32
 #define TAQ_SENS_ATTN(MT) \
-    case MT: hipLaunchKernelGGL((sens_attn_kernel<NB, MT>), dim3(nr / 16, H), dim3(64), 0, st, q_f, kx, vx, D, r0, o, ab); break;
+    case MT: hipLaunchKernelGGL((sens_attn_kernel<NB, MT>), dim3(nr / 16, H), dim3(64), 0, st, q_f, kx, vx, D, r0, o, ab, dom, dcoef, md); break;
         switch ((s.T + 15) / 16) {
             TAQ_SENS_ATTN(1) TAQ_SENS_ATTN(2) TAQ_SENS_ATTN(3) TAQ_SENS_ATTN(4) TAQ_SENS_ATTN(5) TAQ_SENS_ATTN(6)
             default: return hipErrorInvalidValue;
@@ -404,7 +542,8 @@ static hipError_t sens_run(const void* hidden, const void* context, const __half
         const dim3 grid(gx, gy, (ntok + kper - 1) / kper);
         const int part0 = r0 / NR * gy;
 #define TAQ_SENS_MAIN(HT, R, EX)                                                                                              \
-    hipLaunchKernelGGL((sens_main_kernel<HT, R, NB, EX>), grid, dim3(256), 0, st, P, ab, va, bias, D, r0, kper, part, part0, W.npart)
+    hipLaunchKernelGGL((sens_main_kernel<HT, R, NB, EX>), grid, dim3(256), 0, st, P, ab, va, bias, dom, dcoef, md, Wo, D, r0, kper, part, \
+                       part0, W.npart)
         if (H == 8) TAQ_SENS_MAIN(8, 8, true);
         else if (H == 4) TAQ_SENS_MAIN(4, 8, true);
         else if (H < 8) TAQ_SENS_MAIN(8, 8, false);
