@@ -58,6 +58,9 @@ void attn_op_kernel(AttnOpArgs a) {
         for (int j = 0; j < TPH; ++j) qpk[nt][j] = a.q_op[(th * TPH + j) * 64 + lane];
         sq2[nt] = fmaxf(a.s_q[th * 16 + r16] * a.sig2, 1e-37f);
     }
+    // This wavefront's pieces of the image are in LDS before the barrier below: nothing else makes anybody wait for another
+    // wavefront's. (Here and not at the barrier: what is requested next need not be there then.)
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     // the first 16 protected K rows and V columns, operands as they are, whether there are any or not: their number is still
     // on its way (scores of rows past it are dropped, such V columns hold zeros)
     uint2 k16r[FS][2], v16r[TPH];

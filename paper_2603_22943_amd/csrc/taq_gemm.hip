@@ -272,7 +272,7 @@ struct GemmOpArgs {
 // registers. Rule: on every path the destinations pass through `arrived` below (a wait, then an empty asm that takes and gives
 // back each of them) before they are used and before the kernel goes on without them. Until then they are alive to the
 // compiler, so it places nothing else there; a read whose result nobody takes would leave it free to, with only timing to keep
-// the late data from overwriting what it placed. tests/test_inflight_registers.py checks the generated code of every kernel.
+// the late data from overwriting what it placed. tests/test_waits.py checks the generated code of every kernel.
 template <int OFF>
 __device__ __forceinline__ int32x4_t lds_read16(unsigned addr) {
     int32x4_t r;
