@@ -2,7 +2,7 @@
 // projection, Q~ or the probabilities of PersonalQ's Eq. (2) / Eq. (3) are to stay unquantized. These modes exist for
 // reference runs (Eq. (1): "all other parameters and activations in full precision"; the identity "every row protected,
 // nothing quantized = plain softmax attention"): float32 arithmetic, one simple kernel per stage.
-#include "taq_internal.h"
+#include "taq_device.h"
 
 namespace taq {
 
@@ -328,11 +328,6 @@ struct FpAttnArgs {
     float sigma;
 };
 
-__device__ __forceinline__ float fp_wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
 __device__ __forceinline__ float fp_wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -394,7 +389,7 @@ __global__ __launch_bounds__(256) void attn_fp_kernel(FpAttnArgs a) {
             }
             mx = fmaxf(mx, sc[r]);
         }
-        mx = fp_wave_max(mx);
+        mx = wave_allmax(mx);
         float Z = 0.f;
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
@@ -409,7 +404,7 @@ __global__ __launch_bounds__(256) void attn_fp_kernel(FpAttnArgs a) {
             A[r] = A[r] / Z;
             if (t < T && !prot[t]) amax = fmaxf(amax, A[r]);
         }
-        amax = fp_wave_max(amax);
+        amax = wave_allmax(amax);
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             const int t = lane + 64 * r;

@@ -75,7 +75,6 @@ __global__ __launch_bounds__(256) void kv_image_kernel(uint8_t* __restrict__ pac
 
 hipError_t launch_kv_image(uint8_t* packed, const taq_shape& s, hipStream_t st) {
     const KvLayout L = kv_layout(s);
-    if (L.image_bytes == 0) return hipSuccess;
     const KvImage I = kv_image(s);
     hipLaunchKernelGGL(kv_image_kernel, dim3(s.H, s.B, 8), dim3(256), 0, st, packed, L, I, s.T, s.C, s.H, s.bits_kv);
     return hipGetLastError();

@@ -100,7 +100,10 @@ struct FusedCfg {
     // As many as the registers take: two wavefronts per SIMD (256 registers each), three at ten heads (168), four DENSE (128);
     // fewer with three or four token tiles, whose accumulators take the rest. (DENSE 6 -> 12: 65.3 -> 63.4 us for 16 requests
     // of 4096 tokens; 24 and 8 -> 32 and 16 with two token tiles: 20.6 -> 19.9 us at eight heads of 80 and 8192 tokens,
-    // 21.6 -> 20.9 us at ten of 64; one more step up spills.)
+    // 21.6 -> 20.9 us at ten of 64; one more step up spills, and at ten heads, whose wavefronts have 168 registers, three token
+    // tiles do already: 14 registers in 60 bytes of scratch, 21 with row-major weights. 39 -> 29.9 us at 12288 tokens of ten heads
+    // all the same, for one round instead of two. Row-major weights with four tiles at d = 80 spill 3, with run-time T at ten
+    // heads 2.)
     static constexpr int RING_MAX = DENSE ? 12 : NH > 8 ? (NTT > 2 ? 8 : 16) : NTT == 4 ? 20 : NTT == 3 ? 28 : 32;
     static constexpr int RING = (!PREFETCH_W && NG == 1) ? (NF < RING_MAX ? NF : RING_MAX) : 0;
 };
@@ -1130,7 +1133,8 @@ static hipError_t launch_fused_grid(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>&
     if constexpr (F::RING > 0 && NT16 == 5 && NTT == 2) {
         // Workgroups that fill a compute unit run in rounds of one per unit; of 48 or 64 tokens each, instead of 32, they take
         // longer (at d = 80 26 and 33 us, against 20; at d = 64 28), but there may be fewer rounds: 12288 tokens
-        // 37.2 -> 26.3 us, 16384 tokens 38.2 -> 33.1 us.
+        // 37.2 -> 26.3 us, 16384 tokens 38.2 -> 33.1 us. One round of 32, 48 and 64 tokens with row-major weights: 21.9, 28.6 and
+        // 35.1 us at d = 80, 22.6 and 33.1 us at d = 64 (operand-ordered 20.2 and 31.3); the other grids are within 4 % of these.
         const long cu = device_cu_count(), mul = (long)dm.R * dm.B;
         auto rounds = [&](int tok) { return ((dm.N + tok - 1) / tok * mul + cu - 1) / cu; };
         auto fits = [&](int tok) { return bytes + (tok - TOK) * (F::TILE_RS + 4 + NH * 4) <= 160 * 1024; };

@@ -1,8 +1,9 @@
 // int8 x int8 -> int32 GEMM on the gfx950 matrix cores with fused dequantisation.
 //
-// Serves the W8A8 contractions of the TAQ block (to_q, to_out, and the K/V projections of
-// unprotected text tokens): acc[m][n] = sum_k A[m][k] * W[n][k], both operands K-contiguous,
-// result = float(acc) * (sa[m] * sw[n]) (+ bias[n]), in that order of float32 operations.
+// Serves the W8A8 contractions to_q and to_out of the TAQ block outside the single-kernel and head-group shapes:
+// acc[m][n] = sum_k A[m][k] * W[n][k], both operands K-contiguous, result = float(acc) * (sa[m] * sw[n]) (+ bias[n]), in that
+// order of float32 operations. gemm_op_kernel is the one of the quantized block; the two in front of it, on row-major operands
+// with float32 results, run where a stage beside them is left unquantized (bits_q or bits_prob = 16 with bits_proj = 8).
 #include "taq_device.h"
 
 namespace taq {
@@ -54,15 +55,15 @@ __global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__
 }
 
 // ------------------------------------------------------------------------------------------
-// LDS-staged kernel for K % 64 == 0 (every configured channel count): a workgroup of four wavefronts owns 128 rows of A
+// LDS-staged kernel for K % 64 == 0: a workgroup of four wavefronts owns 128 rows of A
 // (image tokens) x 80 rows of W (output channels: 320, 640 and 1280 are multiples of 80, and 2048 x 1280 outputs are then
 // exactly 256 workgroups, one per compute unit). Per K step of 64 the 13 operand blocks (16 rows x 64 codes = 1 KiB
 // each) go through LDS, row-major with the 16-byte segments of a row swizzled (below). Software pipeline, one barrier
 // per K step, three LDS stages, four register sets for loads in flight: while the ten MFMAs of step k run on one operand
 // register set, step k + 1 is read from LDS into the other, steps k + 2 and k + 3 move from registers to LDS and the
 // global loads of up to four later steps are outstanding.
-// (Direct global->LDS loads are not used here: the compiler waits for every outstanding one before any LDS read, which
-// would serialise the stages.)
+// (Direct global->LDS loads are not used here: the compiler waits for every outstanding one before any LDS read that it knows
+// of, which would serialise the stages.)
 // The product is formed transposed (W rows as the A operand, tokens as the B operand), so that a lane ends up with four
 // consecutive output channels of one token: 16-byte float32 / 8-byte fp16 stores.
 // ------------------------------------------------------------------------------------------

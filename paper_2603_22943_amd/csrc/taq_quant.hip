@@ -8,21 +8,6 @@
 
 namespace taq {
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
-
-// One code of the symmetric quantizer; amax > 0.
-__device__ __forceinline__ int symq_code(float x, float qmaxf, float amax) {
-    float t = x * qmaxf;
-    float q = t / amax;  // correctly rounded float32 division
-    float r = __builtin_rintf(q);  // half-to-even
-    r = fminf(fmaxf(r, -qmaxf), qmaxf);
-    return (int)r;
-}
-
 __device__ __forceinline__ void unpack_half8(const uint4& u, float f[8]) {
     const __half2* h = reinterpret_cast<const __half2*>(&u);
 #pragma unroll
@@ -31,11 +16,6 @@ __device__ __forceinline__ void unpack_half8(const uint4& u, float f[8]) {
         f[2 * i] = p.x;
         f[2 * i + 1] = p.y;
     }
-}
-
-__device__ __forceinline__ unsigned pack4_i8(int a, int b, int c, int d) {
-    return (unsigned)(a & 0xFF) | ((unsigned)(b & 0xFF) << 8) | ((unsigned)(c & 0xFF) << 16) |
-           ((unsigned)(d & 0xFF) << 24);
 }
 
 // ---------------------------------------------------------------- fp16 rows -> int8
@@ -283,7 +263,7 @@ __global__ __launch_bounds__(256) void rowquant_f32_kernel(const float* __restri
         float4 f = xr[v];
         amax = fmaxf(amax, fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w))));
     }
-    amax = wave_max(amax);
+    amax = wave_allmax(amax);
     const bool zero = amax == 0.f;
     const float sc = zero ? 1.f : amax / 127.f;
     const float safe = zero ? 1.f : amax;
@@ -291,8 +271,8 @@ __global__ __launch_bounds__(256) void rowquant_f32_kernel(const float* __restri
     unsigned* cr = reinterpret_cast<unsigned*>(code + (size_t)row * K);
     for (int v = lane; v < nv; v += 64) {
         float4 f = xr[v];
-        cr[v] = pack4_i8(symq_code(f.x, 127.f, safe), symq_code(f.y, 127.f, safe),
-                         symq_code(f.z, 127.f, safe), symq_code(f.w, 127.f, safe));
+        cr[v] = pack4(symq_code_f(f.x, 127.f, safe), symq_code_f(f.y, 127.f, safe),
+                         symq_code_f(f.z, 127.f, safe), symq_code_f(f.w, 127.f, safe));
     }
 }
 
@@ -335,8 +315,8 @@ __global__ __launch_bounds__(256) void headquant_f32_kernel(const float* __restr
         float4 f = xr[v];
         float amax = __uint_as_float(smax[wave][(v * 4) / d]);
         float safe = amax == 0.f ? 1.f : amax;
-        cr[v] = pack4_i8(symq_code(f.x, qmaxf, safe), symq_code(f.y, qmaxf, safe),
-                         symq_code(f.z, qmaxf, safe), symq_code(f.w, qmaxf, safe));
+        cr[v] = pack4(symq_code_f(f.x, qmaxf, safe), symq_code_f(f.y, qmaxf, safe),
+                         symq_code_f(f.z, qmaxf, safe), symq_code_f(f.w, qmaxf, safe));
     }
 }
 
@@ -387,15 +367,15 @@ __global__ __launch_bounds__(64) void kv_pack_kernel(const float* __restrict__ r
             float4 f = xr[v];
             float amax = __uint_as_float(smax[ch / d]);
             float safe = amax == 0.f ? 1.f : amax;
-            c0 = symq_code(f.x, qmaxf, safe);
-            c1 = symq_code(f.y, qmaxf, safe);
-            c2 = symq_code(f.z, qmaxf, safe);
-            c3 = symq_code(f.w, qmaxf, safe);
+            c0 = symq_code_f(f.x, qmaxf, safe);
+            c1 = symq_code_f(f.y, qmaxf, safe);
+            c2 = symq_code_f(f.z, qmaxf, safe);
+            c3 = symq_code_f(f.w, qmaxf, safe);
         }
         uint8_t* base = ch < C ? k_code : v_code;
         const int c = ch < C ? ch : ch - C;
         if (bits == 8) {
-            *reinterpret_cast<unsigned*>(base + (size_t)bt * C + c) = pack4_i8(c0, c1, c2, c3);
+            *reinterpret_cast<unsigned*>(base + (size_t)bt * C + c) = pack4(c0, c1, c2, c3);
         } else {
             unsigned short w = (unsigned short)((c0 & 0xF) | ((c1 & 0xF) << 4) | ((c2 & 0xF) << 8) |
                                                 ((c3 & 0xF) << 12));
@@ -495,7 +475,7 @@ hipError_t launch_kv_trigger_rows(const __half* context, const int8_t* w_code, c
 // 16-token column tile (at most six of the eight): the integer projection of the head's K (or V) channels (acc = x_code .
 // w_code over Cc, 16x16x64 int8 MFMA, channels as rows and tokens as columns), the float32 dequantisation float(acc) *
 // (s_x * s_w), the per-(head, token) symmetric quantizer of Eq. (2) (zero codes and scales on protected tokens), and the
-// plain code / scale sections of qkv_packed and, where the shape has one, this head's block of the operand-ordered image.
+// plain code / scale sections of qkv_packed and this head's block of the operand-ordered image.
 // Further workgroups of the launch, a few per 128 output channels and batch element: the protected rows (kvh_protected).
 // WLDS: the head's weight slice (16*TPH rows x Cc codes, Cc % 64 == 0) is fetched once per workgroup, straight into LDS
 // (one KiB per 16 rows x 64 codes, LDS address = base + lane * 16), and every wavefront reads its A operands from there;
@@ -535,7 +515,7 @@ typedef unsigned uint2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 template <int TPH>
 __device__ __forceinline__ void kvh_finish(const int32x4_t (&acc)[TPH], const KvhRow<TPH>& R, int st, int h, int b, int side, int d, int r16,
                                            int q, int T, int C, int bits, float qmaxf, uint8_t* codes, float* scales, uint8_t* img,
-                                           const KvImage& I, bool has_image, float* sc_l, unsigned* scmax) {
+                                           const KvImage& I, float* sc_l, unsigned* scmax) {
     const int t = 16 * st + r16;
     const bool tv = t < T, prot = !tv || R.slot >= 0;  // protected or past the last token: zero codes, zero scale
     float v[TPH][4];
@@ -573,7 +553,7 @@ __device__ __forceinline__ void kvh_finish(const int32x4_t (&acc)[TPH], const Kv
     }
     const int pos = vt_pos(t & ~3, I.nt16);  // place of this lane's group of four tokens in a V^T row
     const unsigned sel1 = (r16 & 1) ? 0x03070105u : 0x06020400u, sel2 = (r16 & 2) ? 0x03020706u : 0x05040100u;
-    if (has_image && side) {
+    if (side) {
         // Vt[channel][pos], stored with the sign bit flipped. The four lanes of a quad hold four channels of four
         // neighbouring tokens each: transposed (two exchanges), a lane stores four tokens of one channel.
 #pragma unroll
@@ -586,13 +566,13 @@ __device__ __forceinline__ void kvh_finish(const int32x4_t (&acc)[TPH], const Kv
     }
 #pragma unroll
     for (int j = 0; j < TPH; j += 4) {
-        if (has_image && !side && TPH % 4 == 0 && t < I.rows_k)  // Kp, heads of a multiple of 4 tiles: [t][tile/4][q][tile%4][4]
+        if (!side && TPH % 4 == 0 && t < I.rows_k)  // Kp, heads of a multiple of 4 tiles: [t][tile/4][q][tile%4][4]
             *reinterpret_cast<uint4*>(img + I.kp + kp_offset(TPH, t, j, q)) = make_uint4(pk[j], pk[j + 1], pk[j + 2], pk[j + 3]);
         unsigned w[4] = {pk[j], pk[j + 1], pk[j + 2], pk[j + 3]};
         quad_transpose(w);  // this lane now: tile j + q, its 16 channels in order
         const int tl = j + q;
         const bool full = 16 * tl + 16 <= d, half = !full && 16 * tl < d;  // (d % 8 == 0)
-        if (has_image && !side && TPH % 4 != 0 && t < I.rows_k && tl < TPH)  // Kp[t][tile][quarter][4]
+        if (!side && TPH % 4 != 0 && t < I.rows_k && tl < TPH)  // Kp[t][tile][quarter][4]
             *reinterpret_cast<uint4*>(img + I.kp + kp_offset(TPH, t, tl, 0)) = make_uint4(w[0], w[1], w[2], w[3]);
         if (tv) {
             if (bits == 8) {
@@ -730,7 +710,6 @@ __global__ __launch_bounds__(512) void kv_head_kernel(const int8_t* __restrict__
     }
     const int h = (int)blockIdx.x >> 1, side = (int)blockIdx.x & 1;  // side 0: K, 1: V
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, q = lane >> 4;
-    const bool has_image = L.image_bytes != 0;
     const int nsub = (T + 15) / 16;  // 16-token column tiles
     if (tid < 96) sc_l[tid] = 0.f;
     if (tid == 0) scmax = 0u;
@@ -806,7 +785,7 @@ __global__ __launch_bounds__(512) void kv_head_kernel(const int8_t* __restrict__
                     }
                 }
             }
-            kvh_finish<TPH>(acc, R, st, h, b, side, d, r16, q, T, C, bits, qmaxf, codes, scales, img, I, has_image, sc_l, &scmax);
+            kvh_finish<TPH>(acc, R, st, h, b, side, d, r16, q, T, C, bits, qmaxf, codes, scales, img, I, sc_l, &scmax);
         }
     } else {
     __syncthreads();
@@ -835,10 +814,9 @@ __global__ __launch_bounds__(512) void kv_head_kernel(const int8_t* __restrict__
 #pragma unroll
                 for (int j = 0; j < TPH; ++j) acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[u][j], xb[u], acc[j], 0, 0, 0);
         }
-        kvh_finish<TPH>(acc, R, st, h, b, side, d, r16, q, T, C, bits, qmaxf, codes, scales, img, I, has_image, sc_l, &scmax);
+        kvh_finish<TPH>(acc, R, st, h, b, side, d, r16, q, T, C, bits, qmaxf, codes, scales, img, I, sc_l, &scmax);
     }
     }
-    if (!has_image) return;
     __syncthreads();
     if (!side) {  // token scales of K and the 0 / -inf token bias
         if (tid < I.ntok) {
