@@ -34,6 +34,9 @@ def test_sweep_sizes(C, H, B, N, T_, bits, tokens):
     for b in bits:
         g = got[b].numpy()
         assert g.shape == (len(toks),)
-        # at 8 bits Delta is a few fp16 steps of few outputs here; the sum over the sweep averages over them
         print(f"[sweep C={C} H={H} N={N}] b={b}: max dev {np.max(np.abs(g / ref[b] - 1)):.2e}, of the sum {abs(g.sum() / ref[b].sum() - 1):.2e}", flush=True)
-        assert np.all(np.abs(g / ref[b] - 1) <= (0.5 if b == 8 else 0.1) / np.sqrt(max(1.0, B * N * C / 2048)) + 1e-2)
+        # Both sides round their outputs to fp16, and of n outputs about one in a hundred comes out one step apart (float32 against
+        # float64 arithmetic in front of the rounding). With a change of s steps in the mean such a one is off by up to 2 / s of its
+        # square: sqrt(0.01 n) * 2 / s of a sum of n, and 5 times that for the largest of a sweep; s is at least 0.45 at 8 bits
+        # and, with steps of the grid 18 times as wide, 8 at 4 bits. The float32 factors themselves are good to 1e-3 of a square.
+        assert np.all(np.abs(g / ref[b] - 1) <= (2.2 if b == 8 else 0.13) / np.sqrt(B * N * C) + 2e-3)
