@@ -53,13 +53,18 @@ def parse():
     p.add_argument("--profile-only", action="store_true",
                    help="run only warmup + timed steps (for rocprofv3), skip the side measurements")
     p.add_argument("--profile-config3", action="store_true",
-                   help="run only the 16-layer UNet step of configs[2] (for rocprofv3)")
+                   help="run only the 16 cross-attention layers of one SD1.5 UNet step (for rocprofv3)")
     p.add_argument("--traffic-probe", action="store_true",
                    help="for `rocprofv3 --pmc FETCH_SIZE|WRITE_SIZE`: a device copy of known size, then eager steps")
     p.add_argument("--summarize-sq", nargs="+", metavar="CSV",
                    help="rocprofv3 --pmc SQ_* counter CSVs of --profile-only runs -> profiles/fused_block_kernel_cfg2_pmc.json")
     p.add_argument("--profile-gemm", action="store_true",
                    help="run only the int8 GEMM of the kernel-per-stage path (to_q at M=2048 C=1280 and M=8192 C=320; for rocprofv3)")
+    p.add_argument("--profile-config4", action="store_true",
+                   help="run only the two SDXL layers (2 x 4096 x 640 on the single-kernel path, 2 x 1024 x 1280 on the "
+                        "kernel-per-stage path; for rocprofv3)")
+    p.add_argument("--profile-sweep", action="store_true",
+                   help="run only the token-sensitivity sweep of a 2 x 256 x 1280 layer (for rocprofv3)")
     p.add_argument("--summarize-trace", nargs="+", metavar=("STATS_CSV", "OUT_TXT"),
                    help="STATS_CSV OUT_TXT COMMAND [NOTE...]: the taq:: rows of a rocprofv3 --kernel-trace --stats "
                         "kernel_stats.csv -> profiles/OUT_TXT, with the command and notes as its header")
@@ -226,7 +231,7 @@ def attn_call(d, debug=None):
 
 
 def profile_config3(dev, use_graph, reps):
-    """For rocprofv3: the 16 cross-attention layers of one UNet step (configs[2]) replayed `reps` times from one HIP
+    """For rocprofv3: the 16 cross-attention layers of one SD1.5 UNet step replayed `reps` times from one HIP
     graph, after one taq_quantize_kv per layer. Prints the measured time per 16-layer step."""
     layers = [prep_layer(L, dev) for L in synth.config3()]
     for d in layers:  # once more, so that the trace holds a second sample of the per-prompt kernels
@@ -234,9 +239,38 @@ def profile_config3(dev, use_graph, reps):
     r = Runner([attn_call(d) for d in layers], use_graph=use_graph)
     r.run(2 * len(layers))
     us = r.time_events(reps * len(layers)) * len(layers) * 1e6
-    print(json.dumps({"workload": "configs[2]: 16 cross-attention layers of one SD1.5 UNet step, batch 2, int4 K/V",
+    print(json.dumps({"workload": "16 cross-attention layers of one SD1.5 UNet step, batch 2, int4 K/V",
                       "us_per_16_layer_step": round(us, 2), "replays": reps,
                       "launch": "hip-graph" if r.graph is not None else "eager"}), flush=True)
+
+
+def profile_config4(dev, use_graph, reps):
+    """For rocprofv3: the two SDXL layers, each replayed `reps` times by itself. Prints the measured time per call."""
+    res = {}
+    for L in synth.config4():
+        d = prep_layer(L, dev)
+        r = Runner([attn_call(d)] * 4, use_graph=use_graph)
+        r.prewarm(20.0)
+        res["%dx%dx%d" % (L.B, L.N, L.C)] = round(r.time_events(4 * reps) * 1e6, 2)
+    print(json.dumps({"workload": "SDXL layers, int4 K/V", "us_per_call": res, "launch": "hip-graph" if use_graph else "eager"}), flush=True)
+
+
+def profile_sweep(dev, reps):
+    """For rocprofv3: taq_token_sensitivity, all 77 tokens and both widths, of a 2 x 256 x 1280 layer (8 heads)."""
+    L = synth.make_layer("sweep", seed=3, B=2, N=256, C=1280, H=8, n_random_triggers=2, trigger_scale=3.0, bias=True)
+    to = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(dev)
+    s = T.make_shape(B=L.B, N=L.N, C=L.C, H=L.H, T=L.T, Cc=L.Cc, bits_q=16, bits_prob=16, bits_proj=16)
+    scales = torch.cat([torch.zeros(2 * L.C, dtype=torch.float32, device=dev), to(L.bias_o)]).contiguous()
+    args = [to(x) for x in (L.hidden, L.context, L.Wk, L.Wv, L.Wq, L.Wo)]
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for k in range(2):
+        e0.record()
+        for _ in range(reps):
+            T.taq_token_sensitivity(*args, scales, list(range(L.T)), [8, 4], s)
+        e1.record()
+        torch.cuda.synchronize()
+    print(json.dumps({"workload": "token-sensitivity sweep, 2 x 256 x 1280, 77 tokens, 8 and 4 bits",
+                      "us_per_sweep": round(e0.elapsed_time(e1) * 1e3 / reps, 2)}), flush=True)
 
 
 def other_configs(dev, use_graph):
@@ -288,25 +322,25 @@ def other_configs(dev, use_graph):
 def gemm_stage_mfma(dev, use_graph, only=("to_q", "to_out")):
     """The int8 GEMM of the kernel-per-stage path alone (stage masks TO_Q / TO_OUT of taq_cross_attn): MFMA utilisation
     at (M = 2048, C = 1280) and (M = 8192, C = 320), cache-resident (one buffer set, re-used by every call), next to the
-    ceiling that this GEMM's own bytes leave: A [M, C] + W [C, C] int8 in, [M, C] float32 (to_q) or fp16 (to_out) out,
-    at the HBM peak; the time of a launch (a few microseconds at these sizes) is not in the ceiling."""
+    ceiling that this GEMM's own bytes leave: A [M, C] + W [C, C] int8 in, [M, C] Q~ codes with a scale per head (to_q)
+    or fp16 (to_out) out, at the HBM peak; the time of a launch (a few microseconds at these sizes) is not in the ceiling."""
     res = {}
     for key, L in (("M2048_C1280", synth.config4()[1]), ("M8192_C320", synth.config2())):
         d = prep_layer(L, dev)
         s = d["s"]
-        allbits = (T.TAQ_STAGE_HIDDEN_QUANT | T.TAQ_STAGE_TO_Q | T.TAQ_STAGE_Q_QUANT | T.TAQ_STAGE_ATTN_CORE
-                   | T.TAQ_STAGE_O_QUANT | T.TAQ_STAGE_TO_OUT)
+        allbits = (T.TAQ_STAGE_HIDDEN_QUANT | T.TAQ_STAGE_TO_Q | T.TAQ_STAGE_ATTN_CORE | T.TAQ_STAGE_O_QUANT
+                   | T.TAQ_STAGE_TO_OUT)
         attn_call(d, T.make_debug(s, dev, stage_mask=allbits, taps=False)[0])()  # valid stage buffers in the workspace
         M = L.B * L.N
         ops = 2.0 * M * L.C * L.C
-        for name, bit, out_bytes in (("to_q", T.TAQ_STAGE_TO_Q, 4), ("to_out", T.TAQ_STAGE_TO_OUT, 2)):
+        for name, bit, out_bytes in (("to_q", T.TAQ_STAGE_TO_Q, M * (L.C + 4 * L.H)), ("to_out", T.TAQ_STAGE_TO_OUT, M * L.C * 2)):
             if name not in only:
                 continue
             dbg = T.make_debug(s, dev, stage_mask=bit, taps=False)[0]
             r = Runner([attn_call(d, dbg)] * 8, use_graph=use_graph)
             r.prewarm(20.0)
             t = r.time_events(400)
-            nbytes = M * L.C + L.C * L.C + M * L.C * out_bytes
+            nbytes = M * L.C + L.C * L.C + out_bytes
             t_floor = max(ops / (INT8_PEAK_TOPS * 1e12), nbytes / (HBM_PEAK_GBS * 1e9))
             res[key + "_" + name] = {"us": round(t * 1e6, 2), "int8_GOP": ops / 1e9, "achieved_TOPS": ops / t / 1e12,
                                      "frac_of_int8_peak": ops / t / 1e12 / INT8_PEAK_TOPS,
@@ -324,10 +358,11 @@ def summarize_sq(csvs):
     """Mean per launch of every SQ_* counter over the fused kernel's dispatches (rocprofv3 --pmc, one CSV per pass);
     writes profiles/fused_block_kernel_cfg2_pmc.json, which the ALU-roofline figure of the bench line reads."""
     import csv
-    acc = {}
+    acc, name = {}, ""
     for path in csvs:
         for r in csv.DictReader(open(path)):
             if "fused_block_kernel" in r["Kernel_Name"]:
+                name = r["Kernel_Name"].split("(")[0].replace("void ", "")
                 acc.setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
     if not acc:
         raise SystemExit("no fused_block_kernel dispatches in " + " ".join(csvs))
@@ -337,8 +372,8 @@ def summarize_sq(csvs):
     json.dump(out, open(path, "w"), indent=1)
     waves = out["wavefronts_per_launch"]
     with open(path[:-5] + ".txt", "w") as f:
-        f.write("# rocprofv3 hardware counters of taq::fused_block_kernel<40, 8, 2, 1, 0, 32, false, 5, false> at configs[1]\n"
-                "# (B=2 N=4096 C=320 H=8 T=77). Commands (run from /tmp on the MI355X box, one pass per counter set):\n"
+        f.write(f"# rocprofv3 hardware counters of {name}\n"
+                "# at B=2 N=4096 C=320 H=8 T=77. Commands (run from /tmp, one pass per counter set):\n"
                 "#   rocprofv3 --pmc <at most 8 SQ_ counters> --output-format csv -d outK -o p -- python3 bench.py --profile-only --no-graph --steps 64 --warmup 16\n"
                 "#   python3 bench.py --summarize-sq out1/p_counter_collection.csv out2/p_counter_collection.csv ...   (writes this file and the .json)\n"
                 "# mean over the dispatches of the kernel (first 4 skipped); per wavefront = mean / wavefronts per launch\n"
@@ -355,7 +390,7 @@ def summarize_trace(stats_csv, out_txt, command, notes):
     import csv
     rows = [r for r in csv.DictReader(open(stats_csv)) if "taq::" in r["Name"]]
     with open(os.path.join(ROOT, "profiles", out_txt), "w") as f:
-        f.write("# rocprofv3 --kernel-trace --stats, this library's kernels. Command (run from /tmp on the MI355X box):\n")
+        f.write("# rocprofv3 --kernel-trace --stats, this library's kernels. Command (run from /tmp):\n")
         f.write("#   " + command + "\n")
         f.write("#   python3 bench.py --summarize-trace <the run's kernel_stats.csv> " + out_txt + " '<command>' <notes>\n")
         for n in notes:
@@ -372,9 +407,9 @@ def summarize_sq_by_kernel(csvs, keep=()):
     """Per kernel (template arguments kept, parameter list dropped) and grid size: the mean over its dispatches of every
     counter found in the CSVs, per launch and per wavefront. Text on stdout, for a summary file under profiles/."""
     import csv
-    print("# rocprofv3 hardware counters per kernel of this library. Commands (run from /tmp on the MI355X box, one pass per\n"
-          "# counter set, at most 8 SQ_ counters each; <workload> is one of bench.py's --profile-config3 / --profile-gemm /\n"
-          "# --profile-only, launched eagerly):\n"
+    print("# rocprofv3 hardware counters per kernel of this library. Commands (run from /tmp, one pass per\n"
+          "# counter set, at most 8 SQ_ counters each; <workload> is one of bench.py's --profile-config3 / --profile-config4 /\n"
+          "# --profile-gemm / --profile-sweep / --profile-only, launched eagerly):\n"
           "#   rocprofv3 --pmc <counters> --output-format csv -d outK -o p -- python3 bench.py <workload> --no-graph\n"
           "#   python3 bench.py --summarize-sq-by-kernel out1/p_counter_collection.csv out2/p_counter_collection.csv ... [--kernel-filter a,b]\n"
           "# mean over all dispatches of the kernel at that grid; SQ_*_CYCLES, SQ_WAIT* and SQ_ACTIVE* tick once per 4 clocks")
@@ -422,8 +457,8 @@ def summarize_pmc(fetch_csv, write_csv):
     path = os.path.join(ROOT, "profiles", "fused_block_kernel_cfg2_hbm_traffic.json")
     json.dump(out, open(path, "w"), indent=1)
     with open(path[:-5] + ".md", "w") as f:
-        f.write("# HBM traffic of taq::fused_block_kernel<40, 8, 2, ...> at configs[1] (B=2 N=4096 C=320 H=8 T=77)\n\n"
-                "Commands (run from /tmp on the MI355X box; each counter in a pass of its own):\n\n"
+        f.write("# HBM traffic of taq::fused_block_kernel<40, 8, 2, ...> at B=2 N=4096 C=320 H=8 T=77\n\n"
+                "Commands (run from /tmp; each counter in a pass of its own):\n\n"
                 "    rocprofv3 --pmc FETCH_SIZE --output-format csv -d fetch -o p -- python3 bench.py --traffic-probe --steps 64\n"
                 "    rocprofv3 --pmc WRITE_SIZE --output-format csv -d write -o p -- python3 bench.py --traffic-probe --steps 64\n"
                 "    python3 bench.py --summarize-pmc fetch/p_counter_collection.csv write/p_counter_collection.csv\n\n"
@@ -466,6 +501,12 @@ def main():
     torch.cuda.set_device(0)
     if a.profile_config3:
         profile_config3(dev, not a.no_graph, reps=50)
+        return
+    if a.profile_config4:
+        profile_config4(dev, not a.no_graph, reps=50)
+        return
+    if a.profile_sweep:
+        profile_sweep(dev, reps=30)
         return
     if a.profile_gemm:
         print(json.dumps({"gemm_i8_stage_mfma": gemm_stage_mfma(dev, not a.no_graph, only=("to_q",))}), flush=True)
@@ -520,7 +561,7 @@ def main():
         "metric": "TAQ cross-attn query-tokens/sec at 4096q SD1.5 shape", "value": value,
         "unit": "query-tokens/s", "n_gpus": 1, "steps": a.steps, "warmup": a.warmup, "ms_per_step": ms_per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "int8", "data": "synthetic",
-        "config": {"workload": "configs[1]: SD1.5 64x64 cross-attn, B=2 N=4096 C=320 H=8 T=77 Cc=768, "
+        "config": {"workload": "SD1.5 64x64 cross-attn, B=2 N=4096 C=320 H=8 T=77 Cc=768, "
                                "1 fp16 trigger row, int8 K/V, 8-bit probs, W8A8 to_q/to_out",
                    "launch": "hip-graph" if runner.graph is not None else "eager",
                    "ring_buffer_sets": len(ring), "ring_MB": round(ring_mb, 1),
@@ -596,8 +637,8 @@ def main():
                                     "ceiling_frac_from_hbm_roofline": min(1.0, int8_ops / alg_bytes * HBM_PEAK_GBS * 1e9 / (INT8_PEAK_TOPS * 1e12)),
                                     "note": "ceiling = the int8 rate at which this shape's algorithmic bytes would saturate HBM"}
     # ---- the same path as one kernel per stage (general path; other shapes run this way), each timed alone
-    stages = [("hidden_quant", T.TAQ_STAGE_HIDDEN_QUANT), ("to_q", T.TAQ_STAGE_TO_Q), ("q_quant", T.TAQ_STAGE_Q_QUANT),
-              ("attn_core", T.TAQ_STAGE_ATTN_CORE), ("o_quant", T.TAQ_STAGE_O_QUANT), ("to_out", T.TAQ_STAGE_TO_OUT)]
+    stages = [("hidden_quant", T.TAQ_STAGE_HIDDEN_QUANT), ("to_q", T.TAQ_STAGE_TO_Q), ("attn_core", T.TAQ_STAGE_ATTN_CORE),
+              ("o_quant", T.TAQ_STAGE_O_QUANT), ("to_out", T.TAQ_STAGE_TO_OUT)]  # (to_q quantizes Q~ itself)
     per_stage = {}
     sring = [dict(r, ws=torch.empty(ws_bytes, dtype=torch.uint8, device=dev)) for r in ring[:8]]  # stages do use the workspace
     for r in sring:  # fill every workspace once with a whole pass, so that each stage alone reads valid data
@@ -610,7 +651,7 @@ def main():
         rr = Runner([step_call(r, d) for r, d in zip(sring, dbgs)], use_graph=not a.no_graph)
         rr.run(len(sring))
         per_stage[name] = rr.time_events(256)
-    core_bytes = tokens * (5 * C + 4 * H)  # int8 Q~ + its scales in, float32 A^ V~ out (what the stage kernel moves)
+    core_bytes = tokens * (5 * C + 8 * H)  # int8 Q~ + its scales in, float32 A^ V~ + its maxima out (what the stage kernel moves)
     gemm_ops = 2.0 * tokens * C * C
     result["unfused_stages"] = {
         "stage_us": {k: round(v * 1e6, 3) for k, v in per_stage.items()},

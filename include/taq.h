@@ -103,8 +103,8 @@ typedef struct taq_debug {
 } taq_debug;
 
 #define TAQ_STAGE_HIDDEN_QUANT 1u  /* per-token int8 codes of hidden            */
-#define TAQ_STAGE_TO_Q         2u  /* to_q integer GEMM + dequantisation         */
-#define TAQ_STAGE_Q_QUANT      4u  /* Q~ = Q_a(Q), Eq. (2) third line            */
+#define TAQ_STAGE_TO_Q         2u  /* to_q integer GEMM, dequantisation and Q~ = Q_a(Q), Eq. (2) third line */
+#define TAQ_STAGE_Q_QUANT      4u  /* part of TAQ_STAGE_TO_Q; accepted, launches nothing */
 #define TAQ_STAGE_ATTN_CORE    8u  /* scores, softmax, Eq. (3), A^ V~            */
 #define TAQ_STAGE_O_QUANT      16u /* per-token int8 codes of the attention out  */
 #define TAQ_STAGE_TO_OUT       32u /* to_out integer GEMM + bias, fp16 store     */

@@ -69,7 +69,7 @@ def test_config5_multi_checkpoint_batch():
 
 
 def test_unet_step_of_16_layers_from_one_graph_matches_the_oracle():
-    """The 16 cross-attention layers of one UNet step (configs[2]) captured into ONE HIP graph, as bench.py replays
+    """The 16 cross-attention layers of one UNet step captured into ONE HIP graph, as bench.py replays
     them: after each of several replays (eager work of the library in between) every layer's output must be bit-identical
     to its eager output, and that output must meet the oracle's within the block tolerance."""
     layers = synth.config3()
