@@ -351,7 +351,7 @@ def gemm_stage_mfma(dev, use_graph, only=("to_q", "to_out")):
 
 COPY_BYTES = 256 << 20  # the known-size copy of the traffic probe reads and writes this many bytes
 ALU_PEAK_TLANEOPS = 256 * 4 * 16 * 2.4e9 / 1e12  # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3e12 lane-ops/s
-#   (the chip's 157.3 TFLOP/s fp32 vector figure is this x 2 for an FMA x 2 for packed fp32, which this build may not use)
+#   (the chip's 157.3 TFLOP/s fp32 vector figure is this x 2 for an FMA x 2 for packed fp32, which this library does not use)
 
 
 def summarize_sq(csvs):
@@ -492,7 +492,7 @@ def main():
         summarize_pmc(*a.summarize_pmc)
         return
     if a.gpus != 1:
-        print("bench.py: this build runs on exactly one GPU (no collectives, no sharding); use --gpus 1",
+        print("bench.py: this library runs on exactly one GPU (no collectives, no sharding); use --gpus 1",
               file=sys.stderr)
         sys.exit(2)
     assert torch.cuda.is_available(), "bench.py needs a GPU"

@@ -46,7 +46,7 @@ extern "C" {
 typedef enum taq_status {
     TAQ_OK = 0,
     TAQ_ERR_INVALID_ARG = -1,      /* NULL pointer, non-positive size, inconsistent arguments */
-    TAQ_ERR_UNSUPPORTED_BITS = -2, /* a bit width outside what this build implements        */
+    TAQ_ERR_UNSUPPORTED_BITS = -2, /* a bit width outside what the library implements      */
     TAQ_ERR_BAD_SHAPE = -3,        /* shape outside the supported set listed above          */
     TAQ_ERR_MISALIGNED = -4,       /* a pointer is not 16-byte aligned                      */
     TAQ_ERR_HIP = -5,              /* the HIP runtime reported an error at launch           */
@@ -134,7 +134,7 @@ int taq_workspace_bytes(const taq_shape* shape, size_t* bytes);
 int taq_quantize_weight(const void* W_f16, int rows, int cols, int8_t* codes, float* scales,
                         void* hip_stream);
 
-/* (Helpers of this build, not operations of the paper: the paper prescribes no memory layout.)
+/* (Helpers of the library, not operations of the paper: the paper prescribes no memory layout.)
  * Optional re-layout of a [C, C] weight-code matrix for taq_cross_attn (shape->w_layout = 1): `out` receives
  * the row-major codes followed by a copy ordered the way the matrix cores read them for this shape's head
  * dimension. The method is unchanged (the paper does not prescribe a memory layout); only load efficiency is.

@@ -18,7 +18,7 @@ What it follows (PersonalQ, Section III-B "Trigger-Aware Quantization"):
 
 The paper gives the structure only. Every numeric detail below that it leaves
 open (quantizer formula, scale granularity, which projections are W8A8) is a
-reading chosen for this build; each is marked "reading:" where it is taken.
+reading chosen here; each is marked "reading:" where it is taken.
 
 Precision: every contraction is float64. The quantizers are *defined* as short
 sequences of IEEE float32 operations (so that a GPU can reproduce their integer
@@ -148,7 +148,7 @@ def pack_int4(codes):
 def quantize_weight(W):
     """Per-output-channel symmetric int8 codes of a weight matrix [out, in]
     (reading: round-to-nearest 8-bit weights; the paper uses 8-bit weights in
-    every setting of Table 1 but calibrates them with data this build lacks)."""
+    every setting of Table 1 but calibrates them with data that is not available)."""
     code, scale = symq(np.asarray(W, dtype=np.float16).astype(f32), 8, axis=1)
     return code.astype(np.int8), scale
 
