@@ -168,11 +168,12 @@ void to_out_tail_kernel(FusedReq rq, FusedDims dm) {
         const bool tap = blockIdx.z == 0 && nq < N;
         if (part == 0) s_o[tk] = sc;
         if (tap && dm.dbg.s_o && part == 0) dm.dbg.s_o[row] = sc;
+        unsigned pk[CH];
+        quant4_group<CH>(pk, [&](int i) { return xv[i]; }, [&](int) { return QuantRow{1.f, cq, safe}; });
 #pragma unroll
         for (int it = 0; it < CH; ++it) {
-            const unsigned pk = quant4_i8(xv[it].x, xv[it].y, xv[it].z, xv[it].w, cq, safe);
-            *reinterpret_cast<unsigned*>(tileq + tk * TILE_RS + (it * 32 + part) * 4) = pk;
-            if (tap && dm.dbg.o_code) *reinterpret_cast<unsigned*>(dm.dbg.o_code + row * C + (it * 32 + part) * 4) = pk;
+            *reinterpret_cast<unsigned*>(tileq + tk * TILE_RS + (it * 32 + part) * 4) = pk[it];
+            if (tap && dm.dbg.o_code) *reinterpret_cast<unsigned*>(dm.dbg.o_code + row * C + (it * 32 + part) * 4) = pk[it];
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

@@ -90,6 +90,9 @@ struct FusedCfg {
     // bytes of one head's image block at T = 96, in 1 KiB pieces (one direct-to-LDS load each)
     static constexpr int IMG_HEAD_MAX = 96 * TPH * 16 + D * 96 + 3 * 96 * 4 + 32;
     static constexpr int IMGC = (IMG_HEAD_MAX + 1023) / 1024;
+    // head_bytes of kv_image() at nt tiles of 16 text tokens
+    static constexpr int up16(int n) { return (n + 15) / 16 * 16; }
+    static constexpr int head_bytes(int nt) { return (16 * nt * TPH * 16 + up16(D * 16 * nt) + 3 * 16 * nt * 4 + 2 * 16 + 255) / 256 * 256; }
     // DENSE: the instantiation meant to run two workgroups per compute unit (layers with more token tiles than compute
     // units): at most 128 registers per lane, so the weights pass through a short ring instead of sitting in registers.
     static constexpr bool PREFETCH_W = TPH * KC <= 16 && NTT == 2 && NG == 1 && !DENSE;  // a head's whole weight slice in registers
@@ -131,6 +134,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     constexpr bool LEAN = DENSE || (NTT > 2 && NH <= 8);  // no register to spare
     constexpr bool LOGP = PG == TAQ_PROB_LOG2, ROWMAX = PG == TAQ_PROB_ROWMAX;  // grid of the probabilities, Eq. (3)
     constexpr int MT16 = NT16 ? NT16 : 6;  // score tiles the code is unrolled for
+    constexpr int QG = F::RING > 0 ? 1 : TPH;  // dwords of codes per test for ties (with a ring of weights, whole groups are no faster, and 4 % slower at d = 80 row-major)
     constexpr bool TAPS = NT16 == 0;       // taps of intermediate codes and scales (tests, profiling)
     extern __shared__ __align__(16) unsigned char smem[];
 
@@ -310,6 +314,20 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         const float safe0 = zero0 ? 1.f : amax;
         const float cq0 = quant_mult(127.f, safe0);
         if (HOLDS && part0 == 0) s_h[tok0] = sc0;
+        const QuantRow hrow = {1.f, cq0, safe0};
+        auto hidden4 = [&](int it, int u) {
+            const half2_t x01 = *reinterpret_cast<const half2_t*>(&xin[it][u].x), x23 = *reinterpret_cast<const half2_t*>(&xin[it][u].y);
+            return make_float4((float)x01[0], (float)x01[1], (float)x23[0], (float)x23[1]);
+        };
+        auto put_hidden = [&](int it, const unsigned (&pk)[XW]) {
+            int8_t* dst = tileq + tok0 * F::TILE_RS + it * 64 + part0 * (4 * XW);
+            if constexpr (XW == 1) *reinterpret_cast<unsigned*>(dst) = pk[0];
+            else *reinterpret_cast<uint2*>(dst) = make_uint2(pk[0], pk[XW - 1]);
+            if (TAPS && dm.dbg.h_code && nq0 < N)
+    #pragma unroll
+                for (int u = 0; u < XW; ++u) *reinterpret_cast<unsigned*>(dm.dbg.h_code + row0 * C + it * 64 + part0 * (4 * XW) + 4 * u) = pk[u];
+        };
+        unsigned doubt = 0u;
     #pragma unroll
         for (int it = 0; it < KC; ++it) {
             if (F::PREFETCH_W) {
@@ -324,17 +342,34 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
                 unsigned pk[XW];
     #pragma unroll
                 for (int u = 0; u < XW; ++u) {
-                    const half2_t x01 = *reinterpret_cast<const half2_t*>(&xin[it][u].x), x23 = *reinterpret_cast<const half2_t*>(&xin[it][u].y);
-                    pk[u] = quant4_i8((float)x01[0], (float)x01[1], (float)x23[0], (float)x23[1], cq0, safe0);
+                    const float4 x = hidden4(it, u);
+                    pk[u] = quant4_fast(x.x, x.y, x.z, x.w, hrow, doubt);
                 }
-                int8_t* dst = tileq + tok0 * F::TILE_RS + it * 64 + part0 * (4 * XW);
-                if constexpr (XW == 1) *reinterpret_cast<unsigned*>(dst) = pk[0];
-                else *reinterpret_cast<uint2*>(dst) = make_uint2(pk[0], pk[XW - 1]);
-                if (TAPS && dm.dbg.h_code && nq0 < N)
+                if (RING > 0) {  // (step by step, as with QG below)
+                    if (TAQ_DOUBT(doubt))
     #pragma unroll
-                    for (int u = 0; u < XW; ++u) *reinterpret_cast<unsigned*>(dm.dbg.h_code + row0 * C + it * 64 + part0 * (4 * XW) + 4 * u) = pk[u];
+                        for (int u = 0; u < XW; ++u) {
+                            const float4 x = hidden4(it, u);
+                            pk[u] = quant4_settle(pk[u], x.x, x.y, x.z, x.w, hrow, 127.f);
+                        }
+                    doubt = 0u;
+                }
+                put_hidden(it, pk);
             }
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if (RING == 0 && TAQ_DOUBT(doubt)) {  // all of this thread's pieces again
+    #pragma unroll
+            for (int it = 0; it < KC; ++it) {
+                unsigned pk[XW];
+    #pragma unroll
+                for (int u = 0; u < XW; ++u) {
+                    const float4 x = hidden4(it, u);
+                    unsigned again = 0u;
+                    pk[u] = quant4_settle(quant4_fast(x.x, x.y, x.z, x.w, hrow, again), x.x, x.y, x.z, x.w, hrow, 127.f);
+                }
+                put_hidden(it, pk);
+            }
         }
         if (TAPS && HOLDS && dm.dbg.s_h && part0 == 0 && nq0 < N) dm.dbg.s_h[row0] = sc0;
         // ---- weight scales into LDS
@@ -390,6 +425,16 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         const int32x4_t* gimg = reinterpret_cast<const int32x4_t*>(packed + dm.L.image + (size_t)b * dm.L.image_bytes +
                                                                    (size_t)by * NH * dm.I.head_bytes);
         constexpr int NLD = TJ * KW + IMV, LPI = (NLD + CH - 1) / CH;  // loads to spread, loads per quantizer step
+        const QuantRow hrow = {1.f, cq0, safe0};
+        auto hidden4 = [&](int it, int u) {
+            const half2_t* x = reinterpret_cast<const half2_t*>(&xin4[it]) + 2 * u;
+            return make_float4((float)x[0][0], (float)x[0][1], (float)x[1][0], (float)x[1][1]);
+        };
+        auto put_hidden = [&](int it, uint2 pk) {
+            *reinterpret_cast<uint2*>(tileq + tok0 * F::TILE_RS + (it * TPT + part0) * 8) = pk;
+            if (TAPS && tap && dm.dbg.h_code) *reinterpret_cast<uint2*>(dm.dbg.h_code + row0 * C + (it * TPT + part0) * 8) = pk;
+        };
+        unsigned doubt = 0u;
 #pragma unroll
         for (int it = 0; it < CH; ++it) {
 #pragma unroll
@@ -406,15 +451,23 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
                     imv[f - TJ * KW] = gimg[i < img16 ? i : img16 - 1];
                 }
             }
-            const __half2* hh2 = reinterpret_cast<const __half2*>(&xin4[it]);
-            const float2 p0 = __half22float2(hh2[0]), p1 = __half22float2(hh2[1]);
-            const float2 p2 = __half22float2(hh2[2]), p3 = __half22float2(hh2[3]);
             uint2 pk;
-            pk.x = quant4_i8(p0.x, p0.y, p1.x, p1.y, cq0, safe0);
-            pk.y = quant4_i8(p2.x, p2.y, p3.x, p3.y, cq0, safe0);
-            *reinterpret_cast<uint2*>(tileq + tok0 * F::TILE_RS + (it * TPT + part0) * 8) = pk;
-            if (TAPS && tap && dm.dbg.h_code) *reinterpret_cast<uint2*>(dm.dbg.h_code + row0 * C + (it * TPT + part0) * 8) = pk;
+            {
+                const float4 x = hidden4(it, 0), y = hidden4(it, 1);
+                pk.x = quant4_fast(x.x, x.y, x.z, x.w, hrow, doubt);
+                pk.y = quant4_fast(y.x, y.y, y.z, y.w, hrow, doubt);
+            }
+            put_hidden(it, pk);
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if (TAQ_DOUBT(doubt)) {
+#pragma unroll
+            for (int it = 0; it < CH; ++it) {
+                const float4 x = hidden4(it, 0), y = hidden4(it, 1);
+                unsigned again = 0u;
+                put_hidden(it, make_uint2(quant4_settle(quant4_fast(x.x, x.y, x.z, x.w, hrow, again), x.x, x.y, x.z, x.w, hrow, 127.f),
+                                          quant4_settle(quant4_fast(y.x, y.y, y.z, y.w, hrow, again), y.x, y.y, y.z, y.w, hrow, 127.f)));
+            }
         }
     }
     __syncthreads();
@@ -557,7 +610,8 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     // wavefront reads it, so only this wavefront waits for it. The last piece may be fetched more than once.
     if constexpr (NG == 1) {
         const unsigned char* gsrc = packed + dm.L.image + (size_t)b * dm.L.image_bytes + (size_t)h * dm.I.head_bytes;
-        const int last = (int)dm.I.head_bytes - 1024;  // the block is a multiple of 256 bytes: the last piece overlaps
+        // the block is a multiple of 256 bytes: the last piece overlaps (a constant where registers are plentiful and the number of score tiles is fixed: no branch per piece)
+        const int last = (NT16 && F::PREFETCH_W ? F::head_bytes(NT16) : (int)dm.I.head_bytes) - 1024;
 #pragma unroll
         for (int k = 0; k < F::IMGC; ++k) {
             if (k == 0 || k * 1024 < last + 1024) {  // (pieces past the block's end at this T are not fetched)
@@ -596,8 +650,8 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         const float sQ = qzero ? 1.f : qmax / dm.qmaxq;
         const float qsafe = qzero ? 1.f : qmax;
         const float cq = quant_mult(dm.qmaxq, qsafe);
-#pragma unroll
-        for (int j = 0; j < TPH; ++j) qpk[nt][j] = quant4_i8(qf[j][0], qf[j][1], qf[j][2], qf[j][3], cq, qsafe, dm.qmaxq);
+        quant4_group<QG>(qpk[nt], [&](int j) { return make_float4(qf[j][0], qf[j][1], qf[j][2], qf[j][3]); },
+                     [&](int) { return QuantRow{1.f, cq, qsafe}; }, dm.qmaxq);
         if (TAPS && dm.dbg.q_code && nvalid[nt]) {
 #pragma unroll
             for (int j = 0; j < TPH; ++j)
@@ -1026,14 +1080,15 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         so[nt] = ozero ? 1.f : oamax / 127.f;
         const float osafe = ozero ? 1.f : oamax;
         const float cq = quant_mult(127.f, osafe);
+        unsigned pk[TPH];
+        quant4_group<QG>(pk, [&](int jt) { return make_float4(oacc[nt][jt][0], oacc[nt][jt][1], oacc[nt][jt][2], oacc[nt][jt][3]); },
+                     [&](int) { return QuantRow{KEEP_O ? 1.f : of[nt], cq, osafe}; });
 #pragma unroll
         for (int jt = 0; jt < TPH; ++jt)
             if (16 * jt + 4 * q2 < D) {
-                const unsigned pk = KEEP_O ? quant4_i8(oacc[nt][jt][0], oacc[nt][jt][1], oacc[nt][jt][2], oacc[nt][jt][3], cq, osafe)
-                                           : quant4_i8_scaled(oacc[nt][jt][0], oacc[nt][jt][1], oacc[nt][jt][2], oacc[nt][jt][3], of[nt], cq, osafe);
                 const int c = h * D + 16 * jt + 4 * q2;
-                *reinterpret_cast<unsigned*>(tileq + (tbase + 16 * nt + r2) * F::TILE_RS + c) = pk;
-                if (TAPS && dm.dbg.o_code && nvalid[nt]) *reinterpret_cast<unsigned*>(dm.dbg.o_code + tok[nt] * C + c) = pk;
+                *reinterpret_cast<unsigned*>(tileq + (tbase + 16 * nt + r2) * F::TILE_RS + c) = pk[jt];
+                if (TAPS && dm.dbg.o_code && nvalid[nt]) *reinterpret_cast<unsigned*>(dm.dbg.o_code + tok[nt] * C + c) = pk[jt];
             }
         if (TAPS && dm.dbg.s_o && nvalid[nt] && q == 0 && h == 0) dm.dbg.s_o[tok[nt]] = so[nt];
     }

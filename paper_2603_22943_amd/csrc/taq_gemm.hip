@@ -423,11 +423,12 @@ void gemm_op_kernel(GemmOpArgs a) {
                 const size_t th = (size_t)t * a.H + h;
                 if (q == 0) a.s_q[th * 16 + r16] = sq;
                 if (a.tap_scale && q == 0 && n < a.N) a.tap_scale[tok * a.H + h] = sq;
+                unsigned pk[TPH ? TPH : 1];
+                quant4_group<TPH ? TPH : 1>(pk, [&](int j) { return make_float4(v[j][0], v[j][1], v[j][2], v[j][3]); }, [&](int) { return QuantRow{1.f, cq, safe}; }, a.qmax);
 #pragma unroll
                 for (int j = 0; j < TPH; ++j) {
-                    const unsigned pk = quant4_i8(v[j][0], v[j][1], v[j][2], v[j][3], cq, safe, a.qmax);
-                    a.q_op[(th * TPH + j) * 64 + lane] = pk;
-                    if (a.tap_code && n < a.N && 16 * j + 4 * q < d) *reinterpret_cast<unsigned*>(a.tap_code + tok * C + h * d + 16 * j + 4 * q) = pk;
+                    a.q_op[(th * TPH + j) * 64 + lane] = pk[j];
+                    if (a.tap_code && n < a.N && 16 * j + 4 * q < d) *reinterpret_cast<unsigned*>(a.tap_code + tok * C + h * d + 16 * j + 4 * q) = pk[j];
                 }
             }
         } else {

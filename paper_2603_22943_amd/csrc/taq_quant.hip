@@ -57,13 +57,15 @@ __device__ __forceinline__ void rowquant_f16_held(const uint4* __restrict__ xr, 
     const float safe = zero ? 1.f : amax;
     const float c = quant_mult(127.f, safe);
     if (lane == 0) *scale = zero ? 1.f : amax / 127.f;
+    unsigned pk[2 * NV];
+    quant4_group<2 * NV>(pk, [&](int i) {
+        const half2_t* x = reinterpret_cast<const half2_t*>(&u[i >> 1]) + 2 * (i & 1);
+        return make_float4((float)x[0][0], (float)x[0][1], (float)x[1][0], (float)x[1][1]);
+    }, [&](int) { return QuantRow{1.f, c, safe}; });
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int v = lane + 64 * i;
-        const half2_t* x = reinterpret_cast<const half2_t*>(&u[i]);
-        if (v < nv)
-            put(v, make_uint2(quant4_i8((float)x[0][0], (float)x[0][1], (float)x[1][0], (float)x[1][1], c, safe),
-                              quant4_i8((float)x[2][0], (float)x[2][1], (float)x[3][0], (float)x[3][1], c, safe)));
+        if (v < nv) put(v, make_uint2(pk[2 * i], pk[2 * i + 1]));
     }
 }
 
@@ -152,8 +154,8 @@ __global__ __launch_bounds__(256) void oquant_op_kernel(StageChunk c, int N, int
     const bool zero = amax == 0.f;
     const float safe = zero ? 1.f : amax, cq = quant_mult(127.f, safe);
     unsigned w[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) w[g] = c0 < C ? quant4_i8(x[g].x, x[g].y, x[g].z, x[g].w, cq, safe) : 0u;
+    quant4_group<4>(w, [&](int g) { return x[g]; }, [&](int) { return QuantRow{1.f, cq, safe}; });
+    if (c0 >= C) w[0] = w[1] = w[2] = w[3] = 0u;
     const uint4 w4 = make_uint4(w[0], w[1], w[2], w[3]);
     *reinterpret_cast<uint4*>(c.code + ((size_t)lt * KC + ks) * 1024 + lane * 16) = w4;
     const int tile = c.tile0 + lt, b = tile / c.NT, n = (tile - b * c.NT) * 16 + r16;
@@ -541,16 +543,10 @@ __device__ __forceinline__ void kvh_finish(const int32x4_t (&acc)[TPH], const Kv
         atomicMax(scmax, __float_as_uint(sc));
     }
     constexpr int TP4 = (TPH + 3) & ~3;
-    unsigned pk[TP4];
+    unsigned pk[TP4], codes4[TPH];
+    quant4_group<TPH>(codes4, [&](int j) { return make_float4(v[j][0], v[j][1], v[j][2], v[j][3]); }, [&](int) { return QuantRow{1.f, cq, safe}; }, qmaxf);
 #pragma unroll
-    for (int j = 0; j < TP4; ++j) {
-        pk[j] = 0u;
-        if (j < TPH) {
-            const int jj = j < TPH ? j : 0;
-            pk[j] = quant4_i8(v[jj][0], v[jj][1], v[jj][2], v[jj][3], cq, safe, qmaxf);
-            if (prot || 16 * j + 4 * q >= d) pk[j] = 0u;
-        }
-    }
+    for (int j = 0; j < TP4; ++j) pk[j] = j < TPH && !prot && 16 * j + 4 * q < d ? codes4[j < TPH ? j : 0] : 0u;
     const int pos = vt_pos(t & ~3, I.nt16);  // place of this lane's group of four tokens in a V^T row
     const unsigned sel1 = (r16 & 1) ? 0x03070105u : 0x06020400u, sel2 = (r16 & 2) ? 0x03020706u : 0x05040100u;
     if (side) {
