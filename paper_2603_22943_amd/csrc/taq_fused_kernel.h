@@ -253,13 +253,15 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     const __half* v16t = reinterpret_cast<const __half*>(packed + dm.L.v16t) + (size_t)b * C * 96;
 
     // protected (trigger) rows of this head, first tile of 16: fp16 K rows and transposed V rows straight from
-    // global memory into MFMA operand registers (slots past the protected tokens hold zeros; K channels past the
-    // head are not read: they would belong to the next head, or lie past the last row of the last head, and a
-    // non-finite bit pattern there would survive the multiplication with a zero Q~ code)
+    // global memory into MFMA operand registers. Wide heads leave out slots past the protected tokens: a load costs by the pieces
+    // of memory that it touches, 16 rows of 32 bytes if all lanes take part, and they stand in the queue that the image and the
+    // weights go through (15.1 -> 14.7 us at 2048 tokens of 640 channels, 18.7 -> 18.1 us at 512 of 1280; heads of 40 have few of
+    // them, and the selection costs as much: 11.35 and 11.42 us at 2 x 4096 tokens; slots past ntrig hold zeros). K channels past the
+    // head are not read either: they would belong to the next head, or lie past the last row of the last head, and a
+    // non-finite bit pattern there would survive the multiplication with a zero Q~ code.
     uint2 k16r[FS][2], v16r[TPS];
     auto load_protected = [&]() {
-        if (nfp > 0) {
-            const int slot = r16 < T ? r16 : T - 1;
+        auto load_k = [&](int slot) {
             const __half* kr = k16 + (size_t)slot * C + h * D + 4 * q;
 #pragma unroll
             for (int s = 0; s < FS; ++s)
@@ -267,6 +269,8 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
                 for (int jj = 0; jj < 2; ++jj)
                     k16r[s][jj] = (2 * s + jj < TPH && 16 * (2 * s + jj) + 4 * q < D)
                                       ? *reinterpret_cast<const uint2*>(kr + 16 * (2 * s + jj)) : make_uint2(0, 0);
+        };
+        auto load_v = [&]() {
 #pragma unroll
             for (int k = 0; k < TPS; ++k) {
                 const int jt = sub + SUB * k;  // this wavefront's k-th channel tile of A^ V~ (may lie past the head: clamped)
@@ -274,6 +278,19 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
                 c = c < C ? c : C - 1;
                 v16r[k] = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 4 * q);
             }
+        };
+        if constexpr (TPH <= 3) {
+            if (nfp > 0) {
+                load_k(r16 < T ? r16 : T - 1);
+                load_v();
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < FS; ++s) k16r[s][0] = k16r[s][1] = make_uint2(0, 0);
+#pragma unroll
+            for (int k = 0; k < TPS; ++k) v16r[k] = make_uint2(0, 0);
+            if (r16 < ntrig) load_k(r16);
+            if (4 * q < ntrig) load_v();
         }
     };
 
