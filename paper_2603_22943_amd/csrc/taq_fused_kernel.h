@@ -107,7 +107,7 @@ struct FusedCfg {
     // tiles do already: 14 registers in 60 bytes of scratch, 21 with row-major weights. 39 -> 29.9 us at 12288 tokens of ten heads
     // all the same, for one round instead of two. Row-major weights with four tiles at d = 80 spill 3, with run-time T at ten
     // heads 2.)
-    static constexpr int RING_MAX = DENSE ? 12 : NH > 8 ? (NTT > 2 ? 8 : 16) : NTT == 4 ? 20 : NTT == 3 ? 28 : 32;
+    static constexpr int RING_MAX = DENSE ? 12 : NH > 8 ? (NTT > 2 ? 8 : NTT == 2 ? 16 : 20) : NTT == 4 ? 20 : NTT == 3 ? 28 : 32;
     static constexpr int RING = (!PREFETCH_W && NG == 1) ? (NF < RING_MAX ? NF : RING_MAX) : 0;
 };
 
@@ -138,7 +138,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     constexpr bool TAPS = NT16 == 0;       // taps of intermediate codes and scales (tests, profiling)
     extern __shared__ __align__(16) unsigned char smem[];
 
-    const int tid = threadIdx.x, hl = (tid >> 6) % NH, lane = tid & 63, r16 = lane & 15, q = LEAN ? opaque(lane >> 4) : lane >> 4;
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), hl = wv % NH, lane = tid & 63, r16 = lane & 15, q = LEAN ? opaque(lane >> 4) : lane >> 4;
     // Grid: x = batch element, y = request, z = token tile; head-group variant (one request): x = batch element,
     // y = token tile, z = head group. Workgroups are dispatched x fastest, so consecutive ones (which round-robin over
     // the 8 XCDs) share a token tile index and differ in the batch element / request: one XCD, few K~/V~ images. The
@@ -148,8 +148,8 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     const int tile = NG > 1 ? (int)blockIdx.y : (int)blockIdx.z;
     const int by = NG > 1 ? (int)blockIdx.z : 0;  // head group
     const int h = by * NH + hl;  // head of the layer; hl = head within the workgroup
-    const int tbase = (((tid >> 6) / NH) % F::G) * 16 * NTT;  // first tile row of this wavefront's tokens
-    const int sub = SUB == 1 ? 0 : (tid >> 6) / (NH * F::G);  // which share of the channel tiles of A^ V~
+    const int tbase = ((wv / NH) % F::G) * 16 * NTT;  // first tile row of this wavefront's tokens
+    const int sub = SUB == 1 ? 0 : wv / (NH * F::G);  // which share of the channel tiles of A^ V~
     const FusedReq rq = tab.req[ri];
     const int N = dm.N, T = dm.T;
     const int nt16 = NT16 ? NT16 : dm.nt16;
@@ -190,6 +190,29 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     }
     __builtin_amdgcn_sched_barrier(0);
 
+    // This head's block of the K~/V~ image: straight into LDS, 1 KiB per wavefront-wide load (LDS address =
+    // base + lane * 16), no registers in between; only this wavefront reads it, so only this wavefront waits for it. The last
+    // piece may be fetched more than once.
+    auto copy_image = [&]() {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint8_t*>(rq.packed) + dm.L.image + (size_t)b * dm.L.image_bytes + (size_t)h * dm.I.head_bytes, 0, (int)dm.I.head_bytes, 0x00020000);
+        // the block is a multiple of 256 bytes: the last piece overlaps (a constant where the number of score tiles is fixed)
+        const int last = (NT16 ? F::head_bytes(NT16) : (int)dm.I.head_bytes) - 1024;
+#pragma unroll
+        for (int k = 0; k < F::IMGC; ++k) {
+            if (k == 0 || k * 1024 < last + 1024) {  // (pieces past the block's end at this T are not fetched)
+                const int c = k * 1024 < last ? k * 1024 : last;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(smem + (size_t)hl * dm.I.head_bytes + c), 16, lane * 16, c, 0, 0);
+            }
+        }
+    };
+    // (row-major weights are exchanged in its place in LDS, and have to be through with it, unless there is a KiB per wavefront besides)
+    constexpr bool SLOTS = ROWMAJ && NG == 1 && NTT <= 2 && NT16 == 5, EARLY = NG == 1 && (!ROWMAJ || SLOTS);
+    if constexpr (EARLY) {
+        copy_image();
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
     // ---- LDS carve-up
     unsigned char* img = smem;                                  // K~/V~ image blocks of this workgroup's heads
     const size_t img_bytes = (size_t)NH * dm.I.head_bytes;
@@ -197,6 +220,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     float* wsc = reinterpret_cast<float*>(smem + img_bytes + TOK * F::TILE_RS);  // s_wq | s_wo | bias_o  [3C]
     float* s_h = wsc + (NG == 1 ? 3 * C : NH * D);               // [TOK]  (NG > 1: only s_wq of the workgroup's heads)
     unsigned* omax = reinterpret_cast<unsigned*>(s_h + TOK);     // [TOK][NH]  (NG == 1)
+    unsigned char* xslot = SLOTS ? reinterpret_cast<unsigned char*>(omax + TOK * NH) + wv * 1024 : nullptr;  // exchange of row-major weights
     int* qacc = reinterpret_cast<int*>(s_h + TOK);               // [K ranges][NH*TPH][64][4] partial to_q sums (NG > 1)
 
     const uint8_t* packed = rq.packed;
@@ -407,7 +431,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     int32x4_t imv[IMV];
     if constexpr (NG > 1) {
         static_assert(NG == 1 || (D % 16 == 0 && TW % 2 == 0 && KC % KP == 0 && C % (8 * TPT) == 0 && (TPT == 16 || TPT == 32)), "head-group split");
-        const int wv = tid >> 6, js = wv & 1, kp = wv >> 1;
+        const int js = wv & 1, kp = wv >> 1;
         float4 swv = make_float4(0.f, 0.f, 0.f, 0.f);  // s_wq of this workgroup's heads: NH*D floats
         if (tid < NH * D / 4) swv = reinterpret_cast<const float4*>(rq.scales + (size_t)by * NH * D)[tid];
         // ---- per-token int8 codes of the hidden tile (every head group of a token tile computes the same codes)
@@ -511,7 +535,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         constexpr int AHEAD = ROWMAJ ? 4 : 0;  // operands on their way through LDS
         int32x4_t op[AHEAD + 1];
         auto operand = [&](int f) {
-            if constexpr (ROWMAJ) op[f % (AHEAD + 1)] = exchange_rows(wring[f % RD], imgh, lane);
+            if constexpr (ROWMAJ) op[f % (AHEAD + 1)] = exchange_rows(wring[f % RD], SLOTS ? xslot : imgh, lane);
             else op[0] = wring[f % RD];
         };
 #pragma unroll
@@ -572,7 +596,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         // Head-group variant: the wavefronts split the workgroup's to_q by weight tile group (js) and K range (kp),
         // each for the workgroup's 16 tokens; every wavefront leaves its int32 partial sums in a slot of its own
         // in LDS, and then adds up the KP partial sums of its own head: integer adds, exact in any order.
-        const int wv = tid >> 6, js = wv & 1, kp = wv >> 1;
+        const int js = wv & 1, kp = wv >> 1;
         if (sub < SUB) load_protected();  // needed only after the second barrier: they travel during the MFMAs
         if constexpr (ROWMAJ) {  // row-major weights: the lanes are exchanged through a KiB of LDS (as under ROWMAJ above), the
                              // place of this wavefront's last partial sum: 26.5 -> 21.1 us at 512 tokens, d = 160
@@ -622,23 +646,10 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     }
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) shv[nt] = s_h[tbase + 16 * nt + r16];
-    // This head's block of the K~/V~ image: straight into LDS, 1 KiB per wavefront-wide load (LDS address =
-    // base + lane * 16), no registers in between; it travels while to_q and Q~ are computed, and only this
-    // wavefront reads it, so only this wavefront waits for it. The last piece may be fetched more than once.
-    if constexpr (NG == 1) {
-        const unsigned char* gsrc = packed + dm.L.image + (size_t)b * dm.L.image_bytes + (size_t)h * dm.I.head_bytes;
-        // the block is a multiple of 256 bytes: the last piece overlaps (a constant where registers are plentiful and the number of score tiles is fixed: no branch per piece)
-        const int last = (NT16 && F::PREFETCH_W ? F::head_bytes(NT16) : (int)dm.I.head_bytes) - 1024;
-#pragma unroll
-        for (int k = 0; k < F::IMGC; ++k) {
-            if (k == 0 || k * 1024 < last + 1024) {  // (pieces past the block's end at this T are not fetched)
-                const int c = k * 1024 < last ? k * 1024 : last;
-                __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void*)(gsrc + c + lane * 16),
-                    (__attribute__((address_space(3))) void*)(imgh + c), 16, 0, 0);
-            }
-        }
-    }
+    // The image has arrived: it was requested in front of the weights that to_q has consumed (row-major weights, which go through
+    // its place in LDS: it is requested now).
+    if constexpr (EARLY) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (NG == 1 && !EARLY) copy_image();
     if constexpr (NG == 1) load_protected();
 
     // ---- Eq. (2), third line: Q~ = Q_a(Q) per (token, head)
@@ -678,12 +689,16 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         sq2[nt] = fmaxf(sQ * dm.sig2, 1e-37f);
     }
 
-    // the head's image block travelled meanwhile; it is private to this wavefront: wait (vmcnt(0)), no barrier
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    if constexpr (RING > 0 && NTT == 1) {  // ... or its first RING loads
+    if constexpr (NG == 1 && !EARLY) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the head's image block travelled meanwhile
+    // One token tile per wavefront: the first RING loads of to_out, a quarter at a time between the phases of the attention (all at
+    // once they fill the queue, and the wavefront stands until it has drained)
+    auto ring_out = [&](int part) {
+        if constexpr (RING > 0 && NTT == 1) {
 #pragma unroll
-        for (int f = 0; f < RING; ++f) wring[f] = ring_load(rs_wo, f);
-    }
+            for (int f = part * RING / 4; f < (part + 1) * RING / 4; ++f) wring[f] = ring_load(rs_wo, f);
+        }
+    };
+    ring_out(0);
 
     // ================= scores: x[t][n] = (K~ Q~^T)[t][n] * s_K[t]   (times sQ * sigma * log2 e later)
     float S[NTT][MT16][4];
@@ -776,6 +791,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         protected_scores(std::false_type{}, ft, code, facc);
     };
 
+    ring_out(1);
     // The LDS operands of O^T = V~^T A^^T (this wavefront's V~ codes and the split V scales) are read now, into
     // registers: issued next to their use, each read's round trip would stand between the softmax and its MFMAs.
     // (Only where registers are plentiful: the instantiation that also holds its weight slices in registers.)
@@ -834,6 +850,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
                 mxs[nt] = fmaxf(mxs[nt], fmaxf(fmaxf(facc[nt][0], facc[nt][1]), fmaxf(facc[nt][2], facc[nt][3])));
         }
     }
+    ring_out(2);
     float Zs[NTT], eus[NTT], offs[NTT];
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) {
@@ -903,6 +920,7 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             protected_values(std::false_type{}, ft, facc);
         }
     }
+    ring_out(3);
     const float vpre = nfp > 0 ? reinterpret_cast<const float*>(imgh + dm.I.vpre)[0] : 0.f;
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) {
@@ -1184,7 +1202,8 @@ static hipError_t launch_fused_one(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& 
 template <int D, int NH, int NTT, int NG, int PG, int TOK, int NT16>
 static hipError_t launch_fused_layout(const FusedTable<NG == 1 ? TAQ_MAX_REQ : 1>& tab, const FusedDims& dm, size_t bytes, hipStream_t st) {
     if constexpr ((FusedCfg<D, NH, NTT, NG, TOK>::RING > 0 || NG > 1) && D % 16 == 0) {
-        if (!dm.w_layout) return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, false, true>(tab, dm, bytes, st);
+        // (with SLOTS a KiB per wavefront more: at most 156 KiB at 80 text tokens)
+        if (!dm.w_layout) return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, false, true>(tab, dm, bytes + (NG == 1 && NTT <= 2 && NT16 == 5 ? NH * 1024 : 0), st);
     }
     return launch_fused_one<D, NH, NTT, NG, PG, TOK, NT16, false, false>(tab, dm, bytes, st);
 }
