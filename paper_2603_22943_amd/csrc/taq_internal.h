@@ -149,13 +149,14 @@ static inline bool mid_supported(const taq_shape& s) {
 }
 // Whether the head-group path takes such a layer, or the kernel-per-stage path. Head groups save three launches and every
 // pass over the workspace but one, but each workgroup reads its share of Wq for 16 tokens only and fills a compute unit, so
-// the time goes with the rounds of 256 workgroups: 16 us + 12 us per further round at d = 160, 14 + 8 us at d = 64 (2 to 5 us
-// more with row-major weights), against 33 to 38 us for the five stage kernels at these sizes (2048 tokens, d = 160: 56.6 and
-// 40.9 us; 8192: 159 and 87 us). shape.tok_tile = 16 or 32 forces head groups or stages (tests and tuning).
+// the time goes with the rounds of 256 workgroups; the five stage kernels take 23 to 30 us at these sizes. Head groups and stages, us:
+// d = 160, 512 tokens (one round) 18.5 and 27.6, 576 (two) 26.2 and 28.2, 1024 (two, full) 30.1 and 29.6, 2048 51.6 and 35.2; row-major
+// weights 20.4 and 28.2 at 512, 29.9 and 29.3 at 576, 34.2 and 30.7 at 1024; d = 64, 400 tokens (one round) 20.9 and 24.9, 800 (two) 25.4 and 28.7, row-major
+// 28.6 and 29.0, 1024 (three) 31.3 and 29.0, 1200 38.5 and 30.1. shape.tok_tile = 16 or 32 forces head groups or stages (tests and tuning).
 static inline bool mid_preferred(const taq_shape& s) {
     if (s.tok_tile) return s.tok_tile == 16;
     const long rounds = ((long)s.B * ((s.N + 15) / 16) * mid_groups(s) + 255) / 256;
-    return rounds <= (s.C / s.H == 160 ? 2 : 3);
+    return rounds <= (s.C / s.H == 160 && s.w_layout != 1 ? 1 : 2);
 }
 
 static inline KvLayout kv_layout(const taq_shape& s) {

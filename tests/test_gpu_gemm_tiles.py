@@ -26,3 +26,9 @@ def test_tiles_do_not_change_results(B, N, C, H, w_layout):
     whole = L.run()
     for lo, hi in ((0, 1), (95, 130), (N - 37, N)):
         assert np.array_equal(whole[:, lo:hi], L.run(lo, hi)), (lo, hi)
+
+
+@pytest.mark.parametrize("B,N,H,w_layout", [(1, 816, 20, 1), (1, 817, 20, 1), (1, 817, 20, 0), (1, 512, 8, 0), (1, 513, 8, 0), (1, 1025, 8, 1)])
+def test_head_groups_and_stages_agree_where_the_rule_changes(B, N, H, w_layout):
+    L = Layer(B, N, 1280, H, w_layout=w_layout)
+    assert np.array_equal(L.run(), L.run(tok_tile=16))
