@@ -14,7 +14,9 @@
 // that the head's image block (8 to 27 KiB, fetched once into LDS) serves them all and several workgroups share a
 // compute unit. Bound by vector issue (softmax and Eq. 3, about 12 instructions per probability). The kernel that stood
 // here before staged and split K~/V~ itself in every workgroup, whatever the number of tokens: 31 us at B = 2, N = 2304,
-// 12 heads of 64, 13 us now.
+// 12 heads of 64. Half of a wavefront's clocks go before the first score, on loads that wait their turn at the texture unit: Q~ codes
+// in the widest pieces, protected rows once per workgroup and taps compiled out took it from 8.6 to 8.2 us there, 7.4 to 6.9 at 2048
+// tokens of 20 heads of 64, 18.1 to 17.7 at 8192, 9.4 to 8.8 at 4000 tokens of 12 heads of 80.
 #include "taq_device.h"
 
 namespace taq {
@@ -23,6 +25,8 @@ template <int TPH, int NTT, int PG, int NT16>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TPH <= 3 ? 3 : 2)))
 void attn_op_kernel(AttnOpArgs a) {
     constexpr bool LOGP = PG == TAQ_PROB_LOG2, ROWMAX = PG == TAQ_PROB_ROWMAX;
+    constexpr bool TAPS = NT16 == 0;  // (of probability codes and O)
+    constexpr bool PLDS = TPH <= 5;   // the first protected rows through LDS
     constexpr int MT16 = NT16 ? NT16 : 6, KS = (TPH + 3) / 4, FS = (TPH + 1) / 2;
     extern __shared__ __align__(16) unsigned char img[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, q = lane >> 4;
@@ -54,38 +58,53 @@ void attn_op_kernel(AttnOpArgs a) {
         live[nt] = first + nt < hi;
         tile[nt] = live[nt] ? first + nt : hi - 1;
         const size_t th = (size_t)(tile[nt] - a.tile0) * H + h;
+        const unsigned* qp = a.q_op + th * TPH * 64;
 #pragma unroll
-        for (int j = 0; j < TPH; ++j) qpk[nt][j] = a.q_op[(th * TPH + j) * 64 + lane];
+        for (int j = 0; j < TPH; ++j) qpk[nt][j] = qp[QPlace<TPH>::at(j, lane)];
         sq2[nt] = fmaxf(a.s_q[th * 16 + r16] * a.sig2, 1e-37f);
     }
-    // This wavefront's pieces of the image are in LDS before the barrier below: nothing else makes anybody wait for another
-    // wavefront's. (Here and not at the barrier: what is requested next need not be there then.)
+    // The first 16 protected K rows [slot][16 TPH channels] and V columns [channel][16 slots] of this head. A load costs by the pieces of
+    // memory that it touches, one a clock at the texture unit. Heads of up to 80 channels put them into LDS behind the image, once for the
+    // workgroup (as operands of every wavefront, up to 10 loads of 16 pieces, they took 1 to 2 of 11 k clocks); of K only the rows that
+    // there are. Wide heads, whose workgroups are few and wait for all of LDS, load operands, without slots past the protected tokens:
+    // for the layer 40.6 us against 41.3 through LDS at 3072 tokens of 8 heads of 160 (75.9 against 74.4 at 8192).
+    unsigned char* prot = img + a.I.head_bytes;
+    if (PLDS && nfp > 0) {
+        constexpr int PPS = 2 * TPH, KIB = 512 * TPH;  // 16-byte pieces of a slot; bytes of the K rows, of the V columns
+        const int slots = ntrig < T ? ntrig : T;
+        for (int o = wave * 1024; o < 2 * KIB; o += 4096) {
+            // (K rows and V columns are taken together as one list of pieces; a KiB holds some of each where TPH is odd)
+            const int i = (o >> 4) + lane, slot = i / PPS, part = i % PPS, v = i - 16 * PPS, c = v >> 1;
+            const bool isv = v >= 0;
+            const __half* src = isv ? v16t + (size_t)(c < d ? c : d - 1) * 96 + 8 * (v & 1) : k16 + (size_t)slot * C + 8 * part;
+            if (o + lane * 16 < 2 * KIB && (isv || (slot < slots && 8 * part < d)))
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)(prot + o), 16, 0, 0);
+        }
+    }
+    // This wavefront's pieces are in LDS before the barrier: nothing else makes anybody wait for another wavefront's.
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    // The first 16 protected K rows and V columns, operands as they are. A load costs by the pieces of memory that it touches, 16 rows
-    // of 32 bytes if all slots are read; wide heads, which have the most of them, leave out those past the protected tokens
-    // (C = 1280, 8 heads, 3072 tokens: 48.5 -> 47.9 us for the layer). At 64 channels that wins nothing: whether there are any or not
-    // their number is still on its way (scores of rows past it are dropped, such V columns hold zeros).
-    const int slots = TPH > 5 ? ntrig : 16;
-    uint2 k16r[FS][2], v16r[TPH];
-#pragma unroll
-    for (int s = 0; s < FS; ++s)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) k16r[s][jj] = make_uint2(0, 0);
-#pragma unroll
-    for (int k = 0; k < TPH; ++k) v16r[k] = make_uint2(0, 0);
-    if (r16 < slots) {
-        const __half* kr = k16 + (size_t)(r16 < T ? r16 : T - 1) * C + 4 * q;
+    uint2 k16r[PLDS ? 1 : FS][2], v16r[PLDS ? 1 : TPH];
+    if constexpr (!PLDS) {
 #pragma unroll
         for (int s = 0; s < FS; ++s)
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
-                if (2 * s + jj < TPH && 16 * (2 * s + jj) + 4 * q < d) k16r[s][jj] = *reinterpret_cast<const uint2*>(kr + 16 * (2 * s + jj));
-    }
-    if (4 * q < slots) {
+            for (int jj = 0; jj < 2; ++jj) k16r[s][jj] = make_uint2(0, 0);
 #pragma unroll
-        for (int k = 0; k < TPH; ++k) {
-            const int c = 16 * k + r16 < d ? 16 * k + r16 : d - 1;
-            v16r[k] = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 4 * q);
+        for (int k = 0; k < TPH; ++k) v16r[k] = make_uint2(0, 0);
+        if (r16 < ntrig) {
+            const __half* kr = k16 + (size_t)(r16 < T ? r16 : T - 1) * C + 4 * q;
+#pragma unroll
+            for (int s = 0; s < FS; ++s)
+#pragma unroll
+                for (int jj = 0; jj < 2; ++jj)
+                    if (2 * s + jj < TPH && 16 * (2 * s + jj) + 4 * q < d) k16r[s][jj] = *reinterpret_cast<const uint2*>(kr + 16 * (2 * s + jj));
+        }
+        if (4 * q < ntrig) {
+#pragma unroll
+            for (int k = 0; k < TPH; ++k) {
+                const int c = 16 * k + r16 < d ? 16 * k + r16 : d - 1;
+                v16r[k] = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 4 * q);
+            }
         }
     }
     __syncthreads();
@@ -135,7 +154,7 @@ void attn_op_kernel(AttnOpArgs a) {
             }
         }
     }
-    // ---- protected rows: scores of tile ft of 16 slots, the first from registers, further ones (rare) straight from the fp16
+    // ---- protected rows: scores of tile ft of 16 slots, the first from LDS, further ones (rare) straight from the fp16
     // K rows; -inf past ntrig
     auto protected_scores = [&](auto head, int ft, floatx4_t (&facc)[NTT]) {
 #pragma unroll
@@ -149,8 +168,10 @@ void attn_op_kernel(AttnOpArgs a) {
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj) {
                 const int j = 2 * s + jj;
-                uint2 w = k16r[s][jj];
-                if constexpr (!decltype(head)::value) w = (j < TPH && 16 * j + 4 * q < d) ? *reinterpret_cast<const uint2*>(kr + 16 * j) : make_uint2(0, 0);
+                uint2 w = make_uint2(0, 0);
+                if (j < TPH && 16 * j + 4 * q < d)
+                    w = !decltype(head)::value ? *reinterpret_cast<const uint2*>(kr + 16 * j)
+                        : PLDS ? *reinterpret_cast<const uint2*>(prot + r16 * (32 * TPH) + 32 * j + 8 * q) : k16r[PLDS ? 0 : s][jj];
                 const half4_t hv = *reinterpret_cast<const half4_t*>(&w);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) ka[4 * jj + e] = hv[e];
@@ -242,8 +263,8 @@ void attn_op_kernel(AttnOpArgs a) {
 #pragma unroll
         for (int k = 0; k < TPH; ++k) {
             const int c = 16 * k + r16 < d ? 16 * k + r16 : d - 1;
-            uint2 w = v16r[k];
-            if constexpr (!decltype(head)::value) w = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 16 * ft + 4 * q);
+            const uint2 w = !decltype(head)::value ? *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 16 * ft + 4 * q)
+                            : PLDS ? *reinterpret_cast<const uint2*>(prot + 512 * TPH + c * 32 + 8 * q) : v16r[PLDS ? 0 : k];
             const half4_t va = *reinterpret_cast<const half4_t*>(&w);  // slots past ntrig hold zeros
 #pragma unroll
             for (int nt = 0; nt < NTT; ++nt) {
@@ -322,13 +343,13 @@ void attn_op_kernel(AttnOpArgs a) {
                                 const float c1 = __builtin_amdgcn_fmed3f(__builtin_rintf(S[nt][tt][2 * i2 + 1] - lz[nt]), -a.plast, 0.f);
                                 const auto pw = __builtin_amdgcn_cvt_pkrtz(ldexpf(256.0f, (int)c0), ldexpf(256.0f, (int)c1));
                                 c = (half2_t){(_Float16)pw[0], (_Float16)pw[1]};
-                                if (a.p_code) tap_pcode(nt, 16 * tt + 4 * q + 2 * i2, (unsigned)(int)(-c0), (unsigned)(int)(-c1));
+                                if (TAPS && a.p_code) tap_pcode(nt, 16 * tt + 4 * q + 2 * i2, (unsigned)(int)(-c0), (unsigned)(int)(-c1));
                             } else {
                                 const float m0 = __builtin_fmaf(S[nt][tt][2 * i2], kq[nt], 12608512.0f);
                                 const float m1 = __builtin_fmaf(S[nt][tt][2 * i2 + 1], kq[nt], 12608512.0f);
                                 const unsigned w = __builtin_amdgcn_perm(__float_as_uint(m1), __float_as_uint(m0), 0x05040100u);
                                 c = *reinterpret_cast<const half2_t*>(&w) - k1024;
-                                if (a.p_code) tap_pcode(nt, 16 * tt + 4 * q + 2 * i2, w & 0xFFu, (w >> 16) & 0xFFu);
+                                if (TAPS && a.p_code) tap_pcode(nt, 16 * tt + 4 * q + 2 * i2, w & 0xFFu, (w >> 16) & 0xFFu);
                             }
                             const half2_t wh = c * sh[i2];
                             const half2_t wl = __builtin_elementwise_fma(c, sl[i2], __builtin_elementwise_fma(c, sh[i2], -wh));
@@ -389,7 +410,7 @@ void attn_op_kernel(AttnOpArgs a) {
             if (valid) omx = fmaxf(omx, fmaxf(fmaxf(fabsf(o4.x), fabsf(o4.y)), fmaxf(fabsf(o4.z), fabsf(o4.w))));
             if (live[nt] && valid) {
                 reinterpret_cast<float4*>(a.o_op)[(th * TPH + k) * 64 + lane] = o4;
-                if (a.O && n < a.N) *reinterpret_cast<float4*>(a.O + ((size_t)b * a.N + n) * C + h * d + 16 * k + 4 * q) = o4;
+                if (TAPS && a.O && n < a.N) *reinterpret_cast<float4*>(a.O + ((size_t)b * a.N + n) * C + h * d + 16 * k + 4 * q) = o4;
             }
         }
         omx = quad_allmax(omx);
@@ -399,14 +420,15 @@ void attn_op_kernel(AttnOpArgs a) {
 
 template <int TPH, int NTT, int PG, int NT16>
 static hipError_t launch_attn_cfg(const AttnOpArgs& a, int tiles_b, int nb, hipStream_t st) {
-    hipLaunchKernelGGL((attn_op_kernel<TPH, NTT, PG, NT16>), dim3((tiles_b + 4 * NTT - 1) / (4 * NTT), a.H, nb), dim3(256), a.I.head_bytes, st, a);
+    hipLaunchKernelGGL((attn_op_kernel<TPH, NTT, PG, NT16>), dim3((tiles_b + 4 * NTT - 1) / (4 * NTT), a.H, nb), dim3(256), a.I.head_bytes + (TPH <= 5 ? 1024 * TPH : 0), st, a);
     return hipGetLastError();
 }
 
 template <int TPH, int PG, int NTT>
 static hipError_t launch_attn_text(const AttnOpArgs& a, int tiles_b, int nb, hipStream_t st) {
-    // 65 to 80 text tokens (the 77-token prompts): no run-time guards around the score tiles
-    if (a.nt16 == 5) return launch_attn_cfg<TPH, NTT, PG, 5>(a, tiles_b, nb, st);
+    // 65 to 80 text tokens (the 77-token prompts): no run-time guards around the score tiles, and no taps, whose branches keep the
+    // compiler from reading V~ ahead of the products
+    if (a.nt16 == 5 && !a.p_code && !a.O) return launch_attn_cfg<TPH, NTT, PG, 5>(a, tiles_b, nb, st);
     return launch_attn_cfg<TPH, NTT, PG, 0>(a, tiles_b, nb, st);
 }
 

@@ -192,4 +192,17 @@ __device__ __forceinline__ void quad_transpose(unsigned (&r)[4]) {
 // Maximum over all 64 lanes.
 __device__ __forceinline__ float wave_allmax(float x) { return quad_allmax(row16_allmax(x)); }
 
+// Q~ codes of a (token tile, head), TPH dwords a lane, lie in units of as many 16-channel blocks as a wavefront of to_q holds at least:
+// within a unit four blocks by four, a lane's four dwords together, then the one to three that are left. Both sides move whole pieces of
+// memory with the widest accesses (blocks of one dword a lane: 10 loads at 160 channels; units cut by a wavefront's share: 1 us more
+// for to_q there).
+template <int TPH>
+struct QPlace {
+    static constexpr int UNIT = TPH == 4 ? 2 : TPH >= 6 && TPH % 2 == 0 ? TPH / 2 : TPH;
+    static __device__ __forceinline__ int at(int j, int lane) {
+        const int u = j / UNIT * UNIT, k = j - u, full = UNIT & ~3, rest = UNIT & 3;
+        return 64 * u + (k < full ? (k & ~3) * 64 + lane * 4 + (k & 3) : full * 64 + lane * rest + (k - full));
+    }
+};
+
 }  // namespace taq

@@ -73,6 +73,7 @@ void gemm_op_kernel(GemmOpArgs a) {
     constexpr int TP = TPH ? TPH : 1, WPH = TPH > NW ? TPH / NW : 1;  // to_q: wavefronts that share a head
     constexpr int JH = WPH > 1 ? NW : TP, HPW = NW / JH;              // blocks of one head, heads in a wavefront
     static_assert(NLD * (STAGES - 1) < 64, "vmcnt");
+    static_assert(TPH == 0 || JH % QPlace<TP>::UNIT == 0, "whole units of Q~");
     static_assert(TPH == 0 || (WPH > 1 ? TPH % NW == 0 && WN % WPH == 0 : NW % TP == 0), "whole heads per workgroup");
     __shared__ __align__(16) unsigned char lds[STAGES * BLK * 1024];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
@@ -255,8 +256,9 @@ void gemm_op_kernel(GemmOpArgs a) {
                 if (q == 0 && j0 == 0) a.s_q[th * 16 + r16] = sq;
                 unsigned pk[JH];
                 quant4_group<JH>(pk, [&](int j) { return value(i, hh * JH + j); }, [&](int) { return QuantRow{1.f, cq, safe}; }, a.qmax);
+                unsigned* qp = a.q_op + (th * TP + j0) * 64;  // (j0: whole units)
 #pragma unroll
-                for (int j = 0; j < JH; ++j) a.q_op[(th * TP + j0 + j) * 64 + lane] = pk[j];
+                for (int j = 0; j < JH; ++j) qp[QPlace<TP>::at(j, lane)] = pk[j];
                 if (a.tap_code || a.tap_scale) {
                     const int b = (a.tile0 + t) / a.NT, n = (a.tile0 + t - b * a.NT) * 16 + r16;
                     const size_t tok = (size_t)b * a.N + n;
