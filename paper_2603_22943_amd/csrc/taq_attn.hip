@@ -31,12 +31,14 @@ void attn_op_kernel(AttnOpArgs a) {
     extern __shared__ __align__(16) unsigned char img[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, q = lane >> 4;
     const int h = blockIdx.y, T = a.T, C = a.C, H = a.H, d = a.d, nt16 = NT16 ? NT16 : a.nt16;
-    // tiles of the chunk: tile index t (of the whole call) = b * NT + tile within the batch element; blockIdx.z counts batch
-    // elements from the chunk's first
-    const int b = a.b0 + (int)blockIdx.z;
+    // tiles of the chunk: tile index t (of the whole call) = b * NT + tile within the batch element. The groups of 4 NTT tiles of all batch
+    // elements, counted from the chunk's first, are dealt to the XCDs in eighths.
+    const int group = ((int)blockIdx.x & 7) * a.groups8 + ((int)blockIdx.x >> 3), bi = group / a.groups, gx = group - bi * a.groups;
+    if (bi >= a.nb) return;
+    const int b = a.b0 + bi;
     const int lo = b * a.NT > a.tile0 ? b * a.NT : a.tile0, hi = (b + 1) * a.NT < a.tile1 ? (b + 1) * a.NT : a.tile1;
-    const int first = lo + ((int)blockIdx.x * 4 + wave) * NTT;  // this wavefront's first tile
-    if (lo + (int)blockIdx.x * 4 * NTT >= hi) return;           // (the whole workgroup)
+    const int first = lo + (gx * 4 + wave) * NTT;  // this wavefront's first tile
+    if (lo + gx * 4 * NTT >= hi) return;           // (the whole workgroup)
     const unsigned char* gimg = a.packed + a.L.image + (size_t)b * a.L.image_bytes + (size_t)h * a.I.head_bytes;
     // straight into LDS in pieces of 1 KiB, all under way at once (of the last one the lanes inside the block)
     for (int o = wave * 1024; o < (int)a.I.head_bytes; o += 4096)
@@ -419,8 +421,11 @@ void attn_op_kernel(AttnOpArgs a) {
 }
 
 template <int TPH, int NTT, int PG, int NT16>
-static hipError_t launch_attn_cfg(const AttnOpArgs& a, int tiles_b, int nb, hipStream_t st) {
-    hipLaunchKernelGGL((attn_op_kernel<TPH, NTT, PG, NT16>), dim3((tiles_b + 4 * NTT - 1) / (4 * NTT), a.H, nb), dim3(256), a.I.head_bytes + (TPH <= 5 ? 1024 * TPH : 0), st, a);
+static hipError_t launch_attn_cfg(AttnOpArgs a, int tiles_b, int nb, hipStream_t st) {
+    a.groups = (tiles_b + 4 * NTT - 1) / (4 * NTT);
+    a.nb = nb;
+    a.groups8 = (a.groups * nb + 7) / 8;
+    hipLaunchKernelGGL((attn_op_kernel<TPH, NTT, PG, NT16>), dim3(8 * a.groups8, a.H), dim3(256), a.I.head_bytes + (TPH <= 5 ? 1024 * TPH : 0), st, a);
     return hipGetLastError();
 }
 

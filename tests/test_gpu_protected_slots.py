@@ -11,7 +11,7 @@ from tests.test_gpu_parity import check_layer
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("C,H", [(320, 8), (640, 8), (640, 10), (1280, 8), (1280, 20), (320, 2)])
+@pytest.mark.parametrize("C,H", [(320, 8), (640, 8), (640, 10), (1280, 8), (1280, 20), (320, 2), (960, 12), (480, 12), (96, 6)])
 @pytest.mark.parametrize("counts", [(0, 1, 4), (5, 15, 16), (17, 33, 3)])
 def test_slots_past_the_last_are_not_read(C, H, counts):
     L = synth.make_layer("few", seed=C + H + counts[0], B=3, N=21, C=C, H=H, Cc=64, T=77, bits_kv=8, trigger_scale=3.0)
