@@ -150,9 +150,10 @@ static inline bool mid_supported(const taq_shape& s) {
 // Whether the head-group path takes such a layer, or the kernel-per-stage path. Head groups save three launches and every
 // pass over the workspace but one, but each workgroup reads its share of Wq for 16 tokens only and fills a compute unit, so
 // the time goes with the rounds of 256 workgroups; the five stage kernels take 23 to 30 us at these sizes. Head groups and stages, us:
-// d = 160, 512 tokens (one round) 18.5 and 27.6, 576 (two) 26.2 and 28.2, 1024 (two, full) 30.1 and 29.6, 2048 51.6 and 35.2; row-major
-// weights 20.4 and 28.2 at 512, 29.9 and 29.3 at 576, 34.2 and 30.7 at 1024; d = 64, 400 tokens (one round) 20.9 and 24.9, 800 (two) 25.4 and 28.7, row-major
-// 28.6 and 29.0, 1024 (three) 31.3 and 29.0, 1200 38.5 and 30.1. shape.tok_tile = 16 or 32 forces head groups or stages (tests and tuning).
+// d = 160, 512 tokens (one round) 18.0 and 27.1, 576 (two) 25.8 and 28.2, 1024 (two, full) 29.5 and 28.5, 2048 51.6 and 34.3; row-major
+// weights 20.4 and 27.1 at 512, 30.1 and 29.3 at 576, 34.2 and 29.6 at 1024; d = 64, 800 tokens (two rounds) 24.2 and 27.6, row-major
+// 26.9 and 28.2, 1024 (three) 28.0 and 27.7, row-major 32.5 and 28.1, 1200 34.9 and 29.8. shape.tok_tile = 16 or 32 forces head groups or
+// stages (tests and tuning).
 static inline bool mid_preferred(const taq_shape& s) {
     if (s.tok_tile) return s.tok_tile == 16;
     const long rounds = ((long)s.B * ((s.N + 15) / 16) * mid_groups(s) + 255) / 256;
