@@ -78,15 +78,18 @@ void gemm_op_kernel(GemmOpArgs a) {
     __shared__ __align__(16) unsigned char lds[STAGES * BLK * 1024];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
     const int wm = wave % WM, wn = wave / WM;
-    // Workgroups are dealt to the 8 XCDs in turn. An XCD has an eighth of the token blocks, one after the other with all their channel
-    // blocks, so that its L2 fetches those tokens once (the weights, which every XCD reads whole, are the smaller operand). All five
-    // stage kernels deal the tokens in the same eighths: a stage finds in its own L2 what the one before it wrote. Whole layers, blocks
-    // in turn and in eighths: 41.4 -> 39.4 us at 8 x 384 tokens of 1280 channels, 34.1 -> 33.4 at 2 x 1024 of 1280 (20 heads), 35.8 -> 34.7
-    // at 2 x 2304 of 768, 38.7 -> 36.9 at 4 x 1000 of 960, 24.6 -> 22.9 at 3 x 711 of 640, 77.3 -> 76.6 at 8 x 1024 of 1280 (where the
-    // float32 O no longer fits the L2s).
-    const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
-    const int row = a.inv_nx ? (int)__umulhi((unsigned)slot, a.inv_nx) : slot / a.NX, mb = xcd * ((a.MX + 7) / 8) + row, nb = slot - row * a.NX;
-    if (mb >= a.MX) return;
+    // An XCD has an eighth of the workgroups (XcdShare), token block after token block with all their channel blocks, so that its L2
+    // fetches those tokens once (the weights, which every XCD reads whole, are the smaller operand). All five stage kernels deal the
+    // tokens that way: a stage finds in its own L2 what the one before it wrote. Whole layers, blocks in turn and in eighths: 41.4 -> 39.4
+    // us at 8 x 384 tokens of 1280 channels, 34.1 -> 33.4 at 2 x 1024 of 1280 (20 heads), 35.8 -> 34.7 at 2 x 2304 of 768, 38.7 -> 36.9 at
+    // 4 x 1000 of 960, 24.6 -> 22.9 at 3 x 711 of 640, 77.3 -> 76.6 at 8 x 1024 of 1280 (where the float32 O no longer fits the L2s). With
+    // whole token blocks to an XCD, 25 blocks of 20 workgroups (2 x 784 tokens) were a third round for three XCDs: to_q and to_out 8.6 ->
+    // 6.9 and 9.0 -> 6.8 us, 35.6 -> 32 the layer; where the blocks divide by 8 nothing changes.
+    // (The arguments that everything waits for are asked for together, not one part behind the branch: 0.1 us.)
+    asm volatile("" ::"s"(a.A), "s"(a.W), "s"(a.sa), "s"(a.sw), "s"(a.pack_off), "s"(a.tiles), "s"(a.KC), "s"(a.H), "s"(a.inv_nx));
+    const int item = XcdShare::item(blockIdx.x, (unsigned)(a.MX * a.NX));
+    if (item < 0) return;
+    const int mb = a.inv_nx ? (int)__umulhi((unsigned)item, a.inv_nx) : (int)((unsigned)item / (unsigned)a.NX), nb = item - mb * a.NX;
     const int t0 = mb * MB, g0 = nb * NB, ng = a.H * a.tph;  // first token tile, first weight block, weight blocks
     const int KC = a.KC, C = a.C, d = a.d, tph = TPH ? TPH : a.tph;
     auto head_of = [&](int g) -> int { return TPH ? g / TP : a.inv_tph ? (int)__umulhi((unsigned)g, a.inv_tph) : g; };
@@ -317,17 +320,13 @@ void gemm_op_kernel(GemmOpArgs a) {
     }
 }
 
-// ceil(2^32 / n), whose product with x has x / n as its high word while x * n < 2^32; 0 (divide) for n = 1 or a larger x
-static inline unsigned inverse32(unsigned n, unsigned long long x) {
-    return n == 1 || x * n >> 32 ? 0u : (unsigned)(((1ull << 32) + n - 1) / n);
-}
-
 template <bool PACKED, int MW, int NW, int WM, int WN, int TPH>
 static hipError_t launch_gemm_op_cfg(GemmOpArgs a, hipStream_t st) {
     a.NX = (a.H * a.tph + NW * WN - 1) / (NW * WN);
     a.MX = (a.tiles + MW * WM - 1) / (MW * WM);
-    const int grid = 8 * ((a.MX + 7) / 8) * a.NX;
-    a.inv_nx = inverse32(a.NX, grid / 8);
+    if ((long)a.MX * a.NX > XcdShare::MOST) return hipErrorInvalidValue;
+    const unsigned items = (unsigned)(a.MX * a.NX), grid = XcdShare::grid(items);
+    a.inv_nx = inverse32(a.NX, items);
     a.inv_tph = inverse32(a.tph, (unsigned long long)a.H * a.tph + 64);
     hipLaunchKernelGGL((gemm_op_kernel<MW, NW, WM, WN, TPH, 4, PACKED>), dim3(grid), dim3(64 * WM * WN), 0, st, a);
     return hipGetLastError();
@@ -335,7 +334,7 @@ static hipError_t launch_gemm_op_cfg(GemmOpArgs a, hipStream_t st) {
 
 // Which tile: per K step a compute unit's matrix cores take 4 clocks for a product of 16 x 16 x 64 (four of them, 16 each) and its path
 // from L2 16 for a KiB; a workgroup that has the unit to itself pays about 60 more (barrier, first reads). The tile whose busiest unit is
-// through first is taken. Measured at 2048 tokens of 1280 channels (640, 220, 256 and 160 workgroups of 64 x 64, 96 x 128, 128 x 80 and
+// through first is taken (XcdShare: an eighth of the workgroups on the 32 units of an XCD). Measured at 2048 tokens of 1280 channels (640, 220, 256 and 160 workgroups of 64 x 64, 96 x 128, 128 x 80 and
 // 128 x 128): to_q 8.2, 7.8, -, 8.5 us, to_out 8.6, 7.8, 7.6, 8.3; at 3072, heads of 160: to_q 11.1, 9.5 (96 x 160), 10.5 (128 x 160),
 // to_out 10.7, 10.7, 10.6, 8.8; at 768: to_q 6.6 (32 x 160), 9.0, 9.8, to_out 6.4, 7.4, 7.2, 7.9; at 4608 of 768: to_q 8.3, 8.8, -, 7.4.
 static inline int tile_cost(const GemmOpArgs& a, int mb, int nb) {

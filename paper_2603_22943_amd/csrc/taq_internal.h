@@ -19,6 +19,23 @@ namespace taq {
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// ceil(2^32 / n), whose product with x has x / n as its high word while x * n < 2^32; 0 (divide) for n = 1 or a larger x
+static inline unsigned inverse32(unsigned n, unsigned long long x) {
+    return n == 1 || x * n >> 32 ? 0u : (unsigned)(((1ull << 32) + n - 1) / n);
+}
+
+// Which of n items of a launch a workgroup has. Workgroups go to the 8 XCDs in turn; every XCD gets an eighth of the items, one after
+// the other, and no two XCDs differ by more than one item (whole rows of items to an XCD would leave its 32 compute units up to a round
+// of workgroups more than those of the others). tests/test_xcd_share.py counts.
+struct XcdShare {
+    static constexpr long MOST = 1l << 28;
+    static unsigned grid(unsigned n) { return 8 * ((n + 7) / 8); }
+    __host__ __device__ static int item(unsigned block, unsigned n) {  // or -1
+        const unsigned xcd = block & 7, i = (xcd * n >> 3) + (block >> 3);
+        return i < ((xcd + 1) * n >> 3) ? (int)i : -1;
+    }
+};
+
 // Layout of qkv_packed: fixed by the shape alone, every section 256-byte aligned.
 struct KvLayout {
     size_t ntrig;     // i32 [B]        number of protected tokens

@@ -101,14 +101,14 @@ __global__ __launch_bounds__(256) void rowquant_f16_kernel(const __half* __restr
 }
 
 // Kernel-per-stage path: per-token codes of hidden in the order to_q's token operand is read (tiles of 16 tokens, per K step
-// of 64 codes one KiB, lane = token + 16 * quarter). C % 64 == 32: the second half of the last step is cleared. An eighth of the tiles
-// for each XCD, as in gemm_op_kernel.
+// of 64 codes one KiB, lane = token + 16 * quarter). C % 64 == 32: the second half of the last step is cleared. Tiles go to
+// the XCDs in the eighths of gemm_op_kernel, four workgroups each.
 __global__ __launch_bounds__(256) void rowquant_op_kernel(const __half* __restrict__ x, StageChunk c, int N, int C,
                                                           int8_t* __restrict__ tap_code, float* __restrict__ tap_scale) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int tiles = c.tile1 - c.tile0, slot = (int)blockIdx.x >> 3;
-    const int lt = ((int)blockIdx.x & 7) * ((tiles + 7) / 8) + (slot >> 2), r = (slot & 3) * 4 + wave;  // tile of the chunk, token of the tile
-    if (lt >= tiles) return;
+    const int slot = (int)blockIdx.x >> 3;
+    const int lt = XcdShare::item((blockIdx.x & 7) + 8 * (slot >> 2), c.tile1 - c.tile0), r = (slot & 3) * 4 + wave;  // tile of the chunk, token of the tile
+    if (lt < 0) return;
     const int tile = c.tile0 + lt, b = tile / c.NT, n = (tile - b * c.NT) * 16 + r;
     if (n >= N) return;  // (codes past the last token are never used)
     const int KC = (C + 63) >> 6;
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void rowquant_op_kernel(const __half* __restri
 }
 
 hipError_t launch_rowquant_op(const StageChunk& c, const taq_shape& s, const __half* hidden, const taq_debug* dbg, hipStream_t st) {
-    hipLaunchKernelGGL(rowquant_op_kernel, dim3(32 * ((c.tile1 - c.tile0 + 7) / 8)), dim3(256), 0, st, hidden, c, s.N, s.C, dbg ? dbg->h_code : nullptr,
+    hipLaunchKernelGGL(rowquant_op_kernel, dim3(4 * XcdShare::grid(c.tile1 - c.tile0)), dim3(256), 0, st, hidden, c, s.N, s.C, dbg ? dbg->h_code : nullptr,
                        dbg ? dbg->s_h : nullptr);
     return hipGetLastError();
 }
@@ -140,9 +140,9 @@ hipError_t launch_rowquant_op(const StageChunk& c, const taq_shape& s, const __h
 __global__ __launch_bounds__(256) void oquant_op_kernel(StageChunk c, int N, int C, int H, int d, int tph, unsigned inv_d,
                                                         int8_t* __restrict__ tap_code, float* __restrict__ tap_scale) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
-    const int tiles = c.tile1 - c.tile0, lt = ((int)blockIdx.x & 7) * ((tiles + 7) / 8) + ((int)blockIdx.x >> 3);
+    const int lt = XcdShare::item(blockIdx.x, c.tile1 - c.tile0);
     const int ks = blockIdx.y * 4 + wave, KC = (C + 63) >> 6;
-    if (lt >= tiles || ks >= KC) return;
+    if (lt < 0 || ks >= KC) return;
     const int c0 = 64 * ks + 16 * q;
     const float4* o = reinterpret_cast<const float4*>(c.o_op) + (size_t)lt * H * tph * 64 + r16;
     float4 x[4];
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void oquant_op_kernel(StageChunk c, int N, int
 
 hipError_t launch_oquant_op(const StageChunk& c, const taq_shape& s, const taq_debug* dbg, hipStream_t st) {
     const int d = s.C / s.H;
-    hipLaunchKernelGGL(oquant_op_kernel, dim3(8 * ((c.tile1 - c.tile0 + 7) / 8), ((s.C + 63) / 64 + 3) / 4), dim3(256), 0, st, c, s.N, s.C, s.H, d, (d + 15) / 16,
+    hipLaunchKernelGGL(oquant_op_kernel, dim3(XcdShare::grid(c.tile1 - c.tile0), ((s.C + 63) / 64 + 3) / 4), dim3(256), 0, st, c, s.N, s.C, s.H, d, (d + 15) / 16,
                        (unsigned)(0x100000000ull / d + 1), dbg ? dbg->o_code : nullptr, dbg ? dbg->s_o : nullptr);
     return hipGetLastError();
 }
