@@ -30,12 +30,16 @@ void attn_op_kernel(AttnOpArgs a) {
     constexpr int MT16 = NT16 ? NT16 : 6, KS = (TPH + 3) / 4, FS = (TPH + 1) / 2;
     extern __shared__ __align__(16) unsigned char img[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, q = lane >> 4;
-    const int h = blockIdx.y, T = a.T, C = a.C, H = a.H, d = a.d, nt16 = NT16 ? NT16 : a.nt16;
+    const int T = a.T, C = a.C, H = a.H, d = a.d, nt16 = NT16 ? NT16 : a.nt16;
     // tiles of the chunk: tile index t (of the whole call) = b * NT + tile within the batch element. The groups of 4 NTT tiles of all batch
-    // elements, counted from the chunk's first, are dealt to the XCDs in eighths.
-    const int group = ((int)blockIdx.x & 7) * a.groups8 + ((int)blockIdx.x >> 3), bi = group / a.groups, gx = group - bi * a.groups;
-    if (bi >= a.nb) return;
-    const int b = a.b0 + bi;
+    // elements, counted from the chunk's first, each with all its heads, are dealt to the XCDs in eighths. (With whole
+    // groups to an XCD, 17 groups of 12 heads were 36 workgroups on five XCDs and none on two: 5.2 -> 4.4 us at 1088 tokens; the image of a
+    // head is small beside what the groups read. The arguments that everything waits for are asked for together, not behind the branch.)
+    asm volatile("" ::"s"(a.q_op), "s"(a.s_q), "s"(a.packed), "s"(a.L.image), "s"(a.L.image_bytes), "s"(a.I.head_bytes), "s"(a.NT), "s"(a.inv_groups), "s"(a.inv_h));
+    const int item = XcdShare::item(blockIdx.x, (unsigned)(a.groups * a.nb * H));
+    if (item < 0) return;
+    const int group = a.inv_h ? (int)__umulhi((unsigned)item, a.inv_h) : (int)((unsigned)item / (unsigned)H), h = item - group * H;
+    const int bi = a.inv_groups ? (int)__umulhi((unsigned)group, a.inv_groups) : (int)((unsigned)group / (unsigned)a.groups), gx = group - bi * a.groups, b = a.b0 + bi;
     const int lo = b * a.NT > a.tile0 ? b * a.NT : a.tile0, hi = (b + 1) * a.NT < a.tile1 ? (b + 1) * a.NT : a.tile1;
     const int first = lo + (gx * 4 + wave) * NTT;  // this wavefront's first tile
     if (lo + gx * 4 * NTT >= hi) return;           // (the whole workgroup)
@@ -424,8 +428,11 @@ template <int TPH, int NTT, int PG, int NT16>
 static hipError_t launch_attn_cfg(AttnOpArgs a, int tiles_b, int nb, hipStream_t st) {
     a.groups = (tiles_b + 4 * NTT - 1) / (4 * NTT);
     a.nb = nb;
-    a.groups8 = (a.groups * nb + 7) / 8;
-    hipLaunchKernelGGL((attn_op_kernel<TPH, NTT, PG, NT16>), dim3(8 * a.groups8, a.H), dim3(256), a.I.head_bytes + (TPH <= 5 ? 1024 * TPH : 0), st, a);
+    if ((long)a.groups * nb * a.H > XcdShare::MOST) return hipErrorInvalidValue;
+    const unsigned items = (unsigned)(a.groups * nb * a.H);
+    a.inv_h = inverse32(a.H, items);
+    a.inv_groups = inverse32(a.groups, (unsigned)(a.groups * nb));
+    hipLaunchKernelGGL((attn_op_kernel<TPH, NTT, PG, NT16>), dim3(XcdShare::grid(items)), dim3(256), a.I.head_bytes + (TPH <= 5 ? 1024 * TPH : 0), st, a);
     return hipGetLastError();
 }
 
@@ -476,7 +483,7 @@ hipError_t launch_attn_op(const StageChunk& c, const taq_shape& s, const uint8_t
     a.b0 = c.tile0 / c.NT;
     const int nb = (c.tile1 - 1) / c.NT - a.b0 + 1;
     const int tiles_b = nb == 1 ? c.tile1 - c.tile0 : c.NT;  // tiles of a batch element in the chunk, at most
-    if (nb > 65535) return hipErrorInvalidValue;
+    if (nb > 65535) return hipErrorInvalidValue;  // (nobody has K~/V~ of more: batch elements are a y dimension in taq_quantize_kv)
     switch ((a.d + 15) / 16) {
 #define TAQ_ATT(N) case N: return launch_attn_tph<N>(a, s.prob_grid, tiles_b, nb, st);
         TAQ_ATT(1) TAQ_ATT(2) TAQ_ATT(3) TAQ_ATT(4) TAQ_ATT(5) TAQ_ATT(6) TAQ_ATT(7) TAQ_ATT(8) TAQ_ATT(9) TAQ_ATT(10)

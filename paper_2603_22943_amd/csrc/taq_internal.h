@@ -446,7 +446,8 @@ struct AttnOpArgs {
     KvLayout L;
     KvImage I;
     int N, NT, tile0, tile1, b0, C, H, d, T, nt16;
-    int groups, groups8, nb;  // groups of tiles per batch element, per XCD; batch elements
+    int groups, nb;              // groups of tiles per batch element, batch elements
+    unsigned inv_groups, inv_h;  // inverse32 of groups and H
     float sig2;   // softmax scale * log2(e)
     float pmax;   // linear grid: 255 or 15; log2 grid: 256 (brings 2^-code * s_V to the linear grid's magnitudes)
     float plast;  // log2 grid: the last code, 255 or 15
