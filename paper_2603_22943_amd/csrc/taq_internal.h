@@ -166,15 +166,24 @@ static inline bool mid_supported(const taq_shape& s) {
 }
 // Whether the head-group path takes such a layer, or the kernel-per-stage path. Head groups save three launches and every
 // pass over the workspace but one, but each workgroup reads its share of Wq for 16 tokens only and fills a compute unit, so
-// the time goes with the rounds of 256 workgroups; the five stage kernels take 23 to 30 us at these sizes. Head groups and stages, us:
-// d = 160, 512 tokens (one round) 18.0 and 27.1, 576 (two) 25.8 and 28.2, 1024 (two, full) 29.5 and 28.5, 2048 51.6 and 34.3; row-major
-// weights 20.4 and 27.1 at 512, 30.1 and 29.3 at 576, 34.2 and 29.6 at 1024; d = 64, 800 tokens (two rounds) 24.2 and 27.6, row-major
-// 26.9 and 28.2, 1024 (three) 28.0 and 27.7, row-major 32.5 and 28.1, 1200 34.9 and 29.8. shape.tok_tile = 16 or 32 forces head groups or
-// stages (tests and tuning).
+// the time goes with the rounds of 256 workgroups (8 groups to a tile of 16 tokens at d = 160, 10 at d = 64); the five stage kernels
+// take 22 to 28 us at these sizes. Workgroups go to the 8 XCDs in turn, tiles fastest: where the number of tiles is a multiple of 8 a
+// tile's groups meet in one L2, of 4 in two, and where it is odd they are spread over all eight, which costs 2 to 5 us. Head groups and
+// stages, us, by tiles:
+//   d = 160: 31 21.9 and 26.1, 32 (one round) 18.4 and 25.8, 33 29.3 and 26.5, 34 27.4 and 26.5, 36 26.4 and 26.6, 40 25.8 and 26.8,
+//     48 26.1 and 26.9, 49 30.5 and 27.7, 52 28.5 and 28.0, 56 28.1 and 28.0, 64 30.1 and 28.2;
+//     row-major weights 31 24.5 and 26.7, 32 20.5 and 26.4, 36 30.0 and 27.6, 48 29.9 and 27.9;
+//   d = 64: 40 20.3 and 25.3, 49 25.6 and 26.6, 51 (two rounds) 26.0 and 26.8, 52 25.3 and 26.8, 53 30.8 and 27.2, 54 28.7 and 27.0,
+//     56 25.9 and 27.2, 60 27.1 and 27.6, 64 27.8 and 27.4, 68 27.7 and 28.1;
+//     row-major weights 25 (one round) 18.5 and 23.6, 26 22.0 and 23.1, 27 24.2 and 23.3, 30 24.4 and 24.3, 39 27.3 and 25.3, 40 23.3 and
+//     25.3, 42 25.6 and 25.5, 48 24.9 and 25.6, 49 28.7 and 27.4, 50 27.0 and 27.4, 52 29.9 and 27.6.
+// shape.tok_tile = 16 or 32 forces head groups or stages (tests and tuning).
 static inline bool mid_preferred(const taq_shape& s) {
     if (s.tok_tile) return s.tok_tile == 16;
-    const long rounds = ((long)s.B * ((s.N + 15) / 16) * mid_groups(s) + 255) / 256;
-    return rounds <= (s.C / s.H == 160 && s.w_layout != 1 ? 1 : 2);
+    const long tiles = (long)s.B * ((s.N + 15) / 16);
+    const bool wide = s.C / s.H == 160, packed = s.w_layout == 1;
+    const int any = wide ? 32 : packed ? 51 : 26, fours = wide ? (packed ? 48 : 32) : packed ? 60 : 48;
+    return tiles <= any || (tiles % 4 == 0 && tiles <= fours);
 }
 
 static inline KvLayout kv_layout(const taq_shape& s) {
