@@ -444,13 +444,14 @@ static hipError_t launch_attn_text(const AttnOpArgs& a, int tiles_b, int nb, hip
     return launch_attn_cfg<TPH, NTT, PG, 0>(a, tiles_b, nb, st);
 }
 
-// Two tiles per wavefront share the operand conversions, one is done sooner: at 20 heads of 64 5.2 and 6.3 us with 64 tokens, 9.0
-// and 9.5 us with 2048 (320 workgroups of two tiles per wavefront), 19.6 and 18.2 us with 8192; at 12 heads 12.3 and 11.4 us with
-// 4608 tokens (432 workgroups). Wide heads have no registers for two.
+// Two tiles per wavefront share the operand conversions, one is done sooner. One and two, us, by workgroups of two: heads of 64, 320
+// workgroups (2048 tokens of 20 heads) 6.9 and 7.5, 432 8.3 and 8.2, 600 9.9 and 10.4, 640 10.5 and 10.7, 768 11.8 and 11.1 (the layer
+// 46.5 and 46.1), 780 11.8 and 13.0, 960 14.0 and 13.8, 1280 16.9 and 16.0, 2048 24.0 and 22.1; of 32, 1128 11.6 and 11.6, 1536 13.9 and
+// 13.0; of 80, 384 8.7 and 9.2, 852 14.7 and 15.4; of 40, 1024 11.7 and 11.0. Wide heads have no registers for two.
 template <int TPH, int PG>
 static hipError_t launch_attn_grid(const AttnOpArgs& a, int tiles_b, int nb, hipStream_t st) {
     if constexpr (TPH <= 5) {
-        if ((long)((tiles_b + 7) / 8) * a.H * nb > 384) return launch_attn_text<TPH, PG, 2>(a, tiles_b, nb, st);
+        if ((long)((tiles_b + 7) / 8) * a.H * nb > 640) return launch_attn_text<TPH, PG, 2>(a, tiles_b, nb, st);
     }
     return launch_attn_text<TPH, PG, 1>(a, tiles_b, nb, st);
 }

@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
     (2, 784, 1280, 20),   # to_q, to_out: 25 blocks of 20 workgroups
     (1, 1088, 768, 12),   # attention: 17 groups of 12 heads
     (3, 1601, 512, 8),    # a group of the attention per batch element that is mostly empty
+    (2, 11003, 320, 4),   # two token tiles per wavefront, heads of 80
     (5, 37, 96, 4),       # a few workgroups
     (7, 1, 64, 1),        # one tile per batch element, one head
 ])
