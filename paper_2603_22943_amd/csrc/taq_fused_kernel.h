@@ -87,12 +87,9 @@ struct FusedCfg {
     static constexpr int NT = NG > 1 ? 512 : 64 * ROLES;  // threads (head-group variant: always eight wavefronts for the
                                                           // hidden codes and to_q; those without a role stop after to_q)
     static constexpr int TILE_RS = C + 16;        // bytes per token row of the int8 tile
-    // bytes of one head's image block at T = 96, in 1 KiB pieces (one direct-to-LDS load each)
-    static constexpr int IMG_HEAD_MAX = 96 * TPH * 16 + D * 96 + 3 * 96 * 4 + 32;
-    static constexpr int IMGC = (IMG_HEAD_MAX + 1023) / 1024;
-    // head_bytes of kv_image() at nt tiles of 16 text tokens
-    static constexpr int up16(int n) { return (n + 15) / 16 * 16; }
-    static constexpr int head_bytes(int nt) { return (16 * nt * TPH * 16 + up16(D * 16 * nt) + 3 * 16 * nt * 4 + 2 * 16 + 255) / 256 * 256; }
+    // one head's image block at nt tiles of 16 text tokens, and the 1 KiB pieces of the largest (one direct-to-LDS load each)
+    static constexpr int head_bytes(int nt) { return (int)kv_image(H, D, 16 * nt).head_bytes; }
+    static constexpr int IMGC = (head_bytes(TAQ_MAX_T / 16) + 1023) / 1024;
     // DENSE: the instantiation meant to run two workgroups per compute unit (layers with more token tiles than compute
     // units): at most 128 registers per lane, so the weights pass through a short ring instead of sitting in registers.
     static constexpr bool PREFETCH_W = TPH * KC <= 16 && NTT == 2 && NG == 1 && !DENSE;  // a head's whole weight slice in registers
@@ -197,7 +194,8 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint8_t*>(rq.packed) + dm.L.image + (size_t)b * dm.L.image_bytes + (size_t)h * dm.I.head_bytes, 0, (int)dm.I.head_bytes, 0x00020000);
         // the block is a multiple of 256 bytes: the last piece overlaps (a constant where the number of score tiles is fixed)
-        const int last = (NT16 ? F::head_bytes(NT16) : (int)dm.I.head_bytes) - 1024;
+        constexpr int fixed = NT16 ? F::head_bytes(NT16) : 0;
+        const int last = (NT16 ? fixed : (int)dm.I.head_bytes) - 1024;
 #pragma unroll
         for (int k = 0; k < F::IMGC; ++k) {
             if (k == 0 || k * 1024 < last + 1024) {  // (pieces past the block's end at this T are not fetched)

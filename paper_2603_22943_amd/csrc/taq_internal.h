@@ -17,7 +17,7 @@
 
 namespace taq {
 
-static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+static constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // ceil(2^32 / n), whose product with x has x / n as its high word while x * n < 2^32; 0 (divide) for n = 1 or a larger x
 static inline unsigned inverse32(unsigned n, unsigned long long x) {
@@ -56,8 +56,7 @@ struct KvLayout {
 
 // LDS-ready image of the integer part of K~/V~ for one batch element (with bits_kv = 16: no integer rows at all): one
 // self-contained block per head, so that the wavefront that owns a head copies and waits for its own
-// block only. Offsets are relative to the head block; head_bytes is a multiple of 1 KiB (the unit of
-// the direct-to-LDS copy).
+// block only. Offsets are relative to the head block.
 struct KvImage {
     int tph;        // 16-channel tiles per head = ceil(d/16)
     int nt16;       // ceil(T/16): score tiles of 16 text tokens
@@ -95,16 +94,16 @@ __host__ __device__ static inline int vt_pos(int t, int nt16) {
     return (t & ~31) + 8 * ((t >> 2) & 3) + 4 * ((t >> 4) & 1) + (t & 3);
 }
 
-static inline KvImage kv_image(const taq_shape& s) {
-    KvImage I;
-    const size_t H = s.H, d = s.C / s.H;
-    I.tph = (int)((d + 15) / 16);
-    I.nt16 = (s.T + 15) / 16;
+// (a constant expression: the fused kernels, which are compiled for a head size, take theirs from here)
+static constexpr KvImage kv_image(int H, int d, int T) {
+    KvImage I = {};
+    I.tph = (d + 15) / 16;
+    I.nt16 = (T + 15) / 16;
     I.ntok = 16 * I.nt16;
     I.rows_k = I.ntok;
     I.cols_v = I.ntok;
     size_t off = 0;
-    auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 16); return o; };
+    auto take = [&off](size_t bytes) { size_t o = off; off = align_up(off + bytes, 16); return o; };
     I.kp = take(I.rows_k * (size_t)I.tph * 16);
     I.vt = take(d * (size_t)I.cols_v);
     I.s_k = take(I.ntok * 4);
@@ -116,6 +115,7 @@ static inline KvImage kv_image(const taq_shape& s) {
     I.bytes = H * I.head_bytes;
     return I;
 }
+static inline KvImage kv_image(const taq_shape& s) { return kv_image(s.H, s.C / s.H, s.T); }
 
 // Operand-ordered copy of a [C, C] weight matrix: for head h, 16-row tile j of the head, K step ks (64 codes),
 // lane l = r + 16*q: the 16 codes W[min(h*d + 16*j + r, C-1)][64*ks + 16*q ...]; 1 KiB per (h, j, ks).
