@@ -255,8 +255,9 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     // touches 64 separate 16-byte pieces, which the texture path serves one per clock: 29.4 us at C = 640 and 2048 tokens.
     // Here four neighbouring lanes take the 64 contiguous bytes of a row, the two halves of a 128-byte line one after the
     // other (23.5 -> 19.5 us at 4096 tokens), and the lanes are exchanged through LDS: 18.3 us (operand-ordered weights: 15.0;
-    // an exchange by DPP selects in registers: 21.2). The KiB for it is the start of the head's K~/V~ block: to_q is done
-    // before the image arrives there, and to_out begins when the attention is through with it.
+    // an exchange by DPP selects in registers: 21.2). The KiB for it lies behind everything else (SLOTS); where it does not fit, it is
+    // the start of the head's K~/V~ block: the image is requested when to_q is done with it, and to_out begins when the attention is
+    // through with the image.
     static_assert(!ROWMAJ || (D % 16 == 0 && KC % 2 == 0), "whole tiles, whole 128-byte lines");
     const int rm_off = (h * D + (lane >> 2)) * C + 16 * (lane & 3);
     auto ring_load = [&](const __amdgpu_buffer_rsrc_t rs, int f) -> int32x4_t {  // the f-th load of a projection
@@ -317,8 +318,8 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
     };
 
     if constexpr (NG == 1) {
-        // ---- phase 0: issue every global read up front, oldest first in the order of use (loads return in
-        // order): hidden tile, weight scales, this head's to_q weight slice, the K~/V~ image
+        // ---- phase 0: the global reads, requested up front (loads return in order): the hidden tile, the K~/V~ image where it is
+        // requested early (both above), the weight scales, then between the steps of the quantizer this head's to_q weights
         constexpr int SCV = (3 * C / 4 + NT - 1) / NT;
         float4 scv[SCV];
     #pragma unroll
@@ -625,8 +626,8 @@ void fused_block_kernel(FusedTable<NG == 1 ? TAQ_MAX_REQ : 1> tab, FusedDims dm)
             for (int p = 1; p < KP; ++p) pacc[0][j] += *reinterpret_cast<const int32x4_t*>(qacc + ((p * TW + hl * TPH + j) * 64 + lane) * 4);
         }
     }
-    // Everything the Q~ step reads from LDS is fetched now, so that no LDS access sits between the issue of the
-    // image copy below and the wait for it (the compiler orders LDS accesses after outstanding direct-to-LDS loads).
+    // Everything the Q~ step reads from LDS is fetched now: where the image is requested below, no LDS access sits between that and
+    // the wait for it (the compiler orders LDS accesses after outstanding direct-to-LDS loads).
     float4 wq4[TPH];
     float shv[NTT];
 #pragma unroll
