@@ -104,12 +104,18 @@ def test_the_check_sees_a_planted_touch(between, found):
     assert len(touched_in_flight(kernels(PLANTED.format(between=between))["_Zk"])) == found
 
 
+ASSEMBLED = {}  # (a source takes up to 40 s)
+
+
 def assembly(source, tmp_path):
+    if source in ASSEMBLED:
+        return ASSEMBLED[source]
     out = str(tmp_path / (source + ".s"))
     include = os.path.join(os.path.dirname(B.HERE), "include")
     r = subprocess.run([B.hipcc_path()] + DEVICE_FLAGS + ["-I", include, os.path.join(B.CSRC, source), "-o", out], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
-    return kernels(open(out).read())
+    ASSEMBLED[source] = kernels(open(out).read())
+    return ASSEMBLED[source]
 
 
 def test_no_register_of_a_read_in_flight_is_touched(tmp_path):
