@@ -24,7 +24,9 @@ namespace taq {
 // A step is bound by what the wavefront issues in order: with all reads (10 clocks each) and all loads (each waits its turn at the
 // texture unit, 64 bytes a clock) in front of the products, a step took 150 clocks more than its products (16 clocks each). So a
 // product goes first, two reads follow each of the first ones and the loads lie evenly behind the others: to_out at 2048 tokens
-// of 1280 channels 8.3 -> 7.7 us. Scales and bias come with the first stage, not at the end. Of the sizes of tile, those that leave no
+// of 1280 channels 8.3 -> 7.7 us. A step now takes 360 clocks alone and 405 in sequence there, of which the products are 192 (to_q, two
+// wavefronts on a SIMD) and 160: 14 and 13 KiB come through the unit's path from L2 (18 clocks a KiB where nothing else is done) and 40
+// and 28 KiB out of LDS. Scales and bias come with the first stage, not at the end. Of the sizes of tile, those that leave no
 // compute unit with a second round (tile_cost below). to_q and to_out at C = 1280, us before and after:
 //   2048 tokens, heads of 64: 9.3 -> 7.9, 9.9 -> 7.7;  3072, heads of 160: 10.7 -> 9.0, 9.8 -> 8.4;  768, of 160: 8.7 -> 5.5, 6.6 -> 5.9;
 //   8192, of 64: 19.8 -> 17.9, 21.3 -> 18.6;  at C = 768 row-major, 4608 tokens: 7.4 -> 6.9, 8.0 -> 7.1.

@@ -1,7 +1,7 @@
 """Waits that the compiler does not place by itself, checked on the generated assembly of every kernel, over all paths. No GPU:
 hipcc cross-compiles.
 
-LDS reads written as inline asm (csrc/taq_gemm.hip): the compiler takes their results to be there at once, so between such a
+LDS reads written as inline asm (csrc/taq_gemm_op.h): the compiler takes their results to be there at once, so between such a
 read and the wait for it no instruction may touch its destination registers, neither the arithmetic that uses the operands nor
 anything the compiler places into registers it believes free.
 
