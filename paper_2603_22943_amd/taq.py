@@ -135,7 +135,10 @@ def _scratch(n: int, dev, stream) -> torch.Tensor:
     """A workspace for one call: memory of the stream that the call runs on, so that giving it back there is in order."""
     if stream is None:
         return torch.empty(n, dtype=torch.uint8, device=dev)
-    with torch.cuda.stream(torch.cuda.ExternalStream(_stream(stream), device=dev)):
+    if not isinstance(stream, torch.cuda.Stream):  # a raw handle (ExternalStream takes that of the default stream, 0, for none)
+        handle = _stream(stream)
+        stream = torch.cuda.ExternalStream(handle, device=dev) if handle else torch.cuda.default_stream(dev)
+    with torch.cuda.stream(stream):
         return torch.empty(n, dtype=torch.uint8, device=dev)
 
 
