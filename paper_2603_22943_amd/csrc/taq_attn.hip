@@ -371,8 +371,7 @@ void attn_op_kernel(AttnOpArgs a) {
                         for (int i = 0; i < 4; ++i) phi[nt][4 * u + i] = plo[nt][4 * u + i] = (_Float16)0.f;
                 }
             }
-            if constexpr (TPH <= 3)  // (more blocks: far more than 8 instructions in between)
-                if (!second && s > 0) sums_settle(oacc);
+            if (!second && s > 0) sums_settle(oacc);
 #pragma unroll
             for (int k = 0; k < TPH; ++k) {
                 const int j = 16 * k + r16 < d ? 16 * k + r16 : d - 1;

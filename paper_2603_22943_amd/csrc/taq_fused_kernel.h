@@ -871,8 +871,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
                             }
                     }
                 }
-                if constexpr (DENSE || KNOWN)  // (elsewhere there are 20 instructions and more in between)
-                    if (!second && s > 0) sums_settle(oacc);
+                if (!second && s > 0) sums_settle(oacc);
 #pragma unroll
                 for (int k = 0; k < TPH; ++k) {
                     int j = 16 * k + r16;
