@@ -371,36 +371,31 @@ int taq_cross_attn_batched(int R, const taq_request* table, const taq_shape* sha
         taq_shape s = *shape;
         per = attn_workspace(s).total > per ? attn_workspace(s).total : per;
     }
-    if (R == 1)
-        return taq_cross_attn_ex(table->hidden, table->qkv_packed, table->Wq, table->Wo, table->scales, table->trigger_mask, shape, table->out,
-                                 workspace, hip_stream, nullptr);
-    // grouped launches: up to 16 requests share a kernel through a pointer table in the arguments
-    const int heads = grouped_heads(*shape, R < TAQ_MAX_REQ ? R : TAQ_MAX_REQ);
-    if (heads || fused_supported(*shape)) {
-        hipStream_t st = static_cast<hipStream_t>(hip_stream);
-        for (int r0 = 0; r0 < R; r0 += TAQ_MAX_REQ) {
+    // grouped launches: up to 16 requests share a kernel through a pointer table in the arguments; what goes out alone goes as a single call
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    for (int r0 = 0; r0 < R;) {
+        const GroupedLaunch g = grouped_launch(*shape, R - r0);
+        uint8_t* ws = static_cast<uint8_t*>(workspace) + (size_t)r0 * per;
+        if (g.n == 1) {
+            const taq_request& q = table[r0];
+            rc = taq_cross_attn_ex(q.hidden, q.qkv_packed, q.Wq, q.Wo, q.scales, q.trigger_mask, shape, q.out, ws, hip_stream, nullptr);
+            if (rc != TAQ_OK) return rc;
+        } else {
             FusedReq rq[TAQ_MAX_REQ];
-            const int n = R - r0 < TAQ_MAX_REQ ? R - r0 : TAQ_MAX_REQ;
-            for (int i = 0; i < n; ++i) {
+            for (int i = 0; i < g.n; ++i) {
                 const taq_request& q = table[r0 + i];
                 rq[i] = {static_cast<const __half*>(q.hidden), static_cast<const uint8_t*>(q.qkv_packed), q.Wq, q.Wo,
                          q.scales, static_cast<__half*>(q.out)};
             }
-            if (heads) {
-                const StageChunk c = stage_chunk(*shape, static_cast<uint8_t*>(workspace) + (size_t)r0 * per, 0, stage_tiles(*shape));
-                TAQ_TRY_HIP(launch_heads(c, *shape, rq, n, per, heads, nullptr, st));
-                TAQ_TRY_HIP(launch_to_out_tail(c, *shape, rq, n, per, nullptr, st));
+            if (g.heads) {
+                const StageChunk c = stage_chunk(*shape, ws, 0, stage_tiles(*shape));
+                TAQ_TRY_HIP(launch_heads(c, *shape, rq, g.n, per, g.heads, nullptr, st));
+                TAQ_TRY_HIP(launch_to_out_tail(c, *shape, rq, g.n, per, nullptr, st));
             } else {
-                TAQ_TRY_HIP(launch_fused_block(rq, n, *shape, nullptr, st));
+                TAQ_TRY_HIP(launch_fused_block(rq, g.n, *shape, nullptr, st));
             }
         }
-        return TAQ_OK;
-    }
-    for (int r = 0; r < R; ++r) {
-        const taq_request& q = table[r];
-        rc = taq_cross_attn_ex(q.hidden, q.qkv_packed, q.Wq, q.Wo, q.scales, q.trigger_mask, shape, q.out,
-                               static_cast<uint8_t*>(workspace) + (size_t)r * per, hip_stream, nullptr);
-        if (rc != TAQ_OK) return rc;
+        r0 += g.n;
     }
     return TAQ_OK;
 }

@@ -217,6 +217,16 @@ static inline int grouped_heads(const taq_shape& s, int R) {
     return t <= 20 || (!packed && n >= 64) ? 1 : 2;
 }
 
+// The next launch of a batched call with `left` requests to go: how many of them it takes, and their head groups' tiles of 16 tokens per workgroup
+// (0: the single kernel, or request after request). Asked for each launch of up to 16: of 17 requests the last goes out as a call of one does.
+struct GroupedLaunch {
+    int n, heads;
+};
+static inline GroupedLaunch grouped_launch(const taq_shape& s, int left) {
+    const int n = left < TAQ_MAX_REQ ? left : TAQ_MAX_REQ, heads = grouped_heads(s, n);
+    return {heads || fused_supported(s) ? n : 1, heads};
+}
+
 static inline KvLayout kv_layout(const taq_shape& s) {
     KvLayout L;
     size_t off = 0;

@@ -91,6 +91,8 @@ def test_head_groups_of_640_channels(B, N, H, more, forced, protected):
     (2, 1, 1, 1280, 8, dict(w_layout=1)),
     (3, 2, 23, 1280, 20, dict(w_layout=1)),                      # 12 tiles: one per workgroup
     (17, 1, 40, 1280, 8, dict(bits_kv=4)),                       # two, an odd number of them; a second launch of one request
+    (17, 1, 16 * 103, 1280, 20, dict(w_layout=1)),               # ... of one that stages take
+    (18, 1, 16 * 17 - 3, 320, 8, dict(w_layout=1)),              # the single kernel: 16, then two
     (5, 3, 70, 1280, 20, dict(prob_grid=1)),
     (2, 1, 16 * 100, 1280, 20, dict(w_layout=1, prob_grid=2)),   # the last size, and the next: request after request
     (2, 1, 16 * 101, 1280, 20, dict(w_layout=1)),
