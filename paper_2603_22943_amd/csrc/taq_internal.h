@@ -158,46 +158,51 @@ static inline bool mid_supported(const taq_shape& s) {
     return s.N <= 16 * 65535;
 }
 // Which kernels take such a layer. In front: the head-group kernel (taq_heads_kernel.h), with one or two tiles of 16 tokens to a workgroup,
-// or three kernels of the stage path. Behind: to_out_tail_kernel, or two kernels of the stage path. us per layer by tiles of 16 tokens;
-// "1t", "2t", "1", "2": head groups of one and two tiles, with and without the tail kernel; "s": stages.
-//   d = 160: 16 1t 13.0, s 24.9; 32 1t 13.9, 2t 16.3, s 25.8; 33 1t 19.8, 2t 17.3, s 25.9; 51 1t 20.9, 2t 18.1, 2 20.8; 52 2t 20.5, 1 23.2, 2 20.7;
-//     64 2t 20.9, 1 23.7, 2 21.1, s 27.6; 65 1 28.3, 2 29.3, s 29.7; 80 1 29.1, s 30.4; 96 1t 31.8, 1 30.0, 2 30.4, s 30.9; 97 1 34.5, 2 30.4, s 31.3;
-//     row-major weights 32 1t 16.4, 2t 18.9, s 26.8; 33 1t 23.6, 2t 19.9; 64 2t 23.5, 2 22.9, s 29.4; 65 1 32.5, s 31.7; 80 2 33.2, s 33.1;
-//     64 and 90 tokens of text: 52 1t 24.3, 1 24.1, s 28.5; 64 1 25.5, s 30.4; 96 1 33.0, s 33.9; row-major 64 1 27.5, s 30.7; 65 1 35.5, s 34.6;
-//   d = 64: 16 1t 13.3, s 21.0; 25 1t 13.5, s 23.8; 51 1t 18.7, 2t 21.3, s 26.3; 52 1t 24.5, 1 23.7, 2 23.9, s 26.6; 64 1 24.6, 2 24.6, s 27.0;
-//     80 1 27.4, 2 25.3, s 28.1; 102 1 28.8, 2 27.2, s 31.2; 103 2 32.0, s 31.1;
-//     row-major weights 25 1t 15.1, s 24.3; 51 1t 21.7, 1 22.7, s 26.7; 52 1t 27.1, 1 26.5, s 26.8; 72 1 28.1, s 29.2; 80 1 31.2, s 29.8.
+// or three kernels of the stage path. Behind: to_out_tail_kernel, or two kernels of the stage path. us per layer by tiles of 16 tokens, six
+// layers with weights, inputs and outputs of their own in turn, 77 text tokens; "1t", "2t", "1", "2": head groups of one and two tiles, with and
+// without the tail kernel; "s": stages.
+//   d = 160: 4 1t 11.7, s 24.3; 32 1t 14.5, 2t 18.3, s 26.2; 33 1t 21.1, 2t 19.5, s 26.7; 51 2t 20.6, 2 22.9, s 27.8; 52 2t 22.8, 2 22.8, 1 24.1, s 27.8;
+//     64 2t 23.0, 2 22.7, 1 24.8, s 28.1; 65 1 28.3, 2 31.5, s 30.7; 80 1 29.1, 2 29.5, s 31.1; 88 1 30.7, s 31.6; 96 1 32.5, 2 33.1, s 31.7;
+//     row-major weights 32 1t 17.4, s 27.2; 33 1t 25.2, 2t 22.4; 52 2t 25.2, 2 24.9; 64 2 24.7, 1 27.8, s 29.4; 65 1 32.9, s 32.7; 80 2 33.1, s 32.9;
+//     64 tokens of text 51 1t 23.0, 1 25.3, s 29.2; 64 1 25.9, s 29.7; 88 1 32.2, s 33.1; 96 1 34.1, s 32.9;
+//   d = 64: 25 1t 14.5, s 24.7; 51 1t 19.3, 2t 22.1, s 27.0; 52 1t 26.1, 1 26.1, s 27.0; 80 1 28.1, 2 27.2, s 28.9; 102 1 30.7, 2 28.9, s 31.9;
+//     103 1 32.1, 2 34.6, s 31.9; row-major weights 25 1t 16.5, s 24.9; 51 1t 22.1, 1 23.7, s 27.4; 52 1 28.5, s 27.6; 80 1 31.9, s 30.6.
 // The lines are rounds of workgroups: two of the head-group kernel share a compute unit (512 of them: 32 and 64 groups of 8 heads, 51 of
 // 10; two tiles of d = 64 with row-major weights leave no LDS for that), and two of the tail kernel (10 to a tile).
 // shape.tok_tile = 16 or 32 forces head groups (of one tile, with the tail kernel) or stages (tests and tuning).
 //
 // C = 640: the single kernel ("f") takes 14 us however few tokens there are, as every workgroup pulls both weight matrices (820 KB) through
-// one compute unit; a head group pulls a quarter or a fifth of one of them. 77 text tokens:
-//   d = 80: 1 1t 9.2, f 14.3; 32 1t 10.8, f 14.4; 64 1t 11.9, f 14.3; 72 1t 13.8, f 14.3; 80 1t 14.0, f 14.1; 96 1t 14.5, f 14.1; 128 2t 15.6, f 14.2;
-//     row-major weights 32 1t 12.0, f 17.8; 64 1t 13.3, 2t 15.2, f 17.7; 65 1t 16.2, 2t 15.3; 128 2t 17.2, f 17.6; 130 1t 22.0, f 17.7;
-//   d = 64: 1 1t 9.0, f 14.2; 51 1t 10.8, f 14.7; 64 1t 13.1, f 14.7; 102 1t 13.9, f 14.7; 103 1t 16.0, f 14.8;
-//     row-major weights 51 1t 12.0, 2t 13.8, f 17.3; 52 1t 14.6, 2t 14.6; 102 1t 15.9, 2t 15.4, f 17.1; 103 2t 19.0, f 17.2.
+// one compute unit; a head group pulls a quarter or a fifth of one of them.
+//   d = 80: 1 1t 9.3, f 13.5; 32 1t 10.5, f 14.2; 64 1t 11.9, f 13.9; 72 1t 13.3, f 13.9; 74 1t 14.2, f 13.9; 80 1t 14.1, f 13.9;
+//     row-major weights 32 1t 11.7, f 17.5; 64 1t 13.4, 2t 15.5, f 17.3; 65 1t 15.2, 2t 16.3; 96 1t 16.6, 2t 16.8, f 17.4; 100 1t 17.0, f 17.3; 104 1t 17.8,
+//     2t 18.0, f 17.3; 128 1t 18.4, 2t 18.2, f 17.5;
+//   d = 64: 1 1t 9.7, f 14.4; 51 1t 11.8, f 14.7; 64 1t 12.1, f 14.6; 102 1t 14.4, f 14.6; 103 1t 15.9, f 14.6;
+//     row-major weights 51 1t 12.8, 2t 14.9, f 17.2; 52 1t 14.1, 2t 15.2; 102 1t 16.2, 2t 16.7, f 17.1; 103 2t 19.4, f 17.1.
 // (One round of workgroups, one to a compute unit or two: 64 and 128 groups of 4, 51 and 102 of 5.) Other lengths of text, one tile: the
-// same lines, but for row-major weights at d = 80 (64 tokens of text: 64 13.7, f 18.9; 80 19.6, f 18.9). At d = 64 and more than 80
-// tokens of text the single kernel does not fit and stages are what is compared with: 51 12.3, s 21.1; 102 15.0, s 23.3.
+// same lines, but for row-major weights at d = 80. At d = 64 and more than 80 tokens of text the single kernel does not fit and stages are
+// what is compared with: 51 13.1, s 21.5; 102 16.0, s 23.6.
 // shape.tok_tile = 16 or 32 forces the single kernel of as many tokens, or stages.
+// Workgroups of two tiles (per head group): both tiles of one are of the same batch element, so one element's last workgroup may have one only.
+// The lines of the two-tile forms count these. us, two tiles per workgroup and one: d = 160, 64 elements of 16 tokens 31.2 and 25.4 (stages
+// 30.1), 12 of 80 tokens 31.0 and 24.7 (stages 28.5), row-major 34.7 and 28.2; d = 64, 100 of 16 39.9 and 33.5, 34 of 48 35.2 and 30.6; C = 640,
+// row-major, 18 of 112 25.6 and 18.6 (single kernel 17.8).
+static inline long tile_pairs(const taq_shape& s) { return (long)s.B * (((s.N + 15) / 16 + 1) / 2); }
 struct HeadsPlan {
     int tiles;  // tiles of 16 tokens per workgroup of the head-group kernel; 0: stages in front
     bool tail;  // to_out_tail_kernel behind it
 };
 static inline HeadsPlan heads_plan(const taq_shape& s) {
     if (s.tok_tile) return {s.tok_tile == 16 && s.C == 1280 ? 1 : 0, true};
-    const long tiles = (long)s.B * ((s.N + 15) / 16);
+    const long tiles = (long)s.B * ((s.N + 15) / 16), pairs = tile_pairs(s);
     const bool wide = s.C / s.H == 160, packed = s.w_layout == 1, two = (s.T + 15) / 16 == 5;  // (two tiles: 65 to 80 text tokens only)
-    if (s.C == 640 && s.H == 8) return {tiles <= (packed ? 80 : 64) ? 1 : !packed && two && tiles <= 128 ? 2 : 0, true};
-    if (s.C == 640) return {tiles > 102 ? 0 : !packed && two && tiles > 51 ? 2 : 1, true};
-    if (wide) return {tiles <= 32 ? 1 : tiles <= 64 ? (two ? 2 : 1) : packed && tiles <= 96 ? 1 : 0, tiles <= 51};
+    if (s.C == 640 && s.H == 8) return {tiles <= (packed ? 80 : 64) ? 1 : !packed && two && pairs <= 64 ? 2 : 0, true};
+    if (s.C == 640) return {tiles > 102 ? 0 : !packed && two && tiles > 51 && pairs <= 51 ? 2 : 1, true};
+    if (wide) return {tiles <= 32 ? 1 : tiles <= 64 ? (two && pairs <= 32 ? 2 : 1) : packed && tiles <= 96 ? 1 : 0, tiles <= 51};
     if (!packed || !two) return {tiles <= 51 ? 1 : 0, true};
-    return {tiles < 80 ? 1 : tiles <= 102 ? 2 : 0, tiles <= 51};
+    return {tiles < 80 ? 1 : tiles <= 102 ? (pairs <= 51 ? 2 : 1) : 0, tiles <= 51};
 }
-static inline bool mid_preferred(const taq_shape& s) { return heads_plan(s).tiles > 0; }
 // R requests in grouped launches of the head-group kernels: tiles of 16 tokens per workgroup, or 0 (the single kernel, or request after
-// request). n: tiles of a request, t: of all. us per call, "1" and "2" grouped with one and two tiles, "r" request after request, "f" the
+// request). n: tiles of a request, t: of all, e: of a request as workgroups of two count them. us per call, "1" and "2" grouped with one and two tiles, "r" request after request, "f" the
 // single kernel's grouped launch; 77 text tokens, operand-ordered weights where nothing else is said.
 //   C = 1280, d = 160: R x n = 2 x 2 1 12.9, r 24.2; 2 x 16 1 17.6, 2 19.9, r 27.3; 16 x 2 1 25.8, 2 24.3, r 187; 4 x 10 1 29.4, 2 24.8, r 52; 16 x 32 2 148,
 //     r 254; 2 x 100 2 62.5, r 65.6; 4 x 128 2 124, r 135; 6 x 160 2 241, r 259; 2 x 160 2 81, r 76; row-major 2 x 16 1 19.2, 2 21.7; 6 x 6 1 32.0, 2 26.7;
@@ -206,15 +211,17 @@ static inline bool mid_preferred(const taq_shape& s) { return heads_plan(s).tile
 //     6 x 8 1 34.8, 2 30.0, r 89; 2 x 64 1 49.4, 2 51.4, r 57.8; 2 x 100 1 69, r 65; 6 x 100 1 186, r 214; 6 x 160 1 284, r 267;
 //   C = 640, d = 80: 2 x 24 1 12.7, f 13.2; 3 x 16 1 13.2, f 16.2; 6 x 10 1 16.5, f 16.2; row-major 6 x 10 1 17.4, f 19.6; 16 x 6 1 24.9, f 19.2; d = 64: 3 x 16 1 13.0,
 //     f 16.5; 2 x 32 1 14.3, f 14.2; row-major 6 x 10 1 19.0, f 19.1; more text than the single kernel takes: 16 x 16 1 40, r 189; 2 x 160 1 44, r 53.
+// Requests of several elements (elements x tiles): d = 160, 16 x (3 x 1) 1 36.3, 2 40.9; 16 x (2 x 3) 1 62.8, 2 56.6; 2 x (20 x 5) 2 61.5, r 67.1; 2 x (34 x 3)
+//     2 70.5, r 68.9; 6 x (40 x 3) 2 216, r 222; 6 x (50 x 3) 2 273, r 255; 6 x (160 x 1) 2 396, r 308; d = 64, row-major, 2 x (21 x 3) 1 46.2, 2 59.4, r 57.1.
 static inline int grouped_heads(const taq_shape& s, int R) {
     if (!mid_supported(s) || s.tok_tile || R < 2) return 0;
-    const long n = (long)s.B * ((s.N + 15) / 16), t = R * n;
-    const bool packed = s.w_layout == 1, two = (s.T + 15) / 16 == 5;
+    const long n = (long)s.B * ((s.N + 15) / 16), t = R * n, e = 2 * tile_pairs(s);
+    const bool packed = s.w_layout == 1, two = (s.T + 15) / 16 == 5 && s.N > 16;
     if (s.C == 640) return fused_supported(s) ? t <= (s.H == 8 ? (packed ? 48 : 64) : 51) : n <= 160;
-    if (n > (packed && two ? (R < 6 ? 100 : 160) : R < 4 ? 64 : 100)) return 0;
+    if (n > (packed && two ? (R < 6 ? 100 : 160) : R < 4 ? 64 : 100) || (packed && two && e > (R < 6 ? 120 : 160))) return 0;
     if (!two) return 1;
     if (s.C / s.H == 160) return t <= 32 ? 1 : 2;
-    return t <= 20 || (!packed && n >= 64) ? 1 : 2;
+    return t <= 20 || (!packed && e >= 64) ? 1 : 2;
 }
 
 // The next launch of a batched call with `left` requests to go: how many of them it takes, and their head groups' tiles of 16 tokens per workgroup

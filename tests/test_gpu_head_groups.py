@@ -21,6 +21,8 @@ from paper_2603_22943_amd import taq as T
     (1, 600, 8, dict(text=64)),                           # other lengths of text: one tile per workgroup
     (2, 330, 20, dict(text=96, w_layout=1)),
     (1, 16 * 96 - 3, 8, dict(w_layout=1)),                # one tile, stage kernels behind
+    (12, 77, 8, dict()),                                  # ... 60 tiles that would be 36 workgroups of two
+    (20, 80, 20, dict(w_layout=1, prob_grid=2)),
     (1, 16 * 64, 8, dict(text=48, w_layout=1)),
     # to_out: 2 or 4 output tiles per workgroup, K range shared by 4 or 2 wavefronts; 8; 10: the last size of each and the next
     (1, 16 * 6, 8, dict(w_layout=1)),

@@ -1,5 +1,5 @@
-"""Which kernels take a C = 1280 layer, against timings of both: tests/host/mid_rule.cpp on the CPU; on the GPU both give the same bits
-on either side of each line."""
+"""Which kernels take a C = 1280 or 640 layer or batched call, against timings of all forms: tests/host/mid_rule.cpp on the CPU; on the GPU head
+groups and stages give the same bits on either side of each line."""
 import os
 import subprocess
 
