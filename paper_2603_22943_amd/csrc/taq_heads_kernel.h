@@ -633,11 +633,12 @@ static hipError_t launch_heads_tiles(const HeadsManyArgs& a, int R, int tiles_b,
     // 65 to 80 text tokens: no run-time guards around the score tiles, no taps
     const bool taps = a.a.dbg.h_code || a.a.dbg.s_h || a.a.dbg.q_code || a.a.dbg.s_Q || a.a.dbg.O || a.a.dbg.p_code;
     if (a.a.nt16 != 5 || taps) return launch_heads_one<D, NH, NG, 1, PG, 0, ROWMAJ>(a, R, tiles_b, st);
-    if (tt == 2) return launch_heads_one<D, NH, NG, 2, PG, 5, ROWMAJ>(a, R, tiles_b, st);
+    if constexpr (D * NH * NG == 1280)
+        if (tt == 2) return launch_heads_one<D, NH, NG, 2, PG, 5, ROWMAJ>(a, R, tiles_b, st);
     return launch_heads_one<D, NH, NG, 1, PG, 5, ROWMAJ>(a, R, tiles_b, st);
 }
 
-// tt: token tiles per workgroup, 1 or 2
+// tt: token tiles per workgroup, 1 or (C = 1280) 2
 template <int D, int NH, int NG>
 static hipError_t launch_heads_cfg(const HeadsManyArgs& a, int R, int grid, int tiles_b, int tt, bool packed, hipStream_t st) {
     if (grid == TAQ_PROB_LOG2) return packed ? launch_heads_tiles<D, NH, NG, TAQ_PROB_LOG2, false>(a, R, tiles_b, tt, st) : launch_heads_tiles<D, NH, NG, TAQ_PROB_LOG2, true>(a, R, tiles_b, tt, st);

@@ -178,14 +178,14 @@ static inline bool mid_supported(const taq_shape& s) {
 //     2t 18.0, f 17.3; 128 1t 18.4, 2t 18.2, f 17.5;
 //   d = 64: 1 1t 9.7, f 14.4; 51 1t 11.8, f 14.7; 64 1t 12.1, f 14.6; 102 1t 14.4, f 14.6; 103 1t 15.9, f 14.6;
 //     row-major weights 51 1t 12.8, 2t 14.9, f 17.2; 52 1t 14.1, 2t 15.2; 102 1t 16.2, 2t 16.7, f 17.1; 103 2t 19.4, f 17.1.
-// (One round of workgroups, one to a compute unit or two: 64 and 128 groups of 4, 51 and 102 of 5.) Other lengths of text, one tile: the
-// same lines, but for row-major weights at d = 80. At d = 64 and more than 80 tokens of text the single kernel does not fit and stages are
-// what is compared with: 51 13.1, s 21.5; 102 16.0, s 23.6.
+// (One round of workgroups, one to a compute unit or two: 64 groups of 4, 51 and 102 of 5; at 65 to 100 and row-major weights the second round
+// costs less than the single kernel's exchange of lanes.) Two tiles to a workgroup are the faster form at no size where head groups are the
+// faster kernels. Other lengths of text: the same lines, but for row-major weights at d = 80 (64). At d = 64 and more than 80 tokens of text the
+// single kernel does not fit and stages are what is compared with: 51 13.1, s 21.5; 102 16.0, s 23.6.
 // shape.tok_tile = 16 or 32 forces the single kernel of as many tokens, or stages.
 // Workgroups of two tiles (per head group): both tiles of one are of the same batch element, so one element's last workgroup may have one only.
 // The lines of the two-tile forms count these. us, two tiles per workgroup and one: d = 160, 64 elements of 16 tokens 31.2 and 25.4 (stages
-// 30.1), 12 of 80 tokens 31.0 and 24.7 (stages 28.5), row-major 34.7 and 28.2; d = 64, 100 of 16 39.9 and 33.5, 34 of 48 35.2 and 30.6; C = 640,
-// row-major, 18 of 112 25.6 and 18.6 (single kernel 17.8).
+// 30.1), 12 of 80 tokens 31.0 and 24.7 (stages 28.5), row-major 34.7 and 28.2; d = 64, 100 of 16 39.9 and 33.5, 34 of 48 35.2 and 30.6.
 static inline long tile_pairs(const taq_shape& s) { return (long)s.B * (((s.N + 15) / 16 + 1) / 2); }
 struct HeadsPlan {
     int tiles;  // tiles of 16 tokens per workgroup of the head-group kernel; 0: stages in front
@@ -194,9 +194,9 @@ struct HeadsPlan {
 static inline HeadsPlan heads_plan(const taq_shape& s) {
     if (s.tok_tile) return {s.tok_tile == 16 && s.C == 1280 ? 1 : 0, true};
     const long tiles = (long)s.B * ((s.N + 15) / 16), pairs = tile_pairs(s);
-    const bool wide = s.C / s.H == 160, packed = s.w_layout == 1, two = (s.T + 15) / 16 == 5;  // (two tiles: 65 to 80 text tokens only)
-    if (s.C == 640 && s.H == 8) return {tiles <= (packed ? 80 : 64) ? 1 : !packed && two && pairs <= 64 ? 2 : 0, true};
-    if (s.C == 640) return {tiles > 102 ? 0 : !packed && two && tiles > 51 && pairs <= 51 ? 2 : 1, true};
+    const bool wide = s.C / s.H == 160, packed = s.w_layout == 1, two = (s.T + 15) / 16 == 5;  // (two tiles: C = 1280, 65 to 80 text tokens)
+    if (s.C == 640 && s.H == 8) return {tiles <= (packed ? 80 : two ? 100 : 64) ? 1 : 0, true};
+    if (s.C == 640) return {tiles <= 102 ? 1 : 0, true};
     if (wide) return {tiles <= 32 ? 1 : tiles <= 64 ? (two && pairs <= 32 ? 2 : 1) : packed && tiles <= 96 ? 1 : 0, tiles <= 51};
     if (!packed || !two) return {tiles <= 51 ? 1 : 0, true};
     return {tiles < 80 ? 1 : tiles <= 102 ? (pairs <= 51 ? 2 : 1) : 0, tiles <= 51};

@@ -59,14 +59,15 @@ def test_head_groups_and_stages_agree(B, N, H, more, protected):
     (4, 16 * 13, 8, dict(w_layout=1), 16),                  # to_out: 10 output tiles per workgroup
     (1, 16 * 64 - 1, 8, dict(), 16),
     (3, 201, 8, dict(bits_kv=4), 16),                       # row-major weights, one tile per workgroup
-    (1, 1419, 8, dict(bits_kv=4), 16),                      # ... two; an odd number of tiles
+    (1, 1419, 8, dict(bits_kv=4), 16),                      # ... in more than one round
+    (14, 77, 8, dict(), 16),
     (2, 1021, 8, dict(prob_grid=2), 16),
     (5, 33, 8, dict(text=64), 16),                          # other lengths of text
     (1, 1009, 8, dict(text=96, w_layout=1, prob_grid=2), 16),
     (1, 17, 10, dict(w_layout=1, prob_grid=2), 16),         # heads of 64
     (2, 16 * 51 - 9, 10, dict(w_layout=1), 16),
     (1, 810, 10, dict(bits_kv=4), 16),
-    (3, 530, 10, dict(prob_grid=1), 16),                    # two tiles per workgroup, an odd number per batch element
+    (3, 530, 10, dict(prob_grid=1), 16),                    # an odd number of tiles per batch element
     (2, 300, 10, dict(text=33), 16),
     (2, 300, 10, dict(text=96), 32),                        # more text than the single kernel has LDS for: against the stages
     (1, 16 * 102, 10, dict(text=81, w_layout=1, prob_grid=2), 32),
@@ -150,7 +151,7 @@ def test_the_image_has_arrived(tmp_path, source):
     from test_waits import assembly, barriers_with_lds_loads_in_flight
 
     bodies = {k: b for k, b in assembly(source, tmp_path).items() if "heads_kernel" in k}
-    assert len(bodies) == 36
+    assert len(bodies) == (24 if source in ("taq_heads80.hip", "taq_heads64x10.hip") else 36)  # (C = 640: no two tiles per workgroup)
     for name, body in bodies.items():
         marked = [(no, "load_lds " + text if text.startswith("buffer_load") and text.endswith(" lds") else text, hand) for no, text, hand in body]
         barriers = [no for no, text, _ in body if text == "s_barrier"]
