@@ -168,7 +168,8 @@ static inline bool mid_supported(const taq_shape& s) {
 //   d = 64: 25 1t 14.5, s 24.7; 51 1t 19.3, 2t 22.1, s 27.0; 52 1t 26.1, 1 26.1, s 27.0; 80 1 28.1, 2 27.2, s 28.9; 102 1 30.7, 2 28.9, s 31.9;
 //     103 1 32.1, 2 34.6, s 31.9; row-major weights 25 1t 16.5, s 24.9; 51 1t 22.1, 1 23.7, s 27.4; 52 1 28.5, s 27.6; 80 1 31.9, s 30.6.
 // The lines are rounds of workgroups: two of the head-group kernel share a compute unit (512 of them: 32 and 64 groups of 8 heads, 51 of
-// 10; two tiles of d = 64 with row-major weights leave no LDS for that), and two of the tail kernel (10 to a tile).
+// 10; two tiles of d = 64 with row-major weights leave no LDS for that), and two of the tail kernel (10 to a tile). Above 64 tiles of d = 160 it is what the
+// partly filled second round is worth: up to 88 tiles faster for 1, 2, 4 and 8 elements, at 92 for 1 (31.1, s 31.7) and not for 2 (32.4, s 31.4).
 // shape.tok_tile = 16 or 32 forces head groups (of one tile, with the tail kernel) or stages (tests and tuning).
 //
 // C = 640: the single kernel ("f") takes 14 us however few tokens there are, as every workgroup pulls both weight matrices (820 KB) through
@@ -178,8 +179,9 @@ static inline bool mid_supported(const taq_shape& s) {
 //     2t 18.0, f 17.3; 128 1t 18.4, 2t 18.2, f 17.5;
 //   d = 64: 1 1t 9.7, f 14.4; 51 1t 11.8, f 14.7; 64 1t 12.1, f 14.6; 102 1t 14.4, f 14.6; 103 1t 15.9, f 14.6;
 //     row-major weights 51 1t 12.8, 2t 14.9, f 17.2; 52 1t 14.1, 2t 15.2; 102 1t 16.2, 2t 16.7, f 17.1; 103 2t 19.4, f 17.1.
-// (One round of workgroups, one to a compute unit or two: 64 groups of 4, 51 and 102 of 5; at 65 to 100 and row-major weights the second round
-// costs less than the single kernel's exchange of lanes.) Two tiles to a workgroup are the faster form at no size where head groups are the
+// (One round of workgroups, one to a compute unit or two: 64 groups of 4, 51 and 102 of 5; behind it the second round grows from unit to unit: up to 72 groups
+// of 4 most calls are still ahead (4 elements of 18 13.4, 8 of 9 13.1, but 2 of 36 14.6), and 100 with row-major weights, which cost the single
+// kernel 3.5 us.) Two tiles to a workgroup are the faster form at no size where head groups are the
 // faster kernels. Other lengths of text: the same lines, but for row-major weights at d = 80 (64). At d = 64 and more than 80 tokens of text the
 // single kernel does not fit and stages are what is compared with: 51 13.1, s 21.5; 102 16.0, s 23.6.
 // shape.tok_tile = 16 or 32 forces the single kernel of as many tokens, or stages.
@@ -195,20 +197,21 @@ static inline HeadsPlan heads_plan(const taq_shape& s) {
     if (s.tok_tile) return {s.tok_tile == 16 && s.C == 1280 ? 1 : 0, true};
     const long tiles = (long)s.B * ((s.N + 15) / 16), pairs = tile_pairs(s);
     const bool wide = s.C / s.H == 160, packed = s.w_layout == 1, two = (s.T + 15) / 16 == 5;  // (two tiles: C = 1280, 65 to 80 text tokens)
-    if (s.C == 640 && s.H == 8) return {tiles <= (packed ? 80 : two ? 100 : 64) ? 1 : 0, true};
+    if (s.C == 640 && s.H == 8) return {tiles <= (packed ? 72 : two ? 100 : 64) ? 1 : 0, true};
     if (s.C == 640) return {tiles <= 102 ? 1 : 0, true};
-    if (wide) return {tiles <= 32 ? 1 : tiles <= 64 ? (two && pairs <= 32 ? 2 : 1) : packed && tiles <= 96 ? 1 : 0, tiles <= 51};
+    if (wide) return {tiles <= 32 ? 1 : tiles <= 64 ? (two && pairs <= 32 ? 2 : 1) : packed && tiles <= 88 ? 1 : 0, tiles <= 51};
     if (!packed || !two) return {tiles <= 51 ? 1 : 0, true};
     return {tiles < 80 ? 1 : tiles <= 102 ? (pairs <= 51 ? 2 : 1) : 0, tiles <= 51};
 }
 // R requests in grouped launches of the head-group kernels: tiles of 16 tokens per workgroup, or 0 (the single kernel, or request after
-// request). n: tiles of a request, t: of all, e: of a request as workgroups of two count them. us per call, "1" and "2" grouped with one and two tiles, "r" request after request, "f" the
-// single kernel's grouped launch; 77 text tokens, operand-ordered weights where nothing else is said.
+// request). n: tiles of a request, t: of all, e: of a request as workgroups of two count them. us per call, "1" and "2" grouped with one and
+// two tiles, "r" request after request, "f" the single kernel's grouped launch; 77 text tokens, operand-ordered weights where nothing else
+// is said.
 //   C = 1280, d = 160: R x n = 2 x 2 1 12.9, r 24.2; 2 x 16 1 17.6, 2 19.9, r 27.3; 16 x 2 1 25.8, 2 24.3, r 187; 4 x 10 1 29.4, 2 24.8, r 52; 16 x 32 2 148,
-//     r 254; 2 x 100 2 62.5, r 65.6; 4 x 128 2 124, r 135; 6 x 160 2 241, r 259; 2 x 160 2 81, r 76; row-major 2 x 16 1 19.2, 2 21.7; 6 x 6 1 32.0, 2 26.7;
-//     2 x 64 2 43.7, r 48.5; 2 x 128 2 78, r 74; 4 x 128 2 141, r 147; 90 tokens of text 2 x 64 1 47.9, r 54.4; 2 x 100 1 72, r 71; 6 x 100 1 186, r 228;
-//   d = 64: 2 x 8 1 17.5, 2 18.4; 3 x 8 1 21.3, 2 20.6, r 40; 16 x 8 2 61.6, r 210; 2 x 100 2 53.1, r 57; 2 x 160 2 84, r 75; 6 x 160 2 219, r 253; row-major
-//     6 x 8 1 34.8, 2 30.0, r 89; 2 x 64 1 49.4, 2 51.4, r 57.8; 2 x 100 1 69, r 65; 6 x 100 1 186, r 214; 6 x 160 1 284, r 267;
+//     r 254; 2 x 100 2 62.5, r 65.6; 4 x 128 2 124, r 135; 6 x 144 2 217, r 217; 6 x 160 2 241, r 231; 8 x 160 2 322, r 332; 2 x 160 2 81, r 76;
+//     row-major 2 x 16 1 19.2, 2 21.7; 6 x 6 1 32.0, 2 26.7; 2 x 64 2 43.7, r 48.5; 2 x 128 2 78, r 74; 4 x 128 2 141, r 147; 90 tokens of text 2 x 64 1 47.9, r 54.4; 2 x 100 1 72, r 71; 6 x 100 1 186, r 228;
+//   d = 64: 2 x 8 1 17.5, 2 18.4; 3 x 8 1 21.3, 2 20.6, r 40; 16 x 8 2 61.6, r 210; 2 x 100 2 53.1, r 57; 2 x 160 2 84, r 75; 6 x 144 2 211, r 210; 6 x 160 2 232, r 225; 8 x 160 2 309, r 324;
+//     row-major 6 x 8 1 34.8, 2 30.0, r 89; 2 x 64 1 49.4, 2 51.4, r 57.8; 2 x 100 1 69, r 65; 6 x 100 1 186, r 214; 6 x 160 1 284, r 267;
 //   C = 640, d = 80: 2 x 24 1 12.7, f 13.2; 3 x 16 1 13.2, f 16.2; 6 x 10 1 16.5, f 16.2; row-major 6 x 10 1 17.4, f 19.6; 16 x 6 1 24.9, f 19.2; d = 64: 3 x 16 1 13.0,
 //     f 16.5; 2 x 32 1 14.3, f 14.2; row-major 6 x 10 1 19.0, f 19.1; more text than the single kernel takes: 16 x 16 1 40, r 189; 2 x 160 1 44, r 53.
 // Requests of several elements (elements x tiles): d = 160, 16 x (3 x 1) 1 36.3, 2 40.9; 16 x (2 x 3) 1 62.8, 2 56.6; 2 x (20 x 5) 2 61.5, r 67.1; 2 x (34 x 3)
@@ -218,7 +221,7 @@ static inline int grouped_heads(const taq_shape& s, int R) {
     const long n = (long)s.B * ((s.N + 15) / 16), t = R * n, e = 2 * tile_pairs(s);
     const bool packed = s.w_layout == 1, two = (s.T + 15) / 16 == 5 && s.N > 16;
     if (s.C == 640) return fused_supported(s) ? t <= (s.H == 8 ? (packed ? 48 : 64) : 51) : n <= 160;
-    if (n > (packed && two ? (R < 6 ? 100 : 160) : R < 4 ? 64 : 100) || (packed && two && e > (R < 6 ? 120 : 160))) return 0;
+    if (n > (packed && two ? (R < 6 ? 100 : R < 8 ? 144 : 160) : R < 4 ? 64 : 100) || (packed && two && e > (R < 6 ? 120 : 160))) return 0;
     if (!two) return 1;
     if (s.C / s.H == 160) return t <= 32 ? 1 : 2;
     return t <= 20 || (!packed && e >= 64) ? 1 : 2;
