@@ -114,6 +114,11 @@ def test_requests_of_one_launch(R, B, N, C, H, more):
     layers = []
     for r in range(R):
         L = Layer(B, N, C, H, **more)
+        g = torch.Generator("cuda").manual_seed(100 + r)
+        normal = lambda *s: torch.randn(s, generator=g, device="cuda")  # noqa: E731
+        L.mask.zero_()
+        L.mask[:, : (1, 0, 3, 20)[r % 4]] = 1
+        L.kv = T.taq_quantize_kv(normal(B, L.text, 64).half(), L.mask, (normal(C, 64) * 0.1).half(), (normal(C, 64) * 0.1).half(), L.more["bits_kv"], L.shape(N))
         L.hidden = L.hidden.roll(3 * r, 1) * (1 + r)
         L.scales = L.scales * (1 + 0.25 * r)
         w = torch.randint(-127, 128, (C, C), generator=torch.Generator("cuda").manual_seed(r), device="cuda", dtype=torch.int8)
