@@ -303,7 +303,8 @@ hipError_t launch_heads(const StageChunk& c, const taq_shape& s, const FusedReq*
     a.image = L.image;
     a.image_bytes = L.image_bytes;
     a.k16 = L.k16;
-    a.v16t = L.v16t;  // (L.ntrig is 0)
+    a.v16t = L.v16t;
+    if (L.ntrig != 0) return hipErrorInvalidValue;  // the kernel reads the number of protected tokens at the front of qkv_packed
     a.I = kv_image(s);
     a.w_off = weight_pack_offset(s);
     a.N = s.N; a.NT = c.NT; a.tile0 = c.tile0; a.tile1 = c.tile1; a.T = s.T;
