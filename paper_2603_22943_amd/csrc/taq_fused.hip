@@ -119,10 +119,9 @@ hipError_t launch_pack_weight(const int8_t* codes, const taq_shape& s, int8_t* o
 // last phase of the fused kernel. An eighth of the (tile, output tiles) pairs to an XCD, tile after tile, as in heads_kernel, whose
 // A^ V~ is then in the XCD's own L2.
 // What bounds it: what the busiest compute unit pulls through its path, 80 KB of rows and 20 KB of weights per output tile at C = 1280
-// (41 and 10 at 640). So: the largest OT of 2, 4, 8, 10 with which all workgroups run at once, one to a unit (launch_to_out_tail). us per
-// layer, d = 160: 64 tokens OT 2 11.7, 4 11.9, 8 12.6; 128 tokens 2 13.3, 4 12.7, 8 13.0; 256 tokens 4 13.5, 8 13.0; 512 tokens 8 14.4
-// (64 units have two workgroups), 10 13.5; 700 tokens (two rounds with 10) 8 17.85, 10 19.8. Before, OT = 8 throughout and all weights in
-// front of the barrier: 12.7, 13.2, 13.3, 15.0, 18.3.
+// (41 and 10 at 640). So: the smallest OT of 2, 4, 8, 10 with which all workgroups run at once, one to a unit (tail_ot, where the timings
+// are). Before, OT = 8 throughout and all weights in front of the barrier, us per layer at d = 160: 64 tokens 12.7, 128 13.2, 256 13.3, 512 15.0,
+// 700 18.3.
 // Registers: at most 128 with eight wavefronts, 96 with ten, 80 with C = 640, for two and three workgroups to a unit (C = 640, 2048
 // tokens: 16.95 -> 15.95 us).
 struct TailReq {
@@ -351,17 +350,16 @@ hipError_t launch_to_out_tail(const StageChunk& c, const taq_shape& s, const Fus
     a.w_off = weight_pack_offset(s);
     m.ws_step = ws_step;
     a.N = s.N; a.NT = c.NT; a.tile0 = c.tile0; a.tiles = c.tile1 - c.tile0; a.H = s.H;
-    // all workgroups at once on the compute units (256), the fewer of them the better
     const bool packed = s.w_layout != 0;
-    const long tiles = (long)a.tiles * R;
+    const int ot = tail_ot(s.C, (long)a.tiles * R);
     if (s.C == 1280) {
-        if (tiles * 40 <= 256) return launch_tail_cfg<1280, 2, 4>(m, R, packed, st);
-        if (tiles * 20 <= 256) return launch_tail_cfg<1280, 4, 2>(m, R, packed, st);
-        if (tiles * 10 > 256 && tiles * 8 <= 256) return launch_tail_cfg<1280, 10, 1>(m, R, packed, st);
+        if (ot == 2) return launch_tail_cfg<1280, 2, 4>(m, R, packed, st);
+        if (ot == 4) return launch_tail_cfg<1280, 4, 2>(m, R, packed, st);
+        if (ot == 10) return launch_tail_cfg<1280, 10, 1>(m, R, packed, st);
         return launch_tail_cfg<1280, 8, 1>(m, R, packed, st);
     }
     if (s.C == 640) {
-        if (tiles * 5 > 256 && tiles * 4 <= 256) return launch_tail_cfg<640, 10, 1>(m, R, packed, st);
+        if (ot == 10) return launch_tail_cfg<640, 10, 1>(m, R, packed, st);
         return launch_tail_cfg<640, 8, 1>(m, R, packed, st);
     }
     return hipErrorInvalidValue;

@@ -227,6 +227,17 @@ static inline int grouped_heads(const taq_shape& s, int R) {
     return t <= 20 || (!packed && e >= 64) ? 1 : 2;
 }
 
+// to_out_tail_kernel: output tiles of 16 channels per workgroup, each by 8 / ot wavefronts at ot = 2 and 4 and by one otherwise. The fewest
+// output tiles with which all workgroups run at once, one to a compute unit; where 10 leave some units a second one, 8. us per layer, d = 160:
+// 64 tokens ot 2 11.7, 4 11.9, 8 12.6; 128 tokens 2 13.3, 4 12.7, 8 13.0; 256 tokens 4 13.5, 8 13.0; 512 tokens 8 14.4 (64 units have two
+// workgroups), 10 13.5; 700 tokens (two rounds with 10) 8 17.85, 10 19.8.
+static inline int tail_ot(int C, long tiles) {
+    const long per = C / 16;  // output tiles of a token tile
+    if (C == 1280 && tiles * (per / 2) <= 256) return 2;
+    if (C == 1280 && tiles * (per / 4) <= 256) return 4;
+    return tiles * (per / 8) > 256 && tiles * (per / 10) <= 256 ? 10 : 8;
+}
+
 // The next launch of a batched call with `left` requests to go: how many of them it takes, and their head groups' tiles of 16 tokens per workgroup
 // (0: the single kernel, or request after request). Asked for each launch of up to 16: of 17 requests the last goes out as a call of one does.
 struct GroupedLaunch {
