@@ -184,7 +184,9 @@ int taq_quantize_kv_w8(const void* context, const uint8_t* trigger_mask, const i
  *   trigger_mask : u8 [B, T] or NULL. The protected-token list recorded in qkv_packed is
  *                  what the kernels use; this argument is accepted for symmetry only.
  *   out          : f16 [B, N, C]
- *   workspace    : taq_workspace_bytes() bytes of scratch */
+ *   workspace    : taq_workspace_bytes() bytes of scratch, contents undefined after. Which shapes use it is the library's
+ *                  choice (with tok_tile = 0, C = 640 of few tokens does): whatever the shape, it is of this shape's size,
+ *                  and calls that may overlap (other streams, other host threads) have one each */
 int taq_cross_attn(const void* hidden, const void* qkv_packed, const int8_t* Wq, const int8_t* Wo,
                    const float* scales, const uint8_t* trigger_mask, const taq_shape* shape,
                    void* out, void* workspace, void* hip_stream);

@@ -148,6 +148,26 @@ def test_chunks_of_tiles_give_the_same_rows(B, N):
     assert np.array_equal(out.cpu().numpy().view(np.uint16), whole)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("R,B,N,C,H", [(1, 1, 5, 640, 8), (3, 1, 5, 640, 8), (1, 3, 33, 640, 10), (3, 3, 33, 640, 10), (1, 1, 16 * 72, 640, 8), (3, 1, 16 * 16, 640, 8),
+                                       (1, 2, 77, 1280, 8), (3, 2, 77, 1280, 8), (1, 1, 16 * 60 - 1, 1280, 20), (3, 1, 16 * 60 - 1, 1280, 20)])
+def test_nothing_is_written_past_the_workspace(R, B, N, C, H):
+    """Calls that go through the workspace keep to taq_workspace_bytes() of their own shape, or R times as much."""
+    from test_gpu_token_tiles import Layer
+
+    L = Layer(B, N, C, H, w_layout=1)
+    s, want = L.shape(N), L.run()
+    n, past = R * T.taq_workspace_bytes(s), 1 << 16
+    ws = torch.full((n + past,), 0xA5, dtype=torch.uint8, device="cuda")
+    outs = [torch.full_like(L.hidden, float("nan")) for _ in range(R)]
+    if R == 1:
+        T.taq_cross_attn(L.hidden, L.kv, L.w, L.w, L.scales, L.mask, s, outs[0], ws[:n])
+    else:
+        T.taq_cross_attn_batched([dict(hidden=L.hidden, qkv_packed=L.kv, Wq=L.w, Wo=L.w, scales=L.scales, out=o) for o in outs], s, ws[:n])
+    assert all(np.array_equal(o.cpu().numpy().view(np.uint16), want) for o in outs)
+    assert bool((ws[n:] == 0xA5).all()) and not bool((ws[:n] == 0xA5).all())
+
+
 @pytest.mark.parametrize("source", ["taq_heads160.hip", "taq_heads64.hip", "taq_heads80.hip", "taq_heads64x10.hip"])
 def test_the_image_has_arrived(tmp_path, source):
     """Image and protected rows go straight into LDS for all wavefronts: a wavefront's own pieces have arrived at every barrier but the first
