@@ -352,8 +352,8 @@ static inline StageChunk stage_chunk(const taq_shape& s, uint8_t* ws, size_t til
     return c;
 }
 
-// Workspace of taq_cross_attn (per request): the head-group path and the full-precision modes use these sections, the
-// kernel-per-stage path lays its tiles out in the same memory.
+// Workspace of taq_cross_attn (per request): the full-precision modes use these sections; head groups and stages lay their tiles (StageChunk) out in
+// the same memory.
 struct AttnWorkspace {
     size_t h_code;  // i8  [B*N][C]
     size_t s_h;     // f32 [B*N]
@@ -363,7 +363,7 @@ struct AttnWorkspace {
     size_t o_f;     // f32 [B*N][C]
     size_t o_code;  // i8  [B*N][C]
     size_t s_o;     // f32 [B*N]
-    size_t least;   // what the calls cannot do without (the stage path goes through fewer tiles at a time)
+    size_t least;   // what taq_cross_attn_static asks for: all sections, also of shapes whose tiles could go through less, a few at a time
     size_t total;   // with all tiles of the stage path at once
 };
 

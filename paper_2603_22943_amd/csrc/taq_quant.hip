@@ -658,10 +658,10 @@ __device__ __forceinline__ void kvh_scales(const float (*amax_l)[96], const int 
 // Slots past the protected tokens are zero in the transposed V copy (they meet zero weights there) and unspecified in
 // the other two.
 //
-// A chain of round trips to memory with almost no work in between: the protected-token list, the context rows, the weight codes. The list,
-// its length and the first weight pieces are requested at once, and the zeros of the unused slots are stored last, by the groups with the
-// fewest slots (a load behind a store waits for it). With the length, the list, the rows and the weights one after the other behind the
-// zeros, these workgroups were the launch's last at C = 320 and Cc = 2048: 9.9 -> 8.9 us of a call at C = 320, Cc = 768, B = 2, and
+// A chain of round trips to memory with almost no work in between: the list and its length at once, then the first weight pieces with the
+// context rows; and the zeros of the unused slots are stored last, by the groups with the fewest slots (a load behind a store waits for
+// it). With the length, the list, the rows and the weights one after the other behind the zeros, these workgroups were the launch's last
+// at C = 320 and Cc = 2048: 9.9 -> 8.9 us of a call at C = 320, Cc = 768, B = 2, and
 // 17.7 -> 14.1 at C = 640 or 1280, Cc = 2048 (2 protected tokens; 8.9 and 13.9 with none). Twelve pieces at a time instead of four are no
 // faster and leave a compute unit one workgroup.
 #define KVH_SLOTS 4
