@@ -63,6 +63,8 @@ def parse():
     p.add_argument("--profile-config4", action="store_true",
                    help="run only the two SDXL layers (2 x 4096 x 640 on the single-kernel path, 2 x 1024 x 1280 on the "
                         "kernel-per-stage path; for rocprofv3)")
+    p.add_argument("--profile-config5", action="store_true",
+                   help="run only the 16 batched requests of 4096 x 320 (for rocprofv3)")
     p.add_argument("--profile-sweep", action="store_true",
                    help="run only the token-sensitivity sweep of a 2 x 256 x 1280 layer (for rocprofv3)")
     p.add_argument("--summarize-trace", nargs="+", metavar=("STATS_CSV", "OUT_TXT"),
@@ -255,6 +257,23 @@ def profile_config4(dev, use_graph, reps):
     print(json.dumps({"workload": "SDXL layers, int4 K/V", "us_per_call": res, "launch": "hip-graph" if use_graph else "eager"}), flush=True)
 
 
+def batch_call(dev):
+    """The 16 requests of one batched call, as a call without arguments."""
+    reqs = [prep_layer(L, dev) for L in synth.config5()]
+    table = [dict(hidden=d["hidden"], qkv_packed=d["packed"], Wq=d["wq"], Wo=d["wo"], scales=d["scales"],
+                  trigger_mask=d["mask"], out=d["out"]) for d in reqs]
+    ws = torch.empty(16 * T.taq_workspace_bytes(reqs[0]["s"]), dtype=torch.uint8, device=dev)
+    return lambda: T.taq_cross_attn_batched(table, reqs[0]["s"], ws)
+
+
+def profile_config5(dev, use_graph, reps):
+    """For rocprofv3: the batched call replayed `reps` times. Prints the measured time per call."""
+    r = Runner([batch_call(dev)] * 2, use_graph=use_graph)
+    r.prewarm(20.0)
+    print(json.dumps({"workload": "16 batched requests of 4096 x 320", "us_per_call": round(r.time_events(2 * reps) * 1e6, 2),
+                      "launch": "hip-graph" if use_graph else "eager"}), flush=True)
+
+
 def profile_sweep(dev, reps):
     """For rocprofv3: taq_token_sensitivity, all 77 tokens and both widths, of a 2 x 256 x 1280 layer (8 heads)."""
     L = synth.make_layer("sweep", seed=3, B=2, N=256, C=1280, H=8, n_random_triggers=2, trigger_scale=3.0, bias=True)
@@ -295,12 +314,7 @@ def other_configs(dev, use_graph):
     for L in synth.config4():
         d = prep(L)
         out["config4_%dx%d" % (L.N, L.C)] = round(timed([attn_call(d)] * 4) / 4, 2)
-    reqs = [prep(L) for L in synth.config5()]
-    table = [dict(hidden=d["hidden"], qkv_packed=d["packed"], Wq=d["wq"], Wo=d["wo"], scales=d["scales"],
-                  trigger_mask=d["mask"], out=d["out"]) for d in reqs]
-    ws5 = torch.empty(16 * T.taq_workspace_bytes(reqs[0]["s"]), dtype=torch.uint8, device=dev)
-    out["config5_16_requests_batched"] = round(timed([lambda: T.taq_cross_attn_batched(table, reqs[0]["s"], ws5)] * 2,
-                                                     reps=10) / 2, 2)
+    out["config5_16_requests_batched"] = round(timed([batch_call(dev)] * 2, reps=10) / 2, 2)
 
     # int8 matrix work of the C = 1280 layers (the shapes at which the projections can be compute-bound) against the
     # int8 MFMA peak, next to the ceiling the HBM roofline leaves: whole taq_cross_attn call, weights + hidden + out +
@@ -408,7 +422,7 @@ def summarize_sq_by_kernel(csvs, keep=()):
     counter found in the CSVs, per launch and per wavefront. Text on stdout, for a summary file under profiles/."""
     import csv
     print("# rocprofv3 hardware counters per kernel of this library. Commands (run from /tmp, one pass per\n"
-          "# counter set, at most 8 SQ_ counters each; <workload> is one of bench.py's --profile-config3 / --profile-config4 /\n"
+          "# counter set, at most 8 SQ_ counters each; <workload> is one of bench.py's --profile-config3 / --profile-config4 / --profile-config5 /\n"
           "# --profile-gemm / --profile-sweep / --profile-only, launched eagerly):\n"
           "#   rocprofv3 --pmc <counters> --output-format csv -d outK -o p -- python3 bench.py <workload> --no-graph\n"
           "#   python3 bench.py --summarize-sq-by-kernel out1/p_counter_collection.csv out2/p_counter_collection.csv ... [--kernel-filter a,b]\n"
@@ -504,6 +518,9 @@ def main():
         return
     if a.profile_config4:
         profile_config4(dev, not a.no_graph, reps=50)
+        return
+    if a.profile_config5:
+        profile_config5(dev, not a.no_graph, reps=50)
         return
     if a.profile_sweep:
         profile_sweep(dev, reps=30)
