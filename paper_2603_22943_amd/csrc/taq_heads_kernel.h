@@ -16,8 +16,8 @@
 // 4.3 k clocks at 8 heads of 160, 1.8 k until the hidden tile is there in front of them; to_q (every wavefront reads the tile's codes out
 // of LDS, 2 k clocks) runs while the weights arrive, and 6 k follow in seven short phases with a barrier each. With the tail kernel of
 // its time, us per layer: 512 tokens of 8 heads of 160 18.3 -> 15.95, 64 tokens 14.7 -> 13.0, 496 tokens 21.9 -> 16.0 (whose tiles were not
-// dealt to the XCDs in eighths before), 784 tokens of 20 heads of 64 25.5 -> 20.0. C = 640, against the single kernel: 14.3 -> 9.2 us at
-// 16 tokens of 8 heads of 80 (6 of them this kernel: the chain of its phases), 14.3 -> 11.9 at 1024, 17.6 -> 15.5 at 1419 with row-major
+// dealt to the XCDs in eighths before), 784 tokens of 20 heads of 64 25.5 -> 20.0. C = 640, against the single kernel: 13.6 -> 9.3 us at
+// 16 tokens of 8 heads of 80 (6 of them this kernel: the chain of its phases), 14.2 -> 12.1 at 1024, 17.9 -> 16.2 at 1419 with row-major
 // weights.
 //
 // Up to 128 registers with eight wavefronts, 96 with ten, and half of LDS: two workgroups share a compute unit. With TT = 2 a workgroup
