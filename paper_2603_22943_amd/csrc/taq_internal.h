@@ -168,8 +168,9 @@ static inline bool mid_supported(const taq_shape& s) {
 //   d = 64: 25 1t 14.5, s 24.7; 51 1t 19.3, 2t 22.1, s 27.0; 52 1t 26.1, 1 26.1, s 27.0; 80 1 28.1, 2 27.2, s 28.9; 102 1 30.7, 2 28.9, s 31.9;
 //     103 1 32.1, 2 34.6, s 31.9; row-major weights 25 1t 16.5, s 24.9; 51 1t 22.1, 1 23.7, s 27.4; 52 1 28.5, s 27.6; 80 1 31.9, s 30.6.
 // The lines are rounds of workgroups: two of the head-group kernel share a compute unit (512 of them: 32 and 64 groups of 8 heads, 51 of
-// 10; two tiles of d = 64 with row-major weights leave no LDS for that), and two of the tail kernel (10 to a tile). Above 64 tiles of d = 160 it is what the
-// partly filled second round is worth: up to 88 tiles faster for 1, 2, 4 and 8 elements, at 92 for 1 (31.1, s 31.7) and not for 2 (32.4, s 31.4).
+// 10; two tiles of d = 64 with row-major weights leave no LDS for that), and two of the tail kernel (10 to a tile). From 89 tiles of
+// d = 160 on, stages are the faster by up to 3 % when the same call is repeated, but in the 16 layers of a UNet step head groups are: 96 tiles
+// (4 elements of 24) 460 and 470 us a step of five such layers, 8 of 12 461 and 471. The line follows the step.
 // shape.tok_tile = 16 or 32 forces head groups (of one tile, with the tail kernel) or stages (tests and tuning).
 //
 // C = 640: the single kernel ("f") takes 14 us however few tokens there are, as every workgroup pulls both weight matrices (820 KB) through
@@ -179,9 +180,10 @@ static inline bool mid_supported(const taq_shape& s) {
 //     2t 18.0, f 17.3; 128 1t 18.4, 2t 18.2, f 17.5;
 //   d = 64: 1 1t 9.7, f 14.4; 51 1t 11.8, f 14.7; 64 1t 12.1, f 14.6; 102 1t 14.4, f 14.6; 103 1t 15.9, f 14.6;
 //     row-major weights 51 1t 12.8, 2t 14.9, f 17.2; 52 1t 14.1, 2t 15.2; 102 1t 16.2, 2t 16.7, f 17.1; 103 2t 19.4, f 17.1.
-// (One round of workgroups, one to a compute unit or two: 64 groups of 4, 51 and 102 of 5; behind it the second round grows from unit to unit: up to 72 groups
-// of 4 most calls are still ahead (4 elements of 18 13.4, 8 of 9 13.1, but 2 of 36 14.6), and 100 with row-major weights, which cost the single
-// kernel 3.5 us.) Two tiles to a workgroup are the faster form at no size where head groups are the
+// (One round of workgroups, one to a compute unit or two: 64 groups of 4, 51 and 102 of 5; behind it the second round grows from unit to unit.
+// From 73 tiles of d = 80 on the single kernel is the faster by up to 5 % when the same call is repeated; in the 16 layers of a UNet step 4 elements
+// of 20 take 226 us with head groups and 233 with it, 2 of 40 226 and 224.5. 100 tiles with row-major weights, which cost the single kernel
+// 3.5 us.) Two tiles to a workgroup are the faster form at no size where head groups are the
 // faster kernels. Other lengths of text: the same lines, but for row-major weights at d = 80 (64). At d = 64 and more than 80 tokens of text the
 // single kernel does not fit and stages are what is compared with: 51 13.1, s 21.5; 102 16.0, s 23.6.
 // shape.tok_tile = 16 or 32 forces the single kernel of as many tokens, or stages.
@@ -197,9 +199,9 @@ static inline HeadsPlan heads_plan(const taq_shape& s) {
     if (s.tok_tile) return {s.tok_tile == 16 && s.C == 1280 ? 1 : 0, true};
     const long tiles = (long)s.B * ((s.N + 15) / 16), pairs = tile_pairs(s);
     const bool wide = s.C / s.H == 160, packed = s.w_layout == 1, two = (s.T + 15) / 16 == 5;  // (two tiles: C = 1280, 65 to 80 text tokens)
-    if (s.C == 640 && s.H == 8) return {tiles <= (packed ? 72 : two ? 100 : 64) ? 1 : 0, true};
+    if (s.C == 640 && s.H == 8) return {tiles <= (packed ? 80 : two ? 100 : 64) ? 1 : 0, true};
     if (s.C == 640) return {tiles <= 102 ? 1 : 0, true};
-    if (wide) return {tiles <= 32 ? 1 : tiles <= 64 ? (two && pairs <= 32 ? 2 : 1) : packed && tiles <= 88 ? 1 : 0, tiles <= 51};
+    if (wide) return {tiles <= 32 ? 1 : tiles <= 64 ? (two && pairs <= 32 ? 2 : 1) : packed && tiles <= 96 ? 1 : 0, tiles <= 51};
     if (!packed || !two) return {tiles <= 51 ? 1 : 0, true};
     return {tiles < 80 ? 1 : tiles <= 102 ? (pairs <= 51 ? 2 : 1) : 0, tiles <= 51};
 }

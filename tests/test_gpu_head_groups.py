@@ -20,7 +20,7 @@ from paper_2603_22943_amd import taq as T
     (3, 33, 20, dict()),
     (1, 600, 8, dict(text=64)),                           # other lengths of text: one tile per workgroup
     (2, 330, 20, dict(text=96, w_layout=1)),
-    (1, 16 * 88 - 3, 8, dict(w_layout=1)),                # one tile, stage kernels behind
+    (1, 16 * 96 - 3, 8, dict(w_layout=1)),                # one tile, stage kernels behind
     (12, 77, 8, dict()),                                  # ... 60 tiles that would be 36 workgroups of two
     (20, 80, 20, dict(w_layout=1, prob_grid=2)),
     (1, 16 * 64, 8, dict(text=48, w_layout=1)),
@@ -55,7 +55,7 @@ def test_head_groups_and_stages_agree(B, N, H, more, protected):
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,N,H,more,forced", [
     (1, 1, 8, dict(w_layout=1), 16),
-    (1, 16 * 72 - 5, 8, dict(w_layout=1, prob_grid=1), 16),
+    (1, 16 * 80 - 5, 8, dict(w_layout=1, prob_grid=1), 16),
     (4, 16 * 13, 8, dict(w_layout=1), 16),                  # to_out: 10 output tiles per workgroup
     (1, 16 * 64 - 1, 8, dict(), 16),
     (3, 201, 8, dict(bits_kv=4), 16),                       # row-major weights, one tile per workgroup
