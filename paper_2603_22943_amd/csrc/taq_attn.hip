@@ -403,7 +403,7 @@ void attn_op_kernel(AttnOpArgs a) {
         }
     }
     // ---- O and its largest magnitude per token of this head
-    const float osc = reinterpret_cast<const float*>(img + a.I.oscale)[0] * (1.0f / a.pmax);
+    const float osc = reinterpret_cast<const float*>(img + a.I.oscale)[0] * inv_pmax(a.pmax);
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) {
         const float of = ROWMAX ? osc * fz[nt] : osc;

@@ -185,7 +185,7 @@ void to_out_tail_kernel(std::conditional_t<MANY, TailManyArgs, TailArgs> args) {
     __builtin_amdgcn_sched_barrier(0);
     amax = quad_allmax(amax);
     const bool zero = amax == 0.f;
-    const float so = zero ? 1.f : amax / 127.f;
+    const float so = zero ? 1.f : div_grid(amax, 127.f);
     const float safe = zero ? 1.f : amax;
     const float cq = quant_mult(127.f, safe);
     const int tile = a.tile0 + lt, b = tile / a.NT, n = (tile - b * a.NT) * 16 + r16;

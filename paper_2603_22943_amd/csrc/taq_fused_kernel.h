@@ -328,11 +328,13 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     // CU pulls ~300 KB of weights and image per launch), so the requests are spread under the ALU work.
     amax = TPT == 16 ? row16_allmax(amax) : row8_allmax(amax);
     const bool zero0 = amax == 0.f;
-    const float sc0 = zero0 ? 1.f : amax / 127.f;
+    const float sc0 = zero0 ? 1.f : div_grid(amax, 127.f);
     const float safe0 = zero0 ? 1.f : amax;
     const float cq0 = quant_mult(127.f, safe0);
     if (HOLDS && part0 == 0) s_h[tok0] = sc0;
     const QuantRow hrow = {1.f, cq0, safe0};
+    const HalfRow half = half_row(cq0, sc0, amax);
+    const bool again = TAQ_DOUBT(half.doubt);
     auto hidden4 = [&](int it, int u) {
         const half2_t x01 = *reinterpret_cast<const half2_t*>(&xin[it][u].x), x23 = *reinterpret_cast<const half2_t*>(&xin[it][u].y);
         return make_float4((float)x01[0], (float)x01[1], (float)x23[0], (float)x23[1]);
@@ -345,7 +347,6 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
 #pragma unroll
             for (int u = 0; u < XW; ++u) *reinterpret_cast<unsigned*>(dm.dbg.h_code + row0 * C + it * 64 + part0 * (4 * XW) + 4 * u) = pk[u];
     };
-    unsigned doubt = 0u;
 #pragma unroll
     for (int it = 0; it < KC; ++it) {
         if (F::PREFETCH_W && it < F::PQ) {
@@ -361,30 +362,26 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
 #pragma unroll
             for (int u = 0; u < XW; ++u) {
                 const float4 x = hidden4(it, u);
-                pk[u] = quant4_fast(x.x, x.y, x.z, x.w, hrow, doubt);
+                pk[u] = quant4_at(x.x, x.y, x.z, x.w, half.m);
             }
-            if (RING > 0) {  // (step by step, as with QG below)
-                if (TAQ_DOUBT(doubt))
+            if (RING > 0 && again)  // (step by step, as with QG below)
 #pragma unroll
-                    for (int u = 0; u < XW; ++u) {
-                        const float4 x = hidden4(it, u);
-                        pk[u] = quant4_settle(pk[u], x.x, x.y, x.z, x.w, hrow, 127.f);
-                    }
-                doubt = 0u;
-            }
+                for (int u = 0; u < XW; ++u) {
+                    const float4 x = hidden4(it, u);
+                    pk[u] = quant4_exact(x.x, x.y, x.z, x.w, hrow, 127.f);
+                }
             put_hidden(it, pk);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (RING == 0 && TAQ_DOUBT(doubt)) {  // all of this thread's pieces again
+    if (RING == 0 && again) {  // all of this thread's pieces again
 #pragma unroll
         for (int it = 0; it < KC; ++it) {
             unsigned pk[XW];
 #pragma unroll
             for (int u = 0; u < XW; ++u) {
                 const float4 x = hidden4(it, u);
-                unsigned again = 0u;
-                pk[u] = quant4_settle(quant4_fast(x.x, x.y, x.z, x.w, hrow, again), x.x, x.y, x.z, x.w, hrow, 127.f);
+                pk[u] = quant4_exact(x.x, x.y, x.z, x.w, hrow, 127.f);
             }
             put_hidden(it, pk);
         }
@@ -523,7 +520,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
         }
         qmax = quad_allmax(qmax);
         const bool qzero = qmax == 0.f;
-        const float sQ = qzero ? 1.f : qmax / dm.qmaxq;
+        const float sQ = qzero ? 1.f : div_grid(qmax, dm.qmaxq);
         const float qsafe = qzero ? 1.f : qmax;
         const float cq = quant_mult(dm.qmaxq, qsafe);
         quant4_group<QG>(qpk[nt], [&](int j) { return make_float4(qf[j][0], qf[j][1], qf[j][2], qf[j][3]); },
@@ -921,7 +918,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     // the products are not formed: the row maximum is max|oacc| * of (a product with a positive
     // constant is monotone, so this IS the maximum of the products), and the quantizer takes oacc and of apart.
     constexpr bool KEEP_O = TAPS;
-    const float osc = reinterpret_cast<const float*>(imgh + field(&KvImage::oscale))[0] * (1.0f / dm.pmax);
+    const float osc = reinterpret_cast<const float*>(imgh + field(&KvImage::oscale))[0] * inv_pmax(dm.pmax);
     float of[NTT];
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) {
@@ -958,7 +955,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
 #pragma unroll
         for (int w = 0; w < NH; ++w) oamax = fmaxf(oamax, __uint_as_float(omax[(tbase + 16 * nt + r2) * NH + w]));
         const bool ozero = oamax == 0.f;
-        so[nt] = ozero ? 1.f : oamax / 127.f;
+        so[nt] = ozero ? 1.f : div_grid(oamax, 127.f);
         const float osafe = ozero ? 1.f : oamax;
         const float cq = quant_mult(127.f, osafe);
         unsigned pk[TPH];

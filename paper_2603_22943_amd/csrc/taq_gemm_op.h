@@ -260,7 +260,7 @@ void gemm_op_kernel(GemmOpArgs a) {
                 const int h = (g0 + wn * NW) / TP + hh;
                 if (h >= a.H) continue;
                 const bool zero = amax[i][hh] == 0.f;
-                const float safe = zero ? 1.f : amax[i][hh], cq = quant_mult(a.qmax, safe), sq = zero ? 1.f : amax[i][hh] / a.qmax;
+                const float safe = zero ? 1.f : amax[i][hh], cq = quant_mult(a.qmax, safe), sq = zero ? 1.f : div_grid(amax[i][hh], a.qmax);
                 const size_t th = (size_t)t * a.H + h;
                 if (q == 0 && j0 == 0) a.s_q[th * 16 + r16] = sq;
                 unsigned pk[JH];

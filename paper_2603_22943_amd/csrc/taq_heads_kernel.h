@@ -197,8 +197,10 @@ void heads_kernel(std::conditional_t<MANY, HeadsManyArgs, HeadsArgs> args) {
             amax = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
         }
         const bool zero0 = amax == 0.f;
-        const float sc0 = zero0 ? 1.f : amax / 127.f, safe0 = zero0 ? 1.f : amax;
+        const float sc0 = zero0 ? 1.f : div_grid(amax, 127.f), safe0 = zero0 ? 1.f : amax;
         const QuantRow hrow = {1.f, quant_mult(127.f, safe0), safe0};
+        const HalfRow half = half_row(hrow.c, sc0, amax);
+        const bool again = TAQ_DOUBT(half.doubt);
         const bool tap = TAPS && by == 0 && nq0 < N;
         if (part0 == 0) s_h[tok0] = sc0;
         if (tap && a.dbg.s_h && part0 == 0) a.dbg.s_h[row0] = sc0;
@@ -212,11 +214,8 @@ void heads_kernel(std::conditional_t<MANY, HeadsManyArgs, HeadsArgs> args) {
 #pragma unroll
             for (int ks = it * LPI; ks < (it + 1) * LPI && ks < KPRE; ++ks) load_w(ks);
             const float4 x = hidden4(it, 0), y = hidden4(it, 1);
-            unsigned doubt = 0u;
-            uint2 pk;
-            pk.x = quant4_fast(x.x, x.y, x.z, x.w, hrow, doubt);
-            pk.y = quant4_fast(y.x, y.y, y.z, y.w, hrow, doubt);
-            if (TAQ_DOUBT(doubt)) pk = make_uint2(quant4_settle(pk.x, x.x, x.y, x.z, x.w, hrow, 127.f), quant4_settle(pk.y, y.x, y.y, y.z, y.w, hrow, 127.f));
+            uint2 pk = make_uint2(quant4_at(x.x, x.y, x.z, x.w, half.m), quant4_at(y.x, y.y, y.z, y.w, half.m));
+            if (again) pk = make_uint2(quant4_exact(x.x, x.y, x.z, x.w, hrow, 127.f), quant4_exact(y.x, y.y, y.z, y.w, hrow, 127.f));
             *reinterpret_cast<uint2*>(tileq + tok0 * F::TILE_RS + (it * TPT + part0) * 8) = pk;
             if (tap && a.dbg.h_code) *reinterpret_cast<uint2*>(a.dbg.h_code + row0 * C + (it * TPT + part0) * 8) = pk;
             __builtin_amdgcn_sched_barrier(0);
@@ -291,7 +290,7 @@ void heads_kernel(std::conditional_t<MANY, HeadsManyArgs, HeadsArgs> args) {
 #pragma unroll
         for (int k = 0; k < TPH; ++k) qmax = fmaxf(qmax, mx[((hl * TPH + k) * TT + nt) * 16 + r16]);
         const bool qzero = qmax == 0.f;
-        const float sQ = qzero ? 1.f : qmax / a.qmaxq, qsafe = qzero ? 1.f : qmax;
+        const float sQ = qzero ? 1.f : div_grid(qmax, a.qmaxq), qsafe = qzero ? 1.f : qmax;
         const int n = n0 + 16 * nt + r16;
         nvalid[nt] = n < N;
         tok[nt] = (size_t)b * N + (nvalid[nt] ? n : N - 1);
@@ -585,7 +584,7 @@ void heads_kernel(std::conditional_t<MANY, HeadsManyArgs, HeadsArgs> args) {
         }
     }
     // ---- O and its largest magnitude per token of each head
-    const float osc = reinterpret_cast<const float*>(imgh + field(&KvImage::oscale))[0] * (1.0f / a.pmax);
+    const float osc = reinterpret_cast<const float*>(imgh + field(&KvImage::oscale))[0] * inv_pmax(a.pmax);
     const size_t th = (size_t)(tile - a.tile0) * H + h;  // (token tile nt: H further on each)
 #pragma unroll
     for (int nt = 0; nt < TT; ++nt) {

@@ -55,13 +55,20 @@ __device__ __forceinline__ void rowquant_f16_held(const uint4* __restrict__ xr, 
     const float amax = wave_allmax(fmaxf((float)am2[0], (float)am2[1]));
     const bool zero = amax == 0.f;
     const float safe = zero ? 1.f : amax;
-    const float c = quant_mult(127.f, safe);
-    if (lane == 0) *scale = zero ? 1.f : amax / 127.f;
+    const float c = quant_mult(127.f, safe), sc = zero ? 1.f : div_grid(amax, 127.f);
+    if (lane == 0) *scale = sc;
+    const HalfRow half = half_row(c, sc, amax);
     unsigned pk[2 * NV];
-    quant4_group<2 * NV>(pk, [&](int i) {
+    auto values = [&](int i) {
         const half2_t* x = reinterpret_cast<const half2_t*>(&u[i >> 1]) + 2 * (i & 1);
         return make_float4((float)x[0][0], (float)x[0][1], (float)x[1][0], (float)x[1][1]);
-    }, [&](int) { return QuantRow{1.f, c, safe}; });
+    };
+#pragma unroll
+    for (int i = 0; i < 2 * NV; ++i) {
+        const float4 f = values(i);
+        pk[i] = quant4_at(f.x, f.y, f.z, f.w, half.m);
+    }
+    if (TAQ_DOUBT(half.doubt)) quant4_group<2 * NV>(pk, values, [&](int) { return QuantRow{1.f, c, safe}; });
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int v = lane + 64 * i;
@@ -86,7 +93,7 @@ __device__ __forceinline__ void rowquant_f16_row(const __half* __restrict__ x, i
     amax = wave_allmax(amax);
     const bool zero = amax == 0.f;
     const float safe = zero ? 1.f : amax;
-    if (lane == 0) *scale = zero ? 1.f : amax / 127.f;
+    if (lane == 0) *scale = zero ? 1.f : div_grid(amax, 127.f);
     rowquant_f16_exact(xr, nv, safe, lane, put);
 }
 
@@ -165,7 +172,7 @@ __global__ __launch_bounds__(256) void oquant_op_kernel(StageChunk c, int N, int
     const int tile = c.tile0 + lt, b = tile / c.NT, n = (tile - b * c.NT) * 16 + r16;
     if (tap_code && n < N && c0 < C) *reinterpret_cast<uint4*>(tap_code + ((size_t)b * N + n) * C + c0) = w4;
     if (ks == 0 && q == 0) {
-        const float sc = zero ? 1.f : amax / 127.f;
+        const float sc = zero ? 1.f : div_grid(amax, 127.f);
         c.s[lt * 16 + r16] = sc;
         if (tap_scale && n < N) tap_scale[(size_t)b * N + n] = sc;
     }
@@ -612,7 +619,7 @@ __device__ __forceinline__ void kvh_scales(const float (*amax_l)[96], const int 
         const bool in = t < I.ntok, tv = t < T, prot = !tv || slot[i] >= 0;
         float amax = in ? amax_l[0][t] : 0.f;
         if (PARTS > 1 && in) amax = fmaxf(amax, amax_l[PARTS - 1][t]);
-        sc[i] = prot ? 0.f : (amax == 0.f ? 1.f : amax / qmaxf);
+        sc[i] = prot ? 0.f : (amax == 0.f ? 1.f : div_grid(amax, qmaxf));
         scmax = __float_as_uint(sc[i]) > scmax ? __float_as_uint(sc[i]) : scmax;
         if (tv) scales[t] = sc[i];
         if (!side && in) {
