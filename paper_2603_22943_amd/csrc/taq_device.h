@@ -95,12 +95,20 @@ __device__ __forceinline__ unsigned quant4_at(float x0, float x1, float x2, floa
     const unsigned hi = __builtin_amdgcn_perm(__float_as_uint(__builtin_fmaf(x3, m, magic)), __float_as_uint(__builtin_fmaf(x2, m, magic)), 0x0c0c0400u);
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
-// The inner candidates; bytes of `doubt` are set where the outer ones differ.
+// The inner candidates. The outer product less the inner result (the constant plus n), rounded to an integer, is minus the constant, unless it is
+// beyond n + 1/2: then a neighbour of it. (On n + 1/2 itself it counts as n: the quotient is on the inner side by more than 1e-7 of it.)
+// `doubt`, the OR of them, starts as TAQ_SURE and stays that while no value is in doubt: three instructions per four values less than
+// packing the outer candidates and comparing.
+#define TAQ_SURE 0xCB400000u
 __device__ __forceinline__ unsigned quant4_fast(float x0, float x1, float x2, float x3, QuantRow r, unsigned& doubt) {
-    const float fc = r.f * r.c;
-    const unsigned pk = quant4_at(x0, x1, x2, x3, __builtin_fmaf(fc, -4.76837158203125e-07f, fc));
-    doubt |= pk ^ quant4_at(x0, x1, x2, x3, __builtin_fmaf(fc, 4.76837158203125e-07f, fc));
-    return pk;
+    const float fc = r.f * r.c, magic = 12582912.0f;
+    const float in = __builtin_fmaf(fc, -4.76837158203125e-07f, fc), out = __builtin_fmaf(fc, 4.76837158203125e-07f, fc);
+    const float t0 = __builtin_fmaf(x0, in, magic), t1 = __builtin_fmaf(x1, in, magic), t2 = __builtin_fmaf(x2, in, magic), t3 = __builtin_fmaf(x3, in, magic);
+    doubt |= __float_as_uint(__builtin_fmaf(x0, out, -t0)) | __float_as_uint(__builtin_fmaf(x1, out, -t1));
+    doubt |= __float_as_uint(__builtin_fmaf(x2, out, -t2)) | __float_as_uint(__builtin_fmaf(x3, out, -t3));
+    const unsigned lo = __builtin_amdgcn_perm(__float_as_uint(t1), __float_as_uint(t0), 0x0c0c0400u);
+    const unsigned hi = __builtin_amdgcn_perm(__float_as_uint(t3), __float_as_uint(t2), 0x0c0c0400u);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 __device__ __forceinline__ unsigned quant4_settle(unsigned pk, float x0, float x1, float x2, float x3, QuantRow r, float qmaxf) {
     const float fc = r.f * r.c;
@@ -108,7 +116,7 @@ __device__ __forceinline__ unsigned quant4_settle(unsigned pk, float x0, float x
     return flags ? quant4_ties(pk, flags, x0, x1, x2, x3, r.f, fc, r.amax, qmaxf) : pk;
 }
 __device__ __forceinline__ unsigned quant4_exact(float x0, float x1, float x2, float x3, QuantRow r, float qmaxf) {
-    unsigned doubt = 0u;
+    unsigned doubt = TAQ_SURE;
     return quant4_settle(quant4_fast(x0, x1, x2, x3, r, doubt), x0, x1, x2, x3, r, qmaxf);
 }
 
@@ -129,20 +137,20 @@ __device__ __forceinline__ HalfRow half_row(float c, float scale, float amax) { 
 // Whether any lane of the wavefront is in doubt: one test for as many values as a wavefront has at hand, and a branch out of line
 // that is hardly ever taken. (A test for every four, each jumping over the rare code, cut the arithmetic into pieces of one
 // dependent chain each: 15.72 -> 15.37 us at 64 tokens of 1280 channels, 11.48 -> 11.35 us at 2 x 4096 x 320.)
-#define TAQ_DOUBT(doubt) __builtin_expect(__builtin_amdgcn_ballot_w64((doubt) != 0u) != 0ull, 0)
+#define TAQ_DOUBT(doubt) __builtin_expect(__builtin_amdgcn_ballot_w64(doubt) != 0ull, 0)
 
 // N dwords of codes, four values x(i) of the row row(i) each; one test for every G of them.
 template <int G, int N, typename X, typename R>
 __device__ __forceinline__ void quant4_group(unsigned (&pk)[N], X x, R row, float qmaxf = 127.f) {
 #pragma unroll
     for (int i0 = 0; i0 < N; i0 += G) {
-        unsigned doubt = 0u;
+        unsigned doubt = TAQ_SURE;
 #pragma unroll
         for (int i = i0; i < (i0 + G < N ? i0 + G : N); ++i) {
             const float4 v = x(i);
             pk[i] = quant4_fast(v.x, v.y, v.z, v.w, row(i), doubt);
         }
-        if (TAQ_DOUBT(doubt)) {
+        if (TAQ_DOUBT(doubt != TAQ_SURE)) {
 #pragma unroll
             for (int i = i0; i < (i0 + G < N ? i0 + G : N); ++i) {
                 const float4 v = x(i);
