@@ -134,7 +134,7 @@ void attn_op_kernel(AttnOpArgs a) {
             if (tt < nt16) {
                 int32x4_t acc[NTT];
 #pragma unroll
-                for (int nt = 0; nt < NTT; ++nt) acc[nt] = (int32x4_t){0, 0, 0, 0};
+                for (int nt = 0; nt < NTT; ++nt) acc[nt] = sum_start();
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
                     int32x4_t ka;
@@ -152,10 +152,10 @@ void attn_op_kernel(AttnOpArgs a) {
                 const float4 bi = *reinterpret_cast<const float4*>(img_bias + 16 * tt + 4 * q);
 #pragma unroll
                 for (int nt = 0; nt < NTT; ++nt) {
-                    S[nt][tt][0] = __builtin_fmaf((float)acc[nt][0], sk.x, bi.x);
-                    S[nt][tt][1] = __builtin_fmaf((float)acc[nt][1], sk.y, bi.y);
-                    S[nt][tt][2] = __builtin_fmaf((float)acc[nt][2], sk.z, bi.z);
-                    S[nt][tt][3] = __builtin_fmaf((float)acc[nt][3], sk.w, bi.w);
+                    S[nt][tt][0] = __builtin_fmaf(sum_float(acc[nt][0]), sk.x, bi.x);
+                    S[nt][tt][1] = __builtin_fmaf(sum_float(acc[nt][1]), sk.y, bi.y);
+                    S[nt][tt][2] = __builtin_fmaf(sum_float(acc[nt][2]), sk.z, bi.z);
+                    S[nt][tt][3] = __builtin_fmaf(sum_float(acc[nt][3]), sk.w, bi.w);
                 }
             }
         }
@@ -250,10 +250,6 @@ void attn_op_kernel(AttnOpArgs a) {
         eus[nt] = eu;
     }
     floatx4_t oacc[NTT][TPH];
-#pragma unroll
-    for (int nt = 0; nt < NTT; ++nt)
-#pragma unroll
-        for (int k = 0; k < TPH; ++k) oacc[nt][k] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
     auto protected_values = [&](auto head, int ft, const floatx4_t (&facc)[NTT]) {  // protected columns keep A, unnormalised here
         half4_t phi[NTT], plo[NTT];
 #pragma unroll
@@ -274,7 +270,7 @@ void attn_op_kernel(AttnOpArgs a) {
             const half4_t va = *reinterpret_cast<const half4_t*>(&w);  // slots past ntrig hold zeros
 #pragma unroll
             for (int nt = 0; nt < NTT; ++nt) {
-                oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, phi[nt], oacc[nt][k], 0, 0, 0);
+                oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, phi[nt], decltype(head)::value ? (floatx4_t){0.f, 0.f, 0.f, 0.f} : oacc[nt][k], 0, 0, 0);
                 oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, plo[nt], oacc[nt][k], 0, 0, 0);
             }
         }
@@ -286,6 +282,11 @@ void attn_op_kernel(AttnOpArgs a) {
             protected_scores(std::false_type{}, ft, facc);
             protected_values(std::false_type{}, ft, facc);
         }
+    } else {
+#pragma unroll
+        for (int nt = 0; nt < NTT; ++nt)
+#pragma unroll
+            for (int k = 0; k < TPH; ++k) oacc[nt][k] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
     }
     float kq[NTT], lz[NTT], fz[NTT];
 #pragma unroll

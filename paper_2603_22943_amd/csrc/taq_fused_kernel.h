@@ -118,7 +118,9 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     constexpr bool LEAN = DENSE || (NTT > 2 && NH <= 8);  // no register to spare
     constexpr bool LOGP = PG == TAQ_PROB_LOG2, ROWMAX = PG == TAQ_PROB_ROWMAX;  // grid of the probabilities, Eq. (3)
     constexpr int MT16 = NT16 ? NT16 : 6;  // score tiles the code is unrolled for
-    constexpr int QG = F::RING > 0 ? 1 : TPH;  // dwords of codes per test for ties (with a ring of weights, whole groups are no faster, and 4 % slower at d = 80 row-major)
+    // dwords of codes per test for ties. Whole groups but with row-major weights (4 % slower there at d = 80) and three or four token tiles (registers): the 16 layers of a step of 2 x 64 x 64 249.9 -> 247.2 us,
+    // of 8 x 96 x 64 642 -> 640, 16 requests of 4096 x 320 59.1 -> 58.8, 2 x 4096 x 640 20.5 -> 20.4.
+    constexpr int QG = ROWMAJ || NTT > 2 ? 1 : TPH;
     constexpr bool TAPS = NT16 == 0;       // taps of intermediate codes and scales (tests, profiling)
     extern __shared__ __align__(16) unsigned char smem[];
 
@@ -256,43 +258,29 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     const __half* v16t = reinterpret_cast<const __half*>(packed + dm.L.v16t) + (size_t)b * C * 96;
 
     // protected (trigger) rows of this head, first tile of 16: fp16 K rows and transposed V rows straight from
-    // global memory into MFMA operand registers. Wide heads leave out slots past the protected tokens: a load costs by the pieces
-    // of memory that it touches, 16 rows of 32 bytes if all lanes take part, and they stand in the queue that the image and the
-    // weights go through (15.1 -> 14.7 us at 2048 tokens of 640 channels, 18.7 -> 18.1 us at 512 of 1280; heads of 40 have few of
-    // them, and the selection costs as much: 11.35 and 11.42 us at 2 x 4096 tokens; slots past ntrig hold zeros). K channels past the
-    // head are not read either: they would belong to the next head, or lie past the last row of the last head, and a
-    // non-finite bit pattern there would survive the multiplication with a zero Q~ code.
+    // global memory into MFMA operand registers. Slots past the protected tokens and channels past the head (which would belong to the next head, or
+    // lie past the last row of the last head, and a non-finite bit pattern there would survive the multiplication with a zero Q~ code) carry an offset
+    // past the end: zeros without a memory access. (A load costs by the pieces of memory that it touches, 16 rows of 32 bytes if all lanes take part: 15.1 -> 14.7 us at 2048
+    // tokens of 640 channels. Flat loads needed a branch, zeroed registers and 64-bit addresses for each of these.)
     uint2 k16r[FS][2], v16r[TPH];
     auto load_protected = [&]() {
-        auto load_k = [&](int slot) {
-            const __half* kr = k16 + (size_t)slot * C + h * D + 4 * q;
+        if (nfp > 0) {
+            const __amdgpu_buffer_rsrc_t rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half*>(k16), 0, T * C * 2, 0x00020000);
+            const __amdgpu_buffer_rsrc_t rs_v = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half*>(v16t), 0, C * 96 * 2, 0x00020000);
+            constexpr int NONE = 0x7fff0000;
+            const int ko = r16 < ntrig ? (r16 * C + h * D + 4 * q) * 2 : NONE, ko_last = D % 16 == 0 || 16 * (TPH - 1) + 4 * q < D ? ko : NONE;
+            const int vo = 4 * q < ntrig ? ((h * D + r16) * 96 + 4 * q) * 2 : NONE;
+            const int vo_last = D % 16 == 0 || r16 < D % 16 ? vo : 4 * q < ntrig ? ((h * D + D % 16 - 1) * 96 + 4 * q) * 2 : NONE;  // (rows past the head repeat its last, as those of V~ do)
 #pragma unroll
-            for (int s = 0; s < FS; ++s)
-#pragma unroll
-                for (int jj = 0; jj < 2; ++jj)
-                    k16r[s][jj] = (2 * s + jj < TPH && 16 * (2 * s + jj) + 4 * q < D)
-                                      ? *reinterpret_cast<const uint2*>(kr + 16 * (2 * s + jj)) : make_uint2(0, 0);
-        };
-        auto load_v = [&]() {
+            for (int j = 0; j < 2 * FS; ++j) {
+                const uint2_t w = j < TPH ? __builtin_amdgcn_raw_buffer_load_b64(rs_k, (j == TPH - 1 ? ko_last : ko) + 32 * j, 0, 0) : (uint2_t){0u, 0u};
+                k16r[j / 2][j % 2] = make_uint2(w[0], w[1]);
+            }
 #pragma unroll
             for (int k = 0; k < TPH; ++k) {
-                int c = h * D + 16 * k + r16;  // (may lie past the head: clamped)
-                c = c < C ? c : C - 1;
-                v16r[k] = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 4 * q);
+                const uint2_t w = __builtin_amdgcn_raw_buffer_load_b64(rs_v, k == TPH - 1 ? vo_last : vo, 16 * k * 192, 0);
+                v16r[k] = make_uint2(w[0], w[1]);
             }
-        };
-        if constexpr (TPH <= 3) {
-            if (nfp > 0) {
-                load_k(r16 < T ? r16 : T - 1);
-                load_v();
-            }
-        } else {
-#pragma unroll
-            for (int s = 0; s < FS; ++s) k16r[s][0] = k16r[s][1] = make_uint2(0, 0);
-#pragma unroll
-            for (int k = 0; k < TPH; ++k) v16r[k] = make_uint2(0, 0);
-            if (r16 < ntrig) load_k(r16);
-            if (4 * q < ntrig) load_v();
         }
     };
 
@@ -507,14 +495,11 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
         float qmax = 0.f;
 #pragma unroll
         for (int j = 0; j < TPH; ++j) {
-            const int cl = 16 * j + 4 * q;  // first of this lane's 4 channels in the head
-            const bool valid = (16 * j + 16 <= D) || cl < D;
             const float wv[4] = {wq4[j].x, wq4[j].y, wq4[j].z, wq4[j].w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float sc = sh * wv[i];
-                const float v = (float)pacc[nt][j][i] * sc;
-                qf[j][i] = valid ? v : 0.f;
+                qf[j][i] = (float)pacc[nt][j][i] * sc;  // (zero past the head: so are the weights there)
                 qmax = fmaxf(qmax, fabsf(qf[j][i]));
             }
         }
@@ -561,7 +546,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
             if (tt < nt16) {
                 int32x4_t acc[NTT];
 #pragma unroll
-                for (int nt = 0; nt < NTT; ++nt) acc[nt] = (int32x4_t){0, 0, 0, 0};
+                for (int nt = 0; nt < NTT; ++nt) acc[nt] = sum_start();
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
                     int32x4_t ka;
@@ -579,10 +564,10 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
                 const float4 bi = *reinterpret_cast<const float4*>(img_bias + 16 * tt + 4 * q);
 #pragma unroll
                 for (int nt = 0; nt < NTT; ++nt) {
-                    S[nt][tt][0] = __builtin_fmaf((float)acc[nt][0], sk.x, bi.x);
-                    S[nt][tt][1] = __builtin_fmaf((float)acc[nt][1], sk.y, bi.y);
-                    S[nt][tt][2] = __builtin_fmaf((float)acc[nt][2], sk.z, bi.z);
-                    S[nt][tt][3] = __builtin_fmaf((float)acc[nt][3], sk.w, bi.w);
+                    S[nt][tt][0] = __builtin_fmaf(sum_float(acc[nt][0]), sk.x, bi.x);
+                    S[nt][tt][1] = __builtin_fmaf(sum_float(acc[nt][1]), sk.y, bi.y);
+                    S[nt][tt][2] = __builtin_fmaf(sum_float(acc[nt][2]), sk.z, bi.z);
+                    S[nt][tt][3] = __builtin_fmaf(sum_float(acc[nt][3]), sk.w, bi.w);
                 }
             }
         }
@@ -593,9 +578,13 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     // exponentials.
     auto protected_scores = [&](auto first, int ft, const unsigned (&code)[NTT][TPH], floatx4_t (&facc)[NTT]) {
 #pragma unroll
-        for (int nt = 0; nt < NTT; ++nt) facc[nt] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < 4; ++i) {
+            const float none = 16 * ft + 4 * q + i < ntrig ? 0.f : TAQ_NEG_INF;
+#pragma unroll
+            for (int nt = 0; nt < NTT; ++nt) facc[nt][i] = none;
+        }
         int slot = 16 * ft + r16;
-        slot = slot < T ? slot : T - 1;
+        slot = slot < ntrig ? slot : ntrig - 1;
         const __half* kr = k16 + (size_t)slot * C + h * D + 4 * q;
 #pragma unroll
         for (int s = 0; s < FS; ++s) {
@@ -619,12 +608,6 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
                 const half8_t qh = {c0[0], c0[1], c1[0], c1[1], c2[0], c2[1], c3[0], c3[1]};
                 facc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka, qh, facc[nt], 0, 0, 0);
             }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bool live = 16 * ft + 4 * q + i < ntrig;
-#pragma unroll
-            for (int nt = 0; nt < NTT; ++nt) facc[nt][i] = live ? facc[nt][i] : TAQ_NEG_INF;
         }
     };
     auto further_scores = [&](int ft, floatx4_t (&facc)[NTT]) {  // (codes as fp16 are not kept for them)
@@ -728,10 +711,6 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
 
     // oacc[nt][k]: channel tile k of this head
     floatx4_t oacc[NTT][TPH];
-#pragma unroll
-    for (int nt = 0; nt < NTT; ++nt)
-#pragma unroll
-        for (int k = 0; k < TPH; ++k) oacc[nt][k] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
     // protected columns keep A (Eq. 3): E = exp2(score - max), not yet divided by Z, as fp16 high + low parts against the
     // fp16 V rows; the accumulators are brought to the unit of the unprotected columns' weights (pmax * A * 2^kexp) once Z
     // is known.
@@ -749,14 +728,13 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
             }
 #pragma unroll
         for (int k = 0; k < TPH; ++k) {
-            int c = h * D + 16 * k + r16;
-            c = c < C ? c : C - 1;
+            const int j = 16 * k + r16, c = h * D + (j < D ? j : D - 1);
             uint2 w = v16r[k];
             if constexpr (!decltype(first)::value) w = *reinterpret_cast<const uint2*>(v16t + (size_t)c * 96 + 16 * ft + 4 * q);
             const half4_t va = *reinterpret_cast<const half4_t*>(&w);  // slots past ntrig hold zeros
 #pragma unroll
             for (int nt = 0; nt < NTT; ++nt) {
-                oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, phi[nt], oacc[nt][k], 0, 0, 0);
+                oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, phi[nt], decltype(first)::value ? (floatx4_t){0.f, 0.f, 0.f, 0.f} : oacc[nt][k], 0, 0, 0);
                 oacc[nt][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(va, plo[nt], oacc[nt][k], 0, 0, 0);
             }
         }
@@ -768,6 +746,11 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
             further_scores(ft, facc);
             protected_values(std::false_type{}, ft, facc);
         }
+    } else {
+#pragma unroll
+        for (int nt = 0; nt < NTT; ++nt)
+#pragma unroll
+            for (int k = 0; k < TPH; ++k) oacc[nt][k] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
     }
     ring_out(3);
     const float vpre = nfp > 0 ? reinterpret_cast<const float*>(imgh + field(&KvImage::vpre))[0] : 0.f;
@@ -929,8 +912,8 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
             const bool valid = (16 * k + 16 <= D) || 16 * k + 4 * q < D;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if constexpr (KEEP_O) oacc[nt][k][i] = valid ? oacc[nt][k][i] * of[nt] : 0.f;
-                omx = fmaxf(omx, valid ? fabsf(oacc[nt][k][i]) : 0.f);
+                if constexpr (KEEP_O) oacc[nt][k][i] *= of[nt];
+                omx = fmaxf(omx, fabsf(oacc[nt][k][i]));  // (rows past the head repeat its last)
             }
             if (KEEP_O && nvalid[nt] && valid) {
                 const float4 o4 = make_float4(oacc[nt][k][0], oacc[nt][k][1], oacc[nt][k][2], oacc[nt][k][3]);

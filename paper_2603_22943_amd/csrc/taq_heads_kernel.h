@@ -332,7 +332,7 @@ void heads_kernel(std::conditional_t<MANY, HeadsManyArgs, HeadsArgs> args) {
     for (int u = 0; u < NTW; ++u) {
         const int p = j + TPH * u, tt = p / TT, nt = p % TT;
         if (tt < nt16) {
-            int32x4_t sc = (int32x4_t){0, 0, 0, 0}, qop[KS];
+            int32x4_t sc = sum_start(), qop[KS];
             q_operand(nt, qop);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
@@ -348,10 +348,10 @@ void heads_kernel(std::conditional_t<MANY, HeadsManyArgs, HeadsArgs> args) {
             }
             const float4 sk = *reinterpret_cast<const float4*>(img_sk + 16 * tt + 4 * q);
             const float4 bi4 = *reinterpret_cast<const float4*>(img_bias + 16 * tt + 4 * q);
-            S[u][0] = __builtin_fmaf((float)sc[0], sk.x, bi4.x);
-            S[u][1] = __builtin_fmaf((float)sc[1], sk.y, bi4.y);
-            S[u][2] = __builtin_fmaf((float)sc[2], sk.z, bi4.z);
-            S[u][3] = __builtin_fmaf((float)sc[3], sk.w, bi4.w);
+            S[u][0] = __builtin_fmaf(sum_float(sc[0]), sk.x, bi4.x);
+            S[u][1] = __builtin_fmaf(sum_float(sc[1]), sk.y, bi4.y);
+            S[u][2] = __builtin_fmaf(sum_float(sc[2]), sk.z, bi4.z);
+            S[u][3] = __builtin_fmaf(sum_float(sc[3]), sk.w, bi4.w);
             const float m = quad_allmax(fmaxf(fmaxf(S[u][0], S[u][1]), fmaxf(S[u][2], S[u][3])));
             if (q == 0) mt[p * 16 + r16] = m;
         }
