@@ -7,6 +7,7 @@
 namespace taq {
 
 typedef float fp_floatx4_t __attribute__((ext_vector_type(4)));
+typedef int fp_int4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 fp_half8_t __attribute__((ext_vector_type(8)));
 
 // ---------------------------------------------------------------- out[m][n] = sum_k A[m][k] * W[n][k]  (+ bias[n])
@@ -14,68 +15,72 @@ typedef _Float16 fp_half8_t __attribute__((ext_vector_type(8)));
 
 // fp16 rows whose sums feed a quantizer: one float32 FMA chain per output in K order, so that a sum, and with it a code,
 // is the same number whatever the tiling (products of fp16 numbers are exact; v_fma_mix reads the fp16 operands as they
-// are). 32 x 64 outputs per workgroup, 2 x 4 per thread; chunks of 64 k go through LDS as k pairs, the next chunk travels
-// in registers meanwhile. Bound by vector issue and LDS reads, 8 FMAs for 6 of them per pair.
-// blockIdx.z = 1: a second matrix W1 of the same size, results `N` columns further (K and V of a context in one launch:
-// 154 x 2 x 1280 x 768, 2 x 122 us with the float32 tiles of before, 27 us so).
+// are). 16 x 32 TN outputs per workgroup, 2 x TN per thread (columns tx, tx + 32, ...). Chunks of 64 k in two LDS buffers, rows of
+// 144 bytes: a thread reads eight k of a row at a time, without conflicts, TN + 2 reads for 16 TN FMAs. The next chunk travels in registers.
+// Bound by vector issue. One wavefront of a SIMD issues an instruction every 8.6 clocks, two and more one in 4.3, so with few rows the
+// tile is the small one: 154 x 2 x 1280 x 768 are 400 workgroups, 1.6 wavefronts to a SIMD, 22.6 us; with 32 x 64 outputs to a workgroup and
+// 2 x 4 to a thread, 200 workgroups, 27. From 1024 small workgroups on (four wavefronts to a SIMD) TN = 4 reads less per
+// FMA, unless half of the last column block would be empty (8192 x 320 x 320: the layer 6 us longer with it).
+// blockIdx.z = 1: a second matrix W1 of the same size, results `N` columns further (K and V of a context in one launch).
+template <int TN>
 __global__ __launch_bounds__(256) void gemm_nt_seq_kernel(const __half* __restrict__ A, const __half* __restrict__ W0,
                                                           const __half* __restrict__ W1, const float* __restrict__ bias, int M,
                                                           int N, int K, float* __restrict__ out_f32, __half* __restrict__ out_f16,
                                                           int ldo) {
-    constexpr int SA = 34, SW = 66;  // row strides in dwords: the transposing stores spread over the banks
-    __shared__ unsigned As[32 * SA], Ws[32 * SW];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.x * 32, n0 = blockIdx.y * 64;
+    constexpr int KC = 64, RS = KC + 8;
+    __shared__ __align__(16) __half As[2][16 * RS], Ws[2][32 * TN * RS];
+    const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
+    const int m0 = blockIdx.x * 16, n0 = blockIdx.y * 32 * TN;
     const __half* W = blockIdx.z ? W1 : W0;
     const int cz = blockIdx.z ? N : 0;
-    const int lr = tid >> 3, ls = tid & 7;  // staging: row, 8-value segment of the chunk
-    const __half* ag = A + (size_t)(m0 + lr < M ? m0 + lr : M - 1) * K + 8 * ls;
-    const __half* wg0 = W + (size_t)(n0 + lr < N ? n0 + lr : N - 1) * K + 8 * ls;
-    const __half* wg1 = W + (size_t)(n0 + 32 + lr < N ? n0 + 32 + lr : N - 1) * K + 8 * ls;
-    uint4 av, w0, w1;
-    auto fetch = [&](int k0) {  // (K % 32 == 0: the last chunk may be half: what lies past the end is not read back)
-        const int k = k0 + 8 * ls < K ? k0 : 0;
-        av = *reinterpret_cast<const uint4*>(ag + k);
-        w0 = *reinterpret_cast<const uint4*>(wg0 + k);
-        w1 = *reinterpret_cast<const uint4*>(wg1 + k);
+    const int lr = tid >> 3, ls = (tid & 7) * 8;  // staging: rows lr, lr + 32, ..., eight halves from ls
+    const __half* ag = A + (size_t)(m0 + (lr & 15) < M ? m0 + (lr & 15) : M - 1) * K;
+    const __half* wg[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) wg[j] = W + (size_t)(n0 + 32 * j + lr < N ? n0 + 32 * j + lr : N - 1) * K;
+    fp_int4_t av, wv[TN];
+    auto fetch = [&](int k0) {  // (K % 32 == 0: the last chunk may be half; what lies past the end is not read back)
+        const int k = k0 + ls < K ? k0 + ls : 0;
+        av = *reinterpret_cast<const fp_int4_t*>(ag + k);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) wv[j] = *reinterpret_cast<const fp_int4_t*>(wg[j] + k);
     };
-    float acc[2][4] = {};
-    if (8 * ls < K) fetch(0); else av = w0 = w1 = make_uint4(0u, 0u, 0u, 0u);
-    for (int k0 = 0; k0 < K; k0 += 64) {
-        __syncthreads();
-        const unsigned ae[4] = {av.x, av.y, av.z, av.w}, we0[4] = {w0.x, w0.y, w0.z, w0.w}, we1[4] = {w1.x, w1.y, w1.z, w1.w};
+    auto store = [&](int s) {
+        if (tid < 128) *reinterpret_cast<fp_int4_t*>(&As[s][lr * RS + ls]) = av;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            As[(4 * ls + e) * SA + lr] = ae[e];
-            Ws[(4 * ls + e) * SW + lr] = we0[e];
-            Ws[(4 * ls + e) * SW + 32 + lr] = we1[e];
-        }
-        __syncthreads();
-        if (k0 + 64 < K) fetch(k0 + 64);
-        const int pairs = K - k0 < 64 ? 16 : 32;
-#pragma unroll 8
-        for (int p = 0; p < pairs; ++p) {
-            __half2 a[2], w[4];
+        for (int j = 0; j < TN; ++j) *reinterpret_cast<fp_int4_t*>(&Ws[s][(32 * j + lr) * RS + ls]) = wv[j];
+    };
+    float acc[2][TN] = {};
+    fetch(0);
+    store(0);
+    fetch(KC);
+    for (int k0 = 0, s = 0; k0 < K; k0 += KC, s ^= 1) {
+        __syncthreads();  // chunk s is in LDS, and everybody is done with the other one
+        if (k0 + KC < K) store(s ^ 1);
+        fetch(k0 + 2 * KC);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const __half2*>(&As[p * SA + ty + 16 * i]);
+        for (int k = 0; k < KC; k += 8) {
+            if (k == KC / 2 && k0 + k >= K) break;
+            fp_half8_t a[2], w[TN];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) w[j] = *reinterpret_cast<const __half2*>(&Ws[p * SW + tx + 16 * j]);
+            for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const fp_half8_t*>(&As[s][(ty + 8 * i) * RS + k]);
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int j = 0; j < TN; ++j) w[j] = *reinterpret_cast<const fp_half8_t*>(&Ws[s][(tx + 32 * j) * RS + k]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    acc[i][j] = __builtin_fmaf(__low2float(a[i]), __low2float(w[j]), acc[i][j]);
-                    acc[i][j] = __builtin_fmaf(__high2float(a[i]), __high2float(w[j]), acc[i][j]);
-                }
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_fmaf((float)a[i][e], (float)w[j][e], acc[i][j]);
         }
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int m = m0 + ty + 16 * i;
+        const int m = m0 + ty + 8 * i;
         if (m >= M) continue;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx + 16 * j;
+        for (int j = 0; j < TN; ++j) {
+            const int n = n0 + tx + 32 * j;
             if (n >= N) continue;
             const float y = acc[i][j] + (bias ? bias[n] : 0.f);
             if (out_f32) out_f32[(size_t)m * ldo + cz + n] = y;
@@ -84,52 +89,66 @@ __global__ __launch_bounds__(256) void gemm_nt_seq_kernel(const __half* __restri
     }
 }
 
-// Matrix-core versions, for sums that feed no quantizer. Both stage 64 rows of A and of W through LDS, K steps of KC
-// double-buffered, the next step in registers while the current one is multiplied: loaded in operand order straight from
+static void launch_gemm_seq(const __half* A, const __half* W0, const __half* W1, const float* bias, int M, int N, int K, float* out_f32,
+                            __half* out_f16, int ldo, hipStream_t st) {
+    const unsigned mx = (M + 15) / 16, z = W1 ? 2 : 1;
+    if ((size_t)mx * ((N + 63) / 64) * z < 1024 || ((N + 63) / 64 & 1))
+        hipLaunchKernelGGL(gemm_nt_seq_kernel<2>, dim3(mx, (N + 63) / 64, z), dim3(256), 0, st, A, W0, W1, bias, M, N, K, out_f32, out_f16, ldo);
+    else
+        hipLaunchKernelGGL(gemm_nt_seq_kernel<4>, dim3(mx, (N + 127) / 128, z), dim3(256), 0, st, A, W0, W1, bias, M, N, K, out_f32, out_f16, ldo);
+}
+
+// Matrix-core versions, for sums that feed no quantizer. All stage rows of A and of W through LDS, in K steps of KC, the
+// next step in registers while the current one is multiplied: loaded in operand order straight from
 // row-major memory (lane = row + 16 * segment) every lane of a load is a cache access of its own, 64 instead of 16 per KiB,
 // and that, not the matrix cores, was the time (512 x 1280 per head slice, 8 heads: 45 us so, 24 us through LDS).
 
-// fp16 rows: V_MFMA_F32_16X16X32_F16 (products of fp16 numbers are exact in float32). 64 x 64 outputs per workgroup of
-// four wavefronts, 32 x 32 each. K % 32 == 0.
+// fp16 rows: V_MFMA_F32_16X16X32_F16 (products of fp16 numbers are exact in float32). 32 MI x 32 MI outputs per workgroup of four
+// wavefronts, 16 MI x 16 MI each; every output is one chain of products in K order, whatever the tile. K % 32 == 0.
+// A step is as long as a load takes, so with few outputs small tiles and long steps: 512 x 1280 x 1280 as 640 workgroups of
+// 32 x 32 and ten steps 11.8 us, as 160 of 64 x 64 and twenty steps 21.
+template <int MI, int KC>
 __global__ __launch_bounds__(256) void gemm_nt_f16_kernel(const __half* __restrict__ A, const __half* __restrict__ W, int M, int N, int K,
                                                           float* __restrict__ out) {
-    constexpr int KC = 64, RS = KC + 8;  // row stride in halves: 144 bytes, conflict-free for the operand reads
-    __shared__ __align__(16) __half As[2][64 * RS], Ws[2][64 * RS];
+    constexpr int TILE = 32 * MI, RS = KC + 8;  // row stride in halves: 144 or 272 bytes, conflict-free for the operand reads
+    constexpr int TR = KC / 8, RPP = 256 / TR, NL = TILE / RPP;  // staging: threads per row, rows at a time, loads per thread and operand
+    static_assert(TILE % RPP == 0, "whole loads");
+    __shared__ __align__(16) __half As[2][TILE * RS], Ws[2][TILE * RS];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r16 = lane & 15, q = lane >> 4;
-    const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
-    const int lr = tid >> 3, ls = (tid & 7) * 8;  // staging: rows lr, lr + 32, eight halves from ls
-    const __half* ag[2];
-    const __half* wg[2];
+    const int m0 = blockIdx.x * TILE, n0 = blockIdx.y * TILE;
+    const int lr = tid / TR, ls = (tid % TR) * 8;  // rows lr, lr + RPP, ..., eight halves from ls
+    const __half* ag[NL];
+    const __half* wg[NL];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {  // rows past the end re-read the last one; their results are dropped
-        const int m = m0 + lr + 32 * i, n = n0 + lr + 32 * i;
+    for (int i = 0; i < NL; ++i) {  // rows past the end re-read the last one; their results are dropped
+        const int m = m0 + lr + RPP * i, n = n0 + lr + RPP * i;
         ag[i] = A + (size_t)(m < M ? m : M - 1) * K;
         wg[i] = W + (size_t)(n < N ? n : N - 1) * K;
     }
-    uint4 av[2], wv[2];
+    uint4 av[NL], wv[NL];
     bool in;
-    auto fetch = [&](int k0) {  // (the last step may be half: zeros past the end, set when the step is stored)
+    auto fetch = [&](int k0) {  // (the last step may be partly filled: zeros past the end, set when the step is stored)
         in = k0 + ls < K;
         const int k = in ? k0 + ls : 0;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < NL; ++i) {
             av[i] = *reinterpret_cast<const uint4*>(ag[i] + k);
             wv[i] = *reinterpret_cast<const uint4*>(wg[i] + k);
         }
     };
     auto store = [&](int s) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            *reinterpret_cast<uint4*>(&As[s][(lr + 32 * i) * RS + ls]) = in ? av[i] : make_uint4(0u, 0u, 0u, 0u);
-            *reinterpret_cast<uint4*>(&Ws[s][(lr + 32 * i) * RS + ls]) = in ? wv[i] : make_uint4(0u, 0u, 0u, 0u);
+        for (int i = 0; i < NL; ++i) {
+            *reinterpret_cast<uint4*>(&As[s][(lr + RPP * i) * RS + ls]) = in ? av[i] : make_uint4(0u, 0u, 0u, 0u);
+            *reinterpret_cast<uint4*>(&Ws[s][(lr + RPP * i) * RS + ls]) = in ? wv[i] : make_uint4(0u, 0u, 0u, 0u);
         }
     };
-    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
-    fp_floatx4_t acc[2][2];
+    const int wm = (wave & 1) * 16 * MI, wn = (wave >> 1) * 16 * MI;
+    fp_floatx4_t acc[MI][MI];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (fp_floatx4_t){0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < MI; ++j) acc[i][j] = (fp_floatx4_t){0.f, 0.f, 0.f, 0.f};
     fetch(0);
     store(0);
     fetch(KC);
@@ -139,23 +158,23 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_kernel(const __half* __restri
         fetch(k0 + 2 * KC);
 #pragma unroll
         for (int u = 0; u < KC / 32; ++u) {
-            fp_half8_t a[2], w[2];
+            fp_half8_t a[MI], w[MI];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
+            for (int i = 0; i < MI; ++i) {
                 a[i] = *reinterpret_cast<const fp_half8_t*>(&As[s][(wm + 16 * i + r16) * RS + 32 * u + 8 * q]);
                 w[i] = *reinterpret_cast<const fp_half8_t*>(&Ws[s][(wn + 16 * i + r16) * RS + 32 * u + 8 * q]);
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i], a[j], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < MI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i], a[j], acc[i][j], 0, 0, 0);
         }
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < MI; ++j) {
         const int m = m0 + wm + 16 * j + r16;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < MI; ++i) {
             const int n = n0 + wn + 16 * i + 4 * q;  // N % 4 == 0: the four channels are in or out together
             if (m < M && n < N)
                 *reinterpret_cast<float4*>(out + (size_t)m * N + n) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
@@ -259,19 +278,20 @@ hipError_t launch_gemm_fp(const void* A, bool a_is_f32, const __half* W, const f
     if (a_is_f32)
         hipLaunchKernelGGL(gemm_nt_f32_kernel, grid, block, 0, st, static_cast<const float*>(A), W, bias, M, N, K, K, out_f32, out_f16, (size_t)ldo);
     else
-        hipLaunchKernelGGL(gemm_nt_seq_kernel, dim3((M + 31) / 32, (N + 63) / 64), block, 0, st, static_cast<const __half*>(A), W, W, bias, M,
-                           N, K, out_f32, out_f16, ldo);
+        launch_gemm_seq(static_cast<const __half*>(A), W, nullptr, bias, M, N, K, out_f32, out_f16, ldo, st);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm_kv_rows(const __half* context, const __half* Wk, const __half* Wv, int M, int C, int K, float* rows_f, hipStream_t st) {
-    hipLaunchKernelGGL(gemm_nt_seq_kernel, dim3((M + 31) / 32, (C + 63) / 64, 2), dim3(256), 0, st, context, Wk, Wv, nullptr, M, C, K, rows_f,
-                       nullptr, 2 * C);
+    launch_gemm_seq(context, Wk, Wv, nullptr, M, C, K, rows_f, nullptr, 2 * C, st);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm_f16(const __half* A, const __half* W, int M, int N, int K, float* out, hipStream_t st) {
-    hipLaunchKernelGGL(gemm_nt_f16_kernel, dim3((M + 63) / 64, (N + 63) / 64), dim3(256), 0, st, A, W, M, N, K, out);
+    if ((size_t)((M + 63) / 64) * ((N + 63) / 64) < 512)
+        hipLaunchKernelGGL((gemm_nt_f16_kernel<1, 128>), dim3((M + 31) / 32, (N + 31) / 32), dim3(256), 0, st, A, W, M, N, K, out);
+    else
+        hipLaunchKernelGGL((gemm_nt_f16_kernel<2, 64>), dim3((M + 63) / 64, (N + 63) / 64), dim3(256), 0, st, A, W, M, N, K, out);
     return hipGetLastError();
 }
 

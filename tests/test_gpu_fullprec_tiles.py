@@ -1,0 +1,55 @@
+"""Tiles of the full-precision projections that the number of outputs selects. Every output is one chain of sums in K order, so a call
+on many image tokens, which takes the large tiles, has the bits of calls on few of them."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_22943_amd import taq as T
+
+pytestmark = pytest.mark.gpu
+
+
+def normal(seed, *shape, std=1.0):
+    g = torch.Generator("cuda")
+    g.manual_seed(seed)
+    return (torch.randn(shape, generator=g, device="cuda") * std).half()
+
+
+def projections(B, N, C, H, text, Cc, bits_q, hidden):
+    """Q~ codes' effect and all: the block with fp16 projections on `hidden` rows."""
+    s = T.make_shape(B, hidden.shape[1], C, H, text, Cc, bits_q=bits_q, bits_proj=16)
+    mask = torch.zeros((B, text), dtype=torch.uint8, device="cuda")
+    mask[:, 1] = 1
+    wk, wv, wq, wo = (normal(7 + i, C, k, std=k ** -0.5) for i, k in enumerate((Cc, Cc, C, C)))
+    kv = T.taq_quantize_kv(normal(3, B, text, Cc), mask, wk, wv, 8, s)
+    scales = torch.zeros(3 * C, device="cuda")
+    return T.taq_cross_attn(hidden, kv, wq, wo, scales, mask, s).cpu().numpy().view(np.uint16)
+
+
+@pytest.mark.parametrize("B,N,C,H,bits_q", [
+    (1, 1700, 640, 8, 8),   # 107 x 10 small workgroups: the large tile, ragged rows
+    (2, 1041, 480, 10, 8),  # 131 x 8, seven and a half chunks of K, columns that end within a tile
+    (1, 3293, 320, 8, 8),   # the small tile: five column blocks of 64
+    (1, 1700, 672, 6, 4),   # the same, ten and a half chunks of K
+])
+def test_many_rows_have_the_bits_of_few(B, N, C, H, bits_q):
+    hidden = normal(1, B, N, C)
+    whole = projections(B, N, C, H, 9, 96, bits_q, hidden)
+    for lo, hi in ((0, 1), (63, 130), (N - 37, N)):
+        assert np.array_equal(whole[:, lo:hi], projections(B, N, C, H, 9, 96, bits_q, hidden[:, lo:hi].contiguous())), (lo, hi)
+
+
+@pytest.mark.parametrize("C,H,n,times", [(640, 8, 33, 125), (1280, 8, 20, 90), (672, 6, 64, 50), (96, 4, 17, 1200)])
+def test_sweep_over_repeated_rows(C, H, n, times):
+    """Rows repeated leave every mean as it is, but for the order of its float64 sum (2^-53 a term, some thousand partial sums)."""
+    Cc, text = 96, 5
+    few = normal(2, 1, n, C)
+    w = [normal(20 + i, C, k, std=k ** -0.5) for i, k in enumerate((Cc, Cc, C, C))]
+    context, scales = normal(4, 1, text, Cc, std=2.0), torch.zeros(3 * C, device="cuda")
+
+    def sweep(hidden):
+        s = T.make_shape(1, hidden.shape[1], C, H, text, Cc, bits_q=16, bits_prob=16, bits_proj=16)
+        return T.taq_token_sensitivity(hidden, context, *w, scales, range(text), (8, 4), s).cpu().numpy()
+
+    a, b = sweep(few), sweep(few.repeat(1, times, 1))
+    assert np.all(a[1] > 0) and np.all(np.abs(a - b) <= 1e-9 * a)
