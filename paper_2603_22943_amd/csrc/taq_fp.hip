@@ -8,6 +8,8 @@ namespace taq {
 
 typedef float fp_floatx4_t __attribute__((ext_vector_type(4)));
 typedef int fp_int4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 fp_bf16x8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 fp_half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 fp_half8_t __attribute__((ext_vector_type(8)));
 
 // ---------------------------------------------------------------- out[m][n] = sum_k A[m][k] * W[n][k]  (+ bias[n])
@@ -184,10 +186,9 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_kernel(const __half* __restri
 
 // float32 rows: V_MFMA_F32_16X16X4_F32, float32 operands throughout. 64 rows x 64 channels per workgroup, a wavefront
 // owns 16 rows. The contraction order within 16 consecutive k is free, so a lane takes four of them with one read and
-// feeds them to four MFMAs. blockIdx.z selects a slice of the contraction: k in [z*Kz, (z+1)*Kz), result at out + z*N
-// (one slice: a plain GEMM; one per head: the to_out contribution of every head by itself). Kz % 8 == 0.
+// feeds them to four MFMAs. K % 8 == 0.
 __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const float* __restrict__ A, const __half* __restrict__ W,
-                                                          const float* __restrict__ bias, int M, int N, int K, int Kz,
+                                                          const float* __restrict__ bias, int M, int N, int K,
                                                           float* __restrict__ out_f32, __half* __restrict__ out_f16, size_t ldo) {
     constexpr int KC = 32, RA = KC + 4, RW = KC + 4;  // row strides: 144 bytes of floats, 72 bytes of halves
     __shared__ __align__(16) float As[2][64 * RA];
@@ -200,14 +201,14 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const float* __restric
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int m = m0 + lr + 32 * i, n = n0 + lr + 32 * i;
-        ag[i] = A + (size_t)(m < M ? m : M - 1) * K + blockIdx.z * Kz;
-        wg[i] = W + (size_t)(n < N ? n : N - 1) * K + blockIdx.z * Kz;
+        ag[i] = A + (size_t)(m < M ? m : M - 1) * K;
+        wg[i] = W + (size_t)(n < N ? n : N - 1) * K;
     }
     float4 av[2];
     uint2 wv[2];
     bool in;
     auto fetch = [&](int k0) {
-        in = k0 + ls < Kz;
+        in = k0 + ls < K;
         const int k = in ? k0 + ls : 0;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -228,13 +229,13 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const float* __restric
     fetch(0);
     store(0);
     fetch(KC);
-    for (int k0 = 0, s = 0; k0 < Kz; k0 += KC, s ^= 1) {
+    for (int k0 = 0, s = 0; k0 < K; k0 += KC, s ^= 1) {
         __syncthreads();
-        if (k0 + KC < Kz) store(s ^ 1);
+        if (k0 + KC < K) store(s ^ 1);
         fetch(k0 + 2 * KC);
 #pragma unroll
         for (int u = 0; u < KC / 16; ++u) {
-            if (k0 + 16 * u >= Kz) break;
+            if (k0 + 16 * u >= K) break;
             const float4 a4 = *reinterpret_cast<const float4*>(&As[s][(16 * wave + r16) * RA + 16 * u + 4 * q]);
             const float ae[4] = {a4.x, a4.y, a4.z, a4.w};
             float we[4][4];
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const float* __restric
             const float4 b4 = *reinterpret_cast<const float4*>(bias + n);
             y = make_float4(y.x + b4.x, y.y + b4.y, y.z + b4.z, y.w + b4.w);
         }
-        const size_t at = (size_t)m * ldo + (size_t)blockIdx.z * N + n;
+        const size_t at = (size_t)m * ldo + n;
         if (out_f32) *reinterpret_cast<float4*>(out_f32 + at) = y;
         if (out_f16) {
             __half2* o = reinterpret_cast<__half2*>(out_f16 + at);
@@ -272,11 +273,114 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const float* __restric
     }
 }
 
+// The same products, a slice of the contraction per head, for finite float32 rows and without bias, on V_MFMA_F32_16X16X32_BF16. Three bfloat16
+// numbers hold the 24 bits of a float32 and two the 11 bits of an fp16 weight (each the leading 8 bits of what the ones before left: no
+// rounding), so six exact products stand for each product of before: 96 clocks of the matrix core for 16 x 16 x 32, against 256 of
+// V_MFMA_F32_16X16X4_F32, and no conversions beside the products. Sums are float32 as before, the small products of a step first.
+// 64 x 64 outputs per workgroup of four wavefronts, 32 x 32 each; what a step of 32 k needs is split when it is stored in LDS (80 bytes to
+// a row: conflict-free operand reads). One buffer of 25 KiB, so that five workgroups share a compute unit: 512 x 1280, eight heads of
+// 160, are 1280 of them, all at once. 24.5 -> 17.0 us (with two buffers, three to a unit, 19.7). Relative error against float64 at heads of 32, 40, 80
+// and 160: 1.0e-7, 1.1e-7, 1.6e-7, 2.3e-7 before, 0.4e-7, 0.6e-7, 1.0e-7, 1.6e-7 so; largest, over the sum of magnitudes, 3.3e-7 and 2.4e-7.
+__global__ __launch_bounds__(256) void gemm_nt_split_kernel(const float* __restrict__ A, const __half* __restrict__ W, int M, int N, int K, int Kz,
+                                                            float* __restrict__ out, size_t ldo) {
+    constexpr int KC = 32, RS = KC + 8;
+    __shared__ __align__(16) unsigned short As[3][64 * RS], Ws[2][64 * RS];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r16 = lane & 15, q = lane >> 4;
+    const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
+    const int lr = tid >> 3, ls = (tid & 7) * 4;  // staging: rows lr, lr + 32, four values from ls
+    const float* ag[2];
+    const __half* wg[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {  // rows past the end re-read the last one; their results are dropped
+        const int m = m0 + lr + 32 * i, n = n0 + lr + 32 * i;
+        ag[i] = A + (size_t)(m < M ? m : M - 1) * K + blockIdx.z * Kz;
+        wg[i] = W + (size_t)(n < N ? n : N - 1) * K + blockIdx.z * Kz;
+    }
+    fp_floatx4_t av[2];
+    fp_half4_t wv[2];
+    bool in;
+    auto fetch = [&](int k0) {
+        in = k0 + ls < Kz;
+        const int k = in ? k0 + ls : 0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            av[i] = *reinterpret_cast<const fp_floatx4_t*>(ag[i] + k);
+            wv[i] = *reinterpret_cast<const fp_half4_t*>(wg[i] + k);
+        }
+    };
+    // the leading 8 bits of four numbers, which become what they leave
+    auto lead = [](float (&x)[4]) {
+        unsigned u[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            u[e] = __float_as_uint(x[e]);
+            x[e] -= __uint_as_float(u[e] & 0xffff0000u);
+        }
+        return make_uint2(__builtin_amdgcn_perm(u[1], u[0], 0x07060302u), __builtin_amdgcn_perm(u[3], u[2], 0x07060302u));
+    };
+    auto store = [&]() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            float x[4], w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[e] = in ? av[i][e] : 0.f;
+                w[e] = in ? (float)wv[i][e] : 0.f;
+            }
+#pragma unroll
+            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(&As[p][(lr + 32 * i) * RS + ls]) = lead(x);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) *reinterpret_cast<uint2*>(&Ws[p][(lr + 32 * i) * RS + ls]) = lead(w);
+        }
+    };
+    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
+    fp_floatx4_t acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = (fp_floatx4_t){0.f, 0.f, 0.f, 0.f};
+    fetch(0);
+    for (int k0 = 0; k0 < Kz; k0 += KC) {
+        if (k0 > 0) __syncthreads();  // everybody is done with the step before
+        store();
+        fetch(k0 + KC);
+        __syncthreads();
+        fp_bf16x8_t a[3][2], w[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int p = 0; p < 3; ++p) a[p][i] = *reinterpret_cast<const fp_bf16x8_t*>(&As[p][(wm + 16 * i + r16) * RS + 8 * q]);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) w[p][i] = *reinterpret_cast<const fp_bf16x8_t*>(&Ws[p][(wn + 16 * i + r16) * RS + 8 * q]);
+        }
+#pragma unroll
+        for (int o = 3; o >= 0; --o)  // a[pa] w[pw], pa + pw = o
+#pragma unroll
+            for (int pw = 1; pw >= 0; --pw) {
+                const int pa = o - pw;
+                if (pa < 0 || pa > 2) continue;
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[pw][i], a[pa][j], acc[i][j], 0, 0, 0);
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int m = m0 + wm + 16 * j + r16;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int n = n0 + wn + 16 * i + 4 * q;  // N % 4 == 0: the four channels are in or out together
+            if (m < M && n < N) *reinterpret_cast<fp_floatx4_t*>(out + (size_t)m * ldo + (size_t)blockIdx.z * N + n) = acc[i][j];
+        }
+    }
+}
+
 hipError_t launch_gemm_fp(const void* A, bool a_is_f32, const __half* W, const float* bias, int M, int N, int K,
                           float* out_f32, __half* out_f16, int ldo, hipStream_t st) {
     const dim3 grid((M + 63) / 64, (N + 63) / 64), block(256);
     if (a_is_f32)
-        hipLaunchKernelGGL(gemm_nt_f32_kernel, grid, block, 0, st, static_cast<const float*>(A), W, bias, M, N, K, K, out_f32, out_f16, (size_t)ldo);
+        hipLaunchKernelGGL(gemm_nt_f32_kernel, grid, block, 0, st, static_cast<const float*>(A), W, bias, M, N, K, out_f32, out_f16, (size_t)ldo);
     else
         launch_gemm_seq(static_cast<const __half*>(A), W, nullptr, bias, M, N, K, out_f32, out_f16, ldo, st);
     return hipGetLastError();
@@ -296,8 +400,7 @@ hipError_t launch_gemm_f16(const __half* A, const __half* W, int M, int N, int K
 }
 
 hipError_t launch_gemm_f32_heads(const float* A, const __half* W, int M, int N, int K, int H, float* out, hipStream_t st) {
-    hipLaunchKernelGGL(gemm_nt_f32_kernel, dim3((M + 63) / 64, (N + 63) / 64, H), dim3(256), 0, st, A, W, nullptr, M, N, K, K / H, out,
-                       nullptr, (size_t)H * N);
+    hipLaunchKernelGGL(gemm_nt_split_kernel, dim3((M + 63) / 64, (N + 63) / 64, H), dim3(256), 0, st, A, W, M, N, K, K / H, out, (size_t)H * N);
     return hipGetLastError();
 }
 
