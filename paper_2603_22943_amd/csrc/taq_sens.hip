@@ -108,53 +108,74 @@ __device__ __forceinline__ float sens_quad_sum(float x) {
 }
 
 // ---------------------------------------------------------------- attention of the reference block and the sweep's factors
-// One workgroup of one wavefront per (16 image tokens, head) (spread over the compute units: 4 in a workgroup left most
-// of them idle): S^T = K Q^T and the score changes (k' - k) Q^T of every text token, softmax, O^T = V^T A^T, all with
+// One workgroup of WV = 1 or 4 wavefronts per (16 image tokens, head): S^T = K Q^T and the score changes (k' - k) Q^T of every text token, softmax, O^T = V^T A^T, all with
 // V_MFMA_F32_16X16X4_F32 (text tokens or channels along the rows, image tokens along the columns: the accumulator
-// registers of the scores are the B operand of the last product). A chain of latencies: each step's operands are
-// requested while the step before is multiplied. o, md [row][C], ab [row][nk][NB][H]{alpha, beta}, dom [row][H] (swept token
+// registers of the scores are the B operand of the last product). Each step's operands are requested while the step before is
+// multiplied. Four wavefronts share out the operand tiles of the scores, the text tokens' factors (element i of each accumulator) and
+// the channel blocks of O; scores and weights pass through LDS. One wavefront by itself on a SIMD issues an instruction every 8.6
+// clocks, and 5000 of them were the time: 34 -> 18.9 us at 512 tokens of eight heads of 160 (256 workgroups), same bits. Where there are
+// wavefronts enough without, the maxima and sums that all four form cost more. Sweeps of 20 tokens with one and with four: 600 workgroups
+// (2 x 240 of 20 heads of 64) 576, 558 us; 1024 (2 x 1024, heads of 80) 169, 165; 4096 (2 x 4096, heads of 40) 278, 314: the line is 1024.
+// o, md [row][C], ab [row][nk][NB][H]{alpha, beta}, dom [row][H] (swept token
 // or -1), dcoef [row][H][NB], rows counted from row0 over all batch elements, D.Np of them each; md is written by wavefronts
 // with a dom >= 0 only. MT: tiles of 16 text tokens.
-template <int NB, int MT>
-__global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__ q_f, const float* __restrict__ kx,
+template <int NB, int MT, int WV>
+__global__ __launch_bounds__(64 * WV) void sens_attn_kernel(const float* __restrict__ q_f, const float* __restrict__ kx,
                                                         const float* __restrict__ vx, SensDims D, int row0,
                                                         float* __restrict__ o, float* __restrict__ ab, int* __restrict__ dom,
                                                         float* __restrict__ dcoef, float* __restrict__ md) {
-    const int lane = threadIdx.x, r16 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
     const int tile = blockIdx.x, h = blockIdx.y;
     const int row = tile * 16 + r16;  // of the chunk
     const int b = (row0 + tile * 16) / D.Np, np = (row0 + row) % D.Np, n = np < D.N ? np : D.N - 1;
     const int d = D.d, C = D.C, T = D.T, S16 = (d + 15) >> 4;
-    constexpr int NP = (1 + NB) * MT;  // operands of a step
-    sens_floatx4_t S[1 + NB][MT];
+    constexpr int NP = (1 + NB) * MT, NW = (NP + WV - 1) / WV;  // operands of a step, of a wavefront: wave, wave + WV, ...
+    __shared__ sens_floatx4_t sS[WV > 1 ? NP : 1][64];    // scores and their changes, as the accumulators hold them
+    __shared__ __align__(16) float sp[WV > 1 ? MT : 1][64][4];        // weights
+    __shared__ int sflag[4][16];
+    sens_floatx4_t acc[NW];
 #pragma unroll
-    for (int j = 0; j <= NB; ++j)
-#pragma unroll
-        for (int tt = 0; tt < MT; ++tt) S[j][tt] = (sens_floatx4_t){0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < NW; ++u) acc[u] = (sens_floatx4_t){0.f, 0.f, 0.f, 0.f};
     const float* qr = q_f + ((size_t)b * D.N + n) * C + h * d;
     const float4* kr = reinterpret_cast<const float4*>(kx) + ((size_t)b * D.H + h) * S16 * NP * 64 + lane;
-    float4 kv[NP], qv;
+    float4 kv[NW], qv;
     auto fetch = [&](int s) {
         const int sc = s < S16 ? s : S16 - 1, k = 16 * sc + 4 * q;
         qv = *reinterpret_cast<const float4*>(qr + (k < d ? k : 0));  // (meets zeros of K past the head)
 #pragma unroll
-        for (int p = 0; p < NP; ++p) kv[p] = kr[((size_t)sc * NP + p) * 64];
+        for (int u = 0; u < NW; ++u) kv[u] = kr[((size_t)sc * NP + (wave + WV * u < NP ? wave + WV * u : NP - 1)) * 64];
     };
     fetch(0);
     for (int s = 0; s < S16; ++s) {
-        float4 kc[NP];
+        float4 kc[NW];
 #pragma unroll
-        for (int p = 0; p < NP; ++p) kc[p] = kv[p];
+        for (int u = 0; u < NW; ++u) kc[u] = kv[u];
         const float qe[4] = {qv.x, qv.y, qv.z, qv.w};
         fetch(s + 1);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const float ke[4] = {kc[p].x, kc[p].y, kc[p].z, kc[p].w};
-                S[p / MT][p % MT] = __builtin_amdgcn_mfma_f32_16x16x4f32(ke[e], qe[e], S[p / MT][p % MT], 0, 0, 0);
+            for (int u = 0; u < NW; ++u) {
+                const float ke[4] = {kc[u].x, kc[u].y, kc[u].z, kc[u].w};
+                acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(ke[e], qe[e], acc[u], 0, 0, 0);
             }
     }
+    sens_floatx4_t S[MT], pw[MT];
+    if constexpr (WV > 1) {
+#pragma unroll
+        for (int u = 0; u < NW; ++u)
+            if (wave + WV * u < NP) sS[wave + WV * u][lane] = acc[u];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int tt = 0; tt < MT; ++tt) {
+        if constexpr (WV > 1) S[tt] = sS[tt][lane];
+        else S[tt] = acc[tt];
+    }
+    auto change = [&](int j, int tt, int i) -> float {  // of the score by width j
+        if constexpr (WV > 1) return reinterpret_cast<const float*>(&sS[(1 + j) * MT + tt][lane])[i];
+        else return acc[(1 + j) * MT + tt][i];
+    };
     // this lane: text tokens 16*tt + 4*q + i of image token r16
     float mx = -__builtin_inff();
 #pragma unroll
@@ -162,8 +183,8 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const bool live = 16 * tt + 4 * q + i < T;
-            S[0][tt][i] = live ? S[0][tt][i] * D.sigma : -__builtin_inff();
-            mx = fmaxf(mx, S[0][tt][i]);
+            S[tt][i] = live ? S[tt][i] * D.sigma : -__builtin_inff();
+            mx = fmaxf(mx, S[tt][i]);
         }
     mx = sens_quad_max(mx);
     int top = TAQ_MAX_T;  // the first token of the largest score
@@ -172,7 +193,7 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int t = 16 * tt + 4 * q + i;
-            if (S[0][tt][i] == mx && t < top) top = t;
+            if (S[tt][i] == mx && t < top) top = t;
         }
     top = min(top, __shfl_xor(top, 16));
     top = min(top, __shfl_xor(top, 32));
@@ -181,7 +202,7 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
     for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (16 * tt + 4 * q + i != top) mr = fmaxf(mr, S[0][tt][i]);
+            if (16 * tt + 4 * q + i != top) mr = fmaxf(mr, S[tt][i]);
     const bool alone = T == 1;
     mr = alone ? mx : sens_quad_max(mr);
     float Z = 0.f, R2 = 0.f;  // sum over all tokens beside the largest score, over the others beside theirs (>= 1 both)
@@ -189,8 +210,8 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
     for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            Z += __expf(S[0][tt][i] - mx);
-            R2 += 16 * tt + 4 * q + i == top ? 0.f : __expf(S[0][tt][i] - mr);
+            Z += __expf(S[tt][i] - mx);
+            R2 += 16 * tt + 4 * q + i == top ? 0.f : __expf(S[tt][i] - mr);
         }
     Z = sens_quad_sum(Z);
     R2 = sens_quad_sum(R2);
@@ -199,20 +220,21 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
 #pragma unroll
     for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int t = 16 * tt + 4 * q + i;
-            const float e = __expf(S[0][tt][i] - mx), p = e / Z;
+        for (int ii = 0; ii < 4 / WV; ++ii) {  // element `wave` of each tile, or all four
+            const int i = WV > 1 ? wave : ii, t = 16 * tt + 4 * q + i;
+            const float s0 = WV == 1 ? S[tt][ii] : wave == 0 ? S[tt][0] : wave == 1 ? S[tt][1] : wave == 2 ? S[tt][2] : S[tt][3];
+            const float e = __expf(s0 - mx), p = e / Z;
             const int k = t < T ? D.slot[t] : -1;
             if (k >= 0) {
                 const bool is_top = t == top;
                 const float R = is_top ? R2 : Z - e;                     // the others' sum, >= 1 but for rounding ...
-                const float lead = S[0][tt][i] - (is_top ? mr : mx);    // ... and this token's score beside the same reference
+                const float lead = s0 - (is_top ? mr : mx);    // ... and this token's score beside the same reference
                 const float u = is_top ? u_top : R * inv_z;
                 float al[NB], be[NB], w[NB], Rc[NB];
                 bool hv[NB], heavy = false;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    const float dl = alone ? 0.f : S[1 + j][tt][i] * D.sigma;
+                    const float dl = alone ? 0.f : change(j, tt, i) * D.sigma;
                     const float x = lead + dl, c = fmaxf(x, 0.f);
                     w[j] = __expf(x - c);
                     Rc[j] = R * __expf(-c);
@@ -235,18 +257,26 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
                 for (int j = 0; j < NB; ++j)
                     reinterpret_cast<float2*>(ab)[(((size_t)row * D.nk + k) * NB + j) * D.H + h] = make_float2(al[j], be[j]);
             }
-            S[1][tt][i] = p;
+            if constexpr (WV > 1) sp[tt][lane][i] = p;
+            else pw[tt][ii] = p;
         }
     flagged = max(flagged, __shfl_xor(flagged, 16));
     flagged = max(flagged, __shfl_xor(flagged, 32));
-    if (q == 0) dom[(size_t)row * D.H + h] = flagged;
+    if constexpr (WV > 1) {
+        if (q == 0) sflag[wave][r16] = flagged;
+        __syncthreads();
+        flagged = max(max(sflag[0][r16], sflag[1][r16]), max(sflag[2][r16], sflag[3][r16]));
+#pragma unroll
+        for (int tt = 0; tt < MT; ++tt) pw[tt] = *reinterpret_cast<const sens_floatx4_t*>(sp[tt][lane]);
+    }
+    if (wave == 0 && q == 0) dom[(size_t)row * D.H + h] = flagged;
     const bool sharp = __any(flagged >= 0);
     if (sharp) {  // m - v as weights of the V rows
         const float inv = 1.f / R2;
 #pragma unroll
         for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) S[0][tt][i] = 16 * tt + 4 * q + i == top ? -1.f : __expf(S[0][tt][i] - mr) * inv;
+            for (int i = 0; i < 4; ++i) S[tt][i] = 16 * tt + 4 * q + i == top ? -1.f : __expf(S[tt][i] - mr) * inv;
     }
     float va[MT][4];
     auto fetch_v = [&](int j0) {
@@ -259,19 +289,19 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
                 va[tt][i] = vx[((size_t)b * T + (t < T ? t : T - 1)) * C + h * d + c];  // (weight 0 past the last token)
             }
     };
-    fetch_v(0);
-    for (int j0 = 0; j0 < d; j0 += 16) {
+    fetch_v(16 * wave);
+    for (int j0 = 16 * wave; j0 < d; j0 += 16 * WV) {
         float vc[MT][4];
 #pragma unroll
         for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) vc[tt][i] = va[tt][i];
-        fetch_v(j0 + 16);
+        fetch_v(j0 + 16 * WV);
         sens_floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[tt][i], S[1][tt][i], acc, 0, 0, 0);
+            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[tt][i], pw[tt][i], acc, 0, 0, 0);
         if (j0 + 4 * q < d)
             *reinterpret_cast<float4*>(o + (size_t)row * C + h * d + j0 + 4 * q) = make_float4(acc[0], acc[1], acc[2], acc[3]);
         if (sharp) {
@@ -279,7 +309,7 @@ __global__ __launch_bounds__(64) void sens_attn_kernel(const float* __restrict__
 #pragma unroll
             for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) m = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[tt][i], S[0][tt][i], m, 0, 0, 0);
+                for (int i = 0; i < 4; ++i) m = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[tt][i], S[tt][i], m, 0, 0, 0);
             if (j0 + 4 * q < d)
                 *reinterpret_cast<float4*>(md + (size_t)row * C + h * d + j0 + 4 * q) = make_float4(m[0], m[1], m[2], m[3]);
         }
@@ -525,7 +555,10 @@ static hipError_t sens_run(const void* hidden, const void* context, const __half
     for (int r0 = 0; r0 < rows; r0 += W.chunk) {
         const int nr = rows - r0 < W.chunk ? rows - r0 : W.chunk;  // a multiple of 32
 #define TAQ_SENS_ATTN(MT) \
-    case MT: hipLaunchKernelGGL((sens_attn_kernel<NB, MT>), dim3(nr / 16, H), dim3(64), 0, st, q_f, kx, vx, D, r0, o, ab, dom, dcoef, md); break;
+    case MT: \
+        if (nr / 16 * H <= 1024) hipLaunchKernelGGL((sens_attn_kernel<NB, MT, 4>), dim3(nr / 16, H), dim3(256), 0, st, q_f, kx, vx, D, r0, o, ab, dom, dcoef, md); \
+        else hipLaunchKernelGGL((sens_attn_kernel<NB, MT, 1>), dim3(nr / 16, H), dim3(64), 0, st, q_f, kx, vx, D, r0, o, ab, dom, dcoef, md); \
+        break;
         switch ((s.T + 15) / 16) {
             TAQ_SENS_ATTN(1) TAQ_SENS_ATTN(2) TAQ_SENS_ATTN(3) TAQ_SENS_ATTN(4) TAQ_SENS_ATTN(5) TAQ_SENS_ATTN(6)
             default: return hipErrorInvalidValue;
