@@ -115,16 +115,13 @@ __device__ __forceinline__ unsigned quant4_settle(unsigned pk, float x0, float x
     const unsigned flags = pk ^ quant4_at(x0, x1, x2, x3, __builtin_fmaf(fc, 4.76837158203125e-07f, fc));
     return flags ? quant4_ties(pk, flags, x0, x1, x2, x3, r.f, fc, r.amax, qmaxf) : pk;
 }
-__device__ __forceinline__ unsigned quant4_exact(float x0, float x1, float x2, float x3, QuantRow r, float qmaxf) {
-    unsigned doubt = TAQ_SURE;
-    return quant4_settle(quant4_fast(x0, x1, x2, x3, r, doubt), x0, x1, x2, x3, r, qmaxf);
-}
 
 // Codes of a row of fp16 values (amax one of them): for most rows one product settles them. |x| 127 / amax = 127 X / (A 2^s) with integer
 // significands X, A < 2^11 and s >= 0 is either half an integer H or, relatively, at least 1 / (2 * 127 * 2047) = 1.9e-6 away from one, further than
 // c (1 + 2^-21) is from 127 / amax (at most 6e-7). And it is H itself only if 254 X = (2 k + 1) A 2^s: where the prime 127 does not
 // divide A, it divides 2 k + 1 <= 254, so H = 63.5, whose even neighbour is the outer one, which that product rounds to. Rows with
-// 127 | A, one in 128, are those whose scale amax / 127 is exact; they go by quant4_fast and quant4_settle. (Every fp16 amax against every fp16 value below it: the definition's codes.)
+// 127 | A, one in 128, are those whose scale amax / 127 is exact; their outer candidates go on to half_row_settle. (Every fp16 amax against
+// every fp16 value below it: the definition's codes.)
 // 7 instructions per four values instead of 15: with div_grid 61.9 -> 60.7 us at 16 requests of 4096 x 320, 10.86 -> 10.78 at 2 x 4096 x 320.
 struct HalfRow {
     float m;      // the product's factor
@@ -132,6 +129,14 @@ struct HalfRow {
 };
 __device__ __forceinline__ HalfRow half_row(float c, float scale, float amax) {  // c = quant_mult(127, amax), scale = amax / 127
     return {__builtin_fmaf(c, 4.76837158203125e-07f, c), __builtin_fmaf(-scale, 127.f, amax) == 0.f};
+}
+
+// Four codes of a row with 127 | A from its outer candidates `pk`: the inner ones, and the ties where they differ. (The quantizer begun
+// anew for such rows, by quant4_fast and quant4_settle: 73 registers instead of 50 in rowquant_op_kernel, six wavefronts to a SIMD instead of
+// eight; 2 x 4096 x 640, us, 5.59 and 5.49 on normal values, 6.44 and 5.72 where every row is one.)
+__device__ __forceinline__ unsigned half_row_settle(unsigned pk, float x0, float x1, float x2, float x3, QuantRow r) {
+    const unsigned in = quant4_at(x0, x1, x2, x3, __builtin_fmaf(r.c, -4.76837158203125e-07f, r.c)), flags = in ^ pk;
+    return flags ? quant4_ties(in, flags, x0, x1, x2, x3, 1.f, r.c, r.amax, 127.f) : pk;
 }
 
 // Whether any lane of the wavefront is in doubt: one test for as many values as a wavefront has at hand, and a branch out of line

@@ -356,7 +356,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
 #pragma unroll
                 for (int u = 0; u < XW; ++u) {
                     const float4 x = hidden4(it, u);
-                    pk[u] = quant4_exact(x.x, x.y, x.z, x.w, hrow, 127.f);
+                    pk[u] = half_row_settle(pk[u], x.x, x.y, x.z, x.w, hrow);
                 }
             put_hidden(it, pk);
         }
@@ -369,7 +369,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
 #pragma unroll
             for (int u = 0; u < XW; ++u) {
                 const float4 x = hidden4(it, u);
-                pk[u] = quant4_exact(x.x, x.y, x.z, x.w, hrow, 127.f);
+                pk[u] = half_row_settle(quant4_at(x.x, x.y, x.z, x.w, half.m), x.x, x.y, x.z, x.w, hrow);
             }
             put_hidden(it, pk);
         }

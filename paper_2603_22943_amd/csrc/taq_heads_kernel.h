@@ -215,7 +215,7 @@ void heads_kernel(std::conditional_t<MANY, HeadsManyArgs, HeadsArgs> args) {
             for (int ks = it * LPI; ks < (it + 1) * LPI && ks < KPRE; ++ks) load_w(ks);
             const float4 x = hidden4(it, 0), y = hidden4(it, 1);
             uint2 pk = make_uint2(quant4_at(x.x, x.y, x.z, x.w, half.m), quant4_at(y.x, y.y, y.z, y.w, half.m));
-            if (again) pk = make_uint2(quant4_exact(x.x, x.y, x.z, x.w, hrow, 127.f), quant4_exact(y.x, y.y, y.z, y.w, hrow, 127.f));
+            if (again) pk = make_uint2(half_row_settle(pk.x, x.x, x.y, x.z, x.w, hrow), half_row_settle(pk.y, y.x, y.y, y.z, y.w, hrow));
             *reinterpret_cast<uint2*>(tileq + tok0 * F::TILE_RS + (it * TPT + part0) * 8) = pk;
             if (tap && a.dbg.h_code) *reinterpret_cast<uint2*>(a.dbg.h_code + row0 * C + (it * TPT + part0) * 8) = pk;
             __builtin_amdgcn_sched_barrier(0);

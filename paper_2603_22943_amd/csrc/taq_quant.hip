@@ -68,7 +68,13 @@ __device__ __forceinline__ void rowquant_f16_held(const uint4* __restrict__ xr, 
         const float4 f = values(i);
         pk[i] = quant4_at(f.x, f.y, f.z, f.w, half.m);
     }
-    if (TAQ_DOUBT(half.doubt)) quant4_group<2 * NV>(pk, values, [&](int) { return QuantRow{1.f, c, safe}; });
+    if (TAQ_DOUBT(half.doubt)) {
+#pragma unroll
+        for (int i = 0; i < 2 * NV; ++i) {
+            const float4 f = values(i);
+            pk[i] = half_row_settle(pk[i], f.x, f.y, f.z, f.w, QuantRow{1.f, c, safe});
+        }
+    }
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int v = lane + 64 * i;
