@@ -93,9 +93,8 @@ struct FusedCfg {
     // fewer with three or four token tiles, whose accumulators take the rest. (DENSE 6 -> 12: 65.3 -> 63.4 us for 16 requests
     // of 4096 tokens; 24 and 8 -> 32 and 16 with two token tiles: 20.6 -> 19.9 us at eight heads of 80 and 8192 tokens,
     // 21.6 -> 20.9 us at ten of 64; one more step up spills, and at ten heads, whose wavefronts have 168 registers, three token
-    // tiles do already: 14 registers in 60 bytes of scratch, 21 with row-major weights. 39 -> 29.9 us at 12288 tokens of ten heads
-    // all the same, for one round instead of two. Row-major weights with four tiles at d = 80 spill 3, with run-time T at ten
-    // heads 2.)
+    // tiles do already: 14 registers in 60 bytes of scratch, 12 in 52 with row-major weights. 39 -> 29.8 us at 12288 tokens of ten
+    // heads all the same, for one round instead of two. Row-major weights with four tiles at d = 80 spill 4 in 20 bytes.)
     static constexpr int RING_MAX = DENSE ? 12 : NH > 8 ? (NTT > 2 ? 8 : NTT == 2 ? 16 : 20) : NTT == 4 ? 20 : NTT == 3 ? 28 : 32;
     static constexpr int RING = !PREFETCH_W ? (NF < RING_MAX ? NF : RING_MAX) : 0;
 };
@@ -121,6 +120,11 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     // dwords of codes per test for ties. Whole groups but with row-major weights (4 % slower there at d = 80) and three or four token tiles (registers): the 16 layers of a step of 2 x 64 x 64 249.9 -> 247.2 us,
     // of 8 x 96 x 64 642 -> 640, 16 requests of 4096 x 320 59.1 -> 58.8, 2 x 4096 x 640 20.5 -> 20.4.
     constexpr int QG = ROWMAJ || NTT > 2 ? 1 : TPH;
+    // Scores past the protected tokens become minus infinity by selects behind the products instead of starting there, where the four
+    // starting values are registers too many: 1 and 8 spilled without, none so. us: 2 x 8192 x 640, eight heads, 33.2 -> 33.0 (0 to 1 % in four
+    // runs), ten heads with 50 text tokens, 20 of them protected, log2 grid, 18.45 -> 17.5. Three token tiles at ten heads (14 and 12 spilled or, so, 12 and 11) and row-major weights
+    // with four (4 or 3) are no faster so: 29.6 and 31.1 us at 12288 tokens against 29.6 and 31.2, 34.3 at 2 x 8192 against 34.5.
+    constexpr bool SELECT = (NTT == 4 && !ROWMAJ) || (NH > 8 && NTT == 1 && NT16 == 0 && LOGP);
     constexpr bool TAPS = NT16 == 0;       // taps of intermediate codes and scales (tests, profiling)
     extern __shared__ __align__(16) unsigned char smem[];
 
@@ -579,7 +583,7 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     auto protected_scores = [&](auto first, int ft, const unsigned (&code)[NTT][TPH], floatx4_t (&facc)[NTT]) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float none = 16 * ft + 4 * q + i < ntrig ? 0.f : TAQ_NEG_INF;
+            const float none = SELECT || 16 * ft + 4 * q + i < ntrig ? 0.f : TAQ_NEG_INF;
 #pragma unroll
             for (int nt = 0; nt < NTT; ++nt) facc[nt][i] = none;
         }
@@ -607,6 +611,14 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
                 if (2 * s + 1 < TPH) biased4_to_half(code[nt][2 * s + 1 < TPH ? 2 * s + 1 : 0] ^ 0x80808080u, c2, c3);
                 const half8_t qh = {c0[0], c0[1], c1[0], c1[1], c2[0], c2[1], c3[0], c3[1]};
                 facc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka, qh, facc[nt], 0, 0, 0);
+            }
+        }
+        if constexpr (SELECT) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool live = 16 * ft + 4 * q + i < ntrig;
+#pragma unroll
+                for (int nt = 0; nt < NTT; ++nt) facc[nt][i] = live ? facc[nt][i] : TAQ_NEG_INF;
             }
         }
     };

@@ -33,3 +33,14 @@ def test_row_quantizers_leave_room_for_eight_wavefronts(metadata, kernel):
     """512 registers of a SIMD's lane: 8192 rows are 8 wavefronts a SIMD, and with 73 registers ran as two rounds of six."""
     found = [int(f["vgpr_count"]) for name, f in metadata.items() if kernel in name]
     assert found and max(found) <= 64, found
+
+
+def test_scratch(metadata):
+    """Bytes of scratch a lane: none but where it is known, and known to cost nothing (csrc/taq_fused_kernel.h, FusedCfg and SELECT)."""
+    spilled = {name: int(f["private_segment_fixed_size"]) for name, f in metadata.items() if int(f["private_segment_fixed_size"])}
+    known = {}
+    for grid in range(3):
+        for d, heads, tiles, rows, most in ((64, 10, 3, 0, 60), (64, 10, 3, 1, 52), (80, 8, 4, 1, 20)):
+            known[f"fused_block_kernelILi{d}ELi{heads}ELi{tiles}ELi{grid}ELi{16 * tiles}ELi5ELb0ELb{rows}EE"] = most
+    for name, size in spilled.items():
+        assert any(k in name and size <= most for k, most in known.items()), (name, size)
