@@ -108,7 +108,7 @@ static void launch_gemm_seq(const __half* A, const __half* W0, const __half* W1,
 // fp16 rows: V_MFMA_F32_16X16X32_F16 (products of fp16 numbers are exact in float32). 32 MI x 32 MI outputs per workgroup of four
 // wavefronts, 16 MI x 16 MI each; every output is one chain of products in K order, whatever the tile. K % 32 == 0.
 // A step is as long as a load takes, so with few outputs small tiles and long steps: 512 x 1280 x 1280 as 640 workgroups of
-// 32 x 32 and ten steps 11.8 us, as 160 of 64 x 64 and twenty steps 21.
+// 32 x 32 and ten steps 10.1 us, as 160 of 64 x 64 and twenty steps 12.0 (gemm_f16_small: where the line lies).
 template <int MI, int KC>
 __global__ __launch_bounds__(256) void gemm_nt_f16_kernel(const __half* __restrict__ A, const __half* __restrict__ W, int M, int N, int K,
                                                           float* __restrict__ out) {
@@ -127,22 +127,23 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_kernel(const __half* __restri
         ag[i] = A + (size_t)(m < M ? m : M - 1) * K;
         wg[i] = W + (size_t)(n < N ? n : N - 1) * K;
     }
-    uint4 av[NL], wv[NL];
+    fp_int4_t av[NL], wv[NL];
     bool in;
     auto fetch = [&](int k0) {  // (the last step may be partly filled: zeros past the end, set when the step is stored)
         in = k0 + ls < K;
         const int k = in ? k0 + ls : 0;
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            av[i] = *reinterpret_cast<const uint4*>(ag[i] + k);
-            wv[i] = *reinterpret_cast<const uint4*>(wg[i] + k);
+            av[i] = *reinterpret_cast<const fp_int4_t*>(ag[i] + k);
+            wv[i] = *reinterpret_cast<const fp_int4_t*>(wg[i] + k);
         }
     };
+    const fp_int4_t zero = {0, 0, 0, 0};  // (a vector: selects; of a struct of four they become branches around the stores, 0.1 to 1.2 us a call)
     auto store = [&](int s) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            *reinterpret_cast<uint4*>(&As[s][(lr + RPP * i) * RS + ls]) = in ? av[i] : make_uint4(0u, 0u, 0u, 0u);
-            *reinterpret_cast<uint4*>(&Ws[s][(lr + RPP * i) * RS + ls]) = in ? wv[i] : make_uint4(0u, 0u, 0u, 0u);
+            *reinterpret_cast<fp_int4_t*>(&As[s][(lr + RPP * i) * RS + ls]) = in ? av[i] : zero;
+            *reinterpret_cast<fp_int4_t*>(&Ws[s][(lr + RPP * i) * RS + ls]) = in ? wv[i] : zero;
         }
     };
     const int wm = (wave & 1) * 16 * MI, wn = (wave >> 1) * 16 * MI;
@@ -392,7 +393,7 @@ hipError_t launch_gemm_kv_rows(const __half* context, const __half* Wk, const __
 }
 
 hipError_t launch_gemm_f16(const __half* A, const __half* W, int M, int N, int K, float* out, hipStream_t st) {
-    if ((size_t)((M + 63) / 64) * ((N + 63) / 64) < 512)
+    if (gemm_f16_small(M, N))
         hipLaunchKernelGGL((gemm_nt_f16_kernel<1, 128>), dim3((M + 31) / 32, (N + 31) / 32), dim3(256), 0, st, A, W, M, N, K, out);
     else
         hipLaunchKernelGGL((gemm_nt_f16_kernel<2, 64>), dim3((M + 63) / 64, (N + 63) / 64), dim3(256), 0, st, A, W, M, N, K, out);

@@ -446,7 +446,10 @@ hipError_t launch_gemm_fp(const void* A, bool a_is_f32, const __half* W, const f
                           float* out_f32, __half* out_f16, int ldo, hipStream_t st);
 //   K and V rows of a context in one launch: rows_f [M][2C], the same sums as two calls of launch_gemm_fp
 hipError_t launch_gemm_kv_rows(const __half* context, const __half* Wk, const __half* Wv, int M, int C, int K, float* rows_f, hipStream_t st);
-//   fp16 rows on the matrix cores (any order of summation: for sums that no quantizer reads), out f32 [M][N]
+//   fp16 rows on the matrix cores (any order of summation: for sums that no quantizer reads), out f32 [M][N]; tiles of 32 x 32 outputs, or of
+//   64 x 64 where that would be more than 1152 small workgroups: four to each of 256 compute units are at work at once, all that
+//   their LDS takes, and an eighth more cost no more than the large tiles do; from 1400 on they do (tests/host/fullprec_rule.cpp has the timings)
+inline bool gemm_f16_small(int M, int N) { return (size_t)((M + 31) / 32) * ((N + 31) / 32) <= 1152; }
 hipError_t launch_gemm_f16(const __half* A, const __half* W, int M, int N, int K, float* out, hipStream_t st);
 //   the same as launch_gemm_fp for every head's slice of the contraction by itself: out[m][h][n] = sum over k in head h (A f32 [M][K], K = H*d)
 hipError_t launch_gemm_f32_heads(const float* A, const __half* W, int M, int N, int K, int H, float* out, hipStream_t st);
