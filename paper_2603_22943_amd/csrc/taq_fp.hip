@@ -17,26 +17,29 @@ typedef _Float16 fp_half8_t __attribute__((ext_vector_type(8)));
 
 // fp16 rows whose sums feed a quantizer: one float32 FMA chain per output in K order, so that a sum, and with it a code,
 // is the same number whatever the tiling (products of fp16 numbers are exact; v_fma_mix reads the fp16 operands as they
-// are). 16 x 32 TN outputs per workgroup, 2 x TN per thread (columns tx, tx + 32, ...). Chunks of 64 k in two LDS buffers, rows of
-// 144 bytes: a thread reads eight k of a row at a time, without conflicts, TN + 2 reads for 16 TN FMAs. The next chunk travels in registers.
+// are). 8 TM x 64 outputs per workgroup, TM x 2 per thread (columns tx, tx + 32). Chunks of 64 k in two LDS buffers, rows of 144 bytes: a
+// thread reads eight k of a row at a time, without conflicts, TM + 2 reads for 16 TM FMAs. The next chunk travels in registers.
 // Bound by vector issue. One wavefront of a SIMD issues an instruction every 8.6 clocks, two and more one in 4.3, so with few rows the
-// tile is the small one: 154 x 2 x 1280 x 768 are 400 workgroups, 1.6 wavefronts to a SIMD, 22.6 us; with 32 x 64 outputs to a workgroup and
-// 2 x 4 to a thread, 200 workgroups, 27. From 1024 small workgroups on (four wavefronts to a SIMD) TN = 4 reads less per
-// FMA, unless half of the last column block would be empty (8192 x 320 x 320: the layer 6 us longer with it).
+// tile is the small one, TM = 2: 154 x 2 x 1280 x 768 are 400 workgroups, 1.6 wavefronts to a SIMD, 19.2 us; with TM = 4 200 workgroups and 26.3.
+// With many rows TM = 4 reads less per FMA (gemm_seq_rows: where the line lies); 128 columns instead of twice the rows, 4 x 64 outputs to
+// a wavefront and 132 registers, are 1 to 20 % slower from 500 small workgroups to 11000.
+// With TM = 2 half of the threads load a row of A that another holds already, and the last two chunks are loaded for nothing: behind a
+// condition the loads no longer lie between the FMAs (154 x 1280 x 1280 20.6 and 24.9 us, 4096 x 320 x 320 17.1 and 17.4, equal from 2500 workgroups on).
 // blockIdx.z = 1: a second matrix W1 of the same size, results `N` columns further (K and V of a context in one launch).
-template <int TN>
+template <int TM>
 __global__ __launch_bounds__(256) void gemm_nt_seq_kernel(const __half* __restrict__ A, const __half* __restrict__ W0,
                                                           const __half* __restrict__ W1, const float* __restrict__ bias, int M,
                                                           int N, int K, float* __restrict__ out_f32, __half* __restrict__ out_f16,
                                                           int ldo) {
-    constexpr int KC = 64, RS = KC + 8;
-    __shared__ __align__(16) __half As[2][16 * RS], Ws[2][32 * TN * RS];
+    constexpr int TN = 2, KC = 64, RS = KC + 8;
+    __shared__ __align__(16) __half As[2][8 * TM * RS], Ws[2][32 * TN * RS];
     const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
-    const int m0 = blockIdx.x * 16, n0 = blockIdx.y * 32 * TN;
+    const int m0 = blockIdx.x * 8 * TM, n0 = blockIdx.y * 32 * TN;
     const __half* W = blockIdx.z ? W1 : W0;
     const int cz = blockIdx.z ? N : 0;
-    const int lr = tid >> 3, ls = (tid & 7) * 8;  // staging: rows lr, lr + 32, ..., eight halves from ls
-    const __half* ag = A + (size_t)(m0 + (lr & 15) < M ? m0 + (lr & 15) : M - 1) * K;
+    const int lr = tid >> 3, ls = (tid & 7) * 8;  // staging: rows lr and lr + 32 of W, eight halves from ls
+    const int la = lr % (8 * TM);  // its row of A
+    const __half* ag = A + (size_t)(m0 + la < M ? m0 + la : M - 1) * K;
     const __half* wg[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) wg[j] = W + (size_t)(n0 + 32 * j + lr < N ? n0 + 32 * j + lr : N - 1) * K;
@@ -48,11 +51,11 @@ __global__ __launch_bounds__(256) void gemm_nt_seq_kernel(const __half* __restri
         for (int j = 0; j < TN; ++j) wv[j] = *reinterpret_cast<const fp_int4_t*>(wg[j] + k);
     };
     auto store = [&](int s) {
-        if (tid < 128) *reinterpret_cast<fp_int4_t*>(&As[s][lr * RS + ls]) = av;
+        if (TM == 4 || tid < 128) *reinterpret_cast<fp_int4_t*>(&As[s][lr * RS + ls]) = av;
 #pragma unroll
         for (int j = 0; j < TN; ++j) *reinterpret_cast<fp_int4_t*>(&Ws[s][(32 * j + lr) * RS + ls]) = wv[j];
     };
-    float acc[2][TN] = {};
+    float acc[TM][TN] = {};
     fetch(0);
     store(0);
     fetch(KC);
@@ -63,21 +66,21 @@ __global__ __launch_bounds__(256) void gemm_nt_seq_kernel(const __half* __restri
 #pragma unroll
         for (int k = 0; k < KC; k += 8) {
             if (k == KC / 2 && k0 + k >= K) break;
-            fp_half8_t a[2], w[TN];
+            fp_half8_t a[TM], w[TN];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const fp_half8_t*>(&As[s][(ty + 8 * i) * RS + k]);
+            for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const fp_half8_t*>(&As[s][(ty + 8 * i) * RS + k]);
 #pragma unroll
             for (int j = 0; j < TN; ++j) w[j] = *reinterpret_cast<const fp_half8_t*>(&Ws[s][(tx + 32 * j) * RS + k]);
 #pragma unroll
             for (int e = 0; e < 8; ++e)
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_fmaf((float)a[i][e], (float)w[j][e], acc[i][j]);
         }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < TM; ++i) {
         const int m = m0 + ty + 8 * i;
         if (m >= M) continue;
 #pragma unroll
@@ -93,11 +96,11 @@ __global__ __launch_bounds__(256) void gemm_nt_seq_kernel(const __half* __restri
 
 static void launch_gemm_seq(const __half* A, const __half* W0, const __half* W1, const float* bias, int M, int N, int K, float* out_f32,
                             __half* out_f16, int ldo, hipStream_t st) {
-    const unsigned mx = (M + 15) / 16, z = W1 ? 2 : 1;
-    if ((size_t)mx * ((N + 63) / 64) * z < 1024 || ((N + 63) / 64 & 1))
-        hipLaunchKernelGGL(gemm_nt_seq_kernel<2>, dim3(mx, (N + 63) / 64, z), dim3(256), 0, st, A, W0, W1, bias, M, N, K, out_f32, out_f16, ldo);
+    const unsigned ny = (N + 63) / 64, z = W1 ? 2 : 1;
+    if (gemm_seq_rows(M, N, z) == 16)
+        hipLaunchKernelGGL(gemm_nt_seq_kernel<2>, dim3((M + 15) / 16, ny, z), dim3(256), 0, st, A, W0, W1, bias, M, N, K, out_f32, out_f16, ldo);
     else
-        hipLaunchKernelGGL(gemm_nt_seq_kernel<4>, dim3(mx, (N + 127) / 128, z), dim3(256), 0, st, A, W0, W1, bias, M, N, K, out_f32, out_f16, ldo);
+        hipLaunchKernelGGL(gemm_nt_seq_kernel<4>, dim3((M + 31) / 32, ny, z), dim3(256), 0, st, A, W0, W1, bias, M, N, K, out_f32, out_f16, ldo);
 }
 
 // Matrix-core versions, for sums that feed no quantizer. All stage rows of A and of W through LDS, in K steps of KC, the

@@ -444,6 +444,9 @@ hipError_t launch_gemm_i8(const int8_t* A, const float* sa, const int8_t* W, con
 //   with fp16 rows one float32 FMA chain per output in K order
 hipError_t launch_gemm_fp(const void* A, bool a_is_f32, const __half* W, const float* bias, int M, int N, int K,
                           float* out_f32, __half* out_f16, int ldo, hipStream_t st);
+//   rows of A to a workgroup of that chain's kernel, z matrices W: 16 up to 20 workgroups to each of 256 compute units, 32 beyond, where reading less
+//   from LDS counts for more than rounds that end evenly (tests/host/fullprec_rule.cpp has the timings)
+inline int gemm_seq_rows(int M, int N, int z) { return (size_t)((M + 15) / 16) * ((N + 63) / 64) * z < 5120 ? 16 : 32; }
 //   K and V rows of a context in one launch: rows_f [M][2C], the same sums as two calls of launch_gemm_fp
 hipError_t launch_gemm_kv_rows(const __half* context, const __half* Wk, const __half* Wv, int M, int C, int K, float* rows_f, hipStream_t st);
 //   fp16 rows on the matrix cores (any order of summation: for sums that no quantizer reads), out f32 [M][N]; tiles of 32 x 32 outputs, or of

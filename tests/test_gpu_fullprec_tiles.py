@@ -27,10 +27,14 @@ def projections(B, N, C, H, text, Cc, bits_q, hidden):
 
 
 @pytest.mark.parametrize("B,N,C,H,bits_q", [
-    (1, 1700, 640, 8, 8),   # 107 x 10 small workgroups: the large tile, ragged rows
-    (2, 1041, 480, 10, 8),  # 131 x 8, seven and a half chunks of K, columns that end within a tile
-    (1, 3293, 320, 8, 8),   # the small tile: five column blocks of 64
-    (1, 1700, 672, 6, 4),   # the same, ten and a half chunks of K
+    (1, 1700, 640, 8, 8),   # 16 rows to a workgroup, a last one of four
+    (2, 1041, 480, 10, 8),  # seven and a half chunks of K, columns that end within a tile
+    (1, 3293, 320, 8, 8),
+    (1, 1700, 672, 6, 4),   # ten and a half chunks of K
+    (1, 8185, 640, 8, 8),   # 5120 workgroups of 16 rows: 32 rows to a workgroup, a last one of 25
+    (2, 5121, 480, 10, 8),  # a last one of two
+    (1, 7441, 672, 6, 4),   # of 17
+    (1, 16369, 320, 8, 8),
 ])
 def test_many_rows_have_the_bits_of_few(B, N, C, H, bits_q):
     hidden = normal(1, B, N, C)
