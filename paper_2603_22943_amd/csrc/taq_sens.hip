@@ -108,17 +108,15 @@ __device__ __forceinline__ float sens_quad_sum(float x) {
 }
 
 // ---------------------------------------------------------------- attention of the reference block and the sweep's factors
-// One workgroup of WV = 1 or 4 wavefronts per (16 image tokens, head): S^T = K Q^T and the score changes (k' - k) Q^T of every text token, softmax, O^T = V^T A^T, all with
-// V_MFMA_F32_16X16X4_F32 (text tokens or channels along the rows, image tokens along the columns: the accumulator
-// registers of the scores are the B operand of the last product). Each step's operands are requested while the step before is
+// One workgroup of WV = 1 or 4 wavefronts per (16 image tokens, head): S^T = K Q^T and the score changes (k' - k) Q^T of every text token,
+// softmax, O^T = V^T A^T, all with V_MFMA_F32_16X16X4_F32 (text tokens or channels along the rows, image tokens along the columns: the
+// accumulator registers of the scores are the B operand of the last product). Each step's operands are requested while the step before is
 // multiplied. Four wavefronts share out the operand tiles of the scores, the text tokens' factors (element i of each accumulator) and
 // the channel blocks of O; scores and weights pass through LDS. One wavefront by itself on a SIMD issues an instruction every 8.6
 // clocks, and 5000 of them were the time: 34 -> 18.9 us at 512 tokens of eight heads of 160 (256 workgroups), same bits. Where there are
-// wavefronts enough without, the maxima and sums that all four form cost more. Sweeps of 20 tokens with one and with four: 600 workgroups
-// (2 x 240 of 20 heads of 64) 576, 558 us; 1024 (2 x 1024, heads of 80) 169, 165; 4096 (2 x 4096, heads of 40) 278, 314: the line is 1024.
-// o, md [row][C], ab [row][nk][NB][H]{alpha, beta}, dom [row][H] (swept token
-// or -1), dcoef [row][H][NB], rows counted from row0 over all batch elements, D.Np of them each; md is written by wavefronts
-// with a dom >= 0 only. MT: tiles of 16 text tokens.
+// wavefronts enough without, the maxima and sums that all four form cost more (sens_wavefronts: where the line lies).
+// o, md [row][C], ab [row][nk][NB][H]{alpha, beta}, dom [row][H] (swept token or -1), dcoef [row][H][NB], rows counted from row0 over all
+// batch elements, D.Np of them each; md is written by workgroups with a dom >= 0 only. MT: tiles of 16 text tokens.
 template <int NB, int MT, int WV>
 __global__ __launch_bounds__(64 * WV) void sens_attn_kernel(const float* __restrict__ q_f, const float* __restrict__ kx,
                                                         const float* __restrict__ vx, SensDims D, int row0,
@@ -556,7 +554,8 @@ static hipError_t sens_run(const void* hidden, const void* context, const __half
         const int nr = rows - r0 < W.chunk ? rows - r0 : W.chunk;  // a multiple of 32
 #define TAQ_SENS_ATTN(MT) \
     case MT: \
-        if (nr / 16 * H <= 1024) hipLaunchKernelGGL((sens_attn_kernel<NB, MT, 4>), dim3(nr / 16, H), dim3(256), 0, st, q_f, kx, vx, D, r0, o, ab, dom, dcoef, md); \
+        if (sens_wavefronts(nr / 16 * H) == 4) \
+            hipLaunchKernelGGL((sens_attn_kernel<NB, MT, 4>), dim3(nr / 16, H), dim3(256), 0, st, q_f, kx, vx, D, r0, o, ab, dom, dcoef, md); \
         else hipLaunchKernelGGL((sens_attn_kernel<NB, MT, 1>), dim3(nr / 16, H), dim3(64), 0, st, q_f, kx, vx, D, r0, o, ab, dom, dcoef, md); \
         break;
         switch ((s.T + 15) / 16) {

@@ -57,3 +57,30 @@ def test_sweep_over_repeated_rows(C, H, n, times):
 
     a, b = sweep(few), sweep(few.repeat(1, times, 1))
     assert np.all(a[1] > 0) and np.all(np.abs(a - b) <= 1e-9 * a)
+
+
+@pytest.mark.parametrize("C,H,n,times,text,bits,factor", [
+    (96, 4, 17, 260, 17, (8, 4), 1.0),     # 1032 workgroups or more of one wavefront against few of four, two to six tiles of text
+    (320, 8, 40, 52, 33, (4,), 1.0),
+    (96, 4, 33, 130, 49, (8, 4), 1.0),
+    (320, 8, 19, 112, 77, (8, 4), 1.0),
+    (640, 8, 33, 64, 77, (4,), 1.0),
+    (320, 2, 21, 400, 96, (8,), 1.0),
+    (96, 4, 20, 210, 5, (4,), 1.0),        # one tile, one width
+    (320, 4, 65, 66, 96, (8, 4), 50.0),    # rows that one token takes almost whole
+    (96, 4, 31, 140, 33, (4,), 50.0),
+])
+def test_sweep_with_one_wavefront_has_the_bits_of_four(C, H, n, times, text, bits, factor):
+    """As above, in the attention: one wavefront to 16 tokens and a head on the repeated rows, four on the few."""
+    Cc = 96
+    few = normal(2, 1, n, C) * factor
+    w = [normal(20 + i, C, k, std=k ** -0.5) for i, k in enumerate((Cc, Cc, C, C))]
+    context, scales = normal(4, 1, text, Cc, std=2.0), torch.zeros(3 * C, device="cuda")
+
+    def sweep(hidden):
+        s = T.make_shape(1, hidden.shape[1], C, H, text, Cc, bits_q=16, bits_prob=16, bits_proj=16)
+        return T.taq_token_sensitivity(hidden, context, *w, scales, range(text), bits, s).cpu().numpy()
+
+    assert (n + 31) // 32 * 2 * H <= 1024 < (n * times + 31) // 32 * 2 * H
+    a, b = sweep(few), sweep(few.repeat(1, times, 1))
+    assert a.max() > 0 and np.all(np.isfinite(a)) and np.all(np.abs(a - b) <= 1e-9 * a)
