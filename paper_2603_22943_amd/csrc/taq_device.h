@@ -26,11 +26,11 @@ __device__ __forceinline__ unsigned pack4(int a, int b, int c, int d) {
 }
 
 // x / d for a grid's largest code d = 127 or 7, correctly rounded, x >= 0: the quotient by the rounded reciprocal, its remainder (exact) and one
-// correction. Compared with the division for every float x from 0 to infinity (the minimum is for infinity, whose remainder is taken of the
-// largest finite quotient). The division itself is 11 dependent instructions, a reciprocal among them, and a block has four or five of them in its
-// chain.
-__device__ __forceinline__ float div_grid(float x, float d) {
-    const float r = __float_as_uint(d) == 0x40e00000u ? 1.0f / 7.0f : 1.0f / 127.0f, q = x * r;
+// correction. Compared with the division for every float x from 0 to infinity (tests/host/grid_quotients.cpp; the minimum is for infinity, whose
+// remainder is taken of the largest finite quotient). The division itself is 11 dependent instructions, a reciprocal among them, and a
+// block has four or five of them in its chain.
+__host__ __device__ __forceinline__ float div_grid(float x, float d) {
+    const float r = __builtin_bit_cast(unsigned, d) == 0x40e00000u ? 1.0f / 7.0f : 1.0f / 127.0f, q = x * r;
     return __builtin_fmaf(__builtin_fmaf(-fminf(q, 3.402823466e+38f), d, x), r, q);
 }
 
@@ -117,17 +117,17 @@ __device__ __forceinline__ unsigned quant4_settle(unsigned pk, float x0, float x
 }
 
 // Codes of a row of fp16 values (amax one of them): for most rows one product settles them. |x| 127 / amax = 127 X / (A 2^s) with integer
-// significands X, A < 2^11 and s >= 0 is either half an integer H or, relatively, at least 1 / (2 * 127 * 2047) = 1.9e-6 away from one, further than
-// c (1 + 2^-21) is from 127 / amax (at most 6e-7). And it is H itself only if 254 X = (2 k + 1) A 2^s: where the prime 127 does not
+// significands X, A < 2^11 and s >= 0 is either half an integer H or, relatively, at least 1 / (2 * 127 * 2047) = 1.9e-6 away from one, further
+// than c (1 + 2^-21) is from 127 / amax (at most 6e-7). And it is H itself only if 254 X = (2 k + 1) A 2^s: where the prime 127 does not
 // divide A, it divides 2 k + 1 <= 254, so H = 63.5, whose even neighbour is the outer one, which that product rounds to. Rows with
 // 127 | A, one in 128, are those whose scale amax / 127 is exact; their outer candidates go on to half_row_settle. (Every fp16 amax against
-// every fp16 value below it: the definition's codes.)
-// 7 instructions per four values instead of 15: with div_grid 61.9 -> 60.7 us at 16 requests of 4096 x 320, 10.86 -> 10.78 at 2 x 4096 x 320.
+// every fp16 value below it gives the definition's codes: tests/host/grid_quotients.cpp.) 7 instructions per four values instead of 13:
+// with div_grid 61.9 -> 60.7 us at 16 requests of 4096 x 320, 10.86 -> 10.78 at 2 x 4096 x 320.
 struct HalfRow {
     float m;      // the product's factor
     bool doubt;   // 127 | A
 };
-__device__ __forceinline__ HalfRow half_row(float c, float scale, float amax) {  // c = quant_mult(127, amax), scale = amax / 127
+__host__ __device__ __forceinline__ HalfRow half_row(float c, float scale, float amax) {  // c = quant_mult(127, amax), scale = amax / 127
     return {__builtin_fmaf(c, 4.76837158203125e-07f, c), __builtin_fmaf(-scale, 127.f, amax) == 0.f};
 }
 
