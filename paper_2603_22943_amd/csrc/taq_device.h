@@ -82,10 +82,10 @@ __device__ __forceinline__ unsigned quant4_ties(unsigned pk, unsigned flags, flo
 //   exact definition: code = rint((y * qmax) / amax) with IEEE float32 operations (qmax = 127, or 7 for 4-bit Q~).
 //   fast path: the defined quotient is within 3 * 2^-24 of y * qmax / amax, relatively (y, where f is not 1, its product and
 //   the division, rounded once each), x times fc = f * quant_mult(qmax, amax) within 2^-23 and a little: together less than
-//   3.1e-7. The FMAs fma(x, fc (1 -+ 2^-21), 1.5 * 2^23) round two exact products, 4.1e-7 and more to either side, half-to-even
-//   to integers (the constant's low mantissa bytes); rounding is monotone, so where they agree the quotient rounds to the same.
-//   Where they differ, quant4_ties decides. (Both products cost two instructions per four values less than one product and its
-//   distance from the integer, and the doubtful zone narrows with the magnitude: a fourth of the visits there.)
+//   3.1e-7. The inner and outer products x fc (1 -+ 2^-21) lie 4.1e-7 and more to either side of it; rounding is monotone, so where both round
+//   to the same integer the quotient does. fma(x, inner factor, 1.5 * 2^23) rounds the inner one half-to-even to an integer, the constant's low
+//   mantissa byte: the code, unless the outer one rounds to another (quant4_fast); then quant4_ties decides. The doubtful zone narrows with
+//   the magnitude.
 struct QuantRow {
     float f, c, amax;  // c = quant_mult(qmax, amax)
 };
@@ -97,7 +97,7 @@ __device__ __forceinline__ unsigned quant4_at(float x0, float x1, float x2, floa
 }
 // The inner candidates. The outer product less the inner result (the constant plus n), rounded to an integer, is minus the constant, unless it is
 // beyond n + 1/2: then a neighbour of it. (On n + 1/2 itself it counts as n: the quotient is on the inner side by more than 1e-7 of it.)
-// `doubt`, the OR of them, starts as TAQ_SURE and stays that while no value is in doubt: three instructions per four values less than
+// `doubt`, the OR of them, starts as TAQ_SURE and stays that while no value is in doubt: 13 instructions per four values, two less than
 // packing the outer candidates and comparing.
 #define TAQ_SURE 0xCB400000u
 __device__ __forceinline__ unsigned quant4_fast(float x0, float x1, float x2, float x3, QuantRow r, unsigned& doubt) {
@@ -242,12 +242,13 @@ __device__ __forceinline__ void biased4_to_half(unsigned w, half2_t& a, half2_t&
     b = *reinterpret_cast<const half2_t*>(&hi) - off;
 }
 
-// Integer sums that become floats: started at the bits of 1.5 * 2^23, a sum below 2^22 is, read as a float, that constant plus the sum, and a subtraction
-// leaves the sum. With two or more wavefronts to a SIMD, additions, products and bit operations on float32 registers and literals take 2.2 clocks of it,
-// conversions, maxima, comparisons, selects, permutations, packed fp16 and anything with a scalar register operand 4 (selects by vcc in a row 22),
-// exponentials and lane swaps 8. Sums of scores stay below 127 * 127 * 160 < 2^22; those of projections need not.
-// This, no selects for rows past a head and protected rows by bounds-checked loads, us: 16 requests of 4096 x 320 59.4 -> 58.6, 2 x 4096 x 640 20.8 -> 20.7,
-// the layers of a UNet step of 8 x 96 x 64 649 -> 642.
+// Integer sums that become floats: started at the bits of 1.5 * 2^23, a sum below 2^22 is, read as a float, that constant plus the sum, and a
+// subtraction leaves the sum. With two or more wavefronts to a SIMD, additions, products and bit operations on float32 registers and literals
+// take 2.2 clocks of it, conversions, maxima, comparisons, selects, permutations, packed fp16 and anything with a scalar register operand 4
+// (selects by vcc in a row 22), exponentials and lane swaps 8. Sums of scores stay below 127 * 127 * TAQ_MAX_D < 2^22; those of projections need
+// not. This, no selects for rows past a head and protected rows by bounds-checked loads, us: 16 requests of 4096 x 320 59.4 -> 58.6,
+// 2 x 4096 x 640 20.8 -> 20.7, the layers of a UNet step of 8 x 96 x 64 649 -> 642.
+static_assert(127 * 127 * TAQ_MAX_D < 1 << 22, "sums of scores as the mantissa of a float");
 __device__ __forceinline__ int32x4_t sum_start() { return (int32x4_t){0x4B400000, 0x4B400000, 0x4B400000, 0x4B400000}; }
 __device__ __forceinline__ float sum_float(int s) { return __int_as_float(s) - 12582912.0f; }
 

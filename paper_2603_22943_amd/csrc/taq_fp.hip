@@ -24,7 +24,8 @@ typedef _Float16 fp_half8_t __attribute__((ext_vector_type(8)));
 // With many rows TM = 4 reads less per FMA (gemm_seq_rows: where the line lies); 128 columns instead of twice the rows, 4 x 64 outputs to
 // a wavefront and 132 registers, are 1 to 20 % slower from 500 small workgroups to 11000.
 // With TM = 2 half of the threads load a row of A that another holds already, and the last two chunks are loaded for nothing: behind a
-// condition the loads no longer lie between the FMAs (154 x 1280 x 1280 20.6 and 24.9 us, 4096 x 320 x 320 17.1 and 17.4, equal from 2500 workgroups on).
+// condition the loads no longer lie between the FMAs (154 x 1280 x 1280 20.6 and 24.9 us, 4096 x 320 x 320 17.1 and 17.4, equal from 2500
+// workgroups on).
 // blockIdx.z = 1: a second matrix W1 of the same size, results `N` columns further (K and V of a context in one launch).
 template <int TM>
 __global__ __launch_bounds__(256) void gemm_nt_seq_kernel(const __half* __restrict__ A, const __half* __restrict__ W0,

@@ -117,13 +117,15 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     constexpr bool LEAN = DENSE || (NTT > 2 && NH <= 8);  // no register to spare
     constexpr bool LOGP = PG == TAQ_PROB_LOG2, ROWMAX = PG == TAQ_PROB_ROWMAX;  // grid of the probabilities, Eq. (3)
     constexpr int MT16 = NT16 ? NT16 : 6;  // score tiles the code is unrolled for
-    // dwords of codes per test for ties. Whole groups but with row-major weights (4 % slower there at d = 80) and three or four token tiles (registers): the 16 layers of a step of 2 x 64 x 64 249.9 -> 247.2 us,
-    // of 8 x 96 x 64 642 -> 640, 16 requests of 4096 x 320 59.1 -> 58.8, 2 x 4096 x 640 20.5 -> 20.4.
+    // dwords of codes per test for ties. Whole groups but with row-major weights (4 % slower there at d = 80) and three or four token tiles
+    // (registers): the 16 layers of a step of 2 x 64 x 64 249.9 -> 247.2 us, of 8 x 96 x 64 642 -> 640, 16 requests of 4096 x 320 59.1 -> 58.8,
+    // 2 x 4096 x 640 20.5 -> 20.4.
     constexpr int QG = ROWMAJ || NTT > 2 ? 1 : TPH;
     // Scores past the protected tokens become minus infinity by selects behind the products instead of starting there, where the four
     // starting values are registers too many: 1 and 8 spilled without, none so. us: 2 x 8192 x 640, eight heads, 33.2 -> 33.0 (0 to 1 % in four
-    // runs), ten heads with 50 text tokens, 20 of them protected, log2 grid, 18.45 -> 17.5. Three token tiles at ten heads (14 and 12 spilled or, so, 12 and 11) and row-major weights
-    // with four (4 or 3) are no faster so: 29.6 and 31.1 us at 12288 tokens against 29.6 and 31.2, 34.3 at 2 x 8192 against 34.5.
+    // runs), ten heads with 50 text tokens, 20 of them protected, log2 grid, 18.45 -> 17.5. Three token tiles at ten heads (14 and 12 spilled or,
+    // so, 12 and 11) and row-major weights with four (4 or 3) are no faster so: 29.6 and 31.1 us at 12288 tokens against 29.6 and 31.2, 34.3 at
+    // 2 x 8192 against 34.5.
     constexpr bool SELECT = (NTT == 4 && !ROWMAJ) || (NH > 8 && NTT == 1 && NT16 == 0 && LOGP);
     constexpr bool TAPS = NT16 == 0;       // taps of intermediate codes and scales (tests, profiling)
     extern __shared__ __align__(16) unsigned char smem[];
@@ -262,10 +264,11 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
     const __half* v16t = reinterpret_cast<const __half*>(packed + dm.L.v16t) + (size_t)b * C * 96;
 
     // protected (trigger) rows of this head, first tile of 16: fp16 K rows and transposed V rows straight from
-    // global memory into MFMA operand registers. Slots past the protected tokens and channels past the head (which would belong to the next head, or
-    // lie past the last row of the last head, and a non-finite bit pattern there would survive the multiplication with a zero Q~ code) carry an offset
-    // past the end: zeros without a memory access. (A load costs by the pieces of memory that it touches, 16 rows of 32 bytes if all lanes take part: 15.1 -> 14.7 us at 2048
-    // tokens of 640 channels. Flat loads needed a branch, zeroed registers and 64-bit addresses for each of these.)
+    // global memory into MFMA operand registers. Slots past the protected tokens and channels past the head (which would belong to the next
+    // head, or lie past the last row of the last head, and a non-finite bit pattern there would survive the multiplication with a zero Q~
+    // code) carry an offset past the end: zeros without a memory access. (A load costs by the pieces of memory that it touches, 16 rows of 32
+    // bytes if all lanes take part: 15.1 -> 14.7 us at 2048 tokens of 640 channels. Flat loads needed a branch, zeroed registers and 64-bit
+    // addresses for each of these.)
     uint2 k16r[FS][2], v16r[TPH];
     auto load_protected = [&]() {
         if (nfp > 0) {
@@ -274,7 +277,8 @@ void fused_block_kernel(FusedTable tab, FusedDims dm) {
             constexpr int NONE = 0x7fff0000;
             const int ko = r16 < ntrig ? (r16 * C + h * D + 4 * q) * 2 : NONE, ko_last = D % 16 == 0 || 16 * (TPH - 1) + 4 * q < D ? ko : NONE;
             const int vo = 4 * q < ntrig ? ((h * D + r16) * 96 + 4 * q) * 2 : NONE;
-            const int vo_last = D % 16 == 0 || r16 < D % 16 ? vo : 4 * q < ntrig ? ((h * D + D % 16 - 1) * 96 + 4 * q) * 2 : NONE;  // (rows past the head repeat its last, as those of V~ do)
+            // (rows past the head repeat its last, as those of V~ do)
+            const int vo_last = D % 16 == 0 || r16 < D % 16 ? vo : 4 * q < ntrig ? ((h * D + D % 16 - 1) * 96 + 4 * q) * 2 : NONE;
 #pragma unroll
             for (int j = 0; j < 2 * FS; ++j) {
                 const uint2_t w = j < TPH ? __builtin_amdgcn_raw_buffer_load_b64(rs_k, (j == TPH - 1 ? ko_last : ko) + 32 * j, 0, 0) : (uint2_t){0u, 0u};

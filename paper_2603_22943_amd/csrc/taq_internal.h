@@ -467,8 +467,8 @@ hipError_t launch_mse_f16(const __half* x, const __half* y, size_t n, double* ou
 
 // Token-sensitivity sweep of Eq. (1) in full precision (taq_sens.hip): workspace sections and the launch sequence.
 #define TAQ_SENS_MAX_H 32
-// Wavefronts to each workgroup of the attention (16 image tokens, head): up to 1024 workgroups four are never slower, from 1536 on one is faster in all
-// but the shortest texts; between the two it depends on the text's length (tests/host/fullprec_rule.cpp has the timings).
+// Wavefronts to each workgroup of the attention (16 image tokens, head): up to 1024 workgroups four are never slower, from 1536 on one is as fast
+// (1 %) or faster; between the two it depends on the text's length (tests/host/fullprec_rule.cpp has the timings).
 inline int sens_wavefronts(int workgroups) { return workgroups <= 1024 ? 4 : 1; }
 struct SensWorkspace {
     size_t rows_f;  // f32 [B*T][2C]             projection rows of the text tokens
