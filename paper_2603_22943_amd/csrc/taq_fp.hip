@@ -116,7 +116,8 @@ static void launch_gemm_seq(const __half* A, const __half* W0, const __half* W1,
 template <int MI, int KC>
 __global__ __launch_bounds__(256) void gemm_nt_f16_kernel(const __half* __restrict__ A, const __half* __restrict__ W, int M, int N, int K,
                                                           float* __restrict__ out) {
-    constexpr int TILE = 32 * MI, RS = KC + 8;  // row stride in halves: 144 or 272 bytes, conflict-free for the operand reads
+    // row stride in halves: 144 or 272 bytes (with 272 a third of the LDS clocks are conflicts, 320 of a wavefront's 960 at 512 x 1280 x 1280)
+    constexpr int TILE = 32 * MI, RS = KC + 8;
     constexpr int TR = KC / 8, RPP = 256 / TR, NL = TILE / RPP;  // staging: threads per row, rows at a time, loads per thread and operand
     static_assert(TILE % RPP == 0, "whole loads");
     __shared__ __align__(16) __half As[2][TILE * RS], Ws[2][TILE * RS];
@@ -283,9 +284,11 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const float* __restric
 // rounding), so six exact products stand for each product of before: 96 clocks of the matrix core for 16 x 16 x 32, against 256 of
 // V_MFMA_F32_16X16X4_F32, and no conversions beside the products. Sums are float32 as before, the small products of a step first.
 // 64 x 64 outputs per workgroup of four wavefronts, 32 x 32 each; what a step of 32 k needs is split when it is stored in LDS (80 bytes to
-// a row: conflict-free operand reads). One buffer of 25 KiB, so that five workgroups share a compute unit: 512 x 1280, eight heads of
-// 160, are 1280 of them, all at once. 24.5 -> 17.0 us (with two buffers, three to a unit, 19.7). Relative error against float64 at heads of 32, 40, 80
-// and 160: 1.0e-7, 1.1e-7, 1.6e-7, 2.3e-7 before, 0.4e-7, 0.6e-7, 1.0e-7, 1.6e-7 so; largest, over the sum of magnitudes, 3.3e-7 and 2.4e-7.
+// a row). Half of the LDS clocks are conflicts, 400 of a wavefront's 800 at 512 x 1280 in heads of 160: the stores, eight bytes a lane, wrap
+// the last of four rows, which lie 20 dwords apart, onto the first one's banks. One buffer of 25 KiB, so that five workgroups share a compute unit:
+// 512 x 1280, eight heads of 160, are 1280 of them, all at once. 24.5 -> 17.0 us (with two buffers, three to a unit, 19.7). Relative error against
+// float64 at heads of 32, 40, 80 and 160: 1.0e-7, 1.1e-7, 1.6e-7, 2.3e-7 before, 0.4e-7, 0.6e-7, 1.0e-7, 1.6e-7 so; largest, over the sum of
+// magnitudes, 3.3e-7 and 2.4e-7.
 __global__ __launch_bounds__(256) void gemm_nt_split_kernel(const float* __restrict__ A, const __half* __restrict__ W, int M, int N, int K, int Kz,
                                                             float* __restrict__ out, size_t ldo) {
     constexpr int KC = 32, RS = KC + 8;
